@@ -132,6 +132,10 @@ struct Layout {
   size_t hdr, units, tchunks, part_acc, part_ml, state_a, state_b;
   // fast
   size_t qn, wkp, wvp, wop, w1p, w2p, wqp, kv;
+  // target update: its cut, the splits' parts of the state and their arrival counters
+  UpdatePlan upd;
+  int max_ch;  // the most chunk records of a target (forward, bf16 path)
+  size_t spart, ucnt;
   // reordered: U, the y partials with their (max, sum) and chunk counts, its
   // schedule (its own header and units when both forms run), fp16 W_V
   size_t un, part_y, ml_r, tch_r, hdr2, units2, wvp16;
@@ -268,6 +272,28 @@ stca_status_t make_layout(const stca_dims_t* dims, const stca_batch_t* b, int wi
         L->wvp16 = m.take(2 * n * d * d);
         L->hdr2 = m.take(sizeof(WsHeader));
         L->units2 = m.take(sizeof(Unit) * (L->max_units2 + 1));
+      }
+      // the splits' buffers come last: a batch that fits the library's own
+      // scratch array only without them keeps fitting, unsplit
+      // the most chunks a request of the standard form is cut into (the
+      // reordered form hands over one record)
+      L->max_ch = std_part && !b->hist_off_host ? kMaxChunks : 1;
+      for (int r = 0; std_part && b->hist_off_host && r < b->n_requests; ++r) {
+        const int64_t mt = b->tgt_off_host[r + 1] - b->tgt_off_host[r];
+        if (mt < L->std_lo) continue;
+        const int64_t nb = ceil_div(b->hist_off_host[r + 1], kBlockTokens) - b->hist_off_host[r] / kBlockTokens;
+        L->max_ch = std::max(L->max_ch, static_cast<int>(std::min<int64_t>(kMaxChunks, ceil_div(nb, L->chunk_blocks))));
+      }
+      L->upd = update_plan(L->nt, L->d, L->F, device_cus());
+      if (L->upd.splits > 1) {
+        Bump with = m;
+        const size_t groups = static_cast<size_t>(ceil_div(L->nt, L->upd.tg));
+        L->spart = with.take(4 * L->upd.splits * groups * 32 * d);
+        L->ucnt = with.take(4 * n * groups);
+        if (with.off > STCA_NOALLOC_SCRATCH_BYTES && m.off <= STCA_NOALLOC_SCRATCH_BYTES)
+          L->upd = {L->upd.tg0, 1, L->upd.tg0};
+        else
+          m = with;
       }
     } else {
       L->kv32 = m.take(4 * nh * 2 * d);
@@ -465,7 +491,10 @@ stca_status_t forward_fast(const Layout& L, const stca_batch_t* b, const void* h
   const size_t kv_layer = (size_t)L.nblocks * kBlockTokens * 2 * d * 2;
   const size_t wlayer = (size_t)d * d * 2;  // bytes of one layer's bf16 W_K
   FastUpdate f{};
-  f.tg = ceil_div(static_cast<int64_t>(L.nt), 32) < device_cus() ? 16 : 32;
+  f.max_ch = L.max_ch;
+  f.plan = L.upd;
+  f.spart = L.upd.splits > 1 ? at<float>(ws, L.spart) : nullptr;
+  f.cnt = L.upd.splits > 1 ? at<int32_t>(ws, L.ucnt) : nullptr;
   f.n_layers = n;
   f.F = F;
   f.n_tgt = L.nt;

@@ -5,6 +5,14 @@
 
 namespace stca {
 
+// How the target update cuts its work: groups of tg targets, each group's
+// hidden layer over `splits` workgroups (1, 2 or 4; more than one only for
+// F = 4 d, d = 256); tg0: the group of the initial queries (one product, no splits).
+struct UpdatePlan {
+  int tg, splits, tg0;
+};
+UpdatePlan update_plan(int64_t n_tgt, int D, int F, int n_cu);
+
 struct FastUpdate {
   int mode;      // 0: s^(0) = x_t and Q^(0); 1: combine + update after `layer`
   int layer, n_layers, F;
@@ -19,7 +27,10 @@ struct FastUpdate {
   void* out;
   void* QN;
   const void *WoP, *W1P, *W2P, *WqP;
-  int tg;  // targets per workgroup: 32, or 16 to spread few targets over more CUs
+  int max_ch;  // no target has more chunk records (1..kMaxChunks)
+  UpdatePlan plan;
+  float* spart;  // [splits][ceil(n_tgt / tg)][32 D]: the splits' parts of the state, and
+  int32_t* cnt;  // [n_layers][ceil(n_tgt / tg)]: their arrival counters (null without splits)
   int32_t* range;  // set to 1 when a value rounded to fp16 (or the merged attention) is not a finite fp16
 };
 

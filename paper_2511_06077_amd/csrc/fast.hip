@@ -671,14 +671,30 @@ __global__ __launch_bounds__(64 * (D / 32)) void fused_kernel(const Unit* __rest
 }
 
 // ------------------------------------------------ K4: target update
-// One workgroup per tg = 32 targets (or 16, when 32-target groups would leave
-// CUs idle: the MFMA tiles then carry 16 empty target columns, and each CU
-// still streams every weight of the layer once), one wave per 32 output
-// dimensions.
+// One wave per 32 output dimensions; a workgroup holds tg = 8, 16 or 32 targets
+// (the other rows of its 32-row tiles stay zero).
 // mode 0 (init): s^(0) = x_t, Q^(0) = x_t W_Q^0.
 // mode 1 (layer i): merge the attention partials into a, then
 //   u = s + a W_O;  s' = u + ReLU(u W_1) W_2;  Q' = s' W_Q^{i+1} (if i+1 < n).
 // Activations go through LDS as fp16 MFMA operands; the state stays fp32.
+//
+// What bounds it is a chain per workgroup: the merge's round trips to records
+// other XCDs wrote (about 1 us each), then ten weight tiles of 128 KB at
+// d = 256, F = 4 d, at 1.0-1.3 us each (a CU takes 64 bytes a clock from L2).
+// Few targets leave most CUs idle meanwhile, so with `splits` > 1 the
+// workgroups (group g, split s) of a target group divide the hidden layer:
+// each merges the partials and forms u (one product), takes its F / splits
+// hidden columns through W_1 and W_2, and leaves its part of s' (split 0's
+// starts at u) in `spart`; the last of a group to arrive (a counter per group
+// and layer, zeroed by the mode 0 launch) sums the parts in split order, so
+// the result does not depend on who is last, and forms Q'.  The parts go
+// through agent-scope relaxed atomics (stores that write through to memory,
+// waited for before the counter; loads that bypass the L2): agent-scope
+// fences instead write back each XCD's whole L2, once a wave, and cost more
+// than the kernel (one request of 40 targets: 370 us a call against 246).
+// Kernel time at d = 256: 128 targets of one chunk 21 -> 11 us, 40 targets of
+// 16 chunks 20 -> 13 us, 4096 targets (no splits, the merge alone changed)
+// 22.5 -> 19 us.
 struct UpdateArgs {
   int mode, layer, n_layers, F;
   int64_t n_tgt;
@@ -694,25 +710,32 @@ struct UpdateArgs {
   bf16_bits* out;              // final layer output, nullable
   f16x8* QN;                   // next queries
   const f16x8 *WoP, *W1P, *W2P, *WqP;  // packed (fp16), all layers
-  int tg;                      // targets per workgroup (16 or 32)
+  int tg;                      // targets per workgroup (at most 32)
   int32_t* range;              // written 1 when a value rounded to fp16 is out of its range
+  int max_ch;                  // mode 1: no target has more chunks
+  int groups, splits;          // mode 1 grid: groups x splits workgroups
+  float* spart;                // [splits][groups][32 D] (splits > 1)
+  int32_t* cnt;                // [n_layers][groups] arrivals (splits > 1; mode 0 zeroes them)
 };
 
-template <int D, int NC>
+// NC: hidden chunks of D columns a workgroup takes (F / (D splits)) when
+// known at compile time, else 0 (any F, no splits).  TG: targets per workgroup.
+template <int D, int NC, int TG>
 __global__ __launch_bounds__(64 * (D / 32)) void update_kernel(UpdateArgs A) {
   constexpr int NW = D / 32;
   constexpr int H = D / DH;
   constexpr int KS = D / 16;
   constexpr int AROW = D + 8;
-  extern __shared__ __attribute__((aligned(16))) uint16_t lds[];  // fp16 MFMA operands
-  uint16_t* act = lds;                  // [32][AROW]
-  uint16_t* hid = lds + 32 * AROW;      // [32][AROW]: D hidden columns at a time
+  constexpr int NT = 64 * NW;
+  __shared__ __attribute__((aligned(16))) uint16_t act[32 * AROW];  // fp16 MFMA operands
+  __shared__ __attribute__((aligned(16))) uint16_t hid[32 * AROW];  // D hidden columns at a time
+  __shared__ int arrived;
   const int w = threadIdx.x / 64, lane = threadIdx.x % 64;
   const int tcol = lane % 32, hi = lane / 32;
-  const int tg = A.tg;  // rows tg..31 of the 32-row tiles stay zero
-  const int64_t tb = (int64_t)blockIdx.x * tg;
-  const int64_t t = tb + tcol;
-  const bool tok = tcol < tg && t < A.n_tgt;
+  constexpr int tg = TG;  // rows tg..31 stay zero
+  const int group = A.mode == 0 ? blockIdx.x : blockIdx.x / A.splits;
+  const int split = A.mode == 0 ? 0 : blockIdx.x % A.splits;
+  const int64_t tb = (int64_t)group * tg;
   auto live = [&](int row) { return row < tg && tb + row < A.n_tgt; };
   // fp16 range check of every value this thread rounds to fp16 (and of the
   // merged attention output, where an overflowed K or V shows as a
@@ -727,14 +750,23 @@ __global__ __launch_bounds__(64 * (D / 32)) void update_kernel(UpdateArgs A) {
   };
 
   // fp32 result of D^T tile: lane holds dims 32w + 4hi + 8g + k for g, k < 4
+  // of target row tcol
   auto store_f32 = [&](float* dst, const f32x16& v) {
-    float* p = dst + t * D + 32 * w + 4 * hi;
+    float* p = dst + (tb + tcol) * D + 32 * w + 4 * hi;
 #pragma unroll
     for (int g = 0; g < 4; ++g)
       *reinterpret_cast<float4*>(p + 8 * g) = make_float4(v[4 * g], v[4 * g + 1], v[4 * g + 2], v[4 * g + 3]);
   };
-  auto put_act = [&](uint16_t* buf, int col0, const f32x16& v) {
-    uint16_t* p = buf + tcol * AROW + col0 + 4 * hi;
+  auto add_f32 = [&](f32x16& v, const float* src) {
+    const float* p = src + (tb + tcol) * D + 32 * w + 4 * hi;
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const float4 x = *reinterpret_cast<const float4*>(p + 8 * g);
+      v[4 * g] += x.x; v[4 * g + 1] += x.y; v[4 * g + 2] += x.z; v[4 * g + 3] += x.w;
+    }
+  };
+  auto put_act = [&](uint16_t* buf, const f32x16& v) {
+    uint16_t* p = buf + tcol * AROW + 32 * w + 4 * hi;
 #pragma unroll
     for (int i = 0; i < 16; ++i) chk(v[i]);
 #pragma unroll
@@ -746,42 +778,48 @@ __global__ __launch_bounds__(64 * (D / 32)) void update_kernel(UpdateArgs A) {
     }
   };
   // Every product of the update is one 32 x 32 tile per wave with KS k-steps:
-  // acc = W^T act^T.  With NC (hidden chunks, F / D) known at compile time,
-  // its weight operands (one KS-step tile, from L2) are loaded one product
-  // ahead into the other of two register sets, so an L2 round trip overlaps
-  // the previous product instead of preceding its own; a register set is
-  // refilled after an instruction that reads the result of the product that
-  // used it.  The chunk loop is then fully unrolled: the same prefetch in a
-  // loop with a run-time trip count gave wrong results.  NC = 0 (any other
-  // F) loads each product's weights right before it.
-  f16x8 wa[KS], wb[KS];
-  auto fetch = [&](f16x8 (&r)[KS], const f16x8* Wp) {
+  // acc += W^T act^T.  With NC known at compile time, its weight operands (one
+  // KS-step tile, from L2) are loaded one product ahead into the other of two
+  // register sets, so an L2 round trip overlaps the previous product instead
+  // of preceding its own; a register set is refilled after an instruction
+  // that reads the result of the product that used it.  The chunk loop is
+  // then fully unrolled: the same prefetch in a loop with a run-time trip
+  // count gave wrong results.  NC = 0 (any other F) loads each product's
+  // weights right before it.
+  constexpr bool W3 = NC == 1;  // a third set: W_O, W_1 and W_2 of the split all requested at the start
+  const int ql = A.layer + 1 < A.n_layers ? A.layer + 1 : -1;
+  f16x8 wa[KS], wb[KS], wc[W3 ? KS : 1];
+  auto fetch = [&](auto& r, const f16x8* Wp) {
 #pragma unroll
     for (int k = 0; k < KS; ++k) r[k] = Wp[k * 64 + lane];
   };
-  auto gemm = [&](const f16x8 (&r)[KS], const uint16_t* src) {
+  auto gemm = [&](f32x16& acc, const auto& r, const uint16_t* src) {
     const uint16_t* b = src + tcol * AROW + 8 * hi;
-    f32x16 acc = {};
 #pragma unroll
     for (int k = 0; k < KS; ++k) acc = mfma(r[k], *reinterpret_cast<const f16x8*>(b + k * 16), acc);
-    return acc;
   };
-  auto gemm_from = [&](const f16x8* Wp, const uint16_t* src) {
+  auto gemm_from = [&](f32x16& acc, const f16x8* Wp, const uint16_t* src) {
     f16x8 r[KS];
     fetch(r, Wp);
-    return gemm(r, src);
+    gemm(acc, r, src);
   };
   constexpr bool PF = NC > 0;
-  const int nc = PF ? NC : A.F / D;  // hidden chunks of D columns
+  const int nc = PF ? NC : A.F / D;      // hidden chunks of D columns of this workgroup
+  const int c0 = PF ? split * NC : 0;    // ... from this one
   const int KSF = A.F / 16;
-  auto w1_tile = [&](int c) { return A.W1P + ((int64_t)A.layer * (A.F / 32) + c * NW + w) * KS * 64; };
-  auto w2_tile = [&](int c) { return A.W2P + ((int64_t)(A.layer * NW + w) * KSF + c * KS) * 64; };
+  auto w1_tile = [&](int c) { return A.W1P + ((int64_t)A.layer * (A.F / 32) + (c0 + c) * NW + w) * KS * 64; };
+  auto w2_tile = [&](int c) { return A.W2P + ((int64_t)(A.layer * NW + w) * KSF + (c0 + c) * KS) * 64; };
   auto wq_tile = [&](int ql) { return A.WqP + ((int64_t)(ql * NW + w) * KS) * 64; };
 
   if (A.mode == 0) {
-    fetch(wb, wq_tile(0));
+    fetch(W3 ? wa : wb, wq_tile(0));
+    // the layers' arrival counters
+    if (A.cnt)
+      for (int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x; i < (int64_t)A.n_layers * A.groups;
+           i += (int64_t)gridDim.x * NT)
+        A.cnt[i] = 0;
     // stage x_t rows into LDS (fp16) and write s^(0) (fp32)
-    for (int c = threadIdx.x; c < 32 * D / 8; c += 64 * NW) {
+    for (int c = threadIdx.x; c < 32 * D / 8; c += NT) {
       const int row = c / (D / 8), col8 = c % (D / 8);
       uint4 v = make_uint4(0, 0, 0, 0);
       if (live(row)) v = *reinterpret_cast<const uint4*>(A.tgt + (tb + row) * D + col8 * 8);
@@ -800,11 +838,94 @@ __global__ __launch_bounds__(64 * (D / 32)) void update_kernel(UpdateArgs A) {
     }
     __syncthreads();
   } else {
+    // the state and the first product's weights are requested before the merge
+    // and arrive behind it
+    f32x16 s_next = {};
+    if (TG < 32 && live(tcol)) add_f32(s_next, A.s_in);
     fetch(wa, A.WoP + ((int64_t)(A.layer * NW + w) * KS) * 64);
-    // merge partials: two threads per (target, head), 16 dimensions each.
-    // Every chunk's (max, sum) is requested at once and the accumulators four
-    // chunks at a time, so the merge costs a few memory round trips.
-    {
+    // merge partials
+    if (TG < 32) {
+      // a wave's lanes read whole rows, four dimensions a lane, CG chunks of
+      // RP rows a round trip; the records of `max_ch` chunks (what any request
+      // of the batch may have) are requested together with the target's own
+      // chunk count, which only masks them
+      constexpr int LPR = D / 4;  // lanes a row; 8 rows a pass
+      constexpr int RP = TG < 32 ? TG / 8 : 1, CG = 8 / RP;
+      const int prow = threadIdx.x / LPR, dim = 4 * (threadIdx.x % LPR), j = dim / DH;
+      float M[RP], Ls[RP], av[RP][4];
+      int nch[RP];
+      int64_t tt[RP];
+#pragma unroll
+      for (int i = 0; i < RP; ++i) {
+        const int row = 8 * i + prow;
+        tt[i] = live(row) ? tb + row : A.n_tgt - 1;
+        nch[i] = live(row) ? A.tchunks[tt[i]] : 0;
+        M[i] = -INFINITY;
+        Ls[i] = 0.f;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) av[i][e] = 0.f;
+      }
+#pragma unroll 1
+      for (int cb = 0; cb < A.max_ch; cb += CG) {
+        float2 ml[RP][CG];
+        float4 x[RP][CG];
+#pragma unroll
+        for (int c = 0; c < CG; ++c)
+#pragma unroll
+          for (int i = 0; i < RP; ++i)
+            if (cb + c < A.max_ch) {
+              ml[i][c] = A.part_ml[((int64_t)(cb + c) * A.n_tgt + tt[i]) * H + j];
+              x[i][c] = *reinterpret_cast<const float4*>(A.part_acc + ((int64_t)(cb + c) * A.n_tgt + tt[i]) * D + dim);
+            }
+#pragma unroll
+        for (int i = 0; i < RP; ++i) {
+          float mn = M[i];
+#pragma unroll
+          for (int c = 0; c < CG; ++c)
+            if (cb + c < nch[i]) mn = fmaxf(mn, ml[i][c].x);
+          const float sc = M[i] == -INFINITY ? 0.f : exp2f(M[i] - mn);
+          M[i] = mn;
+          Ls[i] *= sc;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) av[i][e] *= sc;
+#pragma unroll
+          for (int c = 0; c < CG; ++c)
+            if (cb + c < nch[i]) {
+              const float wgt = exp2f(ml[i][c].x - mn);
+              Ls[i] += wgt * ml[i][c].y;
+              av[i][0] += wgt * x[i][c].x;
+              av[i][1] += wgt * x[i][c].y;
+              av[i][2] += wgt * x[i][c].z;
+              av[i][3] += wgt * x[i][c].w;
+            }
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < RP; ++i) {
+        const int row = 8 * i + prow;
+        if (live(row)) {
+          const float inv = 1.f / Ls[i];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) av[i][e] *= inv;
+          if (A.save_a && split == 0)
+            *reinterpret_cast<float4*>(A.save_a + tt[i] * D + dim) =
+                make_float4(av[i][0], av[i][1], av[i][2], av[i][3]);
+          if (A.save_lse && dim % DH == 0 && split == 0) A.save_lse[tt[i] * H + j] = (M[i] + log2f(Ls[i])) * kLn2;
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) chk(av[i][e]);
+        uint2 pk;
+        pk.x = (uint32_t)f16_bits(av[i][0]) | ((uint32_t)f16_bits(av[i][1]) << 16);
+        pk.y = (uint32_t)f16_bits(av[i][2]) | ((uint32_t)f16_bits(av[i][3]) << 16);
+        *reinterpret_cast<uint2*>(act + row * AROW + dim) = pk;
+      }
+      // tile rows past the group's targets
+      for (int row = tg + prow; row < 32; row += 8) *reinterpret_cast<uint2*>(act + row * AROW + dim) = make_uint2(0, 0);
+    } else {
+      // two threads per (target, head), 16 dimensions each: every chunk's
+      // (max, sum) at once and the accumulators four chunks at a time (with
+      // the mapping above the registers hold half the rows beside the weights:
+      // two passes, the ragged batch 2075 us a call against 2152)
       const int pair = threadIdx.x >> 1, half = threadIdx.x & 1;
       const int row = pair / H, j = pair % H;
       const int64_t tt = tb + row;
@@ -868,51 +989,83 @@ __global__ __launch_bounds__(64 * (D / 32)) void update_kernel(UpdateArgs A) {
     }
     __syncthreads();
     if (PF) fetch(wb, w1_tile(0));  // after the merge, whose registers it would otherwise share
+    if (W3) fetch(wc, w2_tile(0));
     // u = s + a W_O
-    f32x16 u = gemm(wa, act);
-    if (tok) {
-      const float* sp = A.s_in + t * D + 32 * w + 4 * hi;
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const float4 sv = *reinterpret_cast<const float4*>(sp + 8 * g);
-        u[4 * g] += sv.x; u[4 * g + 1] += sv.y; u[4 * g + 2] += sv.z; u[4 * g + 3] += sv.w;
-      }
-      if (A.save_u) store_f32(A.save_u, u);
-    }
+    gemm(s_next, wa, act);
+    if (TG == 32 && live(tcol)) add_f32(s_next, A.s_in);  // (no registers for it before)
+    if (A.save_u && split == 0 && live(tcol)) store_f32(A.save_u, s_next);
     __syncthreads();
-    put_act(act, 32 * w, u);
+    put_act(act, s_next);
     __builtin_amdgcn_sched_barrier(0);
-    if (PF) fetch(wa, w2_tile(0));
+    if (W3 && ql >= 0) fetch(wa, wq_tile(ql));
+    else if (PF && !W3) fetch(wa, w2_tile(0));
     __syncthreads();
     // s' = u + ReLU(u W_1) W_2, the hidden layer taken D columns at a time
-    f32x16 s_next = u;
-    const int ql = A.layer + 1 < A.n_layers ? A.layer + 1 : -1;
+    // (the part of a split other than the first starts at zero)
+    if (split > 0) s_next = f32x16{};
 #pragma unroll
     for (int c = 0; c < (PF ? NC : nc); ++c) {
-      f32x16 h = PF ? gemm(wb, act) : gemm_from(w1_tile(c), act);  // this wave's 32 hidden columns of chunk c
+      f32x16 h = {};  // this wave's 32 hidden columns of chunk c
+      if (PF) gemm(h, wb, act);
+      else gemm_from(h, w1_tile(c), act);
 #pragma unroll
       for (int v = 0; v < 16; ++v) h[v] = fmaxf(h[v], 0.f);
       __builtin_amdgcn_sched_barrier(0);
-      if (PF) {
+      if (PF && !W3) {
         if (c + 1 < nc)
           fetch(wb, w1_tile(c + 1));
         else if (ql >= 0)
           fetch(wb, wq_tile(ql));
       }
-      put_act(hid, 32 * w, h);
+      put_act(hid, h);
       __syncthreads();
-      const f32x16 y = PF ? gemm(wa, hid) : gemm_from(w2_tile(c), hid);
+      // a fresh accumulator: reading its sum into s_next orders the refill of wa behind the product
+      f32x16 y = {};
+      if (W3) gemm(y, wc, hid);
+      else if (PF) gemm(y, wa, hid);
+      else gemm_from(y, w2_tile(c), hid);
 #pragma unroll
       for (int v = 0; v < 16; ++v) s_next[v] += y[v];
       __builtin_amdgcn_sched_barrier(0);
       if (PF && c + 1 < nc) fetch(wa, w2_tile(c + 1));
       __syncthreads();
     }
-    if (tok) {
+    if (A.splits > 1) {
+      // in register order (the reader's thread holds the same elements): every
+      // access of a wave is one contiguous 512-byte piece
+      auto part_at = [&](int k, int i) {
+        return reinterpret_cast<uint64_t*>(A.spart) + (((int64_t)k * A.groups + group) * 8 + i) * NT + threadIdx.x;
+      };
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+        __hip_atomic_store(part_at(split, i),
+                           (uint64_t)__float_as_uint(s_next[2 * i]) |
+                               ((uint64_t)__float_as_uint(s_next[2 * i + 1]) << 32),
+                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the part is in memory before its arrival is counted
+      __syncthreads();
+      if (threadIdx.x == 0)
+        arrived = __hip_atomic_fetch_add(A.cnt + (int64_t)A.layer * A.groups + group, 1, __ATOMIC_RELAXED,
+                                         __HIP_MEMORY_SCOPE_AGENT);
+      __syncthreads();
+      if (arrived != A.splits - 1) {
+        report();
+        return;
+      }
+      s_next = f32x16{};
+      for (int k = 0; k < A.splits; ++k)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          const uint64_t v = __hip_atomic_load(part_at(k, i), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          s_next[2 * i] += __uint_as_float(static_cast<uint32_t>(v));
+          s_next[2 * i + 1] += __uint_as_float(static_cast<uint32_t>(v >> 32));
+        }
+    }
+    if (live(tcol)) {
       if (ql >= 0) {
         store_f32(A.s_out, s_next);
       } else {
-        bf16_bits* p = A.out + t * D + 32 * w + 4 * hi;
+        bf16_bits* p = A.out + (tb + tcol) * D + 32 * w + 4 * hi;
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
           uint2 pk;
@@ -928,18 +1081,22 @@ __global__ __launch_bounds__(64 * (D / 32)) void update_kernel(UpdateArgs A) {
       report();
       return;
     }
-    put_act(act, 32 * w, s_next);  // act (u) was last read before the previous barrier
+    put_act(act, s_next);  // act (u) was last read before the previous barrier
     __syncthreads();
   }
   // next queries: Q = s W_Q^{next}, scaled into log2 units, permuted (QN layout)
-  f32x16 q = PF || A.mode == 0 ? gemm(wb, act) : gemm_from(wq_tile(A.layer + 1), act);
+  f32x16 q = {};
+  if (W3) gemm(q, wa, act);
+  else if (PF || A.mode == 0) gemm(q, wb, act);
+  else gemm_from(q, wq_tile(A.layer + 1), act);
   const float qs = kLog2e * 0.17677669529663687f;  // log2(e) / sqrt(32)
+  if (live(tcol)) {
 #pragma unroll
-  for (int v = 0; v < 16; ++v) q[v] *= qs;
-  if (tok) {
-#pragma unroll
-    for (int v = 0; v < 16; ++v) chk(q[v]);
-    f16x8* qn = A.QN + (t * D + 32 * w) / 8;
+    for (int v = 0; v < 16; ++v) {
+      q[v] *= qs;
+      chk(q[v]);
+    }
+    f16x8* qn = A.QN + ((tb + tcol) * D + 32 * w) / 8;
     qn[hi] = pack8h(q, 0);
     qn[2 + hi] = pack8h(q, 8);
   }
@@ -1030,6 +1187,27 @@ hipError_t fast_fused(int D, int wide, const Unit* units, const WsHeader* hdr, i
   return hipGetLastError();
 }
 
+// At d = 256, F = 4 d: as many splits as the CUs take in one round, with the
+// groups narrow first (a group's merge is a chain over its rows).  Measured a
+// call, us, at 64 requests of 1024 rows: 768 targets 16 x 4 160, 16 x 2 162,
+// 16 x 1 174, 8 x 4 (two rounds) 207; 1536 targets 16 x 2 170, 32 x 4 175,
+// 16 x 1 179; 3072 targets 16 x 1 202, 32 x 2 203; 18000 targets 32 x 1 739,
+// 16 x 1 854.  One request of 40 targets: 8 x 4 246, 16 x 4 256, 16 x 1 275.
+// Smaller models stream too little for the exchange to pay (d = 128, 1024
+// targets: 16 x 1 55, 16 x 2 59).
+UpdatePlan update_plan(int64_t n_tgt, int D, int F, int n_cu) {
+  UpdatePlan p;
+  p.tg0 = ceil_div(n_tgt, 32) < n_cu ? 16 : 32;
+  p.tg = p.tg0;
+  p.splits = 1;
+  if (F != 4 * D || D < 256) return p;
+  if (ceil_div(n_tgt, 8) * 4 <= n_cu) return {8, 4, p.tg0};
+  if (ceil_div(n_tgt, 16) * 4 <= n_cu) return {16, 4, p.tg0};
+  if (ceil_div(n_tgt, 16) * 2 <= n_cu) return {16, 2, p.tg0};
+  p.tg = ceil_div(n_tgt, 16) <= n_cu ? 16 : 32;
+  return p;
+}
+
 hipError_t fast_update(int D, const FastUpdate& f, hipStream_t st) {
   UpdateArgs A;
   A.mode = f.mode;
@@ -1052,24 +1230,45 @@ hipError_t fast_update(int D, const FastUpdate& f, hipStream_t st) {
   A.W1P = (const f16x8*)f.W1P;
   A.W2P = (const f16x8*)f.W2P;
   A.WqP = (const f16x8*)f.WqP;
-  A.tg = f.tg == 16 ? 16 : 32;
   A.range = f.range;
+  A.max_ch = f.max_ch;
   if (f.n_tgt == 0) return hipSuccess;
   if (!f.range) return hipErrorInvalidValue;
-  dim3 g(static_cast<unsigned>(ceil_div(f.n_tgt, A.tg)));
-  const size_t lds = (size_t)32 * (D + 8) * 2 * (f.mode == 0 ? 1 : 2);
-#define STCA_UPD(DD)                                                                         \
-  if (f.F == 4 * (DD))                                                                      \
-    hipLaunchKernelGGL((update_kernel<DD, 4>), g, dim3(64 * (DD / 32)), lds, st, A);        \
-  else                                                                                      \
-    hipLaunchKernelGGL((update_kernel<DD, 0>), g, dim3(64 * (DD / 32)), lds, st, A)
+  const UpdatePlan& P = f.plan;
+  // the cuts with a kernel: see update_plan
+  const bool split_ok = D == 256 && f.F == 4 * D && f.spart && f.cnt &&
+                        ((P.splits == 4 && (P.tg == 8 || P.tg == 16)) || (P.splits == 2 && P.tg == 16));
+  if ((f.mode && (f.max_ch < 1 || f.max_ch > kMaxChunks)) || (P.tg0 != 16 && P.tg0 != 32) ||
+      !(P.splits == 1 ? P.tg == 16 || P.tg == 32 : split_ok))
+    return hipErrorInvalidValue;
+  A.splits = P.splits;
+  A.groups = static_cast<int>(ceil_div(f.n_tgt, P.tg));
+  A.spart = f.spart;
+  A.cnt = P.splits > 1 ? f.cnt : nullptr;
+  // the initial queries are one product: no splits, and groups that fill the CUs
+  A.tg = f.mode == 0 ? P.tg0 : P.tg;
+  const int64_t blocks = f.mode == 0 ? ceil_div(f.n_tgt, A.tg) : (int64_t)A.groups * A.splits;
+  dim3 g(static_cast<unsigned>(blocks));
+#define STCA_UPD1(DD, NC, TG) hipLaunchKernelGGL((update_kernel<DD, NC, TG>), g, dim3(64 * (DD / 32)), 0, st, A)
+#define STCA_UPD(DD)                                                             \
+  if (f.F != 4 * (DD)) {                                                         \
+    if (A.tg == 16) STCA_UPD1(DD, 0, 16); else STCA_UPD1(DD, 0, 32);             \
+  } else {                                                                       \
+    if (A.tg == 16) STCA_UPD1(DD, 4, 16); else STCA_UPD1(DD, 4, 32);             \
+  }
   switch (D) {
     case 64: STCA_UPD(64); break;
     case 128: STCA_UPD(128); break;
-    case 256: STCA_UPD(256); break;
+    case 256:
+      if (f.mode != 0 && A.splits == 4 && A.tg == 8) STCA_UPD1(256, 1, 8);
+      else if (f.mode != 0 && A.splits == 4) STCA_UPD1(256, 1, 16);
+      else if (f.mode != 0 && A.splits == 2) STCA_UPD1(256, 2, 16);
+      else STCA_UPD(256);
+      break;
     default: return hipErrorInvalidValue;
   }
 #undef STCA_UPD
+#undef STCA_UPD1
   return hipGetLastError();
 }
 
