@@ -203,16 +203,28 @@ __device__ __forceinline__ void add4(float (&x)[4], const bf16_bits* p) {
 
 // Backward of one (request chunk, head): dK/dV of the chunk's rows summed over
 // every target of the request (the workgroup of the request's first target
-// group does the whole request, 16 targets at a time; later batches add to
-// what the first wrote), and the chunk's dq partial for each of those targets.
+// group does the whole request), and the chunk's dq partial for each of its
+// targets.  The targets' operands are staged in LDS kPass at a time and a row
+// tile takes every batch of 16 of them before it leaves the registers, so K
+// and V are read and dK | dV written once per kPass targets (a request of
+// more adds to what the first pass wrote) and dK, dV are summed in fp32.  With
+// the batches in the outer loop, K and V were read and dK | dV read, added to
+// and rounded once per 16 targets: 64 requests of 256..2048 rows and 1..64
+// targets took 301 us a layer (d = 256, bf16 rows out), now 144.
+// Two waves a SIMD at d_h = 32 (236 registers; one wave without the bound:
+// 210 us); d_h = 64 holds half the batches instead.
 template <int DH, typename OT>
-__global__ __launch_bounds__(64 * kWaves) void attn_bwd_mfma_kernel(
+__global__ __launch_bounds__(64 * kWaves, DH > 32 ? 1 : 2) void attn_bwd_mfma_kernel(
     const Unit* __restrict__ units, const WsHeader* __restrict__ hdr, const int32_t* __restrict__ toff,
     const float* __restrict__ Q, const float* __restrict__ KV, int d, const float* __restrict__ a,
     const float* __restrict__ da, const float* __restrict__ lse, OT* __restrict__ dKV, int64_t ldkv,
     bf16_bits* __restrict__ dKVT, int64_t ldt, float* __restrict__ dq_part, int64_t n_tgt, int n_heads) {
   constexpr int DT = DH / 16;
   constexpr int KQ = DH / 4;
+  constexpr int kBatches = DH > 32 ? 2 : 4;
+  constexpr int kPass = 16 * kBatches;
+  constexpr int QP = DH + 4;  // padded rows: 16-byte reads of 16 rows spread over the banks
+  __shared__ __attribute__((aligned(16))) float qs[kPass][QP], das[kPass][QP];
   __shared__ float pT[kWaves][kRows][17], eT[kWaves][kRows][17];
   __shared__ float red[kWaves][16][DH];
   const int u = blockIdx.x;
@@ -245,82 +257,99 @@ __global__ __launch_bounds__(64 * kWaves) void attn_bwd_mfma_kernel(
       for (int dt = 0; dt < DT; ++dt) T.kc[dt][ks] = row < hi ? Kh[row * ld + 16 * dt + r] : 0.f;
     }
   };
-  for (int tb = T0; tb < T1; tb += 16) {
-    const int nb = min(16, T1 - tb);
-    const bool first = tb == T0;
-    const bool live = r < nb;
-    const int64_t t = tb + (live ? r : 0);
-    // B operands of S^T and dP^T: target r, dimensions g KQ ..
-    float qb[KQ], dab[KQ];
-    load_run<KQ>(qb, Q + t * d + j * DH + g * KQ, live);
-    load_run<KQ>(dab, da + t * d + j * DH + g * KQ, live);
-    float Dt = 0.f;
-    if (live)
-      for (int e = 0; e < DH; ++e) Dt += da[t * d + j * DH + e] * a[t * d + j * DH + e];
-    const float lt = live ? lse[t * n_heads + j] * kLog2e : INFINITY;
-    // A operands of dV^T and dK^T: target 4 s + g, dimension 16 dt + r
-    float qa[DT][4], daa[DT][4];
-#pragma unroll
-    for (int ks = 0; ks < 4; ++ks) {
-      const int tt = 4 * ks + g;
-#pragma unroll
-      for (int dt = 0; dt < DT; ++dt) {
-        qa[dt][ks] = tt < nb ? Q[(int64_t)(tb + tt) * d + j * DH + 16 * dt + r] : 0.f;
-        daa[dt][ks] = tt < nb ? da[(int64_t)(tb + tt) * d + j * DH + 16 * dt + r] : 0.f;
-      }
+  for (int tp = T0; tp < T1; tp += kPass) {
+    const int np = min(kPass, T1 - tp);
+    const bool first = tp == T0;
+    __syncthreads();  // every wave is done with the previous pass's operands
+    for (int i = threadIdx.x; i < kPass * (DH / 4); i += 64 * kWaves) {
+      const int row = i / (DH / 4), c = 4 * (i % (DH / 4));
+      const int64_t o = (int64_t)(tp + (row < np ? row : 0)) * d + j * DH + c;
+      const float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
+      *reinterpret_cast<float4*>(&qs[row][c]) = row < np ? *reinterpret_cast<const float4*>(Q + o) : z;
+      *reinterpret_cast<float4*>(&das[row][c]) = row < np ? *reinterpret_cast<const float4*>(da + o) : z;
     }
-    f32x4 dq[DT];
+    __syncthreads();
+    // statistics of target 16 b + r
+    float lt[kBatches], Dt[kBatches];
+    f32x4 dq[kBatches][DT];
 #pragma unroll
-    for (int dt = 0; dt < DT; ++dt) dq[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int b = 0; b < kBatches; ++b) {
+      const bool live = 16 * b + r < np;
+      const int64_t t = tp + (live ? 16 * b + r : 0);
+      float dd = 0.f;
+      if (live)
+#pragma unroll
+        for (int e = 0; e < KQ; e += 4) {
+          const float4 x = *reinterpret_cast<const float4*>(a + t * d + j * DH + g * KQ + e);
+          const float4 y = *reinterpret_cast<const float4*>(&das[16 * b + r][g * KQ + e]);
+          dd += x.x * y.x + x.y * y.y + x.z * y.z + x.w * y.w;
+        }
+      dd += __shfl_xor(dd, 16);
+      dd += __shfl_xor(dd, 32);
+      Dt[b] = dd;
+      lt[b] = live ? lse[t * n_heads + j] * kLog2e : INFINITY;
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt) dq[b][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
     Tile cur, nxt;
     if (w < nrt) fetch(w, nxt);
     for (int rt = w; rt < nrt; rt += kWaves) {
       cur = nxt;
       if (rt + kWaves < nrt) fetch(rt + kWaves, nxt);
       const int row0 = lo + rt * kRows;
-      // S^T and dP^T = V dA^T: k-step s, lane group g <-> dimension g KQ + s
-      // (four independent chains: even and odd k-steps of each product)
-      f32x4 s = {0.f, 0.f, 0.f, 0.f}, dp = {0.f, 0.f, 0.f, 0.f};
-      f32x4 s1 = {0.f, 0.f, 0.f, 0.f}, dp1 = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int ks = 0; ks < KQ; ks += 2) {
-        s = mma(cur.k[ks], qb[ks], s);
-        dp = mma(cur.v[ks], dab[ks], dp);
-        s1 = mma(cur.k[ks + 1], qb[ks + 1], s1);
-        dp1 = mma(cur.v[ks + 1], dab[ks + 1], dp1);
-      }
-      s += s1;
-      dp += dp1;
-      float p[4], de[4];
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        p[v] = row0 + 4 * g + v < hi ? exp2f(s[v] - lt) : 0.f;
-        de[v] = p[v] * (dp[v] - Dt);
-      }
-      // dQ^T += K^T dE^T: k-step s, lane group g <-> row 4 g + s
-#pragma unroll
-      for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-        for (int ks = 0; ks < 4; ++ks) dq[dt] = mma(cur.kc[dt][ks], de[ks], dq[dt]);
-      // P and dE to row-major tiles for the products over targets
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        pT[w][4 * g + v][r] = p[v];
-        eT[w][4 * g + v][r] = de[v];
-      }
-      wave_sync();
-      // dV^T += dA^T P, dK^T += Q^T dE: k-step s, lane group g <-> target 4 s + g
       f32x4 dv[DT], dk[DT];
 #pragma unroll
-      for (int dt = 0; dt < DT; ++dt) {
-        dv[dt] = dk[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int dt = 0; dt < DT; ++dt) dv[dt] = dk[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int b = 0; b < kBatches; ++b) {
+        if (16 * b >= np) break;
+        // B operands of S^T and dP^T: target r, dimensions g KQ ..
+        float qb[KQ], dab[KQ];
+        load_run<KQ>(qb, &qs[16 * b + r][g * KQ], true);
+        load_run<KQ>(dab, &das[16 * b + r][g * KQ], true);
+        // S^T and dP^T = V dA^T: k-step s, lane group g <-> dimension g KQ + s
+        // (four independent chains: even and odd k-steps of each product)
+        f32x4 s = {0.f, 0.f, 0.f, 0.f}, dp = {0.f, 0.f, 0.f, 0.f};
+        f32x4 s1 = {0.f, 0.f, 0.f, 0.f}, dp1 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int ks = 0; ks < KQ; ks += 2) {
+          s = mma(cur.k[ks], qb[ks], s);
+          dp = mma(cur.v[ks], dab[ks], dp);
+          s1 = mma(cur.k[ks + 1], qb[ks + 1], s1);
+          dp1 = mma(cur.v[ks + 1], dab[ks + 1], dp1);
+        }
+        s += s1;
+        dp += dp1;
+        float p[4], de[4];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          p[v] = row0 + 4 * g + v < hi ? exp2f(s[v] - lt[b]) : 0.f;
+          de[v] = p[v] * (dp[v] - Dt[b]);
+        }
+        // P and dE to row-major tiles for the products over targets
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          pT[w][4 * g + v][r] = p[v];
+          eT[w][4 * g + v][r] = de[v];
+        }
+        // dQ^T += K^T dE^T: k-step s, lane group g <-> row 4 g + s
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+          for (int ks = 0; ks < 4; ++ks) dq[b][dt] = mma(cur.kc[dt][ks], de[ks], dq[b][dt]);
+        wave_sync();
+        // dV^T += dA^T P, dK^T += Q^T dE: k-step s, lane group g <-> target 4 s + g
 #pragma unroll
         for (int ks = 0; ks < 4; ++ks) {
-          dv[dt] = mma(daa[dt][ks], pT[w][r][4 * ks + g], dv[dt]);
-          dk[dt] = mma(qa[dt][ks], eT[w][r][4 * ks + g], dk[dt]);
+          const float pv = pT[w][r][4 * ks + g], ev = eT[w][r][4 * ks + g];
+#pragma unroll
+          for (int dt = 0; dt < DT; ++dt) {
+            dv[dt] = mma(das[16 * b + 4 * ks + g][16 * dt + r], pv, dv[dt]);
+            dk[dt] = mma(qs[16 * b + 4 * ks + g][16 * dt + r], ev, dk[dt]);
+          }
         }
+        wave_sync();
       }
-      wave_sync();
       // dk[dt][v], dv[dt][v]: dimension 16 dt + 4 g + v of row row0 + r
       const int tok = row0 + r;
       if (tok < hi) {
@@ -348,19 +377,24 @@ __global__ __launch_bounds__(64 * kWaves) void attn_bwd_mfma_kernel(
         }
       }
     }
-    // dq of this batch's targets: sum the four waves' partials
-#pragma unroll
-    for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) red[w][r][16 * dt + 4 * g + v] = dq[dt][v];
-    __syncthreads();
+    // dq of this pass's targets: sum the four waves' partials
     const float scale = 1.f / sqrtf((float)DH);
-    for (int it = threadIdx.x; it < nb * DH; it += 64 * kWaves) {
-      const int tt = it / DH, e = it % DH;
-      const float vsum = red[0][tt][e] + red[1][tt][e] + red[2][tt][e] + red[3][tt][e];
-      dq_part[((int64_t)un.c * n_tgt + tb + tt) * d + j * DH + e] = vsum * scale;
+#pragma unroll
+    for (int b = 0; b < kBatches; ++b) {
+      if (16 * b >= np) break;
+      if (b > 0) __syncthreads();
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) red[w][r][16 * dt + 4 * g + v] = dq[b][dt][v];
+      __syncthreads();
+      const int nb = min(16, np - 16 * b);
+      for (int it = threadIdx.x; it < nb * DH; it += 64 * kWaves) {
+        const int tt = it / DH, e = it % DH;
+        const float vsum = red[0][tt][e] + red[1][tt][e] + red[2][tt][e] + red[3][tt][e];
+        dq_part[((int64_t)un.c * n_tgt + tp + 16 * b + tt) * d + j * DH + e] = vsum * scale;
+      }
     }
-    __syncthreads();
   }
 }
 
