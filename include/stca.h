@@ -99,19 +99,22 @@ typedef enum { STCA_F32 = 0, STCA_BF16 = 1 } stca_dtype_t;
  *          requests of up to 256 / n_heads targets (d_h = 32, host offsets
  *          given); STCA_ERR_UNSUPPORTED for other batches.
  * bwd_form STCA_BWD_AUTO: with d_h = 32, ffn_hidden a multiple of d_model and
- *          host offsets showing at most 32 targets per request, the
- *          backward on bf16 storage runs in the reordered form (the
- *          attention gradients through u = q W_K^T and h = da W_V^T per
- *          target and head, no K, V, dK or dV; Sec. 3.1's reordering applied
- *          to the backward) when d_model is 128 or 256, every request has
- *          at most 128 / n_heads targets and no request's history is longer
- *          than twice one compute unit's share of the batch's history
- *          blocks, else in the fused form (K/V formed
+ *          host offsets showing at most 32 targets per request (128 with
+ *          d_model 128 or 256), the backward on bf16 storage runs in the
+ *          reordered form (the attention gradients through u = q W_K^T and
+ *          h = da W_V^T per target and head, no K, V, dK or dV, in groups of
+ *          128 / n_heads targets; Sec. 3.1's reordering applied to the
+ *          backward; d_model 128 or 256) or in the fused form (K/V formed
  *          inside the attention kernels, dK | dV written for the
- *          history-side products); otherwise K | V are formed by a GEMM and
- *          the attention runs in exact fp32 (generic).
+ *          history-side products; at most 32 targets per request).  It is
+ *          reordered for more than 32 targets, for histories balanced over
+ *          the compute units with at most 128 / n_heads targets, and else
+ *          where an estimate of the two forms' kernels favours it.
+ *          Otherwise K | V are formed by a GEMM and the attention runs in
+ *          exact fp32 (generic).
  *          STCA_BWD_GENERIC: always the generic form.  STCA_BWD_FUSED: the
- *          fused form.  STCA_BWD_REORDERED: the reordered form.  Each is
+ *          fused form.  STCA_BWD_REORDERED: the reordered form with one
+ *          target group per request (at most 128 / n_heads targets).  Each is
  *          STCA_ERR_UNSUPPORTED for a batch outside its conditions.
  * chunk_blocks: history chunk length, in 32-row blocks, of the attention's
  *          split over a request's history (at most 16 chunks per request, so

@@ -65,48 +65,144 @@ bool wide_groups_for(const stca_dims_t* dims, const stca_batch_t* b) {
   return false;
 }
 
-// The bf16 backward projects the history inside its attention kernels (no
-// K/V copy in HBM) and recomputes the target side in one kernel per layer
-// when d_h = 32, the FFN width is a multiple of d and every request has at
-// most 32 targets, which the host offsets must show; otherwise K | V are
-// formed by a GEMM, the attention runs exactly in fp32 and the target side as
-// separate GEMMs.  Within the fused conditions, d_model of 128 or 256 and at
-// most kRbPairs / n_heads targets per request allow the reordered form (no
-// K, V, dK, dV; the automatic choice there when the batch's histories are
-// balanced over the CUs).  STCA_BWD_GENERIC forces the
-// generic form; STCA_BWD_FUSED and STCA_BWD_REORDERED ask for theirs and are
-// unsupported for other batches.  2 (reordered) / 1 (fused) / 0 (generic) /
-// negative status.
-int fused_bwd_for(const stca_dims_t* dims, const stca_batch_t* b) {
-  if (dims->bwd_form == STCA_BWD_GENERIC) return 0;
-  bool ok = dims->dtype == STCA_BF16 && dims->d_model / dims->n_heads == 32 &&
-            (dims->d_model == 64 || dims->d_model == 128 || dims->d_model == 256) &&
-            dims->ffn_hidden % dims->d_model == 0 && b->tgt_off_host != nullptr;
-  bool rd = ok && (dims->d_model == 128 || dims->d_model == 256) && b->hist_off_host != nullptr;
-  for (int r = 0; ok && r < b->n_requests; ++r) {
-    const int64_t m = b->tgt_off_host[r + 1] - b->tgt_off_host[r];
-    if (m > 32) ok = false;
-    if (m * dims->n_heads > kRbPairs) rd = false;
+// The targets of a group of the reordered backward.
+inline int rb_group(const stca_dims_t* dims) { return kRbPairs / dims->n_heads; }
+
+// Chunk length (blocks) of the reordered backward's attention units (history
+// chunk x target group), which the device takes one a CU in descending size:
+// of the longest history cut into 1 .. kMaxChunks pieces and of 1, 3/2, 2 and
+// 4 units a CU, the one whose makespan is least when the units are dealt in
+// descending size in alternating rounds, in blocks of work (about 2.7 us at
+// d = 256): a unit costs its blocks, 3 for loading its operands and, when its
+// request has several chunks, 6 for writing its Z and Y partials.  *span
+// receives the makespan.
+int rb_chunk_for(const stca_dims_t* dims, const stca_batch_t* b, int n_cu, int64_t* span = nullptr) {
+  const int M = rb_group(dims);
+  struct Req {
+    int32_t nb, ng;
+  };
+  std::vector<Req> req;
+  int64_t total = 0, longest = 1, units = 0;
+  for (int r = 0; r < b->n_requests; ++r) {
+    const int32_t m = b->tgt_off_host[r + 1] - b->tgt_off_host[r];
+    if (m < 1) continue;
+    const int32_t nb = static_cast<int32_t>(ceil_div(b->hist_off_host[r + 1], kBlockTokens) -
+                                            b->hist_off_host[r] / kBlockTokens);
+    const int32_t ng = (m + M - 1) / M;
+    req.push_back({nb, ng});
+    total += static_cast<int64_t>(nb) * ng;
+    units += ng;
+    longest = std::max<int64_t>(longest, nb);
   }
-  rd = rd && ok;
-  if (dims->bwd_form == STCA_BWD_FUSED) return ok ? 1 : STCA_ERR_UNSUPPORTED;
-  if (dims->bwd_form == STCA_BWD_REORDERED) return rd ? 2 : STCA_ERR_UNSUPPORTED;
-  // automatic: the reordered form when no request's history is much longer
-  // than one CU's share of the batch (its attention pass streams a request
-  // per unit and splits long requests into chunks whose Z, Y partials cost
-  // extra traffic; on bimodal stochastic-length batches the fused form is
-  // faster)
-  if (rd) {
-    int64_t total = 0, longest = 0;
-    for (int r = 0; r < b->n_requests; ++r) {
-      if (b->tgt_off_host[r + 1] == b->tgt_off_host[r]) continue;
-      const int64_t nb = ceil_div(b->hist_off_host[r + 1], kBlockTokens) - b->hist_off_host[r] / kBlockTokens;
-      total += nb;
-      longest = std::max(longest, nb);
+  std::vector<int64_t> cand;
+  if (dims->chunk_blocks >= 1) {
+    cand.push_back(dims->chunk_blocks);
+  } else {
+    for (int q = 1; q <= kMaxChunks; ++q) cand.push_back(std::max<int64_t>(8, ceil_div(longest, q)));
+    for (const int q : {2, 3, 4, 8})
+      cand.push_back(std::max<int64_t>(8, ceil_div(2 * total, q * static_cast<int64_t>(n_cu))));
+    std::sort(cand.begin(), cand.end(), std::greater<int64_t>());
+    cand.erase(std::unique(cand.begin(), cand.end()), cand.end());
+  }
+  int64_t best = cand[0], best_span = -1;
+  std::vector<int32_t> cnt;
+  std::vector<int64_t> load;
+  for (int64_t c : cand) {
+    c = std::min<int64_t>(c, 1 << 16);
+    const int32_t ci = static_cast<int32_t>(c), top = static_cast<int32_t>(std::min<int64_t>(longest, 1 << 16));
+    // (bounds the host work: beyond, or with a history of 2^21 rows, no estimate)
+    if (longest > (1 << 16) || units * std::min<int64_t>(kMaxChunks, ceil_div(longest, c)) > 32 * (int64_t)n_cu) continue;
+    cnt.assign(top + 10, 0);
+    for (const Req& q : req) {
+      int32_t nch = std::min((q.nb + ci - 1) / ci, static_cast<int32_t>(kMaxChunks));
+      const int32_t cb = (q.nb + nch - 1) / nch;
+      nch = (q.nb + cb - 1) / cb;
+      const int32_t extra = nch > 1 ? 9 : 3;
+      cnt[cb + extra < top + 10 ? cb + extra : top + 9] += q.ng * (nch - 1);
+      cnt[std::min(q.nb - (nch - 1) * cb + extra, top + 9)] += q.ng;
     }
-    rd = longest <= 2 * ceil_div(total, device_cus());
+    load.assign(n_cu, 0);
+    int pos = 0, step = 1;  // 0 .. n_cu - 1, n_cu - 1 .. 0, ...
+    for (int32_t x = top + 9; x > 0; --x)
+      for (int32_t k = 0; k < cnt[x]; ++k) {
+        load[pos] += x;
+        if (pos + step < 0 || pos + step >= n_cu) step = -step;
+        else pos += step;
+      }
+    const int64_t s = *std::max_element(load.begin(), load.end());
+    if (best_span < 0 || s < best_span) {
+      best_span = s;
+      best = c;
+    }
   }
-  return rd ? 2 : ok ? 1 : 0;
+  if (best_span < 0) best = chunk_blocks_for(b, n_cu, 1, dims->chunk_blocks);
+  if (span) *span = best_span < 0 ? ceil_div(total, n_cu) : best_span;
+  return static_cast<int>(best);
+}
+
+// The bf16 backward recomputes the forward with the history projected inside
+// the attention kernel and the target side in one kernel per layer when
+// d_h = 32, the FFN width is a multiple of d and the host offsets are given;
+// its history side is then, for at most 32 targets per request, the fused
+// form (no K/V copy in HBM) or with d_model of 128 or 256 the reordered one (no
+// K, V, dK, dV; groups of rb_group targets), and for more targets the exact
+// fp32 attention over one layer's K | V at a time.  Otherwise every layer's K
+// | V are formed by a GEMM, the attention runs exactly in fp32 both ways and
+// the target side as separate GEMMs.  STCA_BWD_GENERIC forces that generic
+// form; STCA_BWD_FUSED asks for the fused one, STCA_BWD_REORDERED for the
+// reordered one with one target group per request, and both are unsupported
+// for other batches.  3 (fp32 attention) / 2 (reordered) / 1 (fused) / 0
+// (generic) / negative status.  *record: the batch has a training record (at
+// most 32 targets per request).  *rb_chunk: rb_chunk_for where the choice
+// needed it, else 0.
+int fused_bwd_for(const stca_dims_t* dims, const stca_batch_t* b, bool* record, int* rb_chunk) {
+  *record = false;
+  *rb_chunk = 0;
+  if (dims->bwd_form == STCA_BWD_GENERIC) return 0;
+  const bool shape = dims->dtype == STCA_BF16 && dims->d_model / dims->n_heads == 32 &&
+                     (dims->d_model == 64 || dims->d_model == 128 || dims->d_model == 256) &&
+                     dims->ffn_hidden % dims->d_model == 0 && b->tgt_off_host != nullptr;
+  int64_t mmax = 0, total = 0, longest = 0;
+  for (int r = 0; shape && r < b->n_requests; ++r) {
+    const int64_t m = b->tgt_off_host[r + 1] - b->tgt_off_host[r];
+    mmax = std::max(mmax, m);
+    if (m == 0) continue;
+    const int64_t nb = ceil_div(b->hist_off_host[r + 1], kBlockTokens) - b->hist_off_host[r] / kBlockTokens;
+    total += nb;
+    longest = std::max(longest, nb);
+  }
+  const bool ok = shape && mmax <= 32;
+  const bool wide_d = shape && (dims->d_model == 128 || dims->d_model == 256);
+  const bool rd = ok && wide_d && mmax <= rb_group(dims);
+  if (dims->bwd_form == STCA_BWD_FUSED && !ok) return STCA_ERR_UNSUPPORTED;
+  if (dims->bwd_form == STCA_BWD_REORDERED && !rd) return STCA_ERR_UNSUPPORTED;
+  *record = ok;
+  if (dims->bwd_form == STCA_BWD_FUSED) return 1;
+  if (dims->bwd_form == STCA_BWD_REORDERED) return 2;
+  const int n_cu = device_cus();
+  // histories balanced over the CUs: one unit per request, no partials
+  if (rd && longest <= 2 * ceil_div(total, n_cu)) return 2;
+  if (!ok) return shape ? 3 : 0;
+  // Otherwise the cheaper of the two by what their kernels took per layer
+  // (ns): fused, attention and ring GEMMs per block; reordered, the attention
+  // pass per block of its makespan, dX per (block, target group), and the
+  // preparation, partial sums and grouped products.  Measured a step, us,
+  // fused against reordered: stochastic lengths (256 requests) 3490, 2750;
+  // 256 ragged requests of 1..16 targets 2374, 2056, of 16..32 2616, 2715;
+  // 20 of them 716, 830; d = 128, 1..32 targets 1475, 1434.
+  if (!wide_d || total < n_cu) return 1;
+  int64_t span = 0, pairs = 0;
+  *rb_chunk = rb_chunk_for(dims, b, n_cu, &span);
+  for (int r = 0; r < b->n_requests; ++r) {
+    const int64_t m = b->tgt_off_host[r + 1] - b->tgt_off_host[r];
+    if (m > 0)
+      pairs += (ceil_div(b->hist_off_host[r + 1], kBlockTokens) - b->hist_off_host[r] / kBlockTokens) *
+               ceil_div(m, rb_group(dims));
+  }
+  const bool d256 = dims->d_model == 256;
+  const double fused = (d256 ? 41. : 23.) * total + 12e3;
+  const double reordered = d256 ? 2600. * span + 6.5 * pairs + 65e3 : 1500. * span + 3.6 * pairs + 40e3;
+  return reordered < fused ? 2 : 1;
 }
 
 struct Layout {
@@ -127,6 +223,7 @@ struct Layout {
   bool wide;                  // materialised K/V, units of up to kWideGroup targets (bf16 path)
   bool bfused;                // backward with the history projection inside the attention kernels
   bool brd;                   // ... in the reordered form (no K, V, dK, dV)
+  bool b32;                   // ... in the recomputation only, the attention backward exact in fp32
   int group;                  // targets per attention unit
   // common
   size_t hdr, units, tchunks, part_acc, part_ml, state_a, state_b;
@@ -155,7 +252,11 @@ struct Layout {
   size_t rb_e, rb_w, rb_u16, rb_st, rb_z, rb_y, rb_q16, rb_da16, rb_hdr, rb_units, rb_hdrx, rb_unitsx, rb_tch;
   size_t rb_tchx, rb_zp, rb_yp, rb_first;
   int64_t rb_maxx, rb_maxu;
-  int rb_cb;  // history chunk length (blocks) of the reordered attention's units
+  size_t rb_order;
+  int rb_cb;      // history chunk length (blocks) of the reordered attention's units
+  int rb_groups;  // target groups per request (the most of any)
+  bool record;    // the batch has a training record
+  bool rb_partials;  // some request of the reordered backward is cut into several chunks
   int64_t gpart_floats, nh8;
   size_t total;
 };
@@ -209,12 +310,19 @@ stca_status_t make_layout(const stca_dims_t* dims, const stca_batch_t* b, int wi
   L->std_lo = L->mixed ? mixed_cap(dims) + 1 : (L->reord ? 1 << 30 : 1);
   L->reord_lo = 1;
   L->reord_hi = L->mixed ? mixed_cap(dims) : (L->reord ? 1 << 30 : 0);
-  L->bfused = false;
+  L->bfused = L->brd = L->b32 = L->record = false;
+  if (with_backward) {
+    const int fb = fused_bwd_for(dims, b, &L->record, &L->rb_cb);
+    if (fb < 0) return static_cast<stca_status_t>(fb);
+    L->bfused = fb >= 1;
+    L->brd = fb == 2;
+    L->b32 = fb == 3;
+  }
   const bool std_part = !L->reord || L->mixed;
   L->wide = p == 1 && !with_backward && std_part && wide_groups_for(dims, b);
   L->mat = p == 1 && !with_backward && std_part && (L->wide || dims->kv_form == STCA_KV_MATERIALIZE);
-  L->chunk_blocks = chunk_blocks_auto(b, device_cus(), dims->chunk_blocks, L->std_lo);
-  L->group = L->wide ? kWideGroup : kTargetGroup;
+  L->chunk_blocks = chunk_blocks_auto(b, device_cus(), dims->chunk_blocks, L->std_lo, 1 << 30, L->bfused ? 32 : 64);
+  L->group = L->wide ? kWideGroup : L->bfused ? 32 : kTargetGroup;
   L->max_units = std_part ? max_units_for(b, L->chunk_blocks, L->group, L->std_lo) : 0;
   // the reordered schedule spreads its own requests' rows over the chip
   int64_t rows2 = b->n_hist;
@@ -304,11 +412,8 @@ stca_status_t make_layout(const stca_dims_t* dims, const stca_batch_t* b, int wi
     }
   } else {
     const bool bf = dims->dtype == STCA_BF16;
-    const int fb = fused_bwd_for(dims, b);
-    if (fb < 0) return static_cast<stca_status_t>(fb);
-    L->bfused = bf && fb >= 1;
-    L->brd = bf && fb == 2;
-    L->kvs = L->bfused ? 0 : m.take(4 * n * nh * 2 * d);  // every layer's K | V rows, fp32
+    // every layer's K | V rows, fp32 (with b32 one layer's at a time)
+    L->kvs = L->bfused && !L->b32 ? 0 : m.take(4 * (L->b32 ? 1 : n) * nh * 2 * d);
     if (L->bfused) {
       L->fwkp = m.take(2 * n * d * d);
       L->fwvp = m.take(2 * n * d * d);
@@ -381,27 +486,39 @@ stca_status_t make_layout(const stca_dims_t* dims, const stca_batch_t* b, int wi
     }
     if (L->brd) {
       const size_t R = static_cast<size_t>(b->n_requests), hm = kRbPairs;
-      L->rb_e = m.take(2 * nh * n * 2 * hm);
-      L->rb_w = m.take(2 * R * n * 2 * hm * d);
-      L->rb_u16 = m.take(2 * R * hm * d);
-      L->rb_st = m.take(8 * R * hm);
+      const int M = rb_group(dims);
+      L->rb_groups = 1;
+      for (int r = 0; r < b->n_requests; ++r)
+        L->rb_groups = std::max(L->rb_groups, static_cast<int>(ceil_div(b->tgt_off_host[r + 1] - b->tgt_off_host[r], M)));
+      const size_t slots = R * L->rb_groups;
+      L->rb_e = m.take(2 * nh * L->rb_groups * n * 2 * hm);
+      L->rb_w = m.take(2 * slots * n * 2 * hm * d);
+      L->rb_u16 = m.take(2 * slots * hm * d);
+      L->rb_st = m.take(8 * slots * hm);
       L->rb_z = m.take(2 * L->h * nt * d);
       L->rb_y = m.take(2 * L->h * nt * d);
       L->rb_q16 = m.take(2 * nt * d);
       L->rb_da16 = m.take(2 * nt * d);
       L->rb_hdr = m.take(sizeof(WsHeader));
-      // about one unit per CU over the whole batch: long requests are cut into
-      // history chunks whose Z, Y partials are summed afterwards
-      L->rb_cb = chunk_blocks_for(b, device_cus(), 1, dims->chunk_blocks);
+      // long requests are cut into history chunks whose Z, Y partials are
+      // summed afterwards
+      if (L->rb_cb < 1) L->rb_cb = rb_chunk_for(dims, b, device_cus());
+      L->rb_partials = false;
+      for (int r = 0; r < b->n_requests; ++r)
+        if (b->tgt_off_host[r + 1] > b->tgt_off_host[r] &&
+            ceil_div(b->hist_off_host[r + 1], kBlockTokens) - b->hist_off_host[r] / kBlockTokens > L->rb_cb)
+          L->rb_partials = true;
       L->rb_maxu = std::max<int64_t>(1, host_count_units(b->hist_off_host, b->tgt_off_host, b->n_requests,
-                                                         L->rb_cb, 32));
+                                                         L->rb_cb, M));
+      L->rb_order = m.take(4 * static_cast<size_t>(L->rb_maxu));
       L->rb_units = m.take(sizeof(Unit) * static_cast<size_t>(L->rb_maxu));
       L->rb_zp = m.take(4 * static_cast<size_t>(L->rb_maxu) * hm * d);
       L->rb_yp = m.take(4 * static_cast<size_t>(L->rb_maxu) * hm * d);
-      L->rb_first = m.take(4 * std::max<size_t>(R, 1));
+      L->rb_first = m.take(4 * std::max<size_t>(slots, 1));
       L->rb_tchx = m.take(4 * std::max<size_t>(nt, 1));
       L->rb_hdrx = m.take(sizeof(WsHeader));
-      L->rb_maxx = std::max<int64_t>(1, host_count_units(b->hist_off_host, b->tgt_off_host, b->n_requests, 4, 32));
+      L->rb_maxx = std::max<int64_t>(
+          1, host_count_units(b->hist_off_host, b->tgt_off_host, b->n_requests, 4, 32));
       L->rb_unitsx = m.take(sizeof(Unit) * static_cast<size_t>(L->rb_maxx));
       L->rb_tch = m.take(4 * std::max<size_t>(nt, 1));
     }
@@ -639,10 +756,12 @@ stca_status_t backward_generic(const Layout& L, int bf, const stca_batch_t* b, c
   if (L.brd) {
     // history chunks of the requests for the reordered attention backward,
     // units of at most 128 rows for dX
-    HIPCHK(launch_sched(b->hist_off, b->tgt_off, b->n_requests, nh, nt, L.rb_cb, 32, at<Unit>(ws, L.rb_units),
-                        L.rb_maxu, at<int32_t>(ws, L.rb_tch), at<WsHeader>(ws, L.rb_hdr), st));
-    HIPCHK(launch_sched(b->hist_off, b->tgt_off, b->n_requests, nh, nt, 4, 32, at<Unit>(ws, L.rb_unitsx), L.rb_maxx,
-                        at<int32_t>(ws, L.rb_tchx), at<WsHeader>(ws, L.rb_hdrx), st));
+    // (largest first, all in one round: the device takes them in order)
+    HIPCHK(launch_sched(b->hist_off, b->tgt_off, b->n_requests, nh, nt, L.rb_cb, kRbPairs / h,
+                        at<Unit>(ws, L.rb_units), L.rb_maxu, at<int32_t>(ws, L.rb_tch), at<WsHeader>(ws, L.rb_hdr), st,
+                        1, 1 << 30, 1 << 30, at<int32_t>(ws, L.rb_order)));
+    HIPCHK(launch_sched(b->hist_off, b->tgt_off, b->n_requests, nh, nt, 4, 32, at<Unit>(ws, L.rb_unitsx),
+                        L.rb_maxx, at<int32_t>(ws, L.rb_tchx), at<WsHeader>(ws, L.rb_hdrx), st));
   }
   HIPCHK(rec.mark("sched"));
   void* dkv = L.brd ? nullptr : at<char>(ws, L.dkv);
@@ -741,7 +860,7 @@ stca_status_t backward_generic(const Layout& L, int bf, const stca_batch_t* b, c
     up.q_out = RQ(0);
     up.s16_out = FS16(0);
     HIPCHK(fast_update_precise(d, up, st));
-    HIPCHK(rec.mark("target_gemm"));
+    if (!L.b32) HIPCHK(rec.mark("target_gemm"));
   } else {
     HIPCHK(convert(bf, 0, tgt, RS(0), nt * d, st));
   }
@@ -827,7 +946,7 @@ stca_status_t backward_generic(const Layout& L, int bf, const stca_batch_t* b, c
     const float* s = RS(i);
     const float* u = RU(i);
     const float* a = RA(i);
-    const float* kv = L.bfused ? nullptr : KVS(i);
+    const float* kv = L.b32 ? KVS(0) : L.bfused ? nullptr : KVS(i);
     const void* W1 = W(w->w1, i, (size_t)d * F);
     const void* W2 = W(w->w2, i, (size_t)d * F);
     const void* Wo = W(w->wo, i, (size_t)d * d);
@@ -864,6 +983,7 @@ stca_status_t backward_generic(const Layout& L, int bf, const stca_batch_t* b, c
         ug.q_layer = i + 1;
       }
       HIPCHK(fast_update_grad(d, ug, st));
+      if (L.b32) HIPCHK(rec.mark("target_gemm"));
       // dW_2 = h^T ds, dW_1 = u^T dH, dW_O = a^T du, and dW_Q = s^T dq of
       // layer i + 1: one grouped launch
       const GemmSpec wg[4] = {
@@ -929,6 +1049,7 @@ stca_status_t backward_generic(const Layout& L, int bf, const stca_batch_t* b, c
       RbPrep pp{};
       pp.tgt_off = b->tgt_off;
       pp.n_requests = b->n_requests;
+      pp.groups = L.rb_groups;
       pp.layer = i;
       pp.n_layers = n;
       pp.Q = RQ(i);
@@ -955,7 +1076,10 @@ stca_status_t backward_generic(const Layout& L, int bf, const stca_batch_t* b, c
       ra.Wr = pp.Wr;
       ra.stats = pp.stats;
       ra.E = at<bf16_bits>(ws, L.rb_e);
-      ra.lde = (int64_t)n * 2 * kRbPairs;
+      ra.lde = (int64_t)L.rb_groups * n * 2 * kRbPairs;
+      ra.groups = L.rb_groups;
+      ra.tgt_off = b->tgt_off;
+      ra.order = at<int32_t>(ws, L.rb_order);
       ra.Z = Z;
       ra.Y = Y;
       ra.tchunks = at<int32_t>(ws, L.rb_tch);
@@ -963,7 +1087,8 @@ stca_status_t backward_generic(const Layout& L, int bf, const stca_batch_t* b, c
       ra.Yp = at<float>(ws, L.rb_yp);
       ra.first = at<int32_t>(ws, L.rb_first);
       HIPCHK(rb_attn(d, ra, static_cast<int>(L.rb_maxu), st));
-      HIPCHK(rb_reduce(d, b->tgt_off, b->n_requests, ra.tchunks, ra.first, ra.Zp, ra.Yp, Z, Y, nt, st));
+      if (L.rb_partials)
+        HIPCHK(rb_reduce(d, b->tgt_off, b->n_requests, L.rb_groups, ra.tchunks, ra.first, ra.Zp, ra.Yp, Z, Y, nt, st));
       HIPCHK(rec.mark("attn_bwd"));
       const int nti = static_cast<int>(nt);
       GemmSpec g[2 * 8], gq[8];
@@ -977,6 +1102,12 @@ stca_status_t backward_generic(const Layout& L, int bf, const stca_batch_t* b, c
       HIPCHK(gemm_mfma_group(gq, h, nullptr, 0, st));
       HIPCHK(convert(0, 1, dq, at<bf16_bits>(ws, L.b_dq), nt * d, st));
       HIPCHK(rec.mark("kv_grads"));
+    } else if (L.b32) {
+      HIPCHK(gemm_mfma(static_cast<int>(nh), 2 * d, d, static_cast<const bf16_bits*>(hist), d, 0,
+                       wkv_all + (size_t)i * 2 * d, n * 2 * d, 0, KVS(0), 2 * d, 1.f, 0, nullptr, 0, st));
+      HIPCHK(rec.mark("kv_gemm"));
+      HIPCHK(attn_bwd_generic(L.dh, h, units, L.max_units, hdr, b->tgt_off, RQ(i), kv, d, a, da, RL(i), dqp, dkv_i,
+                              n * 2 * d, 1, nullptr, 0, nt, st));
     } else if (L.bfused) {
       FastAttnBwd f{};
       f.units = units;
@@ -1063,9 +1194,10 @@ stca_status_t backward_generic(const Layout& L, int bf, const stca_batch_t* b, c
     std::swap(ds, ds2);
   }
   if (L.brd) {
-    // dX = E W_r over every layer's pairs (K = n 2 kRbPairs), per request
-    const int64_t kr = (int64_t)n * 2 * kRbPairs;
-    HIPCHK(gemm_ring_units(d, static_cast<int>(kr), at<bf16_bits>(ws, L.rb_e), kr, at<bf16_bits>(ws, L.rb_w), d,
+    // dX = E W_r over the pairs of every layer and target group, per request
+    const int kg = n * 2 * kRbPairs;
+    const int64_t kr = (int64_t)L.rb_groups * kg;
+    HIPCHK(gemm_ring_units(d, static_cast<int>(kr), kg, kRbPairs / h, at<bf16_bits>(ws, L.rb_e), kr, at<bf16_bits>(ws, L.rb_w), d,
                            kr * d, dhist, d, at<Unit>(ws, L.rb_unitsx), at<WsHeader>(ws, L.rb_hdrx), device_cus(),
                            st));
     HIPCHK(rec.mark("dx"));
@@ -1209,7 +1341,8 @@ int stca_backward_launch_count(const stca_dims_t* dims, const stca_batch_t* batc
   // reordered: ... 4 per layer (target side, attention, K/V-side gradients,
   // target side), dX, out
   if (L.brd) return 6 + 6 * L.n;
-  if (L.bfused) return 7 + 5 * L.n;
+  if (L.bfused && !L.b32) return 7 + 5 * L.n;
+  // (fp32 attention: 2 per layer of the recomputation and 5 of the reverse)
   return dims->dtype == STCA_BF16 ? 6 + 7 * L.n : 4 + 9 * L.n;
 }
 
@@ -1240,7 +1373,7 @@ stca_status_t stca_backward_profiled(const stca_dims_t* dims, const stca_batch_t
 
 size_t stca_train_record_size(const stca_dims_t* dims, const stca_batch_t* batch) {
   Layout L;
-  if (make_layout(dims, batch, 1, true, &L) != STCA_OK || !L.bfused) return 0;
+  if (make_layout(dims, batch, 1, true, &L) != STCA_OK || !L.record) return 0;
   return record_layout(L).total;
 }
 
@@ -1254,7 +1387,7 @@ stca_status_t stca_forward_train(const stca_dims_t* dims, const stca_batch_t* ba
   Layout L;
   st = make_layout(dims, batch, 1, true, &L);
   if (st != STCA_OK) return st;
-  if (!L.bfused) return STCA_ERR_UNSUPPORTED;
+  if (!L.record) return STCA_ERR_UNSUPPORTED;
   if (ws_bytes < L.total) return STCA_ERR_WORKSPACE;
   Rec none;
   return backward_generic(L, 1, batch, hist, tgt, w, nullptr, nullptr, nullptr, nullptr, ws, stream, none, nullptr,
@@ -1277,7 +1410,7 @@ stca_status_t stca_backward_record(const stca_dims_t* dims, const stca_batch_t* 
   Layout L;
   st = make_layout(dims, batch, 1, true, &L);
   if (st != STCA_OK) return st;
-  if (!L.bfused) return STCA_ERR_UNSUPPORTED;
+  if (!L.record) return STCA_ERR_UNSUPPORTED;
   if (ws_bytes < L.total) return STCA_ERR_WORKSPACE;
   Rec none;
   return backward_generic(L, 1, batch, hist, tgt, w, dout, dhist, dtgt, dw, ws, stream, none, record);

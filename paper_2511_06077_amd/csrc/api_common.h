@@ -94,7 +94,7 @@ inline int chunk_blocks_for(const stca_batch_t* b, int n_cu, int per_cu, int for
 // Chunk length of the standard form's units: with host offsets, the one of
 // one, two, four or eight units per CU whose estimated makespan is least
 // (fewer units on ties).  The estimate cuts the requests the standard form serves
-// (targets in [m_lo, m_hi]) as the device scheduler does and deals their
+// (targets in [m_lo, m_hi], `group` a unit) as the device scheduler does and deals their
 // units (those of up to 32 and of more targets run in separate launches, so
 // their makespans add) in descending size,
 // round-robin over the CUs in alternating directions as the device
@@ -103,7 +103,8 @@ inline int chunk_blocks_for(const stca_batch_t* b, int n_cu, int per_cu, int for
 // CU when the chunks divide evenly (headline batch 1.45 -> 1.41 ms per step),
 // while ragged ones take many (the ragged batch: eight per CU, 2.06 ms per
 // step; four 2.13, two 2.68).
-inline int chunk_blocks_auto(const stca_batch_t* b, int n_cu, int forced, int m_lo = 1, int m_hi = 1 << 30) {
+inline int chunk_blocks_auto(const stca_batch_t* b, int n_cu, int forced, int m_lo = 1, int m_hi = 1 << 30,
+                             int group = kTargetGroup) {
   if (forced >= 1 || !b->hist_off_host || !b->tgt_off_host || n_cu < 1) return chunk_blocks_for(b, n_cu, 4, forced);
   int best = 0;
   int64_t best_span = -1;
@@ -123,9 +124,9 @@ inline int chunk_blocks_auto(const stca_batch_t* b, int n_cu, int forced, int m_
       int64_t nch = std::min<int64_t>(kMaxChunks, std::max<int64_t>(1, ceil_div(nbr, c)));
       const int64_t cb = ceil_div(nbr, nch);
       nch = ceil_div(nbr, cb);
-      const int64_t groups = m <= 64 ? 1 : ceil_div(m, 64);
+      const int64_t groups = ceil_div(m, group);
       for (int64_t g = 0; g < groups; ++g)
-        for (int64_t k = 0; k < nch; ++k) jobs[m > 32].push_back(std::min<int64_t>(cb, nbr - k * cb) + 1);
+        for (int64_t k = 0; k < nch; ++k) jobs[m > 32 && group > 32].push_back(std::min<int64_t>(cb, nbr - k * cb) + 1);
     }
     if (jobs[0].size() + jobs[1].size() > (1u << 18)) return chunk_blocks_for(b, n_cu, 4, 0);  // bound the host work
     int64_t span = 0;

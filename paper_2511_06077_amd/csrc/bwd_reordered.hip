@@ -1,5 +1,5 @@
-// Attention backward in the reordered form (bf16 storage, d_h = 32, at most
-// 128 / n_heads targets per request).
+// Attention backward in the reordered form (bf16 storage, d_h = 32), a
+// request's targets in groups of at most 128 / n_heads.
 //
 // The forward's reordering (Sec. 3.1, Eq. attn-optimized: the score of
 // target t and head j is x_l . u_tj with u_tj = q_tj W_K^j^T, and the head
@@ -12,8 +12,10 @@
 //   dW_K^j = ln(2) sum_t z_tj^T q_tj,  dW_V^j = sum_t y_tj^T da_tj
 //   dq_tj = z_tj W_K^j / sqrt(d_h)
 // with z_tj = sum_l de_tl x_l and y_tj = sum_l p_tl x_l.  The (target, head)
-// pairs of a request are the rows of U and H (HM = 128 of them, index
-// j' = head * M + t, M = 128 / n_heads, padded with zero rows).
+// pairs of a target group are the rows of U and H (HM = 128 of them, index
+// j' = head * M + t, M = 128 / n_heads, padded with zero rows).  Groups only
+// meet in dX, whose products run over the pairs of every group and layer: a
+// group has its own columns of E and its own rows of the request's operand.
 //
 //   rb_prep_kernel:  per request, U (fp16 for the scores; bf16 with H into
 //                    the request's dX operand W_r), the softmax statistics
@@ -96,15 +98,16 @@ __global__ __launch_bounds__(64 * (D / 32)) void rb_prep_kernel(RbPrep A) {
   constexpr int H = D / DH;
   constexpr int M = HM / H;   // target slots per head
   constexpr int MT = (M + 31) / 32;
-  const int r = blockIdx.x;
+  const int r = blockIdx.x, g = blockIdx.y;
   if (r >= A.n_requests) return;
   const int h = threadIdx.x / 64, lane = threadIdx.x % 64, l32 = lane % 32, hi = lane / 32;
-  const int64_t t0 = A.tgt_off[r];
-  const int m = static_cast<int>(A.tgt_off[r + 1] - t0);
-  if (m == 0) return;
+  const int64_t t0 = A.tgt_off[r] + (int64_t)g * M;
+  const int m = static_cast<int>(A.tgt_off[r + 1] - t0);  // targets from the group's first on
+  if (m <= 0) return;
   const int cols = h * DH;
-  _Float16* U16 = A.U16 + (int64_t)r * HM * D;
-  bf16_bits* Wu = A.Wr + (((int64_t)r * A.n_layers + A.layer) * 2) * HM * D;
+  const int64_t slot = (int64_t)r * A.groups + g;
+  _Float16* U16 = A.U16 + slot * HM * D;
+  bf16_bits* Wu = A.Wr + ((slot * A.n_layers + A.layer) * 2) * HM * D;
   bf16_bits* Wh = Wu + (int64_t)HM * D;
   for (int rt = 0; rt < MT; ++rt) {
     // A operands: row i = target slot 32 rt + l32, k = head dims 16 s + 8 hi + e
@@ -151,7 +154,7 @@ __global__ __launch_bounds__(64 * (D / 32)) void rb_prep_kernel(RbPrep A) {
     }
     dsum += __shfl_xor(dsum, 32);  // the two lane halves hold 16 dims each
     if (t < M && hi == 0) {
-      float* st = A.stats + ((int64_t)r * HM + h * M + t) * 2;
+      float* st = A.stats + (slot * HM + h * M + t) * 2;
       st[0] = tok ? A.lse[(t0 + t) * H + h] * kLog2e : INFINITY;
       st[1] = tok ? dsum : 0.f;
     }
@@ -236,10 +239,13 @@ __global__ __launch_bounds__(512) void rb_attn_kernel(RbAttn A) {
   const int m = un.nt;
   const int jp = 32 * tile_id + l32;  // this lane's pair (result column)
   const bf16_bits* __restrict__ X = static_cast<const bf16_bits*>(A.X);
-  constexpr int M = HM / (D / DH);
+  constexpr int M = HM / (D / DH);  // targets of a group
 
-  float lse2 = A.stats[((int64_t)r * HM + jp) * 2];
-  float dsum = A.stats[((int64_t)r * HM + jp) * 2 + 1];
+  const int g = static_cast<int>((t0 - A.tgt_off[r]) / M);
+  const int64_t slot = (int64_t)r * A.groups + g;
+  const int64_t rank = A.order[blockIdx.x];
+  float lse2 = A.stats[(slot * HM + jp) * 2];
+  float dsum = A.stats[(slot * HM + jp) * 2 + 1];
   f32x16 acc[DT];  // role 0: Y, role 1: Z
 #pragma unroll
   for (int i = 0; i < DT; ++i) acc[i] = f32x16{};
@@ -272,7 +278,7 @@ __global__ __launch_bounds__(512) void rb_attn_kernel(RbAttn A) {
     }
   };
   const int64_t lde = A.lde;
-  bf16_bits* __restrict__ ecol = A.E + (int64_t)A.layer * 2 * HM + jp + (role == 0 ? HM : 0);
+  bf16_bits* __restrict__ ecol = A.E + ((int64_t)g * A.n_layers + A.layer) * 2 * HM + jp + (role == 0 ? HM : 0);
   // acc[dt] += op^T X(block in `tile`): op = the 32 x 32 tile of P or dE in
   // result order (element p of k-step s is row 16 s + 4 hi + (p < 4 ? p : p + 4)),
   // X's columns by transposing reads of the same rows
@@ -337,9 +343,9 @@ __global__ __launch_bounds__(512) void rb_attn_kernel(RbAttn A) {
     OpT bop[KS];
     {
       const OpT* src = ROLE == 0
-                           ? reinterpret_cast<const OpT*>(A.U16 + ((int64_t)r * HM + jp) * D)
+                           ? reinterpret_cast<const OpT*>(A.U16 + (slot * HM + jp) * D)
                            : reinterpret_cast<const OpT*>(
-                                 A.Wr + ((((int64_t)r * A.n_layers + A.layer) * 2 + 1) * HM + jp) * D);
+                                 A.Wr + (((slot * A.n_layers + A.layer) * 2 + 1) * HM + jp) * D);
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) bop[ks] = src[2 * ks + hi];
     }
@@ -454,50 +460,56 @@ __global__ __launch_bounds__(512) void rb_attn_kernel(RbAttn A) {
       }
     }
   } else {
-    if (un.c == 0 && threadIdx.x == 0) A.first[r] = blockIdx.x;
+    if (un.c == 0 && threadIdx.x == 0) A.first[slot] = static_cast<int32_t>(rank);
     float* __restrict__ outp = role == 0 ? A.Yp : A.Zp;
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt) {
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
         const int pr = 32 * tile_id + 8 * (v / 4) + 4 * hi + v % 4;
-        outp[((int64_t)blockIdx.x * HM + pr) * D + 32 * dt + l32] = acc[dt][v];
+        outp[(rank * HM + pr) * D + 32 * dt + l32] = acc[dt][v];
       }
     }
   }
 }
 
-// Z, Y (bf16 [head][target][D]) of a request of several chunks: the sum of
-// the partials of its units first[r] .. first[r] + chunks - 1
+// Z, Y (bf16 [head][target][D]) of a target group of a request of several
+// chunks: the sum of the partials of ranks first[slot] .. first[slot] + chunks - 1
 template <int D>
-__global__ __launch_bounds__(256) void rb_reduce_kernel(const int32_t* __restrict__ toff, int n_requests,
+__global__ __launch_bounds__(256) void rb_reduce_kernel(const int32_t* __restrict__ toff, int n_requests, int groups,
                                                         const int32_t* __restrict__ tchunks,
                                                         const int32_t* __restrict__ first, const float* __restrict__ Zp,
                                                         const float* __restrict__ Yp, bf16_bits* __restrict__ Z,
                                                         bf16_bits* __restrict__ Y, int64_t n_tgt) {
-  constexpr int H = D / DH, M = HM / H;
-  const int r = blockIdx.x;
+  constexpr int H = D / DH, M = HM / H, kRedRows = 256 / (D / 4);
+  const int r = blockIdx.x, g = blockIdx.y;
   if (r >= n_requests) return;
-  const int64_t t0 = toff[r];
-  const int m = static_cast<int>(toff[r + 1] - t0);
-  if (m == 0) return;
+  const int64_t t0 = toff[r] + (int64_t)g * M;
+  const int m = min(M, static_cast<int>(toff[r + 1] - t0));
+  if (m <= 0) return;
   const int nch = tchunks[t0];
   if (nch <= 1) return;
-  const int u0 = first[r];
-  const int64_t cnt = (int64_t)H * m * D;
-  for (int64_t e = threadIdx.x; e < cnt; e += blockDim.x) {
-    const int hh = static_cast<int>(e / ((int64_t)m * D));
-    const int tt = static_cast<int>((e / D) % m);
-    const int dd = static_cast<int>(e % D);
-    float z = 0.f, y = 0.f;
+  const int u0 = first[(int64_t)r * groups + g];
+  // kRedRows targets of one head a block, four columns a thread
+  const int hh = blockIdx.z % H;
+  const int tt = blockIdx.z / H * kRedRows + threadIdx.x / (D / 4), dd = 4 * (threadIdx.x % (D / 4));
+  if (tt < m) {
+    float4 z = make_float4(0.f, 0.f, 0.f, 0.f), y = z;
+#pragma unroll 4
     for (int c = 0; c < nch; ++c) {
       const int64_t o = ((int64_t)(u0 + c) * HM + hh * M + tt) * D + dd;
-      z += Zp[o];
-      y += Yp[o];
+      const float4 zc = *reinterpret_cast<const float4*>(Zp + o), yc = *reinterpret_cast<const float4*>(Yp + o);
+      z.x += zc.x, z.y += zc.y, z.z += zc.z, z.w += zc.w;
+      y.x += yc.x, y.y += yc.y, y.z += yc.z, y.w += yc.w;
     }
     const int64_t q = ((int64_t)hh * n_tgt + t0 + tt) * D + dd;
-    Z[q] = from_f32<bf16_bits>(z);
-    Y[q] = from_f32<bf16_bits>(y);
+    auto put = [](bf16_bits* p, const float4& v) {
+      *reinterpret_cast<uint2*>(p) =
+          make_uint2((uint32_t)from_f32<bf16_bits>(v.x) | ((uint32_t)from_f32<bf16_bits>(v.y) << 16),
+                     (uint32_t)from_f32<bf16_bits>(v.z) | ((uint32_t)from_f32<bf16_bits>(v.w) << 16));
+    };
+    put(Z + q, z);
+    put(Y + q, y);
   }
 }
 
@@ -514,7 +526,7 @@ __global__ void rb_zero_rows_kernel(const int32_t* __restrict__ hoff, const int3
 
 hipError_t rb_prep(int D, const RbPrep& a, hipStream_t st) {
   if (a.n_requests == 0) return hipSuccess;
-#define STCA_RBP(DD) hipLaunchKernelGGL(rb_prep_kernel<DD>, dim3(a.n_requests), dim3(64 * (DD / 32)), 0, st, a)
+#define STCA_RBP(DD) hipLaunchKernelGGL(rb_prep_kernel<DD>, dim3(a.n_requests, a.groups), dim3(64 * (DD / 32)), 0, st, a)
   if (D == 256) STCA_RBP(256);
   else if (D == 128) STCA_RBP(128);
   else return hipErrorInvalidValue;
@@ -532,12 +544,12 @@ hipError_t rb_attn(int D, const RbAttn& a, int grid, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t rb_reduce(int D, const int32_t* tgt_off, int n_requests, const int32_t* tchunks, const int32_t* first,
+hipError_t rb_reduce(int D, const int32_t* tgt_off, int n_requests, int groups, const int32_t* tchunks, const int32_t* first,
                      const float* Zp, const float* Yp, bf16_bits* Z, bf16_bits* Y, int64_t n_tgt, hipStream_t st) {
   if (n_requests == 0) return hipSuccess;
 #define STCA_RBR(DD)                                                                                              \
-  hipLaunchKernelGGL(rb_reduce_kernel<DD>, dim3(n_requests), dim3(256), 0, st, tgt_off, n_requests, tchunks, first, \
-                     Zp, Yp, Z, Y, n_tgt)
+  hipLaunchKernelGGL(rb_reduce_kernel<DD>, dim3(n_requests, groups, HM / (256 / (DD / 4))), dim3(256), 0, st, tgt_off,   \
+                     n_requests, groups, tchunks, first, Zp, Yp, Z, Y, n_tgt)
   if (D == 256) STCA_RBR(256);
   else if (D == 128) STCA_RBR(128);
   else return hipErrorInvalidValue;

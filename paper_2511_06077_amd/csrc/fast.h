@@ -104,18 +104,19 @@ struct FastAttnFwdPrecise {
   int64_t n_tgt;
 };
 hipError_t fast_attn_fwd_precise(int D, const FastAttnFwdPrecise& f, int grid, hipStream_t st);
-// Attention backward in the reordered form (bwd_reordered.hip): requests of
-// at most kRbPairs / n_heads targets; pair j' = head * M + target slot
-// (M = kRbPairs / n_heads), zero-padded per request.
+// Attention backward in the reordered form (bwd_reordered.hip): a request's
+// targets in `groups` slots of M = kRbPairs / n_heads; within a group pair
+// j' = head * M + target slot, zero-padded.  Slot r * groups + g is group g of
+// request r; groups past a request's targets are neither written nor read.
 constexpr int kRbPairs = 128;
-// Per layer and request: U = q W_K^j^T per pair (U16: fp16 [R][kRbPairs][D];
+// Per layer and slot: U = q W_K^j^T per pair (U16: fp16 [slots][kRbPairs][D];
 // also bf16 in the request's dX operand), H = da W_V^j^T (bf16), the
-// statistics (log2-unit lse, D = da . a per pair; [R][kRbPairs][2]) and bf16
-// copies of q and da ([n_tgt][D]).  Wr: [R][n_layers][2][kRbPairs][D], this
+// statistics (log2-unit lse, D = da . a per pair; [slots][kRbPairs][2]) and bf16
+// copies of q and da ([n_tgt][D]).  Wr: [slots][n_layers][2][kRbPairs][D], this
 // layer's U rows then H rows.
 struct RbPrep {
   const int32_t* tgt_off;
-  int n_requests, layer, n_layers;
+  int n_requests, groups, layer, n_layers;
   const float *Q, *da, *a, *lse;  // Q scaled by log2(e)/sqrt(d_h); lse natural, [n_tgt][H]
   const bf16_bits *Wk, *Wv;       // this layer's [D][D]
   _Float16* U16;
@@ -124,19 +125,21 @@ struct RbPrep {
   bf16_bits *q16, *da16;
 };
 hipError_t rb_prep(int D, const RbPrep& a, hipStream_t st);
-// Per unit (a history chunk of a request, all its targets): E (this layer's
-// columns [layer 2 kRbPairs, + 2 kRbPairs) of rows [N_hist][lde], bf16:
-// ln(2) dE then P per pair), and the chunk's Z = dE^T X and Y = P^T X: into
+// Per unit (a history chunk of a request, one group of its targets): E (the
+// columns [(g n_layers + layer) 2 kRbPairs, + 2 kRbPairs) of rows
+// [N_hist][lde], bf16: ln(2) dE then P per pair), and the chunk's Z = dE^T X and Y = P^T X: into
 // Z, Y (bf16 [n_heads][n_tgt][D]) directly for a request of one chunk
 // (tchunks of its first target), else as fp32 partials Zp, Yp
-// ([unit][kRbPairs][D]) that rb_reduce sums; `first` records each request's
-// first unit.
+// ([rank of the unit][kRbPairs][D]) that rb_reduce sums; `first` records each
+// slot's first rank.
 struct RbAttn {
   const void* units;
   const void* hdr;
   const void* X;
   int64_t n_hist, n_tgt;
-  int layer, n_layers;
+  int groups, layer, n_layers;
+  const int32_t* tgt_off;
+  const int32_t* order;  // rank of each unit in request, group, chunk order
   const _Float16* U16;
   const bf16_bits* Wr;
   const float* stats;
@@ -149,7 +152,7 @@ struct RbAttn {
 };
 hipError_t rb_attn(int D, const RbAttn& a, int grid, hipStream_t st);
 // Z, Y of the requests of several chunks: the sum of their units' partials.
-hipError_t rb_reduce(int D, const int32_t* tgt_off, int n_requests, const int32_t* tchunks, const int32_t* first,
+hipError_t rb_reduce(int D, const int32_t* tgt_off, int n_requests, int groups, const int32_t* tchunks, const int32_t* first,
                      const float* Zp, const float* Yp, bf16_bits* Z, bf16_bits* Y, int64_t n_tgt, hipStream_t st);
 // Zero the rows [hoff[r], hoff[r + 1]) x cols (fp32) of every request without targets.
 hipError_t rb_zero_untargeted(const int32_t* hoff, const int32_t* toff, int n_requests, float* dst, int cols,

@@ -130,6 +130,7 @@ struct RingProblem {
   const Unit* units;
   const WsHeader* hdr;
   int64_t b_stride;
+  int k_group, m_group;  // unit mode: a unit of nt targets has ceil(nt / m_group) * k_group of the K columns
 };
 
 // Work item in flight: output rows (from m0, below mend, BM per tile), K
@@ -159,10 +160,10 @@ __device__ __forceinline__ void set_item(const RingProblem& P, Cursor& c) {
       c.mend = min(u.b1 * kBlockTokens, u.l1);
       c.n0 = 0;
       c.kb = 0;
-      c.ke = P.K;
+      c.ke = min(P.K, (u.nt + P.m_group - 1) / P.m_group * P.k_group);
       c.split = 0;
       c.bofs = (int64_t)u.r * P.b_stride;
-      c.kpt = (P.K + BK - 1) / BK;
+      c.kpt = (c.ke + BK - 1) / BK;
       c.nks = c.mend > c.m0 ? c.kpt * ((c.mend - c.m0 + BM - 1) / BM) : 0;
       if (c.nks > 0) return;
       ++c.round;
@@ -378,7 +379,7 @@ hipError_t gemm_ring(int M, int N, int K, const bf16_bits* A, int64_t lda, int t
   if (work > 0x7fffffff) return hipErrorInvalidValue;
   RingProblem P{M, N, K, A, lda, B, ldb, C, ldc, alpha, accumulate, k_chunk, static_cast<int>(tm),
                 static_cast<int>(tn), splits, static_cast<int>(work), splits > 1 ? part : nullptr, nullptr, nullptr,
-                0};
+                0, 0, 1};
   // one workgroup per CU (the ring takes most of the LDS), a multiple of
   // the XCD count
   const int64_t grid = round_up(std::min<int64_t>(work, n_cu), kXcds);
@@ -394,14 +395,14 @@ hipError_t gemm_ring(int M, int N, int K, const bf16_bits* A, int64_t lda, int t
   return hipGetLastError();
 }
 
-hipError_t gemm_ring_units(int N, int K, const bf16_bits* A, int64_t lda, const bf16_bits* B, int64_t ldb,
+hipError_t gemm_ring_units(int N, int K, int k_group, int m_group, const bf16_bits* A, int64_t lda, const bf16_bits* B, int64_t ldb,
                            int64_t b_stride, float* C, int64_t ldc, const Unit* units, const WsHeader* hdr,
                            int n_cu, hipStream_t st) {
   if (N == 0 || K == 0) return hipSuccess;
-  if (K % 8 || N % 8 || lda % 8 || ldb % 8 || b_stride % 8 || !al16(A) || !al16(B) || n_cu < 1)
+  if (K % 8 || k_group < 8 || k_group % 8 || m_group < 1 || N % 8 || lda % 8 || ldb % 8 || b_stride % 8 || !al16(A) || !al16(B) || n_cu < 1)
     return hipErrorInvalidValue;
   RingProblem P{0, N, K, A, lda, B, ldb, C, ldc, 1.f, 0, K, 1, static_cast<int>(ceil_div(N, 256)), 1, 0, nullptr,
-                units, hdr, b_stride};
+                units, hdr, b_stride, k_group, m_group};
   if (N > 256) return hipErrorInvalidValue;  // one tile spans N
   hipLaunchKernelGGL((ring_gemm_kernel<true, false, 128, 256, kBK, kNS>), dim3(static_cast<unsigned>(round_up(n_cu, kXcds))),
                      dim3(kRingThreads), 0, st, P);

@@ -12,9 +12,12 @@ namespace stca {
 // history blocks, complete rounds of `deal` units alternating in direction
 // (for persistent kernels of `deal` workgroups that take units round-robin
 // and place every partial by its chunk index); 0: request and chunk order.
+// order (nullable, [max_units]): each unit's rank in request, group and chunk
+// order, in which the chunks of one target group are consecutive.
 hipError_t launch_sched(const int32_t* hoff, const int32_t* toff, int R, int64_t n_hist, int64_t n_tgt,
                         int chunk_blocks, int group, Unit* units, int64_t max_units, int32_t* tchunks,
-                        WsHeader* hdr, hipStream_t st, int m_lo = 1, int m_hi = 1 << 30, int deal = 0);
+                        WsHeader* hdr, hipStream_t st, int m_lo = 1, int m_hi = 1 << 30, int deal = 0,
+                        int32_t* order = nullptr);
 int64_t host_count_units(const int32_t* hoff, const int32_t* toff, int R, int chunk_blocks, int group,
                          int m_lo = 1, int m_hi = 1 << 30);
 
@@ -69,8 +72,9 @@ hipError_t gemm_ring(int M, int N, int K, const bf16_bits* A, int64_t lda, int t
 // The same kernel over the units of a schedule (hdr->n_units of them): unit
 // u's rows [max(32 b0, l0), min(32 b1, l1)) of C ([rows][ldc] fp32, N <= 256
 // columns) = A rows (bf16, k contiguous, lda) times B + r * b_stride (bf16
-// [K][ldb], rows contiguous), r the unit's request.
-hipError_t gemm_ring_units(int N, int K, const bf16_bits* A, int64_t lda, const bf16_bits* B, int64_t ldb,
+// [K][ldb], rows contiguous), r the unit's request.  A unit of nt targets
+// takes the first ceil(nt / m_group) * k_group (at most K) of the K columns.
+hipError_t gemm_ring_units(int N, int K, int k_group, int m_group, const bf16_bits* A, int64_t lda, const bf16_bits* B, int64_t ldb,
                            int64_t b_stride, float* C, int64_t ldc, const Unit* units, const WsHeader* hdr,
                            int n_cu, hipStream_t st);
 // dst[c][r] = src[r][c] (bf16; R x C source, row pitches lds / ldd); dst

@@ -16,6 +16,9 @@
 // target's chunk count is recorded so the combine step knows how many partial
 // results to merge.
 //
+// With `order`, entry u is unit u's rank in request, group and chunk order (the
+// chunks of one target group have consecutive ranks).
+//
 // One workgroup of 1024 threads; each thread owns a contiguous run of requests.
 // Invalid segments produce no units and set the workspace status, so no later
 // kernel reads outside the buffers whatever the offsets hold.  Only requests
@@ -107,7 +110,8 @@ __global__ __launch_bounds__(kSchedThreads) void sched_kernel(const int32_t* __r
                                                               Unit* __restrict__ units,
                                                               int64_t max_units,
                                                               int32_t* __restrict__ tchunks,
-                                                              WsHeader* __restrict__ hdr) {
+                                                              WsHeader* __restrict__ hdr,
+                                                              int32_t* __restrict__ order) {
   __shared__ int64_t scan[kSchedThreads];
   __shared__ int bad;
   __shared__ unsigned cursor[2][kSizeBuckets];  // by_size: units, then next rank, per (class, bucket)
@@ -186,6 +190,7 @@ __global__ __launch_bounds__(kSchedThreads) void sched_kernel(const int32_t* __r
         un_.l0 = p.h0;
         un_.l1 = p.h1;
         units[u] = un_;
+        if (order) order[u] = static_cast<int32_t>(ur);
       }
     }
     for (int t = p.t0; t < p.t1; ++t) tchunks[t] = p.nch;
@@ -202,11 +207,11 @@ __global__ __launch_bounds__(kSchedThreads) void sched_kernel(const int32_t* __r
 
 hipError_t launch_sched(const int32_t* hoff, const int32_t* toff, int R, int64_t n_hist, int64_t n_tgt,
                         int chunk_blocks, int group, Unit* units, int64_t max_units, int32_t* tchunks,
-                        WsHeader* hdr, hipStream_t st, int m_lo, int m_hi, int deal) {
+                        WsHeader* hdr, hipStream_t st, int m_lo, int m_hi, int deal, int32_t* order) {
   if (group < 1 || group > kWideGroup || deal < 0) return hipErrorInvalidValue;
   hipLaunchKernelGGL(sched_kernel, dim3(1), dim3(kSchedThreads), 0, st, hoff, toff, R, n_hist, n_tgt,
                      chunk_blocks, group, m_lo, m_hi, deal > 0 ? 1 : 0, static_cast<unsigned>(deal > 0 ? deal : 1),
-                     units, max_units, tchunks, hdr);
+                     units, max_units, tchunks, hdr, order);
   return hipGetLastError();
 }
 

@@ -107,3 +107,37 @@ def test_reordered_long_history(torch):
     b = W.make_custom_batch("glong", [3000, 64, 517], [16, 5, 9], d_model=256, n_heads=8, n_layers=2,
                             dtype="bf16", seed=97, with_grad=True)
     check(b, gpu_grads(torch, b, bwd="reordered"), TOL["bf16"])
+
+
+def test_reordered_unbalanced_histories(torch):
+    """Histories from 8 to 8000 rows (a stochastic-length batch's shape) large
+    enough for the automatic choice to take the reordered form: chunks in
+    descending size, their partials summed by rank."""
+    from paper_2511_06077_amd import stca
+    from paper_2511_06077_amd.device import DeviceBatch
+    rng = np.random.default_rng(5)
+    L = np.where(rng.random(96) < 0.5, 8, rng.integers(2000, 8000, 96))
+    b = W.make_custom_batch("grunb", L, rng.integers(1, 17, 96), d_model=256, n_heads=8, n_layers=1, dtype="bf16",
+                            seed=103, with_grad=True)
+    db = DeviceBatch(b, backward=True)
+    assert stca.stca_backward_launch_count(db.dims, db.batch) == 6 + 6 * b.wl.n_layers
+    check(b, gpu_grads(torch, b), TOL["bf16"])
+
+
+def test_reordered_target_groups(torch):
+    """Requests of more than one group of 16 targets among others (the
+    automatic choice for a large enough batch): every group has its own pairs,
+    E columns and rows of the dX operand, and a request's K of the dX product
+    ends with its last group (16, 17, 32 targets, one, none)."""
+    from paper_2511_06077_amd import stca
+    from paper_2511_06077_amd.device import DeviceBatch
+    rng = np.random.default_rng(6)
+    L = rng.integers(700, 2400, 128)
+    m = np.where(rng.random(128) < 0.2, rng.integers(17, 33, 128), rng.integers(0, 17, 128))
+    m[:5] = [16, 17, 32, 1, 0]
+    b = W.make_custom_batch("grgrp", L, m, d_model=256, n_heads=8, n_layers=2, dtype="bf16", seed=101, with_grad=True)
+    db = DeviceBatch(b, backward=True)
+    assert stca.stca_backward_launch_count(db.dims, db.batch) == 6 + 6 * b.wl.n_layers
+    g = gpu_grads(torch, b)
+    check(b, g, TOL["bf16"])
+    assert not np.any(g["dhist"][b.hist_off[4]:b.hist_off[5]])
