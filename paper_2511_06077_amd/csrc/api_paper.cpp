@@ -7,6 +7,7 @@
 // request for all its targets (Sec. 3.2).
 #include <algorithm>
 #include <cmath>
+#include <vector>
 
 #include "api_common.h"
 #include "common.h"
@@ -29,6 +30,10 @@ struct PaperLayout {
   size_t hdr, units, tchunks, part_acc, part_ml;
   size_t q, a, cat, f, hu, hv, y, qs;  // target side, fp32
   size_t qn, wsp, wkp, wvp, xt16;      // bf16 MFMA path
+  // ... target side: packed weights, W_C^(2..n) one after the other, W_Z and
+  // the head block; the splits' parts of a stage and their arrival counters
+  size_t wop, wqp, wup, wvup, wdp, wcp, wzp, zup, zvp, zdp, spart, cnt;
+  int splits, max_ch;
   size_t hhu, hhv, hy, xt32, kv32;     // generic path: history side
   size_t total;
 };
@@ -77,15 +82,42 @@ bool make_paper_layout(const stca_dims_t* dims, const stca_batch_t* b, PaperLayo
   L->tchunks = m.take(4 * (nt + 1));
   L->part_acc = m.take(4 * kMaxChunks * nt * d);
   L->part_ml = m.take(8 * kMaxChunks * nt * L->h);
-  L->q = m.take(4 * nt * d);
-  L->a = m.take(4 * nt * d);
   L->cat = m.take(4 * nt * n * d);
-  L->f = m.take(4 * nt * d);
-  L->hu = m.take(4 * nt * F);
-  L->hv = m.take(4 * nt * F);
-  L->y = m.take(4 * nt * d);
-  L->qs = m.take(4 * nt * d);
+  if (p == 0) {
+    L->q = m.take(4 * nt * d);
+    L->a = m.take(4 * nt * d);
+    L->f = m.take(4 * nt * d);
+    L->hu = m.take(4 * nt * F);
+    L->hv = m.take(4 * nt * F);
+    L->y = m.take(4 * nt * d);
+    L->qs = m.take(4 * nt * d);
+  }
   if (p == 1) {
+    // the most workgroups per target group that the CUs take in one round (64
+    // requests, us a call: 65 groups x 1 3210, x 2 3115, x 4, two rounds, 3285;
+    // one request x 1 714, x 2 634, x 4 600)
+    const int64_t groups = ceil_div(b->n_tgt, 32), nc = L->F / L->d;
+    L->splits = 1;
+    for (const int s : {4, 2})
+      if (L->splits == 1 && nc % s == 0 && groups * s <= device_cus()) L->splits = s;
+    L->max_ch = b->hist_off_host ? 1 : kMaxChunks;
+    for (int r = 0; b->hist_off_host && r < b->n_requests; ++r) {
+      if (b->tgt_off_host[r + 1] == b->tgt_off_host[r]) continue;
+      const int64_t nb = ceil_div(b->hist_off_host[r + 1], kBlockTokens) - b->hist_off_host[r] / kBlockTokens;
+      L->max_ch = std::max(L->max_ch, static_cast<int>(std::min<int64_t>(kMaxChunks, ceil_div(nb, L->chunk_blocks))));
+    }
+    L->wop = m.take(2 * n * d * d);
+    L->wqp = m.take(2 * n * d * d);
+    L->wup = m.take(2 * n * d * F);
+    L->wvup = m.take(2 * n * d * F);
+    L->wdp = m.take(2 * n * d * F);
+    L->wcp = m.take(2 * (n * (n + 1) / 2 - 1) * d * d);
+    L->wzp = m.take(2 * (n + 1) * d * d);
+    L->zup = m.take(2 * d * F);
+    L->zvp = m.take(2 * d * F);
+    L->zdp = m.take(2 * d * F);
+    L->spart = m.take(L->splits > 1 ? 4 * L->splits * static_cast<size_t>(groups) * 32 * d : 0);
+    L->cnt = m.take(L->splits > 1 ? 4 * (n + 1) * static_cast<size_t>(groups) : 0);
     L->qn = m.take(2 * nt * d);
     L->wsp = m.take(n * swiglu_packed_bytes(L->d, L->F));
     L->wkp = m.take(2 * n * d * d);
@@ -103,10 +135,13 @@ bool make_paper_layout(const stca_dims_t* dims, const stca_batch_t* b, PaperLayo
 }
 
 int paper_launch_count(const PaperLayout& L) {
+  // bf16: schedule, the SwiGLU pack and the other packs, the first query
+  // stage; per layer the history transform, the attention (two widths) and the
+  // target stage that ends in the next query or the head
+  if (L.path == 1) return 4 + 4 * L.n;
   // q^(1): block (4) + LN; per layer the history transform, the query, the
   // attention, the merge and W_O; per fusion two GEMMs, the block and LN; the
   // head: two GEMMs, the block and the output conversion
-  if (L.path == 1) return 4 + 5 + 7 * L.n + 7 * (L.n - 1) + 7;
   return 1 + 5 + 11 * L.n + 7 * (L.n - 1) + 7;
 }
 
@@ -127,6 +162,117 @@ stca_status_t check_paper(const stca_dims_t* dims, const stca_batch_t* b, const 
   return STCA_OK;
 }
 
+// The bf16 path: per layer the history transform, the attention over it and
+// one target stage.
+stca_status_t forward_paper_fast(const PaperLayout& L, const stca_batch_t* b, const void* hist, const void* tgt,
+                                 const stca_paper_weights_t* w, void* z, void* saved,
+                                 const stca_paper_saved_layout_t& SL, void* ws, hipStream_t st, Rec& rec) {
+  HIPCHK(rec.start());
+  const int d = L.d, n = L.n, F = L.F, h = L.h;
+  const int64_t nt = L.nt, nh = L.nh;
+  WsHeader* hdr = at<WsHeader>(ws, L.hdr);
+  Unit* units = at<Unit>(ws, L.units);
+  float* pacc = at<float>(ws, L.part_acc);
+  float* pml = at<float>(ws, L.part_ml);
+  const size_t dd = (size_t)d * d, dF = (size_t)d * F;
+  auto elems = [](const void* base, size_t k) { return static_cast<const bf16_bits*>(base) + k; };
+  auto pk = [&](size_t off, size_t k) { return at<bf16_bits>(ws, off) + k; };
+  HIPCHK(launch_sched(b->hist_off, b->tgt_off, b->n_requests, nh, nt, L.chunk_blocks, kTargetGroup, units,
+                      L.max_units, at<int32_t>(ws, L.tchunks), hdr, st, 1, 1 << 30, device_cus()));
+  HIPCHK(rec.mark("sched"));
+  HIPCHK(swiglu_pack(w->ffn_u, w->ffn_v, w->ffn_o, n, d, F, at<char>(ws, L.wsp), st));
+  HIPCHK(rec.mark("pack_swiglu"));
+  {
+    PackJobs pj{};
+    pj.job[0] = {w->wk, pk(L.wkp, 0), d, d, 0};
+    pj.job[1] = {w->wv, pk(L.wvp, 0), d, d, 0};
+    pj.job[2] = {w->wo, pk(L.wop, 0), d, d, 0};
+    pj.job[3] = {w->wq, pk(L.wqp, 0), d, d, 0};
+    pj.job[4] = {w->ffn_u, pk(L.wup, 0), d, F, 0};
+    pj.job[5] = {w->ffn_v, pk(L.wvup, 0), d, F, 0};
+    pj.job[6] = {w->ffn_o, pk(L.wdp, 0), F, d, 0};
+    HIPCHK(fast_pack_many(pj, 7, n, st));
+    // the weights without a layer axis, kMaxPackJobs at a time
+    std::vector<PackJob> one = {{w->wz, pk(L.wzp, 0), (n + 1) * d, d, 0},
+                                {w->z_u, pk(L.zup, 0), d, F, 0},
+                                {w->z_v, pk(L.zvp, 0), d, F, 0},
+                                {w->z_o, pk(L.zdp, 0), F, d, 0}};
+    size_t rows = 0;
+    for (int k = 2; k <= n; ++k) {
+      one.push_back({elems(w->wc, rows * d), pk(L.wcp, rows * d), k * d, d, 0});
+      rows += (size_t)k * d;
+    }
+    for (size_t j = 0; j < one.size(); j += kMaxPackJobs) {
+      const int c = static_cast<int>(std::min<size_t>(kMaxPackJobs, one.size() - j));
+      std::copy(one.begin() + j, one.begin() + j + c, pj.job);
+      HIPCHK(fast_pack_many(pj, c, 1, st));
+    }
+  }
+  const int64_t groups = ceil_div(nt, 32);
+  if (L.splits > 1) HIPCHK(fill_f32(at<float>(ws, L.cnt), 0.f, (n + 1) * groups, st));
+  HIPCHK(rec.mark("pack"));
+  PaperTarget f{};
+  f.F = F;
+  f.n_tgt = nt;
+  f.tgt = static_cast<const bf16_bits*>(tgt);
+  f.tchunks = at<int32_t>(ws, L.tchunks);
+  f.part_acc = pacc;
+  f.part_ml = pml;
+  f.max_ch = L.max_ch;
+  // row t of `cat` is [o^(1) || ... || o^(n)]
+  f.cat = saved ? at<float>(saved, SL.o) : at<float>(ws, L.cat);
+  f.ldcat = (int64_t)n * d;
+  f.QN = at<char>(ws, L.qn);
+  f.splits = L.splits;
+  f.spart = at<float>(ws, L.spart);
+  // q^(1) = LN(SwiGLUFFN^(1)(x_t)) and the first layer's queries
+  f.first = 1;
+  f.WuP = pk(L.wup, 0);
+  f.WvP = pk(L.wvup, 0);
+  f.WdP = pk(L.wdp, 0);
+  f.WqP = pk(L.wqp, 0);
+  f.q_out = saved ? at<float>(saved, SL.q) : nullptr;
+  f.cnt = at<int32_t>(ws, L.cnt);
+  HIPCHK(paper_target(d, f, st));
+  HIPCHK(rec.mark("target"));
+  f.first = 0;
+  const int fgrid = static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(L.max_units, device_cus())));
+  size_t rows = 0;  // of W_C^(2), ..., W_C^(i+1) before W_C^(i+2)
+  for (int i = 0; i < n; ++i) {
+    // X~^(i) = LN(SwiGLUFFN^(i)(X)), then the layer's attention over it
+    HIPCHK(swiglu_ln(d, hist, nh, at<char>(ws, L.wsp) + i * swiglu_packed_bytes(d, F), F, at<char>(ws, L.xt16),
+                     saved ? at<float>(saved, SL.xt) + (size_t)i * nh * d : nullptr, st));
+    HIPCHK(rec.mark("swiglu_ln"));
+    for (int wide = 0; wide < 2; ++wide) {
+      if (wide ? L.any_wide : L.any_narrow)
+        HIPCHK(fast_fused(d, wide, units, hdr, fgrid, at<char>(ws, L.qn), at<char>(ws, L.xt16), nh,
+                          at<char>(ws, L.wkp), at<char>(ws, L.wvp), i, pacc, pml, nt, st));
+      HIPCHK(rec.mark(wide ? "fused_wide" : "fused"));
+    }
+    // o^(i) = [heads] W_O^(i) (Eq. layer-output); then q^(i+2) =
+    // LN(SwiGLUFFN^(i+2)([o^(1) .. o^(i+1) || x_t] W_C^(i+2))) and its queries,
+    // or z = SwiGLUFFN_z([o^(1) .. o^(n) || x_t] W_Z)
+    const bool head = i + 1 == n;
+    f.n_cat = i + 1;
+    f.a_out = saved ? at<float>(saved, SL.a) + (size_t)i * nt * d : nullptr;
+    f.lse_out = saved ? at<float>(saved, SL.lse) + (size_t)i * nt * h : nullptr;
+    f.WoP = pk(L.wop, i * dd);
+    f.WcP = head ? pk(L.wzp, 0) : pk(L.wcp, rows * d);
+    f.WuP = head ? pk(L.zup, 0) : pk(L.wup, (i + 1) * dF);
+    f.WvP = head ? pk(L.zvp, 0) : pk(L.wvup, (i + 1) * dF);
+    f.WdP = head ? pk(L.zdp, 0) : pk(L.wdp, (i + 1) * dF);
+    f.WqP = head ? nullptr : pk(L.wqp, (i + 1) * dd);
+    f.q_out = saved && !head ? at<float>(saved, SL.q) + (size_t)(i + 1) * nt * d : nullptr;
+    f.z_out = head ? static_cast<bf16_bits*>(z) : nullptr;
+    f.cnt = at<int32_t>(ws, L.cnt) + (i + 1) * groups;
+    HIPCHK(paper_target(d, f, st));
+    HIPCHK(rec.mark("target"));
+    rows += (size_t)(i + 2) * d;
+  }
+  return STCA_OK;
+}
+
+// The generic path: fp32 arithmetic throughout.
 stca_status_t forward_paper(const PaperLayout& L, int bf, const stca_batch_t* b, const void* hist, const void* tgt,
                             const stca_paper_weights_t* w, void* z, void* saved,
                             const stca_paper_saved_layout_t& SL, void* ws, hipStream_t st, Rec& rec) {
@@ -152,12 +298,6 @@ stca_status_t forward_paper(const PaperLayout& L, int bf, const stca_batch_t* b,
   HIPCHK(launch_sched(b->hist_off, b->tgt_off, b->n_requests, nh, nt, L.chunk_blocks, kTargetGroup, units,
                       L.max_units, tch, hdr, st, 1, 1 << 30, device_cus()));
   HIPCHK(rec.mark("sched"));
-  if (L.path == 1) {
-    HIPCHK(swiglu_pack(w->ffn_u, w->ffn_v, w->ffn_o, n, d, F, at<char>(ws, L.wsp), st));
-    HIPCHK(rec.mark("pack_swiglu"));
-    HIPCHK(fast_pack(w->wk, at<char>(ws, L.wkp), n, d, d, 0, st)); HIPCHK(rec.mark("pack_wk"));
-    HIPCHK(fast_pack(w->wv, at<char>(ws, L.wvp), n, d, d, 0, st)); HIPCHK(rec.mark("pack_wv"));
-  }
   // y = SwiGLUFFN(x) on the target rows (Eq. swigluffn), fp32 result
   auto target_block = [&](const void* x, int x_bf16, const void* wu, const void* wv, const void* wo) -> hipError_t {
     hipError_t e;
@@ -185,22 +325,7 @@ stca_status_t forward_paper(const PaperLayout& L, int bf, const stca_batch_t* b,
     float* lse = saved ? at<float>(saved, SL.lse) + (size_t)i * nt * h : nullptr;
     float* xt32 = saved ? at<float>(saved, SL.xt) + (size_t)i * nh * d : nullptr;
     // X~^(i) = LN(SwiGLUFFN^(i)(X)), then the layer's attention over it
-    if (L.path == 1) {
-      HIPCHK(swiglu_ln(d, hist, nh, at<char>(ws, L.wsp) + i * swiglu_packed_bytes(d, F), F, at<char>(ws, L.xt16),
-                       xt32, st));
-      HIPCHK(rec.mark("swiglu_ln"));
-      HIPCHK(gemm_generic(0, bf, (int)nt, d, d, q, d, 0, W(w->wq, i * dd), d, 0, qs, d, qscale, kEpiStore, nullptr,
-                          0, nullptr, 0, st));
-      HIPCHK(rec.mark("gemm_q"));
-      HIPCHK(qn_pack(qs, at<char>(ws, L.qn), nt, d, st)); HIPCHK(rec.mark("qn_pack"));
-      const int fgrid = static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(L.max_units, device_cus())));
-      for (int wide = 0; wide < 2; ++wide) {
-        if (wide ? L.any_wide : L.any_narrow)
-          HIPCHK(fast_fused(d, wide, units, hdr, fgrid, at<char>(ws, L.qn), at<char>(ws, L.xt16), nh,
-                            at<char>(ws, L.wkp), at<char>(ws, L.wvp), i, pacc, pml, nt, st));
-        HIPCHK(rec.mark(wide ? "fused_wide" : "fused"));
-      }
-    } else {
+    {
       float* xt = xt32 ? xt32 : at<float>(ws, L.xt32);
       float* hhu = at<float>(ws, L.hhu);
       float* hhv = at<float>(ws, L.hhv);
@@ -272,6 +397,7 @@ stca_status_t run_paper(const stca_dims_t* dims, const stca_batch_t* b, const vo
   if (rec.ev && rec.n < paper_launch_count(L) + 1) return STCA_ERR_INVALID_ARG;
   stca_paper_saved_layout_t SL{};
   paper_saved_layout(dims, b, &SL);
+  if (L.path == 1) return forward_paper_fast(L, b, hist, tgt, w, z, saved, SL, ws, st, rec);
   return forward_paper(L, dims->dtype == STCA_BF16, b, hist, tgt, w, z, saved, SL, ws, st, rec);
 }
 

@@ -34,9 +34,8 @@ struct FastUpdate {
   int32_t* range;  // set to 1 when a value rounded to fp16 (or the merged attention) is not a finite fp16
 };
 
-// Repack W [n_layers][K][N] (bf16) into MFMA operand order, as bf16 or fp16.
-hipError_t fast_pack(const void* W, void* P, int n_layers, int K, int N, int to_f16, hipStream_t st);
-// The same for up to kMaxPackJobs weights (same layer count) in one launch.
+// Repack weights [n_layers][K][N] (bf16) into MFMA operand order, as bf16 or
+// fp16: up to kMaxPackJobs weights (same layer count) in one launch.
 constexpr int kMaxPackJobs = 10;
 struct PackJob {
   const void* src;

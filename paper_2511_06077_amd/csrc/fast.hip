@@ -97,25 +97,6 @@ struct elem_of<f16x8> {
 // W: [layers][K][N] bf16 row-major -> P: [layers][N/32][K/16][64][8], kept
 // bf16 (V8 = bf16x8) or converted to fp16 (V8 = f16x8, exact for every bf16
 // value inside fp16's range).
-template <typename V8>
-__global__ void pack_kernel(const bf16_bits* __restrict__ W, V8* __restrict__ P, int K, int N,
-                            int64_t per_layer_groups) {
-  const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int layer = blockIdx.y;
-  if (g >= per_layer_groups) return;
-  const int lane = g % 64;
-  const int64_t rest = g / 64;
-  const int ks = rest % (K / 16);
-  const int nb = rest / (K / 16);
-  const int n = nb * 32 + lane % 32;
-  const int k0 = ks * 16 + 8 * (lane / 32);
-  const bf16_bits* w = W + (int64_t)layer * K * N;
-  V8 r;
-#pragma unroll
-  for (int e = 0; e < 8; ++e) r[e] = static_cast<typename elem_of<V8>::type>(to_f32(w[(int64_t)(k0 + e) * N + n]));
-  P[(int64_t)layer * per_layer_groups + g] = r;
-}
-
 // Several weights in one launch (blockIdx.z = job): the per-call repacking of
 // a forward costs one launch instead of one per weight.
 template <typename V8>
@@ -1106,16 +1087,6 @@ __global__ __launch_bounds__(64 * (D / 32)) void update_kernel(UpdateArgs A) {
 }  // namespace
 
 // ------------------------------------------------------------ launchers
-hipError_t fast_pack(const void* W, void* P, int n_layers, int K, int N, int to_f16, hipStream_t st) {
-  const int64_t groups = (int64_t)(N / 32) * (K / 16) * 64;
-  dim3 g(static_cast<unsigned>(ceil_div(groups, 256)), n_layers);
-  if (to_f16)
-    hipLaunchKernelGGL(pack_kernel<f16x8>, g, dim3(256), 0, st, (const bf16_bits*)W, (f16x8*)P, K, N, groups);
-  else
-    hipLaunchKernelGGL(pack_kernel<bf16x8>, g, dim3(256), 0, st, (const bf16_bits*)W, (bf16x8*)P, K, N, groups);
-  return hipGetLastError();
-}
-
 hipError_t fast_pack_many(const PackJobs& jobs, int n_jobs, int n_layers, hipStream_t st) {
   if (n_jobs < 1 || n_jobs > kMaxPackJobs) return hipErrorInvalidValue;
   int64_t groups = 0;

@@ -221,17 +221,328 @@ __global__ __launch_bounds__(256) void ln_rows_kernel(const float* __restrict__ 
   for (int e = lane; e < d; e += 64) out[r * d + e] = (p[e] - mean) * rstd;
 }
 
-// fp32 queries (already scaled) -> the fused attention kernel's QN layout:
-// per head, position 16s + 8hi + i holds dimension 16s + 4hi + (i<4 ? i : i+4), fp16
-__global__ void qn_pack_kernel(const float* __restrict__ Q, _Float16* __restrict__ QN, int64_t n_groups) {
-  const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (g >= n_groups) return;
-  const int64_t base = g * 8;  // first position of this group
-  const int64_t head0 = base / 32 * 32;
-  const int p = static_cast<int>(base % 32);
-  const int s = p / 16, hi = (p / 8) % 2;
+// One target-side stage of the bf16 path in one launch: the merge of layer i's
+// attention partials into a and o^(i) = a W_O (unless `first`), the fusion
+// f = [o^(1) .. o^(i) || x_t] W_C (f = x_t when `first`), the SwiGLU block
+// y = ((f W_u) * silu(f W_v)) W_o, and either q = LN(y) with the next layer's
+// attention queries Q = q W_Q (fp16, the attention kernel's order) or, for the
+// head, z = y.  32-target tiles, one wave per 32 output columns, as the
+// target update of the standard stack; every product multiplies the bf16
+// weights by the fp32 activation split into three bf16 terms (exact products,
+// fp32 sums).
+//
+// As separate GEMMs (64 x 64 tiles, the down projection on the fp32 matrix
+// cores with its K split over atomics), gates, norms, merges and query
+// packing, 11 launches a layer took 930 us of the 3730 us step at 2080 targets;
+// here a stage streams its weights once per target group (2.3 MB at the last
+// fusion of four layers, d = 256) and is bound by that stream and by the 3 x
+// MFMA of the terms: 59 us a stage, 3115 us the step (two splits).  With `splits` > 1 workgroups (group, split) divide the
+// hidden columns and the last to arrive sums their parts of y in split order
+// (agent-scope relaxed atomics, no fences), so few targets use more CUs.
+template <int D, int NC>
+__global__ __launch_bounds__(64 * (D / 32)) void paper_target_kernel(PaperTarget A) {
+  constexpr int NW = D / 32;
+  constexpr int H = D / 32;
+  constexpr int KS = D / 16;
+  constexpr int AROW = D + 8;  // padded LDS row (bf16 elements)
+  constexpr int NT = 64 * NW;
+  __shared__ __attribute__((aligned(16))) bf16_bits act[3][32 * AROW];
+  __shared__ __attribute__((aligned(16))) bf16_bits hid[3][32 * AROW];
+  __shared__ float red[NW][32];
+  __shared__ int arrived;
+  const int w = threadIdx.x / 64, lane = threadIdx.x % 64;
+  const int tcol = lane % 32, hi = lane / 32;
+  const int group = blockIdx.x / A.splits, split = blockIdx.x % A.splits;
+  const int64_t tb = (int64_t)group * 32;
+  const int64_t t = tb + tcol;
+  const bool tok = t < A.n_tgt;
+
+  // 4 consecutive fp32 values (row r, columns c..c+3) as three bf16 terms
+  auto put4 = [&](bf16_bits (*buf)[32 * AROW], int r, int c, const float* v) {
+    float x[4] = {v[0], v[1], v[2], v[3]};
 #pragma unroll
-  for (int i = 0; i < 8; ++i) QN[base + i] = static_cast<_Float16>(Q[head0 + 16 * s + 4 * hi + (i < 4 ? i : i + 4)]);
+    for (int term = 0; term < 3; ++term) {
+      bf16_bits b[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        b[e] = from_f32<bf16_bits>(x[e]);
+        x[e] -= to_f32(b[e]);
+      }
+      *reinterpret_cast<uint2*>(buf[term] + r * AROW + c) =
+          make_uint2((uint32_t)b[0] | ((uint32_t)b[1] << 16), (uint32_t)b[2] | ((uint32_t)b[3] << 16));
+    }
+  };
+  // a wave's result tile: lane = target tcol, elements = columns 32 w + 8 q + 4 hi + e
+  auto put_tile = [&](bf16_bits (*buf)[32 * AROW], const f32x16& v) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const float x[4] = {v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]};
+      put4(buf, tcol, 32 * w + 8 * q + 4 * hi, x);
+    }
+  };
+  auto store_tile = [&](float* dst, int64_t ld, const f32x16& v) {
+    if (!tok) return;
+    float* p = dst + t * ld + 32 * w + 4 * hi;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      *reinterpret_cast<float4*>(p + 8 * q) = make_float4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
+  };
+  // x_t (bf16: its second and third terms are zero)
+  auto put_targets = [&]() {
+    for (int c = threadIdx.x; c < 32 * D / 8; c += NT) {
+      const int row = c / (D / 8), col = (c % (D / 8)) * 8;
+      const uint4 z = make_uint4(0, 0, 0, 0);
+      *reinterpret_cast<uint4*>(act[0] + row * AROW + col) =
+          tb + row < A.n_tgt ? *reinterpret_cast<const uint4*>(A.tgt + (tb + row) * D + col) : z;
+      *reinterpret_cast<uint4*>(act[1] + row * AROW + col) = z;
+      *reinterpret_cast<uint4*>(act[2] + row * AROW + col) = z;
+    }
+  };
+  auto fetch = [&](bf16x8 (&r)[KS], const bf16x8* __restrict__ Wp) {
+#pragma unroll
+    for (int k = 0; k < KS; ++k) r[k] = Wp[k * 64 + lane];
+  };
+  auto operand = [&](const bf16_bits (*src)[32 * AROW], int term, int k) {
+    return *reinterpret_cast<const bf16x8*>(src[term] + tcol * AROW + 8 * hi + 16 * k);
+  };
+  auto gemm_r = [&](const bf16x8 (&wt)[KS], const bf16_bits (*src)[32 * AROW], f32x16& acc) {
+#pragma unroll
+    for (int k = 0; k < KS; ++k)
+#pragma unroll
+      for (int term = 0; term < 3; ++term) acc = mfma_bf16(wt[k], operand(src, term, k), acc);
+  };
+  auto gemm = [&](const bf16x8* __restrict__ Wp, const bf16_bits (*src)[32 * AROW], f32x16& acc) {
+    bf16x8 wt[KS];
+    fetch(wt, Wp);
+    gemm_r(wt, src, acc);
+  };
+  const bf16x8* WoP = static_cast<const bf16x8*>(A.WoP);
+  const bf16x8* WcP = static_cast<const bf16x8*>(A.WcP);
+  const bf16x8* WuP = static_cast<const bf16x8*>(A.WuP);
+  const bf16x8* WvP = static_cast<const bf16x8*>(A.WvP);
+  const bf16x8* WdP = static_cast<const bf16x8*>(A.WdP);
+  const bf16x8* WqP = static_cast<const bf16x8*>(A.WqP);
+  const int KC = (A.n_cat + 1) * KS;  // k-steps of W_C
+  auto wc_tile = [&](int blk) { return WcP + ((int64_t)w * KC + (int64_t)blk * KS) * 64; };
+
+  if (A.first) {
+    put_targets();
+    __syncthreads();
+  } else {
+    bf16x8 wo[KS];
+    fetch(wo, WoP + (int64_t)w * KS * 64);  // lands during the merge
+    // merge the chunk partials: a wave's lanes read whole rows, four
+    // dimensions a lane, eight rows a pass, four chunks a round trip; the
+    // records of max_ch chunks are requested together with the target's own
+    // chunk count, which only masks them
+    constexpr int LPR = D / 4, CG = 4;
+    const int prow = threadIdx.x / LPR, dim = 4 * (threadIdx.x % LPR), j = dim / 32;
+#pragma unroll 1
+    for (int p0 = 0; p0 < 32; p0 += 16) {
+      float M[2], Ls[2], av[2][4];
+      int nch[2];
+      int64_t tt[2];
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const int64_t r = tb + p0 + 8 * i + prow;
+        tt[i] = r < A.n_tgt ? r : A.n_tgt - 1;
+        nch[i] = r < A.n_tgt ? A.tchunks[tt[i]] : 0;
+        M[i] = -INFINITY;
+        Ls[i] = 0.f;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) av[i][e] = 0.f;
+      }
+#pragma unroll 1
+      for (int cb = 0; cb < A.max_ch; cb += CG) {
+        float2 ml[2][CG];
+        float4 x[2][CG];
+#pragma unroll
+        for (int c = 0; c < CG; ++c)
+#pragma unroll
+          for (int i = 0; i < 2; ++i)
+            if (cb + c < A.max_ch) {
+              ml[i][c] = static_cast<const float2*>(A.part_ml)[((int64_t)(cb + c) * A.n_tgt + tt[i]) * H + j];
+              x[i][c] = *reinterpret_cast<const float4*>(A.part_acc + ((int64_t)(cb + c) * A.n_tgt + tt[i]) * D + dim);
+            }
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          float mn = M[i];
+#pragma unroll
+          for (int c = 0; c < CG; ++c)
+            if (cb + c < nch[i]) mn = fmaxf(mn, ml[i][c].x);
+          const float sc = M[i] == -INFINITY ? 0.f : exp2f(M[i] - mn);
+          M[i] = mn;
+          Ls[i] *= sc;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) av[i][e] *= sc;
+#pragma unroll
+          for (int c = 0; c < CG; ++c)
+            if (cb + c < nch[i]) {
+              const float wgt = exp2f(ml[i][c].x - mn);
+              Ls[i] += wgt * ml[i][c].y;
+              av[i][0] += wgt * x[i][c].x;
+              av[i][1] += wgt * x[i][c].y;
+              av[i][2] += wgt * x[i][c].z;
+              av[i][3] += wgt * x[i][c].w;
+            }
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const int row = p0 + 8 * i + prow;
+        if (tb + row < A.n_tgt) {
+          const float inv = 1.f / Ls[i];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) av[i][e] *= inv;
+          if (A.a_out && split == 0)
+            *reinterpret_cast<float4*>(A.a_out + tt[i] * D + dim) =
+                make_float4(av[i][0], av[i][1], av[i][2], av[i][3]);
+          if (A.lse_out && split == 0 && dim % 32 == 0) A.lse_out[tt[i] * H + j] = (M[i] + log2f(Ls[i])) * kLn2;
+        }
+        put4(act, row, dim, av[i]);
+      }
+    }
+    __syncthreads();
+    f32x16 o = {};
+    gemm_r(wo, act, o);
+    if (split == 0) store_tile(A.cat + (int64_t)(A.n_cat - 1) * D, A.ldcat, o);
+    // f = [o^(1) .. o^(i) || x_t] W_C: the block in registers first, then the
+    // earlier layers' blocks and x_t through LDS
+    f32x16 f = {};
+    __syncthreads();  // every wave is done with a
+    put_tile(act, o);
+    __syncthreads();
+    gemm(wc_tile(A.n_cat - 1), act, f);
+#pragma unroll 1
+    for (int blk = 0; blk + 1 < A.n_cat; ++blk) {
+      __syncthreads();
+      for (int c = threadIdx.x; c < 32 * D / 4; c += NT) {
+        const int row = c / (D / 4), col = (c % (D / 4)) * 4;
+        const float4 v = tb + row < A.n_tgt
+                             ? *reinterpret_cast<const float4*>(A.cat + (tb + row) * A.ldcat + (int64_t)blk * D + col)
+                             : make_float4(0.f, 0.f, 0.f, 0.f);
+        const float x[4] = {v.x, v.y, v.z, v.w};
+        put4(act, row, col, x);
+      }
+      __syncthreads();
+      gemm(wc_tile(blk), act, f);
+    }
+    __syncthreads();
+    put_targets();
+    __syncthreads();
+    gemm(wc_tile(A.n_cat), act, f);
+    __syncthreads();
+    put_tile(act, f);
+    __syncthreads();
+  }
+
+  // the SwiGLU block, D hidden columns at a time (this split's)
+  f32x16 y = {};
+  const int nc = NC > 0 ? NC : A.F / (D * A.splits);
+  const int c0 = split * nc;
+#pragma unroll(NC > 0 ? NC : 1)
+  for (int c = 0; c < nc; ++c) {
+    const int64_t up = (int64_t)((c0 + c) * NW + w) * KS * 64;
+    f32x16 u = {}, v = {};
+    {
+      bf16x8 wu[KS], wv[KS];
+      fetch(wu, WuP + up);
+      fetch(wv, WvP + up);
+#pragma unroll
+      for (int k = 0; k < KS; ++k)
+#pragma unroll
+        for (int term = 0; term < 3; ++term) {
+          const bf16x8 x = operand(act, term, k);
+          u = mfma_bf16(wu[k], x, u);
+          v = mfma_bf16(wv[k], x, v);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < 16; ++i) u[i] = u[i] * v[i] / (1.f + expf(-v[i]));
+    if (c > 0) __syncthreads();  // hid was read by the previous chunk's down projection
+    put_tile(hid, u);
+    __syncthreads();
+    gemm(WdP + ((int64_t)w * (A.F / 16) + (int64_t)(c0 + c) * KS) * 64, hid, y);
+  }
+  if (A.splits > 1) {
+    // in register order (the reader's thread holds the same elements)
+    auto part_at = [&](int k, int i) {
+      return reinterpret_cast<uint64_t*>(A.spart) + (((int64_t)k * A.groups + group) * 8 + i) * NT + threadIdx.x;
+    };
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      __hip_atomic_store(part_at(split, i),
+                         (uint64_t)__float_as_uint(y[2 * i]) | ((uint64_t)__float_as_uint(y[2 * i + 1]) << 32),
+                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the part is in memory before its arrival is counted
+    __syncthreads();
+    if (threadIdx.x == 0)
+      arrived = __hip_atomic_fetch_add(A.cnt + group, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    if (arrived != A.splits - 1) return;
+    y = f32x16{};
+    for (int k = 0; k < A.splits; ++k)
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const uint64_t x = __hip_atomic_load(part_at(k, i), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        y[2 * i] += __uint_as_float(static_cast<uint32_t>(x));
+        y[2 * i + 1] += __uint_as_float(static_cast<uint32_t>(x >> 32));
+      }
+  }
+  if (A.z_out) {
+    if (tok) {
+      bf16_bits* p = A.z_out + t * D + 32 * w + 4 * hi;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        uint2 pk;
+        pk.x = (uint32_t)from_f32<bf16_bits>(y[4 * q]) | ((uint32_t)from_f32<bf16_bits>(y[4 * q + 1]) << 16);
+        pk.y = (uint32_t)from_f32<bf16_bits>(y[4 * q + 2]) | ((uint32_t)from_f32<bf16_bits>(y[4 * q + 3]) << 16);
+        *reinterpret_cast<uint2*>(p + 8 * q) = pk;
+      }
+    }
+    return;
+  }
+  // LayerNorm over the row (all waves), mean then centred squares
+  auto row_sum = [&](float s) {
+    s += __shfl_xor(s, 32);
+    if (hi == 0) red[w][tcol] = s;
+    __syncthreads();
+    float r = 0.f;
+#pragma unroll
+    for (int k = 0; k < NW; ++k) r += red[k][tcol];
+    __syncthreads();
+    return r;
+  };
+  float s = 0.f;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) s += y[i];
+  const float mean = row_sum(s) / D;
+  float q2 = 0.f;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    y[i] -= mean;
+    q2 += y[i] * y[i];
+  }
+  const float rstd = 1.f / sqrtf(row_sum(q2) / D + kLnEps);
+#pragma unroll
+  for (int i = 0; i < 16; ++i) y[i] *= rstd;
+  if (A.q_out) store_tile(A.q_out, D, y);
+  put_tile(act, y);  // act was last read before the row sums' barriers
+  __syncthreads();
+  f32x16 q = {};
+  gemm(WqP + (int64_t)w * KS * 64, act, q);
+  if (tok) {
+    const float qs = kLog2e * 0.17677669529663687f;  // log2(e) / sqrt(32)
+    f16x8 h0, h1;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      h0[i] = static_cast<_Float16>(q[i] * qs);
+      h1[i] = static_cast<_Float16>(q[8 + i] * qs);
+    }
+    f16x8* qn = static_cast<f16x8*>(A.QN) + (t * D + 32 * w) / 8;
+    qn[hi] = h0;
+    qn[2 + hi] = h1;
+  }
 }
 
 }  // namespace
@@ -285,12 +596,32 @@ hipError_t layer_norm_rows(const float* y, int64_t rows, int d, float* out, hipS
   return hipGetLastError();
 }
 
-hipError_t qn_pack(const float* Q, void* QN, int64_t n_tgt, int D, hipStream_t st) {
-  const int64_t groups = n_tgt * D / 8;
-  if (groups == 0) return hipSuccess;
-  if (D % 32) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(qn_pack_kernel, dim3(static_cast<unsigned>(ceil_div(groups, 256))), dim3(256), 0, st, Q,
-                     (_Float16*)QN, groups);
+hipError_t paper_target(int D, const PaperTarget& f, hipStream_t st) {
+  if (f.n_tgt == 0) return hipSuccess;
+  if (f.splits < 1 || f.F % (D * f.splits) || (f.splits > 1 && (!f.spart || !f.cnt)) ||
+      (!f.first && (f.n_cat < 1 || f.max_ch < 1 || f.max_ch > kMaxChunks)))
+    return hipErrorInvalidValue;
+  PaperTarget A = f;
+  A.groups = static_cast<int>(ceil_div(f.n_tgt, 32));
+  const dim3 g(static_cast<unsigned>((int64_t)A.groups * A.splits));
+  // hidden chunks a workgroup at F = 4 d: 1, 2 or 4, known to the compiler
+  const int nc = f.F == 4 * D ? 4 / f.splits : 0;
+#define STCA_PT1(DD, NC) hipLaunchKernelGGL((paper_target_kernel<DD, NC>), g, dim3(64 * (DD / 32)), 0, st, A)
+#define STCA_PT(DD)                     \
+  switch (nc) {                         \
+    case 1: STCA_PT1(DD, 1); break;     \
+    case 2: STCA_PT1(DD, 2); break;     \
+    case 4: STCA_PT1(DD, 4); break;     \
+    default: STCA_PT1(DD, 0); break;    \
+  }
+  switch (D) {
+    case 64: STCA_PT(64); break;
+    case 128: STCA_PT(128); break;
+    case 256: STCA_PT(256); break;
+    default: return hipErrorInvalidValue;
+  }
+#undef STCA_PT
+#undef STCA_PT1
   return hipGetLastError();
 }
 
