@@ -241,7 +241,7 @@ stca_status_t forward_paper_fast(const PaperLayout& L, const stca_batch_t* b, co
   for (int i = 0; i < n; ++i) {
     // X~^(i) = LN(SwiGLUFFN^(i)(X)), then the layer's attention over it
     HIPCHK(swiglu_ln(d, hist, nh, at<char>(ws, L.wsp) + i * swiglu_packed_bytes(d, F), F, at<char>(ws, L.xt16),
-                     saved ? at<float>(saved, SL.xt) + (size_t)i * nh * d : nullptr, st));
+                     saved ? at<float>(saved, SL.xt) + (size_t)i * nh * d : nullptr, device_cus(), st));
     HIPCHK(rec.mark("swiglu_ln"));
     for (int wide = 0; wide < 2; ++wide) {
       if (wide ? L.any_wide : L.any_narrow)

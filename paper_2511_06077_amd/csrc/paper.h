@@ -17,7 +17,7 @@ hipError_t swiglu_pack(const void* Wu, const void* Wv, const void* Wo, int n_lay
 // LN(SwiGLUFFN(X)) with one layer's packed weights; D in {64, 128, 256},
 // F % 32 == 0.
 hipError_t swiglu_ln(int D, const void* X, int64_t n_rows, const void* Wp_layer, int F, void* out16, float* out32,
-                     hipStream_t st);
+                     int n_cu, hipStream_t st);
 // u = u * v * sigmoid(v), elementwise (fp32).
 hipError_t swiglu_gate_f32(float* u, const float* v, int64_t n, hipStream_t st);
 // out[r] = LN(y[r]) over d features (fp32; out may alias y).

@@ -76,11 +76,11 @@ __global__ void swiglu_pack_kernel(const bf16_bits* __restrict__ Wu, const bf16_
   }
 }
 
-constexpr int kSwWaves = 8;  // waves per workgroup (two per SIMD), 32 rows each
-
-template <int D>
-__global__ __launch_bounds__(kSwWaves * 64)
-__attribute__((amdgpu_waves_per_eu(kSwWaves / 4, kSwWaves / 4))) void swiglu_ln_kernel(
+// NW waves per workgroup, 32 rows each: eight (two per SIMD), or four for few
+// rows (see swiglu_ln).
+template <int D, int NW>
+__global__ __launch_bounds__(NW * 64)
+__attribute__((amdgpu_waves_per_eu(NW / 4, NW / 4))) void swiglu_ln_kernel(
     const bf16_bits* __restrict__ X, int64_t n_rows, const unsigned char* __restrict__ Wp, int F,
     bf16_bits* __restrict__ out16, float* __restrict__ out32) {
   constexpr int KS = D / 16;       // k-steps of the up projections
@@ -90,7 +90,7 @@ __attribute__((amdgpu_waves_per_eu(kSwWaves / 4, kSwWaves / 4))) void swiglu_ln_
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];  // [2][CB]
   const int w = threadIdx.x / 64, lane = threadIdx.x % 64;
   const int tcol = lane % 32, hi = lane / 32;
-  const int64_t row = (int64_t)blockIdx.x * (32 * kSwWaves) + 32 * w + tcol;
+  const int64_t row = (int64_t)blockIdx.x * (32 * NW) + 32 * w + tcol;
   const bool live = row < n_rows;
 
   // X^T as B operands: lane (row, hi), k-step ks holds X[row][16ks + 8hi .. +7]
@@ -106,7 +106,7 @@ __attribute__((amdgpu_waves_per_eu(kSwWaves / 4, kSwWaves / 4))) void swiglu_ln_
   auto dma = [&](int c, int buf) {
     const unsigned char* src = Wp + (size_t)c * CB + lane * 16;
     unsigned char* dst = smem + buf * CB;
-    for (int i = w; i < CB / 1024; i += kSwWaves)
+    for (int i = w; i < CB / 1024; i += NW)
       __builtin_amdgcn_global_load_lds(static_cast<const void*>(src + i * 1024),
                                        (void __attribute__((address_space(3)))*)(dst + i * 1024), 16, 0, 0);
   };
@@ -176,8 +176,9 @@ constexpr size_t swiglu_chunk_bytes() {
   return (size_t)2 * (D / 16) * 1024 + (size_t)(D / 32) * 2048;
 }
 
-template <typename K>
-hipError_t allow_lds(K kernel, size_t bytes) {
+// (a parameter of the template, so that each kernel has its own record)
+template <auto kernel>
+hipError_t allow_lds(size_t bytes) {
   static int set_for[64] = {0};  // per device: bytes granted so far
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
@@ -560,19 +561,27 @@ hipError_t swiglu_pack(const void* Wu, const void* Wv, const void* Wo, int n_lay
   return hipGetLastError();
 }
 
+// One wave per SIMD takes 73 us for its rows' chunks and two 97-102 (d = 256,
+// F = 4 d), whatever share of the rows is live, so few rows, up to 128 a CU,
+// go out as four-wave workgroups (14000 rows 81 -> 73 us); more as eight-wave
+// ones throughout (the rest of whole rounds as a four-wave launch: 512 + 73 us
+// against 585 in one, 333397 rows).
 hipError_t swiglu_ln(int D, const void* X, int64_t n_rows, const void* Wp_layer, int F, void* out16, float* out32,
-                     hipStream_t st) {
+                     int n_cu, hipStream_t st) {
   if (n_rows == 0) return hipSuccess;
-  if (F % 32) return hipErrorInvalidValue;
-  const dim3 grid(static_cast<unsigned>(ceil_div(n_rows, 32 * kSwWaves)));
-#define STCA_SWIGLU(DD)                                                                                      \
-  {                                                                                                          \
-    const size_t lds = 2 * swiglu_chunk_bytes<DD>();                                                         \
-    hipError_t e = allow_lds(swiglu_ln_kernel<DD>, lds);                                                     \
-    if (e != hipSuccess) return e;                                                                           \
-    hipLaunchKernelGGL(swiglu_ln_kernel<DD>, grid, dim3(64 * kSwWaves), lds, st, (const bf16_bits*)X, n_rows, \
-                       (const unsigned char*)Wp_layer, F, (bf16_bits*)out16, out32);                         \
+  if (F % 32 || n_cu < 1) return hipErrorInvalidValue;
+  const bool few = n_rows <= 128 * static_cast<int64_t>(n_cu);
+#define STCA_SWIGLU1(DD, NW)                                                                               \
+  {                                                                                                        \
+    const size_t lds = 2 * swiglu_chunk_bytes<DD>();                                                       \
+    hipError_t e = allow_lds<swiglu_ln_kernel<DD, NW>>(lds);                                               \
+    if (e != hipSuccess) return e;                                                                         \
+    hipLaunchKernelGGL((swiglu_ln_kernel<DD, NW>), dim3(static_cast<unsigned>(ceil_div(n_rows, 32 * NW))), \
+                       dim3(64 * NW), lds, st, (const bf16_bits*)X, n_rows,                                \
+                       (const unsigned char*)Wp_layer, F, (bf16_bits*)out16, out32);                       \
   }
+#define STCA_SWIGLU(DD) \
+  if (few) STCA_SWIGLU1(DD, 4) else STCA_SWIGLU1(DD, 8)
   switch (D) {
     case 64: STCA_SWIGLU(64); break;
     case 128: STCA_SWIGLU(128); break;
@@ -580,6 +589,7 @@ hipError_t swiglu_ln(int D, const void* X, int64_t n_rows, const void* Wp_layer,
     default: return hipErrorInvalidValue;
   }
 #undef STCA_SWIGLU
+#undef STCA_SWIGLU1
   return hipGetLastError();
 }
 
