@@ -575,15 +575,16 @@ stca_status_t forward_fast(const Layout& L, const stca_batch_t* b, const void* h
   WsHeader* hdr2 = L.mixed ? at<WsHeader>(ws, L.hdr2) : hdr;
   Unit* units2 = reo_part ? at<Unit>(ws, L.units2) : nullptr;
   int32_t* tch_r = reo_part ? at<int32_t>(ws, L.tch_r) : nullptr;
-  if (std_part)
-    HIPCHK(launch_sched(b->hist_off, b->tgt_off, b->n_requests, L.nh, L.nt, L.chunk_blocks, L.group, units,
-                        L.max_units, tch, hdr, st, L.std_lo, 1 << 30, device_cus()));
-  if (std_part) HIPCHK(rec.mark("sched"));
-  if (reo_part)
-    HIPCHK(launch_sched(b->hist_off, b->tgt_off, b->n_requests, L.nh, L.nt, L.chunk_blocks2, L.group2, units2,
-                        L.max_units2, tch_r, hdr2, st, L.reord_lo, L.reord_hi, device_cus()));
-  if (reo_part) HIPCHK(rec.mark("sched"));
   {
+    // the schedules and the repacked weights, in one launch
+    SchedSpec sp[2];
+    int ns = 0;
+    if (std_part)
+      sp[ns++] = {b->hist_off, b->tgt_off, b->n_requests, L.nh, L.nt, L.chunk_blocks, L.group, units, L.max_units,
+                  tch, hdr, L.std_lo, 1 << 30, device_cus()};
+    if (reo_part)
+      sp[ns++] = {b->hist_off, b->tgt_off, b->n_requests, L.nh, L.nt, L.chunk_blocks2, L.group2, units2,
+                  L.max_units2, tch_r, hdr2, L.reord_lo, L.reord_hi, device_cus()};
     PackJobs pj{};
     int nj = 0;
     if (std_part) {
@@ -595,7 +596,8 @@ stca_status_t forward_fast(const Layout& L, const stca_batch_t* b, const void* h
     pj.job[nj++] = {w->wq, at<char>(ws, L.wqp), d, d, 1};
     pj.job[nj++] = {w->w1, at<char>(ws, L.w1p), d, F, 1};
     pj.job[nj++] = {w->w2, at<char>(ws, L.w2p), F, d, 1};
-    HIPCHK(fast_pack_many(pj, nj, n, st));
+    HIPCHK(launch_setup(sp, ns, pj, nj, n, st));
+    for (int i = 0; i < ns; ++i) HIPCHK(rec.mark("sched"));
     HIPCHK(rec.mark("pack"));
   }
   char* kv = at<char>(ws, L.kv);
@@ -694,8 +696,8 @@ stca_status_t forward_generic(const Layout& L, int bf, const stca_batch_t* b, co
   WsHeader* hdr = at<WsHeader>(ws, L.hdr);
   Unit* units = at<Unit>(ws, L.units);
   int32_t* tch = at<int32_t>(ws, L.tchunks);
-  HIPCHK(launch_sched(b->hist_off, b->tgt_off, b->n_requests, L.nh, L.nt, L.chunk_blocks, L.group, units, L.max_units,
-                      tch, hdr, st, 1, 1 << 30, device_cus())); HIPCHK(rec.mark("sched"));
+  HIPCHK(launch_sched({b->hist_off, b->tgt_off, b->n_requests, L.nh, L.nt, L.chunk_blocks, L.group, units, L.max_units,
+                       tch, hdr, 1, 1 << 30, device_cus()}, st)); HIPCHK(rec.mark("sched"));
   float* kv = at<float>(ws, L.kv32);
   float* q = at<float>(ws, L.q32);
   float* hid = at<float>(ws, L.hid);
@@ -751,18 +753,23 @@ stca_status_t backward_generic(const Layout& L, int bf, const stca_batch_t* b, c
   Unit* units = at<Unit>(ws, L.units);
   int32_t* tch = at<int32_t>(ws, L.tchunks);
   HIPCHK(rec.start());
-  HIPCHK(launch_sched(b->hist_off, b->tgt_off, b->n_requests, nh, nt, L.chunk_blocks, L.group, units, L.max_units, tch,
-                      hdr, st, 1, 1 << 30, device_cus()));
+  // the schedules; with the fused recomputation in one launch with the
+  // repacked weights
+  SchedSpec sp[3];
+  int ns = 0;
+  sp[ns++] = {b->hist_off, b->tgt_off, b->n_requests, nh, nt, L.chunk_blocks, L.group, units, L.max_units, tch, hdr, 1,
+              1 << 30, device_cus()};
   if (L.brd) {
     // history chunks of the requests for the reordered attention backward,
     // units of at most 128 rows for dX
     // (largest first, all in one round: the device takes them in order)
-    HIPCHK(launch_sched(b->hist_off, b->tgt_off, b->n_requests, nh, nt, L.rb_cb, kRbPairs / h,
-                        at<Unit>(ws, L.rb_units), L.rb_maxu, at<int32_t>(ws, L.rb_tch), at<WsHeader>(ws, L.rb_hdr), st,
-                        1, 1 << 30, 1 << 30, at<int32_t>(ws, L.rb_order)));
-    HIPCHK(launch_sched(b->hist_off, b->tgt_off, b->n_requests, nh, nt, 4, 32, at<Unit>(ws, L.rb_unitsx),
-                        L.rb_maxx, at<int32_t>(ws, L.rb_tchx), at<WsHeader>(ws, L.rb_hdrx), st));
+    sp[ns++] = {b->hist_off, b->tgt_off, b->n_requests, nh, nt, L.rb_cb, kRbPairs / h, at<Unit>(ws, L.rb_units),
+                L.rb_maxu, at<int32_t>(ws, L.rb_tch), at<WsHeader>(ws, L.rb_hdr), 1, 1 << 30, 1 << 30,
+                at<int32_t>(ws, L.rb_order)};
+    sp[ns++] = {b->hist_off, b->tgt_off, b->n_requests, nh, nt, 4, 32, at<Unit>(ws, L.rb_unitsx), L.rb_maxx,
+                at<int32_t>(ws, L.rb_tchx), at<WsHeader>(ws, L.rb_hdrx)};
   }
+  if (!L.bfused) HIPCHK(launch_sched(sp[0], st));
   HIPCHK(rec.mark("sched"));
   void* dkv = L.brd ? nullptr : at<char>(ws, L.dkv);
   // the recomputed per-layer tensors: in the workspace, or the training record
@@ -834,7 +841,7 @@ stca_status_t backward_generic(const Layout& L, int bf, const stca_batch_t* b, c
       pj.job[7] = {w->w1, at<char>(ws, L.fw1t), F, d, 0, 1};
       pj.job[8] = {w->wo, at<char>(ws, L.fwot), d, d, 0, 1};
       pj.job[9] = {w->wq, at<char>(ws, L.fwqt), d, d, 0, 1};
-      HIPCHK(fast_pack_many(pj, 10, n, st));
+      HIPCHK(launch_setup(sp, ns, pj, 10, n, st));
     }
   }
   // persistent grid of the fused kernels: one workgroup per CU

@@ -177,9 +177,8 @@ stca_status_t forward_paper_fast(const PaperLayout& L, const stca_batch_t* b, co
   const size_t dd = (size_t)d * d, dF = (size_t)d * F;
   auto elems = [](const void* base, size_t k) { return static_cast<const bf16_bits*>(base) + k; };
   auto pk = [&](size_t off, size_t k) { return at<bf16_bits>(ws, off) + k; };
-  HIPCHK(launch_sched(b->hist_off, b->tgt_off, b->n_requests, nh, nt, L.chunk_blocks, kTargetGroup, units,
-                      L.max_units, at<int32_t>(ws, L.tchunks), hdr, st, 1, 1 << 30, device_cus()));
-  HIPCHK(rec.mark("sched"));
+  const SchedSpec sp{b->hist_off, b->tgt_off, b->n_requests, nh, nt, L.chunk_blocks, kTargetGroup, units,
+                     L.max_units, at<int32_t>(ws, L.tchunks), hdr, 1, 1 << 30, device_cus()};
   HIPCHK(swiglu_pack(w->ffn_u, w->ffn_v, w->ffn_o, n, d, F, at<char>(ws, L.wsp), st));
   HIPCHK(rec.mark("pack_swiglu"));
   {
@@ -191,7 +190,8 @@ stca_status_t forward_paper_fast(const PaperLayout& L, const stca_batch_t* b, co
     pj.job[4] = {w->ffn_u, pk(L.wup, 0), d, F, 0};
     pj.job[5] = {w->ffn_v, pk(L.wvup, 0), d, F, 0};
     pj.job[6] = {w->ffn_o, pk(L.wdp, 0), F, d, 0};
-    HIPCHK(fast_pack_many(pj, 7, n, st));
+    HIPCHK(launch_setup(&sp, 1, pj, 7, n, st));
+    HIPCHK(rec.mark("sched"));
     // the weights without a layer axis, kMaxPackJobs at a time
     std::vector<PackJob> one = {{w->wz, pk(L.wzp, 0), (n + 1) * d, d, 0},
                                 {w->z_u, pk(L.zup, 0), d, F, 0},
@@ -295,8 +295,8 @@ stca_status_t forward_paper(const PaperLayout& L, int bf, const stca_batch_t* b,
   const int64_t ldcat = (int64_t)n * d;
   auto W = [&](const void* base, size_t elems) { return static_cast<const char*>(base) + elems * es; };
   auto qbuf = [&](int i) { return saved ? at<float>(saved, SL.q) + (size_t)i * nt * d : at<float>(ws, L.q); };
-  HIPCHK(launch_sched(b->hist_off, b->tgt_off, b->n_requests, nh, nt, L.chunk_blocks, kTargetGroup, units,
-                      L.max_units, tch, hdr, st, 1, 1 << 30, device_cus()));
+  HIPCHK(launch_sched({b->hist_off, b->tgt_off, b->n_requests, nh, nt, L.chunk_blocks, kTargetGroup, units,
+                       L.max_units, tch, hdr, 1, 1 << 30, device_cus()}, st));
   HIPCHK(rec.mark("sched"));
   // y = SwiGLUFFN(x) on the target rows (Eq. swigluffn), fp32 result
   auto target_block = [&](const void* x, int x_bf16, const void* wu, const void* wv, const void* wo) -> hipError_t {

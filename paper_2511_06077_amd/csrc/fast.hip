@@ -82,53 +82,6 @@ __device__ __forceinline__ uint16_t f16_bits(float x) {
   return __builtin_bit_cast(uint16_t, static_cast<_Float16>(x));
 }
 
-template <typename V8>
-struct elem_of;
-template <>
-struct elem_of<bf16x8> {
-  typedef __bf16 type;
-};
-template <>
-struct elem_of<f16x8> {
-  typedef _Float16 type;
-};
-
-// ------------------------------------------------------------- repacking
-// W: [layers][K][N] bf16 row-major -> P: [layers][N/32][K/16][64][8], kept
-// bf16 (V8 = bf16x8) or converted to fp16 (V8 = f16x8, exact for every bf16
-// value inside fp16's range).
-// Several weights in one launch (blockIdx.z = job): the per-call repacking of
-// a forward costs one launch instead of one per weight.
-template <typename V8>
-__device__ __forceinline__ void pack_one(const bf16_bits* __restrict__ w, V8* __restrict__ P, int K, int N,
-                                         int64_t g, bool trans) {
-  const int lane = g % 64;
-  const int64_t rest = g / 64;
-  const int ks = rest % (K / 16);
-  const int nb = rest / (K / 16);
-  const int n = nb * 32 + lane % 32;
-  const int k0 = ks * 16 + 8 * (lane / 32);
-  V8 r;
-#pragma unroll
-  for (int e = 0; e < 8; ++e)
-    r[e] = static_cast<typename elem_of<V8>::type>(
-        to_f32(w[trans ? (int64_t)n * K + k0 + e : (int64_t)(k0 + e) * N + n]));
-  P[g] = r;
-}
-
-__global__ void pack_many_kernel(PackJobs J) {
-  const int j = blockIdx.z, layer = blockIdx.y;
-  const int64_t groups = (int64_t)(J.job[j].N / 32) * (J.job[j].K / 16) * 64;
-  const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (g >= groups) return;
-  const PackJob& b = J.job[j];
-  const bf16_bits* w = static_cast<const bf16_bits*>(b.src) + (int64_t)layer * b.K * b.N;
-  if (b.to_f16)
-    pack_one(w, static_cast<f16x8*>(b.dst) + (int64_t)layer * groups, b.K, b.N, g, b.trans != 0);
-  else
-    pack_one(w, static_cast<bf16x8*>(b.dst) + (int64_t)layer * groups, b.K, b.N, g, b.trans != 0);
-}
-
 // ------------------------------------------------------ K1: projection
 // Grid: n_layers * parts workgroups, one wave per head.  Each wave keeps its
 // head's W_K and W_V columns in registers for the whole kernel; the
@@ -1087,16 +1040,6 @@ __global__ __launch_bounds__(64 * (D / 32)) void update_kernel(UpdateArgs A) {
 }  // namespace
 
 // ------------------------------------------------------------ launchers
-hipError_t fast_pack_many(const PackJobs& jobs, int n_jobs, int n_layers, hipStream_t st) {
-  if (n_jobs < 1 || n_jobs > kMaxPackJobs) return hipErrorInvalidValue;
-  int64_t groups = 0;
-  for (int j = 0; j < n_jobs; ++j)
-    groups = std::max<int64_t>(groups, (int64_t)(jobs.job[j].N / 32) * (jobs.job[j].K / 16) * 64);
-  dim3 g(static_cast<unsigned>(ceil_div(groups, 256)), n_layers, n_jobs);
-  hipLaunchKernelGGL(pack_many_kernel, g, dim3(256), 0, st, jobs);
-  return hipGetLastError();
-}
-
 int fast_proj_parts(int n_layers, int64_t n_blocks, int n_cu) {
   // workgroups = n_layers * parts; parts a multiple of 8 (XCD grouping), about
   // one resident workgroup per CU, and at least one block per part

@@ -14,10 +14,24 @@ namespace stca {
 // and place every partial by its chunk index); 0: request and chunk order.
 // order (nullable, [max_units]): each unit's rank in request, group and chunk
 // order, in which the chunks of one target group are consecutive.
-hipError_t launch_sched(const int32_t* hoff, const int32_t* toff, int R, int64_t n_hist, int64_t n_tgt,
-                        int chunk_blocks, int group, Unit* units, int64_t max_units, int32_t* tchunks,
-                        WsHeader* hdr, hipStream_t st, int m_lo = 1, int m_hi = 1 << 30, int deal = 0,
-                        int32_t* order = nullptr);
+struct SchedSpec {
+  const int32_t *hoff, *toff;
+  int R;
+  int64_t n_hist, n_tgt;
+  int chunk_blocks, group;
+  Unit* units;
+  int64_t max_units;
+  int32_t* tchunks;
+  WsHeader* hdr;
+  int m_lo = 1, m_hi = 1 << 30, deal = 0;
+  int32_t* order = nullptr;
+};
+hipError_t launch_sched(const SchedSpec& s, hipStream_t st);
+struct PackJobs;
+// Up to kMaxSetupScheds schedules and a repacking (fast_pack_many's jobs) in one launch.
+constexpr int kMaxSetupScheds = 3;
+hipError_t launch_setup(const SchedSpec* sched, int n_sched, const PackJobs& jobs, int n_jobs, int n_layers,
+                        hipStream_t st);
 int64_t host_count_units(const int32_t* hoff, const int32_t* toff, int R, int chunk_blocks, int group,
                          int m_lo = 1, int m_hi = 1 << 30);
 

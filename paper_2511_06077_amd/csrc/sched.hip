@@ -19,12 +19,23 @@
 // With `order`, entry u is unit u's rank in request, group and chunk order (the
 // chunks of one target group have consecutive ranks).
 //
-// One workgroup of 1024 threads; each thread owns a contiguous run of requests.
+// One workgroup of 1024 threads.  Up to 1024 requests: a thread per request
+// counts its units, then the threads share the units (each finds its request
+// by a binary search over the counts' prefix sums) and the targets' chunk
+// counts.  One thread writing all its request's units and targets took 14 us
+// for one request of 16 chunks and 40 targets, 27 us for 16 requests of 256
+// targets.  More requests: each thread owns a contiguous run of them.
 // Invalid segments produce no units and set the workspace status, so no later
 // kernel reads outside the buffers whatever the offsets hold.  Only requests
 // with m_lo..m_hi targets get units (a batch can be split between two forms
 // of the attention, each with its own schedule); every request is validated.
+//
+// The per-call weight repacking lives here too: a forward's schedules (one
+// workgroup each) and its repacking run as one launch, side by side.
+#include <algorithm>
+
 #include "common.h"
+#include "fast.h"
 #include "internal.h"
 
 namespace stca {
@@ -102,116 +113,321 @@ __device__ __forceinline__ int size_bucket(int size, int chunk_blocks) {
   return min(kSizeBuckets - 1, static_cast<int>((int64_t)size * kSizeBuckets / (chunk_blocks + 1)));
 }
 
-__global__ __launch_bounds__(kSchedThreads) void sched_kernel(const int32_t* __restrict__ hoff,
-                                                              const int32_t* __restrict__ toff, int R,
-                                                              int64_t n_hist, int64_t n_tgt,
-                                                              int chunk_blocks, int group, int m_lo, int m_hi,
-                                                              int by_size, unsigned deal,
-                                                              Unit* __restrict__ units,
-                                                              int64_t max_units,
-                                                              int32_t* __restrict__ tchunks,
-                                                              WsHeader* __restrict__ hdr,
-                                                              int32_t* __restrict__ order) {
-  __shared__ int64_t scan[kSchedThreads];
-  __shared__ int bad;
-  __shared__ unsigned cursor[2][kSizeBuckets];  // by_size: units, then next rank, per (class, bucket)
+// One schedule: launch_sched's arguments.
+struct SchedJob {
+  const int32_t *hoff, *toff;
+  int R;
+  int64_t n_hist, n_tgt;
+  int chunk_blocks, group, m_lo, m_hi, by_size;
+  unsigned deal;
+  Unit* units;
+  int64_t max_units;
+  int32_t* tchunks;
+  WsHeader* hdr;
+  int32_t* order;
+};
+
+struct SchedLds {
+  int64_t scan[kSchedThreads];
+  int bad;
+  unsigned cursor[2][kSizeBuckets];  // by_size: units, then next rank, per (class, bucket)
+  // up to kSchedThreads requests: first unit of each request within its class
+  // (then the total), first target, chunk count
+  int32_t pn[kSchedThreads + 1], pw[kSchedThreads + 1], toff[kSchedThreads], nch[kSchedThreads];
+};
+
+__device__ void sched_body(const SchedJob& S, SchedLds& L) {
   const int tid = threadIdx.x;
-  if (tid == 0) bad = (hoff[0] != 0 || toff[0] != 0 || hoff[R] != n_hist || toff[R] != n_tgt) ? 1 : 0;
-  if (tid < 2 * kSizeBuckets) cursor[tid / kSizeBuckets][tid % kSizeBuckets] = 0;
-  for (int64_t t = tid; t < n_tgt; t += kSchedThreads) tchunks[t] = 0;
+  const int R = S.R, group = S.group;
+  const int64_t n_tgt = S.n_tgt;
+  const bool few = R <= kSchedThreads;
+  if (tid == 0)
+    L.bad = (S.hoff[0] != 0 || S.toff[0] != 0 || S.hoff[R] != S.n_hist || S.toff[R] != n_tgt) ? 1 : 0;
+  if (tid < 2 * kSizeBuckets) L.cursor[tid / kSizeBuckets][tid % kSizeBuckets] = 0;
+  if (!few)
+    for (int64_t t = tid; t < n_tgt; t += kSchedThreads) S.tchunks[t] = 0;
   __syncthreads();
 
+  auto plan = [&](int r) {
+    return plan_request(S.hoff, S.toff, r, S.n_hist, n_tgt, S.chunk_blocks, group, S.m_lo, S.m_hi);
+  };
   const int per = static_cast<int>(ceil_div(R, kSchedThreads));
   const int rb = tid * per;
   const int re = min(R, rb + per);
   int64_t narrow = 0, wide = 0;
   bool any_bad = false;
   for (int r = rb; r < re; ++r) {
-    ReqPlan p = plan_request(hoff, toff, r, n_hist, n_tgt, chunk_blocks, group, m_lo, m_hi);
+    const ReqPlan p = plan(r);
     any_bad |= !p.ok;
-    const int32_t bh = static_cast<int32_t>(ceil_div(p.h1, kBlockTokens));
-    for (int g = 0; g < p.ng; ++g) {
-      const int cls = group_size(p, g, group) > 32 ? 1 : 0;
-      (cls ? wide : narrow) += p.nch;
-      if (by_size)  // units per (class, size bucket)
+    if (p.ng > 0) {
+      // every group but the last is full
+      const int last_wide = group_size(p, p.ng - 1, group) > 32 ? 1 : 0;
+      const int64_t w = (int64_t)(group > 32 ? p.ng - 1 : 0) + last_wide;
+      wide += w * p.nch;
+      narrow += (p.ng - w) * p.nch;
+    }
+    if (few) {
+      L.toff[r] = p.t0;
+      L.nch[r] = p.nch;
+    } else if (S.by_size) {  // units per (class, size bucket)
+      const int32_t bh = static_cast<int32_t>(ceil_div(p.h1, kBlockTokens));
+      for (int g = 0; g < p.ng; ++g)
         for (int c = 0; c < p.nch; ++c) {
           const int b0 = p.bl + c * p.cb;
-          atomicAdd(&cursor[cls][size_bucket(min(b0 + p.cb, bh) - b0, chunk_blocks)], 1u);
+          atomicAdd(&L.cursor[group_size(p, g, group) > 32][size_bucket(min(b0 + p.cb, bh) - b0, S.chunk_blocks)], 1u);
         }
     }
   }
-  if (any_bad) atomicOr(&bad, 1);
-  int64_t un = block_scan(scan, narrow);
-  const int64_t total_narrow = scan[kSchedThreads - 1];
+  if (any_bad) atomicOr(&L.bad, 1);
+  int64_t un = block_scan(L.scan, narrow);
+  const int64_t total_narrow = L.scan[kSchedThreads - 1];
   __syncthreads();
-  int64_t uw = total_narrow + block_scan(scan, wide);
-  const int64_t total = total_narrow + scan[kSchedThreads - 1];
-  if (by_size) {
-    // each bucket's rank range within its class, from the largest bucket down
+  const int64_t uwc = block_scan(L.scan, wide);
+  const int64_t total = total_narrow + L.scan[kSchedThreads - 1];
+  int64_t uw = total_narrow + uwc;
+
+  // the place of the unit of rank ur: with by_size, rank k in the class's
+  // descending order; complete rounds of `deal` units are dealt in alternating
+  // directions, so that a workgroup taking a large unit in one round takes a
+  // small one in the next
+  auto place = [&](int cls, int size, int64_t ur) -> int64_t {
+    if (!S.by_size) return ur;
+    const unsigned k = atomicAdd(&L.cursor[cls][size_bucket(size, S.chunk_blocks)], 1u);
+    const unsigned nc = static_cast<unsigned>(cls ? total - total_narrow : total_narrow);
+    const unsigned j = k / S.deal, i = k - j * S.deal;
+    const bool back = (j & 1) && (j + 1) * S.deal <= nc;
+    return (cls ? total_narrow : 0) + static_cast<int64_t>(j) * S.deal + (back ? S.deal - 1 - i : i);
+  };
+  auto emit = [&](const ReqPlan& p, int r, int g, int c, int64_t ur) {
+    const int32_t bh = static_cast<int32_t>(ceil_div(p.h1, kBlockTokens));
+    Unit v;
+    v.r = r;
+    v.t0 = p.t0 + g * group;
+    v.nt = group_size(p, g, group);
+    v.c = c;
+    v.b0 = p.bl + c * p.cb;
+    v.b1 = min(v.b0 + p.cb, bh);
+    v.l0 = p.h0;
+    v.l1 = p.h1;
+    const int64_t u = place(v.nt > 32 ? 1 : 0, v.b1 - v.b0, ur);
+    if (u >= S.max_units) return;
+    S.units[u] = v;
+    if (S.order) S.order[u] = static_cast<int32_t>(ur);
+  };
+  // each bucket's rank range within its class, from the largest bucket down
+  auto bucket_ranks = [&]() {
     if (tid < 2) {
       unsigned pos = 0u;
       for (int k = kSizeBuckets - 1; k >= 0; --k) {
-        const unsigned n = cursor[tid][k];
-        cursor[tid][k] = pos;
+        const unsigned n = L.cursor[tid][k];
+        L.cursor[tid][k] = pos;
         pos += n;
       }
     }
     __syncthreads();
-  }
-  for (int r = rb; r < re; ++r) {
-    ReqPlan p = plan_request(hoff, toff, r, n_hist, n_tgt, chunk_blocks, group, m_lo, m_hi);
-    if (p.nch == 0) continue;
-    const int32_t bh = static_cast<int32_t>(ceil_div(p.h1, kBlockTokens));
-    for (int g = 0; g < p.ng; ++g) {
-      const int cls = group_size(p, g, group) > 32 ? 1 : 0;
-      int64_t& ur = cls ? uw : un;
-      for (int c = 0; c < p.nch; ++c, ++ur) {
+  };
+  // last entry of the non-decreasing a[0..R) that is <= k (a[0] <= k)
+  auto find = [&](const int32_t* a, int32_t k) {
+    int lo = 0, hi = R;
+    while (hi - lo > 1) {
+      const int mid = (lo + hi) / 2;
+      if (a[mid] <= k) lo = mid;
+      else hi = mid;
+    }
+    return lo;
+  };
+  if (few) {
+    if (tid < R) {
+      L.pn[tid] = static_cast<int32_t>(un);
+      L.pw[tid] = static_cast<int32_t>(uwc);
+    }
+    __syncthreads();
+    const bool bad = L.bad != 0;
+    // (request, group, chunk) of the unit of rank i
+    auto locate = [&](int64_t i, int& r, int& g, int& c) {
+      const bool cls = i >= total_narrow;
+      const int32_t k = static_cast<int32_t>(cls ? i - total_narrow : i);
+      r = find(cls ? L.pw : L.pn, k);
+      const ReqPlan p = plan(r);
+      const int32_t local = k - (cls ? L.pw : L.pn)[r];
+      // groups wider than 32: only the last of a request may be narrow
+      const bool last = group > 32 && !cls;
+      g = last ? p.ng - 1 : local / max(p.nch, 1);
+      c = last ? local : local % max(p.nch, 1);
+      return p;
+    };
+    if (S.by_size) {
+      for (int64_t i = tid; i < total; i += kSchedThreads) {
+        int r, g, c;
+        const ReqPlan p = locate(i, r, g, c);
+        const int32_t bh = static_cast<int32_t>(ceil_div(p.h1, kBlockTokens));
         const int b0 = p.bl + c * p.cb;
-        int64_t u = ur;
-        if (by_size) {
-          // rank k in the class's descending order; complete rounds of
-          // `deal` units are dealt in alternating directions, so that a
-          // workgroup taking a large unit in one round takes a small one in
-          // the next
-          const unsigned k = atomicAdd(&cursor[cls][size_bucket(min(b0 + p.cb, bh) - b0, chunk_blocks)], 1u);
-          const unsigned nc = static_cast<unsigned>(cls ? total - total_narrow : total_narrow);
-          const unsigned j = k / deal, i = k - j * deal;
-          const bool back = (j & 1) && (j + 1) * deal <= nc;
-          u = (cls ? total_narrow : 0) + static_cast<int64_t>(j) * deal + (back ? deal - 1 - i : i);
-        }
-        if (u >= max_units) continue;
-        Unit un_;
-        un_.r = r;
-        un_.t0 = p.t0 + g * group;
-        un_.nt = group_size(p, g, group);
-        un_.c = c;
-        un_.b0 = p.bl + c * p.cb;
-        un_.b1 = min(un_.b0 + p.cb, bh);
-        un_.l0 = p.h0;
-        un_.l1 = p.h1;
-        units[u] = un_;
-        if (order) order[u] = static_cast<int32_t>(ur);
+        atomicAdd(&L.cursor[i >= total_narrow][size_bucket(min(b0 + p.cb, bh) - b0, S.chunk_blocks)], 1u);
+      }
+      __syncthreads();
+      bucket_ranks();
+    }
+    for (int64_t i = tid; i < total; i += kSchedThreads) {
+      int r, g, c;
+      const ReqPlan p = locate(i, r, g, c);
+      emit(p, r, g, c, i);
+    }
+    if (!bad) {
+      for (int64_t t = tid; t < n_tgt; t += kSchedThreads)
+        S.tchunks[t] = L.nch[find(L.toff, static_cast<int32_t>(t))];
+    } else {  // offsets that may not ascend: request by request
+      for (int64_t t = tid; t < n_tgt; t += kSchedThreads) S.tchunks[t] = 0;
+      __syncthreads();
+      if (tid < R) {
+        const ReqPlan p = plan(tid);
+        if (p.nch > 0)
+          for (int t = p.t0; t < p.t1; ++t) S.tchunks[t] = p.nch;
       }
     }
-    for (int t = p.t0; t < p.t1; ++t) tchunks[t] = p.nch;
+  } else {
+    if (S.by_size) bucket_ranks();
+    for (int r = rb; r < re; ++r) {
+      const ReqPlan p = plan(r);
+      if (p.nch == 0) continue;
+      for (int g = 0; g < p.ng; ++g) {
+        int64_t& ur = group_size(p, g, group) > 32 ? uw : un;
+        for (int c = 0; c < p.nch; ++c, ++ur) emit(p, r, g, c, ur);
+      }
+      for (int t = p.t0; t < p.t1; ++t) S.tchunks[t] = p.nch;
+    }
   }
   if (tid == 0) {
-    hdr->n_units = static_cast<int32_t>(total < max_units ? total : max_units);
-    hdr->n_narrow = static_cast<int32_t>(total_narrow < max_units ? total_narrow : max_units);
-    hdr->status = (bad || total > max_units) ? STCA_ERR_INVALID_ARG : STCA_OK;
-    hdr->range = 0;  // set by later kernels of the call that find an fp16 overflow
+    S.hdr->n_units = static_cast<int32_t>(total < S.max_units ? total : S.max_units);
+    S.hdr->n_narrow = static_cast<int32_t>(total_narrow < S.max_units ? total_narrow : S.max_units);
+    S.hdr->status = (L.bad || total > S.max_units) ? STCA_ERR_INVALID_ARG : STCA_OK;
+    S.hdr->range = 0;  // set by later kernels of the call that find an fp16 overflow
   }
+}
+
+__global__ __launch_bounds__(kSchedThreads) void sched_kernel(SchedJob S) {
+  __shared__ SchedLds L;
+  sched_body(S, L);
+}
+
+// ------------------------------------------------------------- repacking
+template <typename V8>
+struct elem_of;
+template <>
+struct elem_of<bf16x8> {
+  typedef __bf16 type;
+};
+template <>
+struct elem_of<f16x8> {
+  typedef _Float16 type;
+};
+
+// W: [K][N] bf16 row-major -> P: [N/32][K/16][64][8], kept bf16 (V8 = bf16x8)
+// or converted to fp16 (V8 = f16x8, exact for every bf16 value inside fp16's
+// range); vector g of it.
+template <typename V8>
+__device__ __forceinline__ void pack_one(const bf16_bits* __restrict__ w, V8* __restrict__ P, int K, int N,
+                                         int64_t g, bool trans) {
+  const int lane = g % 64;
+  const int64_t rest = g / 64;
+  const int ks = rest % (K / 16);
+  const int nb = rest / (K / 16);
+  const int n = nb * 32 + lane % 32;
+  const int k0 = ks * 16 + 8 * (lane / 32);
+  V8 r;
+#pragma unroll
+  for (int e = 0; e < 8; ++e)
+    r[e] = static_cast<typename elem_of<V8>::type>(
+        to_f32(w[trans ? (int64_t)n * K + k0 + e : (int64_t)(k0 + e) * N + n]));
+  P[g] = r;
+}
+
+__device__ __forceinline__ int64_t pack_groups(const PackJob& b) { return (int64_t)(b.N / 32) * (b.K / 16) * 64; }
+
+__device__ __forceinline__ void pack_layer(const PackJob& b, int layer, int64_t g) {
+  const int64_t groups = pack_groups(b);
+  const bf16_bits* w = static_cast<const bf16_bits*>(b.src) + (int64_t)layer * b.K * b.N;
+  if (b.to_f16)
+    pack_one(w, static_cast<f16x8*>(b.dst) + (int64_t)layer * groups, b.K, b.N, g, b.trans != 0);
+  else
+    pack_one(w, static_cast<bf16x8*>(b.dst) + (int64_t)layer * groups, b.K, b.N, g, b.trans != 0);
+}
+
+// Several weights in one launch (blockIdx.z = job).
+__global__ void pack_many_kernel(PackJobs J) {
+  const PackJob& b = J.job[blockIdx.z];
+  const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (g < pack_groups(b)) pack_layer(b, blockIdx.y, g);
+}
+
+// A call's schedules (workgroups 0 .. n_sched - 1) and its repacking (the
+// rest: kSchedThreads vectors each of one job and layer) in one launch: they
+// are independent, and each alone leaves the chip nearly idle (one request:
+// 14 + 7 us as two launches, the schedule's 10 together).
+struct SetupArgs {
+  SchedJob sched[kMaxSetupScheds];
+  int n_sched, n_jobs, n_layers;
+  PackJobs pack;
+};
+__global__ __launch_bounds__(kSchedThreads) void setup_kernel(SetupArgs A) {
+  __shared__ SchedLds L;
+  const int bid = blockIdx.x;
+  if (bid < A.n_sched) {
+    sched_body(A.sched[bid], L);
+    return;
+  }
+  int64_t i = bid - A.n_sched;
+  for (int j = 0; j < A.n_jobs; ++j) {
+    const PackJob& b = A.pack.job[j];
+    const int64_t per = ceil_div(pack_groups(b), kSchedThreads), n = per * A.n_layers;
+    if (i < n) {
+      const int64_t g = i % per * kSchedThreads + threadIdx.x;
+      if (g < pack_groups(b)) pack_layer(b, static_cast<int>(i / per), g);
+      return;
+    }
+    i -= n;
+  }
+}
+
+bool make_job(const SchedSpec& s, SchedJob* j) {
+  if (s.group < 1 || s.group > kWideGroup || s.deal < 0) return false;
+  *j = {s.hoff, s.toff, s.R, s.n_hist, s.n_tgt, s.chunk_blocks, s.group, s.m_lo, s.m_hi, s.deal > 0 ? 1 : 0,
+        static_cast<unsigned>(s.deal > 0 ? s.deal : 1), s.units, s.max_units, s.tchunks, s.hdr, s.order};
+  return true;
 }
 
 }  // namespace
 
-hipError_t launch_sched(const int32_t* hoff, const int32_t* toff, int R, int64_t n_hist, int64_t n_tgt,
-                        int chunk_blocks, int group, Unit* units, int64_t max_units, int32_t* tchunks,
-                        WsHeader* hdr, hipStream_t st, int m_lo, int m_hi, int deal, int32_t* order) {
-  if (group < 1 || group > kWideGroup || deal < 0) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(sched_kernel, dim3(1), dim3(kSchedThreads), 0, st, hoff, toff, R, n_hist, n_tgt,
-                     chunk_blocks, group, m_lo, m_hi, deal > 0 ? 1 : 0, static_cast<unsigned>(deal > 0 ? deal : 1),
-                     units, max_units, tchunks, hdr, order);
+hipError_t launch_sched(const SchedSpec& s, hipStream_t st) {
+  SchedJob j;
+  if (!make_job(s, &j)) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(sched_kernel, dim3(1), dim3(kSchedThreads), 0, st, j);
+  return hipGetLastError();
+}
+
+hipError_t launch_setup(const SchedSpec* sched, int n_sched, const PackJobs& jobs, int n_jobs, int n_layers,
+                        hipStream_t st) {
+  if (n_sched < 0 || n_sched > kMaxSetupScheds || n_jobs < 0 || n_jobs > kMaxPackJobs) return hipErrorInvalidValue;
+  SetupArgs A{};
+  for (int i = 0; i < n_sched; ++i)
+    if (!make_job(sched[i], &A.sched[i])) return hipErrorInvalidValue;
+  A.n_sched = n_sched;
+  A.n_jobs = n_jobs;
+  A.n_layers = n_layers;
+  A.pack = jobs;
+  int64_t blocks = n_sched;
+  for (int j = 0; j < n_jobs; ++j)
+    blocks += n_layers * ceil_div((int64_t)(jobs.job[j].N / 32) * (jobs.job[j].K / 16) * 64, kSchedThreads);
+  hipLaunchKernelGGL(setup_kernel, dim3(static_cast<unsigned>(blocks)), dim3(kSchedThreads), 0, st, A);
+  return hipGetLastError();
+}
+
+hipError_t fast_pack_many(const PackJobs& jobs, int n_jobs, int n_layers, hipStream_t st) {
+  if (n_jobs < 1 || n_jobs > kMaxPackJobs) return hipErrorInvalidValue;
+  int64_t groups = 0;
+  for (int j = 0; j < n_jobs; ++j)
+    groups = std::max<int64_t>(groups, (int64_t)(jobs.job[j].N / 32) * (jobs.job[j].K / 16) * 64);
+  dim3 g(static_cast<unsigned>(ceil_div(groups, 256)), n_layers, n_jobs);
+  hipLaunchKernelGGL(pack_many_kernel, g, dim3(256), 0, st, jobs);
   return hipGetLastError();
 }
 

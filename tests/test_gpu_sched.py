@@ -1,0 +1,35 @@
+"""GPU: the device scheduler at the edges of its two ways to share the units
+(up to 1024 requests a thread each, then runs of requests), through the
+forward against the oracle."""
+import numpy as np
+import pytest
+
+from oracle import stca_oracle as O
+from paper_2511_06077_amd import workload as W
+
+pytestmark = pytest.mark.gpu
+
+
+def rowerr(y, ref):
+    return float((np.abs(y - ref).max(-1) / np.maximum(np.abs(ref).max(-1), 1e-30)).max())
+
+
+@pytest.mark.parametrize("requests,m_hi,host", [(1, 70, True), (1023, 3, True), (1024, 40, False), (1025, 40, False),
+                                                (1500, 70, True), (300, 130, True)])
+def test_schedule(requests, m_hi, host):
+    """Empty target segments, both width classes (33.. targets, the narrow last
+    group of a wide request), chunks, device and host offsets."""
+    import torch
+    from paper_2511_06077_amd.device import DeviceBatch
+    rng = np.random.default_rng(requests)
+    m = np.where(rng.random(requests) < 0.9, rng.integers(0, 4, requests), rng.integers(0, m_hi + 1, requests))
+    m[0] = m_hi
+    L = rng.integers(1, 40, requests)
+    L[-1] = 700
+    b = W.make_custom_batch("sched", L, m, d_model=64, n_heads=2, n_layers=1, dtype="bf16", seed=41)
+    ref = O.forward(b.f64())["out"]
+    for chunk in (0, 1):
+        db = DeviceBatch(b, host_offsets=host, chunk_blocks=chunk)
+        y = db.forward().float().cpu().numpy()
+        assert db.device_status() == 0
+        assert rowerr(y, ref) <= 2e-2  # the bar of the bf16 forward
