@@ -212,6 +212,8 @@ struct Layout {
   int chunk_blocks;
   int64_t max_units;
   bool any_narrow, any_wide;  // requests with 1..32 / 33+ targets (both true without host offsets)
+  int64_t wide_units;         // units of more than 32 targets (-1 without host offsets)
+  int max_chunks;             // history chunks per request, at most (standard form)
   bool reord;                 // some requests in the reordered form (bf16 path)
   bool reord_wide;            // ... in units of up to 256 rows (t, j)
   bool mixed;                 // ... and the others in the standard form
@@ -283,8 +285,10 @@ RecordLayout record_layout(const Layout& L) {
   return R;
 }
 
-stca_status_t make_layout(const stca_dims_t* dims, const stca_batch_t* b, int with_backward, bool with_saved,
-                          Layout* L) {
+// few: let a forward of few targets take what makes it faster at the cost of
+// workspace (the update's splits, more chunks per request).
+stca_status_t make_layout_for(const stca_dims_t* dims, const stca_batch_t* b, int with_backward, bool with_saved,
+                              bool few, Layout* L) {
   const int p = path_of(dims);
   if (p < 0) return static_cast<stca_status_t>(p);
   const stca_status_t bst = check_batch(b);
@@ -323,7 +327,9 @@ stca_status_t make_layout(const stca_dims_t* dims, const stca_batch_t* b, int wi
   L->mat = p == 1 && !with_backward && std_part && (L->wide || dims->kv_form == STCA_KV_MATERIALIZE);
   L->chunk_blocks = chunk_blocks_auto(b, device_cus(), dims->chunk_blocks, L->std_lo, 1 << 30, L->bfused ? 32 : 64);
   L->group = L->wide ? kWideGroup : L->bfused ? 32 : kTargetGroup;
-  L->max_units = std_part ? max_units_for(b, L->chunk_blocks, L->group, L->std_lo) : 0;
+  L->upd = p == 1 && !with_backward && few ? update_plan(L->nt, L->d, L->F, device_cus())
+                                           : UpdatePlan{ceil_div(L->nt, 32) < device_cus() ? 16 : 32, 1,
+                                                        ceil_div(L->nt, 32) < device_cus() ? 16 : 32};
   // the reordered schedule spreads its own requests' rows over the chip
   int64_t rows2 = b->n_hist;
   if (L->mixed) {
@@ -339,6 +345,21 @@ stca_status_t make_layout(const stca_dims_t* dims, const stca_batch_t* b, int wi
   if (L->mixed && dims->chunk_blocks == 0) L->chunk_blocks2 = std::max(L->chunk_blocks2, 16);
   L->group2 = (L->reord_wide ? 256 : 32) / L->h;
   L->max_units2 = L->reord ? max_units_for(b, L->chunk_blocks2, L->group2, L->reord_lo, L->reord_hi) : 0;
+  L->max_chunks = kMaxChunks;
+  if (p == 1 && !with_backward && few && std_part && !L->mat && dims->chunk_blocks == 0 && L->upd.tg < 32) {
+    // (the reordered form's units run beside them)
+    const int c = forward_chunks(b, std::max<int>(1, device_cus() - static_cast<int>(std::min<int64_t>(
+                                                         L->max_units2, device_cus() / 2))),
+                                 L->std_lo);
+    if (c > 0) {
+      L->chunk_blocks = c;
+      L->max_chunks = kMaxChunksFew;
+    }
+  }
+  L->wide_units = -1;
+  L->max_units = std_part ? max_units_for(b, L->chunk_blocks, L->group, L->std_lo, 1 << 30, L->max_chunks,
+                                          &L->wide_units)
+                          : 0;
   L->any_narrow = L->any_wide = std_part;
   if (b->tgt_off_host && std_part) {
     L->any_narrow = L->any_wide = false;
@@ -360,8 +381,19 @@ stca_status_t make_layout(const stca_dims_t* dims, const stca_batch_t* b, int wi
   L->state_a = m.take(4 * nt * d);
   L->state_b = m.take(4 * nt * d);
   if (!with_backward) {
-    L->part_acc = m.take(4 * kMaxChunks * nt * d);
-    L->part_ml = m.take(8 * kMaxChunks * nt * L->h);
+    // (as many records as any request of the batch has chunks)
+    L->max_ch = std_part && !b->hist_off_host
+                    ? static_cast<int>(std::min<int64_t>(L->max_chunks, ceil_div(L->nblocks + 1, L->chunk_blocks)))
+                    : 1;
+    for (int r = 0; std_part && b->hist_off_host && r < b->n_requests; ++r) {
+      const int64_t mt = b->tgt_off_host[r + 1] - b->tgt_off_host[r];
+      if (mt < std::max(L->std_lo, 1)) continue;
+      const int64_t nb = ceil_div(b->hist_off_host[r + 1], kBlockTokens) - b->hist_off_host[r] / kBlockTokens;
+      L->max_ch = std::max(L->max_ch, static_cast<int>(std::min<int64_t>(L->max_chunks, ceil_div(nb, L->chunk_blocks))));
+    }
+    const size_t records = std::max(kMaxChunks, L->max_ch);
+    L->part_acc = m.take(4 * records * nt * d);
+    L->part_ml = m.take(8 * records * nt * L->h);
     if (p == 1) {
       L->qn = m.take(2 * nt * d);
       L->wkp = m.take(2 * n * d * d);
@@ -381,27 +413,10 @@ stca_status_t make_layout(const stca_dims_t* dims, const stca_batch_t* b, int wi
         L->hdr2 = m.take(sizeof(WsHeader));
         L->units2 = m.take(sizeof(Unit) * (L->max_units2 + 1));
       }
-      // the splits' buffers come last: a batch that fits the library's own
-      // scratch array only without them keeps fitting, unsplit
-      // the most chunks a request of the standard form is cut into (the
-      // reordered form hands over one record)
-      L->max_ch = std_part && !b->hist_off_host ? kMaxChunks : 1;
-      for (int r = 0; std_part && b->hist_off_host && r < b->n_requests; ++r) {
-        const int64_t mt = b->tgt_off_host[r + 1] - b->tgt_off_host[r];
-        if (mt < L->std_lo) continue;
-        const int64_t nb = ceil_div(b->hist_off_host[r + 1], kBlockTokens) - b->hist_off_host[r] / kBlockTokens;
-        L->max_ch = std::max(L->max_ch, static_cast<int>(std::min<int64_t>(kMaxChunks, ceil_div(nb, L->chunk_blocks))));
-      }
-      L->upd = update_plan(L->nt, L->d, L->F, device_cus());
       if (L->upd.splits > 1) {
-        Bump with = m;
         const size_t groups = static_cast<size_t>(ceil_div(L->nt, L->upd.tg));
-        L->spart = with.take(4 * L->upd.splits * groups * 32 * d);
-        L->ucnt = with.take(4 * n * groups);
-        if (with.off > STCA_NOALLOC_SCRATCH_BYTES && m.off <= STCA_NOALLOC_SCRATCH_BYTES)
-          L->upd = {L->upd.tg0, 1, L->upd.tg0};
-        else
-          m = with;
+        L->spart = m.take(4 * L->upd.splits * groups * 32 * d);
+        L->ucnt = m.take(4 * n * groups);
       }
     } else {
       L->kv32 = m.take(4 * nh * 2 * d);
@@ -527,6 +542,21 @@ stca_status_t make_layout(const stca_dims_t* dims, const stca_batch_t* b, int wi
   return STCA_OK;
 }
 
+// A batch that fits the library's own scratch array only without the extra
+// workspace of few targets keeps fitting, without.
+stca_status_t make_layout(const stca_dims_t* dims, const stca_batch_t* b, int with_backward, bool with_saved,
+                          Layout* L) {
+  const stca_status_t st = make_layout_for(dims, b, with_backward, with_saved, true, L);
+  if (st != STCA_OK || with_backward || L->total <= STCA_NOALLOC_SCRATCH_BYTES ||
+      (L->upd.splits == 1 && L->max_chunks == kMaxChunks))
+    return st;
+  Layout plain;
+  if (make_layout_for(dims, b, with_backward, with_saved, false, &plain) == STCA_OK &&
+      plain.total <= STCA_NOALLOC_SCRATCH_BYTES)
+    *L = plain;
+  return st;
+}
+
 bool saved_layout(const stca_dims_t* dims, const stca_batch_t* b, stca_saved_layout_t* s) {
   const int p = path_of(dims);
   if (p < 0 || check_batch(b) != STCA_OK) return false;
@@ -581,7 +611,7 @@ stca_status_t forward_fast(const Layout& L, const stca_batch_t* b, const void* h
     int ns = 0;
     if (std_part)
       sp[ns++] = {b->hist_off, b->tgt_off, b->n_requests, L.nh, L.nt, L.chunk_blocks, L.group, units, L.max_units,
-                  tch, hdr, L.std_lo, 1 << 30, device_cus()};
+                  tch, hdr, L.std_lo, 1 << 30, device_cus(), nullptr, L.max_chunks};
     if (reo_part)
       sp[ns++] = {b->hist_off, b->tgt_off, b->n_requests, L.nh, L.nt, L.chunk_blocks2, L.group2, units2,
                   L.max_units2, tch_r, hdr2, L.reord_lo, L.reord_hi, device_cus()};
@@ -641,6 +671,11 @@ stca_status_t forward_fast(const Layout& L, const stca_batch_t* b, const void* h
   // the fused kernel is persistent: one workgroup per CU, looping over its
   // units with its weight columns loaded once
   const int fgrid = static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(L.max_units, device_cus())));
+  // a batch of both widths, or (d = 256) of both forms, runs its attention as
+  // one launch; without host offsets the widths' unit counts are not known
+  const bool reord_inside = L.mixed && !L.mat && d == 256 && L.wide_units >= 0;
+  const bool mixed_launch = std_part && !L.mat && L.wide_units >= 0 &&
+                            (reord_inside || (L.wide_units > 0 && L.wide_units < L.max_units));
   for (int i = 0; i < n; ++i) {
     if (reo_part) {
       HIPCHK(fast_reord_qu(d, f.QN, static_cast<const char*>(w->wk) + i * wlayer, at<char>(ws, L.un), tch_r, L.nt,
@@ -652,13 +687,17 @@ stca_status_t forward_fast(const Layout& L, const stca_batch_t* b, const void* h
                        at<char>(ws, L.part_ml), L.nt, st));
       HIPCHK(rec.mark("attn"));
     } else if (std_part) {
+      const FastFused ff{units, hdr, f.QN, hist, L.nh, at<char>(ws, L.wkp), at<char>(ws, L.wvp), i,
+                         at<float>(ws, L.part_acc), at<char>(ws, L.part_ml), L.nt};
+      if (mixed_launch) {
+        const FastMixed fm{static_cast<int>(std::min<int64_t>(L.wide_units, device_cus())),
+                           static_cast<int>(std::min<int64_t>(L.max_units - L.wide_units, device_cus())),
+                           reord_inside ? L.max_units2 : 0, units2, hdr2, reo_part ? at<char>(ws, L.un) : nullptr,
+                           reo_part ? at<float>(ws, L.part_y) : nullptr, reo_part ? at<char>(ws, L.ml_r) : nullptr};
+        HIPCHK(fast_attn_mixed(d, ff, fm, st));
+      }
       for (int wide = 0; wide < 2; ++wide) {
-        if (!(wide ? L.any_wide : L.any_narrow)) {  // no request of this width: nothing to launch
-          HIPCHK(rec.mark(wide ? "fused_wide" : "fused"));
-          continue;
-        }
-        HIPCHK(fast_fused(d, wide, units, hdr, fgrid, f.QN, hist, L.nh, at<char>(ws, L.wkp), at<char>(ws, L.wvp), i,
-                          at<float>(ws, L.part_acc), at<char>(ws, L.part_ml), L.nt, st));
+        if (!mixed_launch && (wide ? L.any_wide : L.any_narrow)) HIPCHK(fast_fused(d, wide, fgrid, ff, st));
         HIPCHK(rec.mark(wide ? "fused_wide" : "fused"));
       }
     }
@@ -666,7 +705,7 @@ stca_status_t forward_fast(const Layout& L, const stca_batch_t* b, const void* h
       if (L.reord_wide)
         HIPCHK(fast_reord_wide(d, units2, hdr2, L.max_units2, at<char>(ws, L.un), hist, L.nh,
                                at<float>(ws, L.part_y), at<char>(ws, L.ml_r), L.nt, &hdr->range, st));
-      else
+      else if (!reord_inside)
         HIPCHK(fast_reord_attn(d, units2, hdr2, L.max_units2, at<char>(ws, L.un), hist, L.nh,
                                at<float>(ws, L.part_y), at<char>(ws, L.ml_r), L.nt, st));
       HIPCHK(rec.mark("reord_attn"));

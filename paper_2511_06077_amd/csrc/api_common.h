@@ -159,11 +159,51 @@ inline int chunk_blocks_auto(const stca_batch_t* b, int n_cu, int forced, int m_
   return best;
 }
 
-inline int64_t max_units_for(const stca_batch_t* b, int chunk_blocks, int group, int m_lo = 1,
-                             int m_hi = 1 << 30) {
+// *wide: how many of them hold more than 32 targets (-1 without host offsets).
+inline int64_t max_units_for(const stca_batch_t* b, int chunk_blocks, int group, int m_lo = 1, int m_hi = 1 << 30,
+                             int max_chunks = kMaxChunks, int64_t* wide = nullptr) {
   if (b->hist_off_host)
-    return host_count_units(b->hist_off_host, b->tgt_off_host, b->n_requests, chunk_blocks, group, m_lo, m_hi);
-  return (ceil_div(b->n_tgt, group) + b->n_requests) * kMaxChunks;
+    return host_count_units(b->hist_off_host, b->tgt_off_host, b->n_requests, chunk_blocks, group, m_lo, m_hi,
+                            max_chunks, wide);
+  if (wide) *wide = -1;
+  return (ceil_div(b->n_tgt, group) + b->n_requests) * max_chunks;
+}
+
+// Chunk length of a forward that leaves CUs idle at 8 blocks and kMaxChunks
+// chunks: over the lengths from 2 to 8 blocks whose units (of the requests with
+// at least m_lo targets, up to kMaxChunksFew chunks) fit the n_cu CUs, the one
+// that costs a layer least: 1.9 us a block of the chunk, and 1.2 us per 8 chunk
+// records that the update merges (a round trip).  0 when the batch fills the
+// CUs without.  Without host offsets the whole history counts as one request.
+// One request of 9001 rows and 40 targets: 18 blocks on 16 CUs 233 us a call, 8
+// blocks 176, 6 166, 5 167; 8 requests of 700 rows: 8 blocks 135, 5 120.
+inline int forward_chunks(const stca_batch_t* b, int n_cu, int m_lo) {
+  if (b->n_requests > n_cu / 2 || ceil_div(b->n_hist, kBlockTokens) >= 8 * static_cast<int64_t>(n_cu)) return 0;
+  const int R = b->hist_off_host ? b->n_requests : 1;
+  int best = 0;
+  double best_cost = 0.;
+  for (int c = 2; c <= 8; ++c) {
+    int64_t units = 0, longest = 0;
+    for (int r = 0; r < R; ++r) {
+      int64_t nb = ceil_div(b->n_hist, kBlockTokens), groups = 1;
+      if (b->hist_off_host) {
+        const int64_t m = b->tgt_off_host[r + 1] - b->tgt_off_host[r];
+        if (m < std::max(m_lo, 1)) continue;
+        nb = ceil_div(b->hist_off_host[r + 1], kBlockTokens) - b->hist_off_host[r] / kBlockTokens;
+        groups = ceil_div(m, kTargetGroup);
+      }
+      const int64_t nch = std::min<int64_t>(kMaxChunksFew, ceil_div(nb, c));
+      units += nch * groups;
+      longest = std::max(longest, nch);
+    }
+    if (units > n_cu) continue;
+    const double cost = 1.9 * c + 1.2 * static_cast<double>(ceil_div(longest, 8));
+    if (best == 0 || cost < best_cost) {
+      best = c;
+      best_cost = cost;
+    }
+  }
+  return best;
 }
 
 template <typename T>

@@ -27,6 +27,7 @@ struct PaperLayout {
   int chunk_blocks;
   int64_t max_units;
   bool any_narrow, any_wide;
+  int64_t wide_units;  // units of more than 32 targets (-1 without host offsets)
   size_t hdr, units, tchunks, part_acc, part_ml;
   size_t q, a, cat, f, hu, hv, y, qs;  // target side, fp32
   size_t qn, wsp, wkp, wvp, xt16;      // bf16 MFMA path
@@ -63,7 +64,7 @@ bool make_paper_layout(const stca_dims_t* dims, const stca_batch_t* b, PaperLayo
   L->nh = b->n_hist;
   L->nt = b->n_tgt;
   L->chunk_blocks = chunk_blocks_auto(b, device_cus(), dims->chunk_blocks);
-  L->max_units = max_units_for(b, L->chunk_blocks, kTargetGroup);
+  L->max_units = max_units_for(b, L->chunk_blocks, kTargetGroup, 1, 1 << 30, kMaxChunks, &L->wide_units);
   L->any_narrow = L->any_wide = true;
   if (b->tgt_off_host) {
     L->any_narrow = L->any_wide = false;
@@ -243,10 +244,17 @@ stca_status_t forward_paper_fast(const PaperLayout& L, const stca_batch_t* b, co
     HIPCHK(swiglu_ln(d, hist, nh, at<char>(ws, L.wsp) + i * swiglu_packed_bytes(d, F), F, at<char>(ws, L.xt16),
                      saved ? at<float>(saved, SL.xt) + (size_t)i * nh * d : nullptr, device_cus(), st));
     HIPCHK(rec.mark("swiglu_ln"));
+    const FastFused ff{units, hdr, at<char>(ws, L.qn), at<char>(ws, L.xt16), nh, at<char>(ws, L.wkp),
+                       at<char>(ws, L.wvp), i, pacc, pml, nt};
+    // both widths in one launch where their unit counts are known
+    const bool mixed = L.wide_units > 0 && L.wide_units < L.max_units;
+    if (mixed) {
+      const FastMixed fm{static_cast<int>(std::min<int64_t>(L.wide_units, device_cus())),
+                         static_cast<int>(std::min<int64_t>(L.max_units - L.wide_units, device_cus())), 0};
+      HIPCHK(fast_attn_mixed(d, ff, fm, st));
+    }
     for (int wide = 0; wide < 2; ++wide) {
-      if (wide ? L.any_wide : L.any_narrow)
-        HIPCHK(fast_fused(d, wide, units, hdr, fgrid, at<char>(ws, L.qn), at<char>(ws, L.xt16), nh,
-                          at<char>(ws, L.wkp), at<char>(ws, L.wvp), i, pacc, pml, nt, st));
+      if (!mixed && (wide ? L.any_wide : L.any_narrow)) HIPCHK(fast_fused(d, wide, fgrid, ff, st));
       HIPCHK(rec.mark(wide ? "fused_wide" : "fused"));
     }
     // o^(i) = [heads] W_O^(i) (Eq. layer-output); then q^(i+2) =

@@ -18,6 +18,7 @@ constexpr int kBlockTokens = 32;  // history rows per K/V block (one MFMA tile e
 constexpr int kTargetGroup = 64;  // targets one attention unit holds (two 32-wide MFMA column groups)
 constexpr int kWideGroup = 128;   // targets per unit of the materialised-K/V attention for m > 64
 constexpr int kMaxChunks = 16;    // at most this many history chunks per request
+constexpr int kMaxChunksFew = 64; // ... in a forward of few targets (see forward_chunks)
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 constexpr float kF16Max = 65504.f;  // largest finite fp16 value

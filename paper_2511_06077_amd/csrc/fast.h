@@ -55,12 +55,33 @@ hipError_t fast_proj(int D, const void* X, int64_t n_hist, int64_t n_blocks, con
 hipError_t fast_attn(int D, const Unit* units, const WsHeader* hdr, int grid, const void* QN, const void* KVl,
                      float* part_acc, void* part_ml, int64_t n_tgt, hipStream_t st);
 // K13: one layer's attention with the history projected inside the kernel
-// (no K/V in HBM); persistent over the scheduled units with `streams`
-// workgroup pairs.  wide = 0 runs the units with up to 32 targets, wide = 1
+// (no K/V in HBM); persistent over the scheduled units with `grid`
+// workgroups.  wide = 0 runs the units with up to 32 targets, wide = 1
 // those with 33..64.
-hipError_t fast_fused(int D, int wide, const Unit* units, const WsHeader* hdr, int streams, const void* QN,
-                      const void* X, int64_t n_hist, const void* WkP, const void* WvP, int layer, float* part_acc,
-                      void* part_ml, int64_t n_tgt, hipStream_t st);
+struct FastFused {
+  const Unit* units;
+  const WsHeader* hdr;
+  const void *QN, *X;
+  int64_t n_hist;
+  const void *WkP, *WvP;
+  int layer;
+  float* part_acc;
+  void* part_ml;
+  int64_t n_tgt;
+};
+hipError_t fast_fused(int D, int wide, int grid, const FastFused& f, hipStream_t st);
+// Both widths in one launch, n_wide and n_narrow workgroups, and (D = 256)
+// n_reord units of the reordered form as fast_reord_attn runs them.
+struct FastMixed {
+  int n_wide, n_narrow;
+  int64_t n_reord;
+  const Unit* units2;
+  const WsHeader* hdr2;
+  const void* UN;
+  float* part_y;
+  void* ml_r;
+};
+hipError_t fast_attn_mixed(int D, const FastFused& f, const FastMixed& m, hipStream_t st);
 // K4: combine partials, W_O, residual FFN, next queries.
 hipError_t fast_update(int D, const FastUpdate& f, hipStream_t st);
 
@@ -211,7 +232,6 @@ hipError_t fast_update_grad(int D, const UpdateGrad& f, hipStream_t st);
 // [16][n_tgt][H]), and the merge that forms a = y W_V^j (fp32 [n_tgt][D]) as
 // a single-chunk record for fast_update (ml_out (log2-sum-exp, 1), tch_out 1)
 // for every target with a nonzero chunk count in `tchunks`.
-size_t reord_attn_lds(int D);
 hipError_t fast_reord_qu(int D, const void* QN, const void* Wk_layer, void* UN, const int32_t* tchunks,
                          int64_t n_tgt, hipStream_t st);
 hipError_t fast_reord_attn(int D, const Unit* units, const WsHeader* hdr, int64_t max_units, const void* UN,

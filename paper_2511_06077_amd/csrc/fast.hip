@@ -43,6 +43,7 @@
 
 #include "common.h"
 #include "fast.h"
+#include "reord_attn.h"
 #include "ring.h"
 
 namespace stca {
@@ -362,6 +363,28 @@ __global__ __launch_bounds__(64 * H) void attn_kernel(const Unit* __restrict__ u
 constexpr int kStages = 4;
 constexpr int kSegPitch = 1024 + 16;  // one direct-load segment (64 lanes x 16 B) plus padding
 
+struct FusedArgs {
+  const Unit* units;
+  const WsHeader* hdr;
+  const f16x8* QN;
+  const bf16_bits* X;
+  int64_t n_hist;
+  const bf16x8 *WkP, *WvP;
+  int layer;
+  float* part_acc;
+  float2* part_ml;
+  int64_t n_tgt;
+};
+struct MixedArgs {
+  int n_wide, n_narrow;  // workgroups of each width
+  const Unit* units2;    // the reordered form's schedule, U and partials
+  const WsHeader* hdr2;
+  const __bf16* UN;
+  float* part_y;
+  float2* ml_r;
+};
+constexpr size_t cmax(size_t a, size_t b) { return a > b ? a : b; }
+
 // The value unchanged, but opaque to the compiler: quantities derived from it
 // are recomputed where used instead of being hoisted out of the loop and kept
 // live (or spilled) across it.
@@ -370,15 +393,24 @@ __device__ __forceinline__ int opaque(int v) {
   return v;
 }
 
+// LDS of the body: X tiles, then query areas, then the waves' SIMD counts.
 template <int D, int NG>
-__global__ __launch_bounds__(64 * (D / 32)) void fused_kernel(const Unit* __restrict__ units,
-                                                              const WsHeader* __restrict__ hdr,
-                                                              const f16x8* __restrict__ QN,
-                                                              const bf16_bits* __restrict__ X, int64_t n_hist,
-                                                              const bf16x8* __restrict__ WkP,
-                                                              const bf16x8* __restrict__ WvP, int layer,
-                                                              float* __restrict__ part_acc,
-                                                              float2* __restrict__ part_ml, int64_t n_tgt) {
+struct FusedLds {
+  static constexpr int TILE = 32 / (64 / (D / 8)) * kSegPitch;
+  static constexpr int kQa = NG == 1 ? 2 : 3, kStg = NG == 1 ? kStages : 3;
+  static constexpr int kX = kStg * TILE, kQ = kQa * (D / DH) * NG * 32 * DH * 2;
+  static constexpr int kBytes = kX + kQ + 16;
+};
+
+// Workgroup `bid` of `nwg` over the units of its width, on LDS areas of
+// FusedLds' sizes.
+template <int D, int NG>
+__device__ __forceinline__ void fused_body(unsigned char* xs, unsigned char* qs, int* simd_waves, int bid, int nwg,
+                                           const Unit* __restrict__ units, const WsHeader* __restrict__ hdr,
+                                           const f16x8* __restrict__ QN, const bf16_bits* __restrict__ X,
+                                           int64_t n_hist, const bf16x8* __restrict__ WkP,
+                                           const bf16x8* __restrict__ WvP, int layer, float* __restrict__ part_acc,
+                                           float2* __restrict__ part_ml, int64_t n_tgt) {
   constexpr int H = D / DH;
   constexpr int KS = D / 16;
   constexpr int CPR = D / 8;        // 16-byte chunks per history row
@@ -394,14 +426,13 @@ __global__ __launch_bounds__(64 * (D / 32)) void fused_kernel(const Unit* __rest
   constexpr int NQA = QREG ? 2 : 3;
   constexpr int STG = QREG ? kStages : 3;
   static_assert(NS == 2 * H, "two segments per wave");
-  __shared__ __attribute__((aligned(16))) unsigned char xs[STG * TILE];
-  __shared__ __attribute__((aligned(16))) unsigned char qs[NQA * H * QA];
-  __shared__ int simd_waves[4];
+  typedef FusedLds<D, NG> Lds;
+  static_assert(Lds::TILE == TILE && Lds::kX == STG * TILE && Lds::kQ == NQA * H * QA, "LDS layout");
 
   // this width's units: [0, n_narrow) or [n_narrow, n_units)
   const int ub = NG == 1 ? 0 : hdr->n_narrow;
   const int ue = NG == 1 ? hdr->n_narrow : hdr->n_units;
-  if (ub + static_cast<int>(blockIdx.x) >= ue) return;
+  if (ub + bid >= ue) return;
   const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
   const int tcol = lane % 32, hi = lane / 32;
 
@@ -428,7 +459,7 @@ __global__ __launch_bounds__(64 * (D / 32)) void fused_kernel(const Unit* __rest
   }
 
   // ---- loads: this wave's parts of the ring's blocks and of the query slices
-  int lu = ub + blockIdx.x;  // load cursor: next (unit, block) to bring in
+  int lu = ub + bid;  // load cursor: next (unit, block) to bring in
   Unit lun = units[lu];
   int lb = lun.b0;
   int p_load = 0;   // blocks issued so far
@@ -446,7 +477,7 @@ __global__ __launch_bounds__(64 * (D / 32)) void fused_kernel(const Unit* __rest
     ++p_load;
     ++q_after;
     if (++lb >= lun.b1) {
-      lu += gridDim.x;
+      lu += nwg;
       if (lu < ue) {
         lun = units[lu];
         lb = lun.b0;
@@ -548,7 +579,7 @@ __global__ __launch_bounds__(64 * (D / 32)) void fused_kernel(const Unit* __rest
       else
         st.finish(un, opaque(wave), opaque(tcol), opaque(hi), part_acc, part_ml, n_tgt);
     };
-    int cu = ub + blockIdx.x;  // compute cursor: unit index, its ordinal, block
+    int cu = ub + bid;  // compute cursor: unit index, its ordinal, block
     int ck = 0;
     Unit cun = units[cu];
     int cb = cun.b0;
@@ -562,7 +593,7 @@ __global__ __launch_bounds__(64 * (D / 32)) void fused_kernel(const Unit* __rest
       const int ahead = 2 * (p_load - 1 - p_use);
       wait_vm(first ? min(ahead, 2 * q_after) : ahead);
       ring_barrier();  // everyone's parts; the slot of p_use - 1 is free
-      if (last && cu + static_cast<int>(gridDim.x) < ue) issue_q(units[cu + gridDim.x], ck + 1);
+      if (last && cu + nwg < ue) issue_q(units[cu + nwg], ck + 1);
       if (p_load < p_use + STG) issue_x();
       const unsigned char* tile = xs + (p_use % STG) * TILE;
       if (PHASE == 0) {
@@ -583,7 +614,7 @@ __global__ __launch_bounds__(64 * (D / 32)) void fused_kernel(const Unit* __rest
         hk = ck;
       }
       if (last) {
-        cu += gridDim.x;
+        cu += nwg;
         ++ck;
         if (cu < ue) {
           cun = units[cu];
@@ -604,8 +635,52 @@ __global__ __launch_bounds__(64 * (D / 32)) void fused_kernel(const Unit* __rest
     run(std::integral_constant<int, 1>{});
 }
 
+template <int D, int NG>
+__global__ __launch_bounds__(64 * (D / 32)) void fused_kernel(
+    const Unit* __restrict__ units, const WsHeader* __restrict__ hdr,
+    const f16x8* __restrict__ QN, const bf16_bits* __restrict__ X,
+    int64_t n_hist, const bf16x8* __restrict__ WkP,
+    const bf16x8* __restrict__ WvP, int layer, float* __restrict__ part_acc,
+    float2* __restrict__ part_ml, int64_t n_tgt) {
+  typedef FusedLds<D, NG> Lds;
+  __shared__ __attribute__((aligned(16))) unsigned char xs[Lds::kX];
+  __shared__ __attribute__((aligned(16))) unsigned char qs[Lds::kQ];
+  __shared__ int simd_waves[4];
+  fused_body<D, NG>(xs, qs, simd_waves, blockIdx.x, gridDim.x, units, hdr, QN, X, n_hist, WkP, WvP, layer, part_acc,
+                    part_ml, n_tgt);
+}
+
+// The attention of a batch that mixes widths (and forms) in one launch:
+// workgroups [0, n_wide) take the units of 33..64 targets, the next n_narrow
+// those of up to 32 and, at d = 256, the rest one unit each of the requests
+// in the reordered form.  As launches of their own each form waits for the
+// last workgroup of the one before and loads its weights again: 8 requests
+// of 1..49 targets, 33 + 27 + 19 us a layer as three launches.
+template <int D>
+__global__ __launch_bounds__(64 * (D / 32)) void attn_mixed_kernel(FusedArgs A, MixedArgs M) {
+  constexpr size_t kLds = cmax((size_t)FusedLds<D, 2>::kBytes,
+                               cmax((size_t)FusedLds<D, 1>::kBytes, D == 256 ? reord::attn_lds(D) : 0));
+  __shared__ __attribute__((aligned(16))) unsigned char smem[kLds];
+  const int bid = blockIdx.x;
+  auto width = [&](auto ng, int id, int nwg) {
+    typedef FusedLds<D, decltype(ng)::value> Lds;
+    fused_body<D, decltype(ng)::value>(smem, smem + Lds::kX, reinterpret_cast<int*>(smem + Lds::kX + Lds::kQ), id, nwg,
+                                       A.units, A.hdr, A.QN, A.X, A.n_hist, A.WkP, A.WvP, A.layer, A.part_acc,
+                                       A.part_ml, A.n_tgt);
+  };
+  if (bid < M.n_wide) {
+    width(std::integral_constant<int, 2>{}, bid, M.n_wide);
+  } else if (bid < M.n_wide + M.n_narrow) {
+    width(std::integral_constant<int, 1>{}, bid - M.n_wide, M.n_narrow);
+  } else {
+    if constexpr (D == 256)
+      reord::attn_body<D>(smem, bid - M.n_wide - M.n_narrow, M.units2, M.hdr2, M.UN, A.X, A.n_hist, M.part_y, M.ml_r,
+                          A.n_tgt);
+  }
+}
+
 // ------------------------------------------------ K4: target update
-// One wave per 32 output dimensions; a workgroup holds tg = 8, 16 or 32 targets
+// One wave per 32 output dimensions; a workgroup holds tg = 4, 8, 16 or 32 targets
 // (the other rows of its 32-row tiles stay zero).
 // mode 0 (init): s^(0) = x_t, Q^(0) = x_t W_Q^0.
 // mode 1 (layer i): merge the attention partials into a, then
@@ -784,8 +859,13 @@ __global__ __launch_bounds__(64 * (D / 32)) void update_kernel(UpdateArgs A) {
       // of the batch may have) are requested together with the target's own
       // chunk count, which only masks them
       constexpr int LPR = D / 4;  // lanes a row; 8 rows a pass
-      constexpr int RP = TG < 32 ? TG / 8 : 1, CG = 8 / RP;
-      const int prow = threadIdx.x / LPR, dim = 4 * (threadIdx.x % LPR), j = dim / DH;
+      // (four targets: two threads a row, half of the chunks each)
+      constexpr int HV = TG == 4 ? 2 : 1;
+      constexpr int RP = TG >= 8 && TG < 32 ? TG / 8 : 1, CG = 8 / RP;
+      const int prow = threadIdx.x / LPR % (8 / HV), half = threadIdx.x / LPR / (8 / HV);
+      const int dim = 4 * (threadIdx.x % LPR), j = dim / DH;
+      const int ch0 = HV == 1 ? 0 : half * ((A.max_ch + 1) / 2);
+      const int ch1 = HV == 1 || half == 1 ? A.max_ch : (A.max_ch + 1) / 2;
       float M[RP], Ls[RP], av[RP][4];
       int nch[RP];
       int64_t tt[RP];
@@ -793,21 +873,21 @@ __global__ __launch_bounds__(64 * (D / 32)) void update_kernel(UpdateArgs A) {
       for (int i = 0; i < RP; ++i) {
         const int row = 8 * i + prow;
         tt[i] = live(row) ? tb + row : A.n_tgt - 1;
-        nch[i] = live(row) ? A.tchunks[tt[i]] : 0;
+        nch[i] = live(row) ? min(A.tchunks[tt[i]], ch1) : 0;
         M[i] = -INFINITY;
         Ls[i] = 0.f;
 #pragma unroll
         for (int e = 0; e < 4; ++e) av[i][e] = 0.f;
       }
 #pragma unroll 1
-      for (int cb = 0; cb < A.max_ch; cb += CG) {
+      for (int cb = ch0; cb < ch1; cb += CG) {
         float2 ml[RP][CG];
         float4 x[RP][CG];
 #pragma unroll
         for (int c = 0; c < CG; ++c)
 #pragma unroll
           for (int i = 0; i < RP; ++i)
-            if (cb + c < A.max_ch) {
+            if (cb + c < ch1) {
               ml[i][c] = A.part_ml[((int64_t)(cb + c) * A.n_tgt + tt[i]) * H + j];
               x[i][c] = *reinterpret_cast<const float4*>(A.part_acc + ((int64_t)(cb + c) * A.n_tgt + tt[i]) * D + dim);
             }
@@ -834,8 +914,27 @@ __global__ __launch_bounds__(64 * (D / 32)) void update_kernel(UpdateArgs A) {
             }
         }
       }
+      if (HV == 2) {
+        // the second half's sums through LDS (hid is not in use yet)
+        float* ex = reinterpret_cast<float*>(hid) + (prow * LPR + threadIdx.x % LPR) * 6;
+        if (half == 1) {
+          ex[0] = M[0], ex[1] = Ls[0];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) ex[2 + e] = av[0][e];
+        }
+        __syncthreads();
+        if (half == 0) {
+          const float mn = fmaxf(M[0], ex[0]);
+          const float f0 = M[0] == -INFINITY ? 0.f : exp2f(M[0] - mn), f1 = ex[0] == -INFINITY ? 0.f : exp2f(ex[0] - mn);
+          M[0] = mn;
+          Ls[0] = f0 * Ls[0] + f1 * ex[1];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) av[0][e] = f0 * av[0][e] + f1 * ex[2 + e];
+        }
+      }
 #pragma unroll
       for (int i = 0; i < RP; ++i) {
+        if (half != 0) break;
         const int row = 8 * i + prow;
         if (live(row)) {
           const float inv = 1.f / Ls[i];
@@ -854,7 +953,7 @@ __global__ __launch_bounds__(64 * (D / 32)) void update_kernel(UpdateArgs A) {
         *reinterpret_cast<uint2*>(act + row * AROW + dim) = pk;
       }
       // tile rows past the group's targets
-      for (int row = tg + prow; row < 32; row += 8) *reinterpret_cast<uint2*>(act + row * AROW + dim) = make_uint2(0, 0);
+      for (int row = tg + threadIdx.x / LPR; row < 32; row += 8) *reinterpret_cast<uint2*>(act + row * AROW + dim) = make_uint2(0, 0);
     } else {
       // two threads per (target, head), 16 dimensions each: every chunk's
       // (max, sum) at once and the accumulators four chunks at a time (with
@@ -1080,14 +1179,19 @@ hipError_t fast_attn(int D, const Unit* units, const WsHeader* hdr, int grid, co
   return hipGetLastError();
 }
 
-hipError_t fast_fused(int D, int wide, const Unit* units, const WsHeader* hdr, int grid, const void* QN,
-                      const void* X, int64_t n_hist, const void* WkP, const void* WvP, int layer, float* part_acc,
-                      void* part_ml, int64_t n_tgt, hipStream_t st) {
+namespace {
+FusedArgs fused_args(const FastFused& f) {
+  return {f.units, f.hdr, (const f16x8*)f.QN, (const bf16_bits*)f.X, f.n_hist, (const bf16x8*)f.WkP,
+          (const bf16x8*)f.WvP, f.layer, f.part_acc, (float2*)f.part_ml, f.n_tgt};
+}
+}  // namespace
+
+hipError_t fast_fused(int D, int wide, int grid, const FastFused& f, hipStream_t st) {
   if (grid == 0) return hipSuccess;
-#define STCA_FUSED1(DD, NG)                                                                                  \
-  hipLaunchKernelGGL((fused_kernel<DD, NG>), dim3(grid), dim3(64 * (DD / 32)), 0, st, units, hdr,                \
-                     (const f16x8*)QN, (const bf16_bits*)X, n_hist, (const bf16x8*)WkP, (const bf16x8*)WvP, layer, \
-                     part_acc, (float2*)part_ml, n_tgt)
+  const FusedArgs A = fused_args(f);
+#define STCA_FUSED1(DD, NG)                                                                                      \
+  hipLaunchKernelGGL((fused_kernel<DD, NG>), dim3(grid), dim3(64 * (DD / 32)), 0, st, A.units, A.hdr, A.QN, A.X, \
+                     A.n_hist, A.WkP, A.WvP, A.layer, A.part_acc, A.part_ml, A.n_tgt)
 #define STCA_FUSED(DD) \
   if (wide) STCA_FUSED1(DD, 2); else STCA_FUSED1(DD, 1)
   switch (D) {
@@ -1098,6 +1202,24 @@ hipError_t fast_fused(int D, int wide, const Unit* units, const WsHeader* hdr, i
   }
 #undef STCA_FUSED
 #undef STCA_FUSED1
+  return hipGetLastError();
+}
+
+hipError_t fast_attn_mixed(int D, const FastFused& f, const FastMixed& m, hipStream_t st) {
+  if (m.n_wide < 0 || m.n_narrow < 0 || m.n_reord < 0 || (m.n_reord > 0 && D != 256)) return hipErrorInvalidValue;
+  const int64_t grid = (int64_t)m.n_wide + m.n_narrow + m.n_reord;
+  if (grid == 0) return hipSuccess;
+  const FusedArgs A = fused_args(f);
+  const MixedArgs M{m.n_wide, m.n_narrow, m.units2, m.hdr2, (const __bf16*)m.UN, m.part_y, (float2*)m.ml_r};
+#define STCA_MIXED(DD) \
+  hipLaunchKernelGGL(attn_mixed_kernel<DD>, dim3(static_cast<unsigned>(grid)), dim3(64 * (DD / 32)), 0, st, A, M)
+  switch (D) {
+    case 64: STCA_MIXED(64); break;
+    case 128: STCA_MIXED(128); break;
+    case 256: STCA_MIXED(256); break;
+    default: return hipErrorInvalidValue;
+  }
+#undef STCA_MIXED
   return hipGetLastError();
 }
 
@@ -1115,6 +1237,7 @@ UpdatePlan update_plan(int64_t n_tgt, int D, int F, int n_cu) {
   p.tg = p.tg0;
   p.splits = 1;
   if (F != 4 * D || D < 256) return p;
+  if (ceil_div(n_tgt, 4) * 4 <= n_cu) return {4, 4, p.tg0};
   if (ceil_div(n_tgt, 8) * 4 <= n_cu) return {8, 4, p.tg0};
   if (ceil_div(n_tgt, 16) * 4 <= n_cu) return {16, 4, p.tg0};
   if (ceil_div(n_tgt, 16) * 2 <= n_cu) return {16, 2, p.tg0};
@@ -1151,8 +1274,8 @@ hipError_t fast_update(int D, const FastUpdate& f, hipStream_t st) {
   const UpdatePlan& P = f.plan;
   // the cuts with a kernel: see update_plan
   const bool split_ok = D == 256 && f.F == 4 * D && f.spart && f.cnt &&
-                        ((P.splits == 4 && (P.tg == 8 || P.tg == 16)) || (P.splits == 2 && P.tg == 16));
-  if ((f.mode && (f.max_ch < 1 || f.max_ch > kMaxChunks)) || (P.tg0 != 16 && P.tg0 != 32) ||
+                        ((P.splits == 4 && (P.tg == 4 || P.tg == 8 || P.tg == 16)) || (P.splits == 2 && P.tg == 16));
+  if ((f.mode && (f.max_ch < 1 || f.max_ch > (P.tg < 32 ? kMaxChunksFew : kMaxChunks))) || (P.tg0 != 16 && P.tg0 != 32) ||
       !(P.splits == 1 ? P.tg == 16 || P.tg == 32 : split_ok))
     return hipErrorInvalidValue;
   A.splits = P.splits;
@@ -1174,7 +1297,8 @@ hipError_t fast_update(int D, const FastUpdate& f, hipStream_t st) {
     case 64: STCA_UPD(64); break;
     case 128: STCA_UPD(128); break;
     case 256:
-      if (f.mode != 0 && A.splits == 4 && A.tg == 8) STCA_UPD1(256, 1, 8);
+      if (f.mode != 0 && A.splits == 4 && A.tg == 4) STCA_UPD1(256, 1, 4);
+      else if (f.mode != 0 && A.splits == 4 && A.tg == 8) STCA_UPD1(256, 1, 8);
       else if (f.mode != 0 && A.splits == 4) STCA_UPD1(256, 1, 16);
       else if (f.mode != 0 && A.splits == 2) STCA_UPD1(256, 2, 16);
       else STCA_UPD(256);

@@ -25,6 +25,7 @@ struct SchedSpec {
   WsHeader* hdr;
   int m_lo = 1, m_hi = 1 << 30, deal = 0;
   int32_t* order = nullptr;
+  int max_chunks = kMaxChunks;  // per request
 };
 hipError_t launch_sched(const SchedSpec& s, hipStream_t st);
 struct PackJobs;
@@ -32,8 +33,9 @@ struct PackJobs;
 constexpr int kMaxSetupScheds = 3;
 hipError_t launch_setup(const SchedSpec* sched, int n_sched, const PackJobs& jobs, int n_jobs, int n_layers,
                         hipStream_t st);
-int64_t host_count_units(const int32_t* hoff, const int32_t* toff, int R, int chunk_blocks, int group,
-                         int m_lo = 1, int m_hi = 1 << 30);
+// *wide (nullable): how many of them hold more than 32 targets.
+int64_t host_count_units(const int32_t* hoff, const int32_t* toff, int R, int chunk_blocks, int group, int m_lo = 1,
+                         int m_hi = 1 << 30, int max_chunks = kMaxChunks, int64_t* wide = nullptr);
 
 // ---- generic fp32-arithmetic path (generic.hip)
 enum GemmEpi { kEpiStore = 0, kEpiAddRes = 1, kEpiRelu = 2 };

@@ -24,48 +24,18 @@
 // cheaper than converting X.
 #include "common.h"
 #include "fast.h"
+#include "reord_attn.h"
 #include "ring.h"
 
 namespace stca {
 
 namespace {
 
-constexpr int DH = 32;
-constexpr float kSlack = 8.f;  // log2 units: softmax weights stay <= 256 between rescales
-constexpr int kWaves = 4;      // X blocks per round of the attention workgroup (two waves each)
-
-// X tile in LDS: the 32 rows in 1 KB segments (512 / D rows each, as one
-// wave's direct global-to-LDS load fills them), segments padded by 16 bytes,
-// which spreads the rows over the banks while keeping every operand address
-// a per-lane base plus a compile-time offset.
-constexpr int kSegPitch = 1024 + 16;
-__host__ __device__ constexpr size_t reord_tile_bytes(int D) { return (size_t)(D / 16) * kSegPitch; }
-// attention kernel LDS: the pairs' double-buffered X tiles (later the merge
-// area), then the unit's U rows
-__host__ __device__ constexpr size_t reord_main_lds(int D) {
-  return (size_t)kWaves * 2 * reord_tile_bytes(D) > (size_t)kWaves * 32 * (D + 2) * 4
-             ? (size_t)kWaves * 2 * reord_tile_bytes(D)
-             : (size_t)kWaves * 32 * (D + 2) * 4;
-}
+using namespace reord;
 
 __device__ __forceinline__ f32x16 mfma16(const f16x8& a, const f16x8& b, const f32x16& c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0);
 }
-__device__ __forceinline__ f32x16 mfmab(const bf16x8& a, const bf16x8& b, const f32x16& c) {
-  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
-}
-
-// v ~ hi + lo, both bf16 (round to nearest even)
-__device__ __forceinline__ __bf16 bf_hi(float v) { return static_cast<__bf16>(v); }
-__device__ __forceinline__ __bf16 bf_lo(float v, __bf16 hi) { return static_cast<__bf16>(v - static_cast<float>(hi)); }
-
-__device__ __forceinline__ bf16x8 zero8b() {
-  bf16x8 r;
-#pragma unroll
-  for (int i = 0; i < 8; ++i) r[i] = static_cast<__bf16>(0.f);
-  return r;
-}
-
 __device__ __forceinline__ f16x8 pack8(const f32x16& a, int off) {
   f16x8 r;
 #pragma unroll
@@ -146,21 +116,7 @@ __global__ __launch_bounds__(64) void reord_qu_kernel(const f16x8* __restrict__ 
   }
 }
 
-// ------------------------------------------------------------ attention
-// One workgroup per unit (request, target group of up to 32 / H targets,
-// history chunk): its rows r = t H + j (at most 32) are the 32 columns of
-// every tile.  Eight waves in four pairs; in each round the pairs take the
-// next four 32-row X blocks (direct global-to-LDS loads into a per-pair
-// double buffer, the next round's blocks in flight while this round's are
-// used).  Both waves of a pair form
-// the block's scores; each accumulates half of the d columns of Y.  Every
-// pair keeps its own online-softmax state; the pairs' partials are merged at
-// the end.
-//   S^T (32 history rows x 32 rows (t, j)) = X U^T, K = d: A = X row operand,
-//   B = U rows (staged once in LDS).
-//   Y^T (d x 32) += X^T P^T, K = 32 history rows: B = P^T from the S^T
-//   registers (k-step s: rows 16 s + 4 hi + {0..3, 8..11}), A = X^T gathered
-//   from the LDS tile for the same history rows.
+// The narrow attention (reord_attn.h): one workgroup per unit.
 template <int D>
 __global__ __launch_bounds__(128 * kWaves) void reord_attn_kernel(const Unit* __restrict__ units,
                                                                   const WsHeader* __restrict__ hdr,
@@ -168,163 +124,8 @@ __global__ __launch_bounds__(128 * kWaves) void reord_attn_kernel(const Unit* __
                                                                   const bf16_bits* __restrict__ X, int64_t n_hist,
                                                                   float* __restrict__ part_y,
                                                                   float2* __restrict__ part_ml, int64_t n_tgt) {
-  constexpr int H = D / DH;
-  constexpr int KS = D / 16;
-  constexpr int CPR = D / 8;          // 16-byte chunks per X row
-  constexpr int NDT = D / 32;         // 32-dim tiles of Y^T
-  constexpr int HALF = NDT / 2;       // tiles per wave of a pair
-  constexpr int PER = 32 * CPR / 64;  // 1 KB segments per block
-  constexpr int RPS = 512 / D;        // rows per segment
-  constexpr int NT = 128 * kWaves;
-  constexpr int TB = static_cast<int>(reord_tile_bytes(D));
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  const int u = blockIdx.x;
-  if (u >= hdr->n_units) return;
-  const Unit un = units[u];
-  const int w = threadIdx.x / 64, lane = threadIdx.x % 64;
-  const int pw = w % kWaves, half = w / kWaves;
-  const int tcol = lane % 32, hi = lane / 32;
-  const int R = un.nt * H;
-  unsigned char* xb = smem + (size_t)pw * 2 * TB;
-  // byte offset of element (row, col) in a tile
-  auto xoff = [](int row, int col) { return (row / RPS) * kSegPitch + (row % RPS) * 2 * D + col * 2; };
-  // the unit's U: hi terms in registers (B operand: row tcol, model dims
-  // 16 ks + 8 hi ..), lo terms staged in LDS (padded rows) past the X tiles
-  // and the merge area
-  constexpr int UROW = D + 8;
-  __bf16* us = reinterpret_cast<__bf16*>(smem + reord_main_lds(D));
-  for (int e = threadIdx.x; e < 32 * (D / 8); e += NT) {
-    const int row = e / (D / 8), c8 = e % (D / 8);
-    const bf16x8 v = row < R ? *reinterpret_cast<const bf16x8*>(UN + ((int64_t)un.t0 * H + row) * 2 * D + D + c8 * 8)
-                             : zero8b();
-    *reinterpret_cast<bf16x8*>(us + row * UROW + c8 * 8) = v;
-  }
-  const __bf16* ulo = us + tcol * UROW + 8 * hi;
-  bf16x8 uhi[KS];
-  {
-    const __bf16* up = UN + ((int64_t)un.t0 * H + tcol) * 2 * D + 8 * hi;
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) uhi[ks] = tcol < R ? *reinterpret_cast<const bf16x8*>(up + 16 * ks) : zero8b();
-  }
-  f32x16 Y[HALF];
-#pragma unroll
-  for (int dt = 0; dt < HALF; ++dt) Y[dt] = f32x16{};
-  float m = -INFINITY, l = 0.f;
-  const int rounds = (un.b1 - un.b0 + kWaves - 1) / kWaves;
-  // this pair's block of round r: each wave of the pair loads half of it
-  auto dma = [&](int r, int buf) {
-    const int b = un.b0 + r * kWaves + pw;
-    if (b >= un.b1) return;
-#pragma unroll
-    for (int i = half * (PER / 2); i < (half + 1) * (PER / 2); ++i) {
-      const int p = i * 64 + lane;
-      const int row = p / CPR, c = p % CPR;
-      const int64_t grow = min((int64_t)b * 32 + row, n_hist - 1);
-      __builtin_amdgcn_global_load_lds(static_cast<const void*>(X + grow * D + c * 8),
-                                       (void __attribute__((address_space(3)))*)(xb + buf * TB + i * kSegPitch), 16,
-                                       0, 0);
-    }
-  };
-  dma(0, 0);
-  for (int r = 0; r < rounds; ++r) {
-    const int cur = r & 1;
-    // round r's blocks have landed (every wave waited for its own loads), and
-    // every wave is done with the buffers of round r - 1
-    __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();
-    if (r + 1 < rounds) dma(r + 1, cur ^ 1);
-    const int b = un.b0 + r * kWaves + pw;
-    if (b >= un.b1) continue;
-    const unsigned char* xt = xb + cur * TB;
-    f32x16 s = {};
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      const bf16x8 xr = *reinterpret_cast<const bf16x8*>(xt + xoff(tcol, 16 * ks + 8 * hi));
-      s = mfmab(xr, uhi[ks], s);
-      s = mfmab(xr, *reinterpret_cast<const bf16x8*>(ulo + 16 * ks), s);
-    }
-    if (b * 32 < un.l0 || b * 32 + 32 > un.l1) {
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int tok = b * 32 + 8 * (v / 4) + 4 * hi + (v % 4);
-        s[v] = (tok < un.l0 || tok >= un.l1) ? -INFINITY : s[v];
-      }
-    }
-    float bm = s[0];
-#pragma unroll
-    for (int v = 1; v < 16; ++v) bm = fmaxf(bm, s[v]);
-    bm = fmaxf(bm, __shfl_xor(bm, 32));
-    // per-lane threshold rescale: the reference max moves only when the block
-    // maximum exceeds it by kSlack (every block has a valid row, so bm is finite)
-    const float mn = bm > m + kSlack ? bm : m;
-    const float sc = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - mn);
-    m = mn;
-    float ps = 0.f;
-#pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      s[v] = __builtin_amdgcn_exp2f(s[v] - mn);
-      ps += s[v];
-    }
-    l = l * sc + ps;
-    bf16x8 ph[2], pl[2];
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const __bf16 h = bf_hi(s[i]);
-      ph[i / 8][i % 8] = h;
-      pl[i / 8][i % 8] = bf_lo(s[i], h);
-    }
-#pragma unroll
-    for (int dt = 0; dt < HALF; ++dt) {
-      f32x16 acc = Y[dt] * sc;
-      const int dim = 32 * (half * HALF + dt) + tcol;
-#pragma unroll
-      for (int k2 = 0; k2 < 2; ++k2) {
-        bf16x8 a;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          const int row = 16 * k2 + 4 * hi + (i < 4 ? i : i + 4);
-          a[i] = *reinterpret_cast<const __bf16*>(xt + xoff(row, dim));
-        }
-        acc = mfmab(a, ph[k2], acc);
-        acc = mfmab(a, pl[k2], acc);
-      }
-      Y[dt] = acc;
-      // two gathers in flight at a time: hoisting all of them would take
-      // eight registers per element
-      __builtin_amdgcn_sched_barrier(0);
-    }
-  }
-  // merge the four pairs (the X tiles are dead: their LDS holds the partials)
-  __syncthreads();
-  float* red = reinterpret_cast<float*>(smem);  // [kWaves][32][D + 2]
-  const float lt = l + __shfl_xor(l, 32);
-  float* rw = red + ((size_t)pw * 32 + tcol) * (D + 2);
-  if (hi == 0 && half == 0) {
-    rw[0] = m;
-    rw[1] = lt;
-  }
-#pragma unroll
-  for (int dt = 0; dt < HALF; ++dt)
-#pragma unroll
-    for (int v = 0; v < 16; ++v) rw[2 + 32 * (half * HALF + dt) + 8 * (v / 4) + 4 * hi + (v % 4)] = Y[dt][v];
-  __syncthreads();
-  for (int it = threadIdx.x; it < R * (D + 1); it += NT) {
-    const int row = it / (D + 1), e = it % (D + 1);  // e == D: (max, sum)
-    float M = -INFINITY;
-    for (int pp = 0; pp < kWaves; ++pp) M = fmaxf(M, red[((size_t)pp * 32 + row) * (D + 2)]);
-    float val = 0.f;
-    for (int pp = 0; pp < kWaves; ++pp) {
-      const float* rr = red + ((size_t)pp * 32 + row) * (D + 2);
-      const float f = rr[0] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(rr[0] - M);
-      val += f * (e == D ? rr[1] : rr[2 + e]);
-    }
-    const int t = row / H, j = row % H;
-    const int64_t prow = ((int64_t)un.c * n_tgt + un.t0 + t) * H + j;
-    if (e == D)
-      part_ml[prow] = make_float2(M, val);
-    else
-      part_y[prow * D + e] = val;
-  }
+  attn_body<D>(smem, blockIdx.x, units, hdr, UN, X, n_hist, part_y, part_ml, n_tgt);
 }
 
 // ----------------------------------------------- attention, wide units
@@ -580,92 +381,108 @@ __global__ __launch_bounds__(64 * kWideWaves) void reord_wide_kernel(const Unit*
 }
 
 // ---------------------------------------------------------------- merge
-// One wave per (32 targets, head j): it merges the chunk partials of y_tj
-// into fp16 rows in LDS (two lanes per target, half of the d columns each),
-// then forms a_j^T = W_V^j^T y_j^T (A operand: the packed fp16 W_V, whose
-// column block j is head j) and writes a (fp32) as the single chunk of the
-// update kernel's partials: chunk count 1, (max, sum) = (the scores'
-// log2-sum-exp, 1), so the update's merge returns a and the lse unchanged.
-// Targets whose chunk count is 0 (requests in the standard form when a
-// batch runs both forms) are left alone.
+// One workgroup of eight waves per (32 targets, head j): it merges the chunk
+// partials of y_tj into fp16 rows in LDS, whole rows coalesced over the lanes
+// and four chunks of every row a round trip, then one wave forms a_j^T =
+// W_V^j^T y_j^T (A operand: the packed fp16 W_V, whose column block j is head j)
+// and writes a (fp32) as the single chunk of the update kernel's partials:
+// chunk count 1, (max, sum) = (the scores' log2-sum-exp, 1), so the update's
+// merge returns a and the lse unchanged.  Targets whose chunk count is 0
+// (requests in the standard form when a batch runs both forms) are left
+// alone.  With two lanes of one wave a row, each walking its 128 columns 16 at
+// a time, the round trips took 12 us (one chunk) to 19 us (16) a launch.
+constexpr int kMergeThreads = 512;
 template <int D>
-__global__ __launch_bounds__(64) void reord_merge_kernel(const float* __restrict__ part_y,
-                                                        const float2* __restrict__ part_ml,
-                                                        const int32_t* __restrict__ tchunks,
-                                                        const f16x8* __restrict__ WvP16, int layer,
-                                                        float* __restrict__ a_out, float2* __restrict__ ml_out,
-                                                        int32_t* __restrict__ tch_out, int64_t n_tgt) {
+__global__ __launch_bounds__(kMergeThreads) void reord_merge_kernel(const float* __restrict__ part_y,
+                                                                    const float2* __restrict__ part_ml,
+                                                                    const int32_t* __restrict__ tchunks,
+                                                                    const f16x8* __restrict__ WvP16, int layer,
+                                                                    float* __restrict__ a_out,
+                                                                    float2* __restrict__ ml_out,
+                                                                    int32_t* __restrict__ tch_out, int64_t n_tgt) {
   constexpr int H = D / DH;
   constexpr int KS = D / 16;
   constexpr int YROW = D + 8;  // padded fp16 row
+  constexpr int LPR = D / 4;   // lanes a row
+  constexpr int RPP = kMergeThreads / LPR, NP = 32 / RPP;  // rows a pass, passes
+  constexpr int CG = 4;
   __shared__ __attribute__((aligned(16))) uint16_t ys[32 * YROW];
   const int64_t tb = (int64_t)blockIdx.x * 32;
   const int j = blockIdx.y;
-  const int lane = threadIdx.x;
-  {
-    const int row = lane / 2, part = lane % 2;  // columns [part D/2, (part + 1) D/2)
-    const int64_t t = tb + row;
-    uint16_t* y = ys + row * YROW + part * (D / 2);
-    const int nch = t < n_tgt ? tchunks[t] : 0;
-    if (__builtin_amdgcn_ballot_w64(nch > 0) == 0) return;  // no target of this wave in the reordered form
-    if (nch > 0) {
-      // every chunk's (max, sum) requested at once, and each chunk's weight
-      float2 mlc[kMaxChunks];
+  const int prow = threadIdx.x / LPR, dim = 4 * (threadIdx.x % LPR);
+  int nch[NP];
+  bool any = false;
 #pragma unroll
-      for (int c = 0; c < kMaxChunks; ++c)
-        mlc[c] = c < nch ? part_ml[((int64_t)c * n_tgt + t) * H + j] : make_float2(-INFINITY, 0.f);
-      float M = mlc[0].x;
+  for (int p = 0; p < NP; ++p) {
+    const int64_t t = tb + p * RPP + prow;
+    nch[p] = t < n_tgt ? tchunks[t] : 0;
+    any |= nch[p] > 0;
+  }
+  if (!__syncthreads_or(any)) return;  // no target of this workgroup in the reordered form
+  float M[NP], L[NP], av[NP][4];
 #pragma unroll
-      for (int c = 1; c < kMaxChunks; ++c) M = fmaxf(M, mlc[c].x);
-      float L = 0.f;
-      float wch[kMaxChunks];
+  for (int p = 0; p < NP; ++p) {
+    M[p] = -INFINITY;
+    L[p] = 0.f;
 #pragma unroll
-      for (int c = 0; c < kMaxChunks; ++c) {
-        wch[c] = c < nch ? __builtin_amdgcn_exp2f(mlc[c].x - M) : 0.f;
-        L += wch[c] * mlc[c].y;
+    for (int e = 0; e < 4; ++e) av[p][e] = 0.f;
+  }
+#pragma unroll 1
+  for (int cb = 0; cb < kMaxChunks; cb += CG) {
+    bool more = false;
+#pragma unroll
+    for (int p = 0; p < NP; ++p) more |= cb < nch[p];
+    if (__builtin_amdgcn_ballot_w64(more) == 0) break;  // no barrier inside: each wave ends by itself
+    float2 ml[NP][CG];
+    float4 x[NP][CG];
+#pragma unroll
+    for (int c = 0; c < CG; ++c)
+#pragma unroll
+      for (int p = 0; p < NP; ++p) {
+        const int64_t row = ((int64_t)(cb + c) * n_tgt + tb + p * RPP + prow) * H + j;
+        const bool ok = cb + c < nch[p];
+        ml[p][c] = ok ? part_ml[row] : make_float2(-INFINITY, 0.f);
+        x[p][c] = ok ? *reinterpret_cast<const float4*>(part_y + row * D + dim) : make_float4(0.f, 0.f, 0.f, 0.f);
       }
-      const float inv = 1.f / L;
 #pragma unroll
-      for (int c = 0; c < kMaxChunks; ++c) wch[c] *= inv;
-      for (int c0 = 0; c0 < D / 2; c0 += 16) {
-        float acc[16];
+    for (int p = 0; p < NP; ++p) {
+      float mn = M[p];
 #pragma unroll
-        for (int i = 0; i < 16; ++i) acc[i] = 0.f;
-        // four chunks' loads in flight at a time (one memory round trip per
-        // four chunks instead of one per chunk)
-        for (int cb = 0; cb < nch; cb += 4) {
-          float4 v[4][4];
-          float wc[4];
+      for (int c = 0; c < CG; ++c) mn = fmaxf(mn, ml[p][c].x);
+      const float sc = M[p] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(M[p] - mn);
+      M[p] = mn;
+      L[p] *= sc;
 #pragma unroll
-          for (int cc = 0; cc < 4; ++cc) {
-            const int c = cb + cc < nch ? cb + cc : cb;
-            wc[cc] = cb + cc < nch ? wch[cb + cc < kMaxChunks ? cb + cc : 0] : 0.f;
-            const float4* py = reinterpret_cast<const float4*>(part_y + (((int64_t)c * n_tgt + t) * H + j) * D +
-                                                               part * (D / 2) + c0);
+      for (int e = 0; e < 4; ++e) av[p][e] *= sc;
 #pragma unroll
-            for (int q = 0; q < 4; ++q) v[cc][q] = py[q];
-          }
-#pragma unroll
-          for (int cc = 0; cc < 4; ++cc)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-              acc[4 * q] += wc[cc] * v[cc][q].x, acc[4 * q + 1] += wc[cc] * v[cc][q].y;
-              acc[4 * q + 2] += wc[cc] * v[cc][q].z, acc[4 * q + 3] += wc[cc] * v[cc][q].w;
-            }
+      for (int c = 0; c < CG; ++c)
+        if (cb + c < nch[p]) {
+          const float wgt = __builtin_amdgcn_exp2f(ml[p][c].x - mn);
+          L[p] += wgt * ml[p][c].y;
+          av[p][0] += wgt * x[p][c].x, av[p][1] += wgt * x[p][c].y;
+          av[p][2] += wgt * x[p][c].z, av[p][3] += wgt * x[p][c].w;
         }
+    }
+  }
 #pragma unroll
-        for (int i = 0; i < 16; ++i) y[c0 + i] = __builtin_bit_cast(uint16_t, static_cast<_Float16>(acc[i]));
-      }
-      if (part == 0) {
-        ml_out[t * H + j] = make_float2(M + log2f(L), 1.f);
-        if (j == 0) tch_out[t] = 1;
-      }
-    } else {
-      for (int i = 0; i < D / 2; ++i) y[i] = 0;
+  for (int p = 0; p < NP; ++p) {
+    const int row = p * RPP + prow;
+    const float inv = nch[p] > 0 ? 1.f / L[p] : 0.f;
+    uint16_t h[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      h[e] = nch[p] > 0 ? __builtin_bit_cast(uint16_t, static_cast<_Float16>(av[p][e] * inv)) : 0;
+    *reinterpret_cast<uint2*>(ys + row * YROW + dim) =
+        make_uint2((uint32_t)h[0] | ((uint32_t)h[1] << 16), (uint32_t)h[2] | ((uint32_t)h[3] << 16));
+    if (dim == 0 && nch[p] > 0) {
+      const int64_t t = tb + row;
+      ml_out[t * H + j] = make_float2(M[p] + log2f(L[p]), 1.f);
+      if (j == 0) tch_out[t] = 1;
     }
   }
   __syncthreads();
-  const int tcol = lane % 32, hi = lane / 32;
+  if (threadIdx.x >= 64) return;
+  const int lane = threadIdx.x, tcol = lane % 32, hi = lane / 32;
   const f16x8* wp = WvP16 + ((int64_t)(layer * H + j) * KS) * 64 + lane;
   const uint16_t* yb = ys + tcol * YROW + 8 * hi;
   f16x8 wr[KS];
@@ -699,8 +516,6 @@ hipError_t allow_lds(K kernel, size_t bytes) {
 
 }  // namespace
 
-size_t reord_attn_lds(int D) { return reord_main_lds(D) + (size_t)32 * (D + 8) * 2; }
-
 hipError_t fast_reord_qu(int D, const void* QN, const void* Wk_layer, void* UN, const int32_t* tchunks,
                          int64_t n_tgt, hipStream_t st) {
   if (n_tgt == 0) return hipSuccess;
@@ -722,7 +537,7 @@ hipError_t fast_reord_attn(int D, const Unit* units, const WsHeader* hdr, int64_
                            const void* X, int64_t n_hist, float* part_y, void* part_ml, int64_t n_tgt,
                            hipStream_t st) {
   if (max_units == 0) return hipSuccess;
-  const size_t lds = reord_attn_lds(D);
+  const size_t lds = reord::attn_lds(D);
 #define STCA_RA(DD)                                                                                               \
   do {                                                                                                            \
     hipError_t e = allow_lds(reord_attn_kernel<DD>, lds);                                                         \
@@ -766,7 +581,7 @@ hipError_t fast_reord_merge(int D, const float* part_y, const void* part_ml, con
   if (n_tgt == 0) return hipSuccess;
   dim3 g(static_cast<unsigned>(ceil_div(n_tgt, 32)), D / DH);
 #define STCA_RM(DD)                                                                                             \
-  hipLaunchKernelGGL(reord_merge_kernel<DD>, g, dim3(64), 0, st, part_y, (const float2*)part_ml, tchunks,      \
+  hipLaunchKernelGGL(reord_merge_kernel<DD>, g, dim3(kMergeThreads), 0, st, part_y, (const float2*)part_ml, tchunks,      \
                      (const f16x8*)WvP16, layer, a_out, (float2*)ml_out, tch_out, n_tgt)
   switch (D) {
     case 64: STCA_RM(64); break;

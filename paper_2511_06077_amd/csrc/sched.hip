@@ -3,7 +3,7 @@
 // The ragged batch is packed without padding and segmented by per-request
 // offsets (App. A.4, index-based ragged target attention).  Each request's
 // history rows are covered by whole 32-row blocks of the packed history
-// ([floor(h0/32), ceil(h1/32))); the blocks are cut into at most kMaxChunks
+// ([floor(h0/32), ceil(h1/32))); the blocks are cut into at most max_chunks
 // chunks of about `chunk_blocks` blocks, and the request's targets into groups
 // of `group` (at most kWideGroup).  One unit = (target group, chunk).  Units of groups with at
 // most 32 targets are listed first, the wider ones after them, so kernels
@@ -50,7 +50,7 @@ struct ReqPlan {
 };
 
 __device__ ReqPlan plan_request(const int32_t* hoff, const int32_t* toff, int r, int64_t n_hist,
-                                int64_t n_tgt, int chunk_blocks, int group, int m_lo, int m_hi) {
+                                int64_t n_tgt, int chunk_blocks, int group, int m_lo, int m_hi, int max_chunks) {
   ReqPlan p{};
   p.h0 = hoff[r];
   p.h1 = hoff[r + 1];
@@ -65,7 +65,7 @@ __device__ ReqPlan plan_request(const int32_t* hoff, const int32_t* toff, int r,
   const int32_t bh = static_cast<int32_t>(ceil_div(p.h1, kBlockTokens));
   const int32_t nb = bh - p.bl;
   int32_t nch = static_cast<int32_t>(ceil_div(nb, chunk_blocks));
-  nch = nch < 1 ? 1 : (nch > kMaxChunks ? kMaxChunks : nch);
+  nch = nch < 1 ? 1 : (nch > max_chunks ? max_chunks : nch);
   p.cb = static_cast<int32_t>(ceil_div(nb, nch));
   p.nch = static_cast<int32_t>(ceil_div(nb, p.cb));  // no empty chunk
   p.ng = static_cast<int32_t>(ceil_div(p.t1 - p.t0, group));
@@ -118,7 +118,7 @@ struct SchedJob {
   const int32_t *hoff, *toff;
   int R;
   int64_t n_hist, n_tgt;
-  int chunk_blocks, group, m_lo, m_hi, by_size;
+  int chunk_blocks, group, m_lo, m_hi, max_chunks, by_size;
   unsigned deal;
   Unit* units;
   int64_t max_units;
@@ -149,7 +149,7 @@ __device__ void sched_body(const SchedJob& S, SchedLds& L) {
   __syncthreads();
 
   auto plan = [&](int r) {
-    return plan_request(S.hoff, S.toff, r, S.n_hist, n_tgt, S.chunk_blocks, group, S.m_lo, S.m_hi);
+    return plan_request(S.hoff, S.toff, r, S.n_hist, n_tgt, S.chunk_blocks, group, S.m_lo, S.m_hi, S.max_chunks);
   };
   const int per = static_cast<int>(ceil_div(R, kSchedThreads));
   const int rb = tid * per;
@@ -185,13 +185,15 @@ __device__ void sched_body(const SchedJob& S, SchedLds& L) {
   const int64_t uwc = block_scan(L.scan, wide);
   const int64_t total = total_narrow + L.scan[kSchedThreads - 1];
   int64_t uw = total_narrow + uwc;
+  // (units that all go out in the first round need no order; `order` asks for it)
+  const bool by_size = S.by_size && (S.order || !few || total > S.deal);
 
   // the place of the unit of rank ur: with by_size, rank k in the class's
   // descending order; complete rounds of `deal` units are dealt in alternating
   // directions, so that a workgroup taking a large unit in one round takes a
   // small one in the next
   auto place = [&](int cls, int size, int64_t ur) -> int64_t {
-    if (!S.by_size) return ur;
+    if (!by_size) return ur;
     const unsigned k = atomicAdd(&L.cursor[cls][size_bucket(size, S.chunk_blocks)], 1u);
     const unsigned nc = static_cast<unsigned>(cls ? total - total_narrow : total_narrow);
     const unsigned j = k / S.deal, i = k - j * S.deal;
@@ -256,7 +258,7 @@ __device__ void sched_body(const SchedJob& S, SchedLds& L) {
       c = last ? local : local % max(p.nch, 1);
       return p;
     };
-    if (S.by_size) {
+    if (by_size) {
       for (int64_t i = tid; i < total; i += kSchedThreads) {
         int r, g, c;
         const ReqPlan p = locate(i, r, g, c);
@@ -285,7 +287,7 @@ __device__ void sched_body(const SchedJob& S, SchedLds& L) {
       }
     }
   } else {
-    if (S.by_size) bucket_ranks();
+    if (by_size) bucket_ranks();
     for (int r = rb; r < re; ++r) {
       const ReqPlan p = plan(r);
       if (p.nch == 0) continue;
@@ -390,7 +392,8 @@ __global__ __launch_bounds__(kSchedThreads) void setup_kernel(SetupArgs A) {
 
 bool make_job(const SchedSpec& s, SchedJob* j) {
   if (s.group < 1 || s.group > kWideGroup || s.deal < 0) return false;
-  *j = {s.hoff, s.toff, s.R, s.n_hist, s.n_tgt, s.chunk_blocks, s.group, s.m_lo, s.m_hi, s.deal > 0 ? 1 : 0,
+  *j = {s.hoff, s.toff, s.R, s.n_hist, s.n_tgt, s.chunk_blocks, s.group, s.m_lo, s.m_hi, s.max_chunks,
+        s.deal > 0 ? 1 : 0,
         static_cast<unsigned>(s.deal > 0 ? s.deal : 1), s.units, s.max_units, s.tchunks, s.hdr, s.order};
   return true;
 }
@@ -433,17 +436,21 @@ hipError_t fast_pack_many(const PackJobs& jobs, int n_jobs, int n_layers, hipStr
 
 // Host mirror of plan_request for exact unit counts when host offsets exist.
 int64_t host_count_units(const int32_t* hoff, const int32_t* toff, int R, int chunk_blocks, int group, int m_lo,
-                         int m_hi) {
-  int64_t n = 0;
+                         int m_hi, int max_chunks, int64_t* wide) {
+  int64_t n = 0, nw = 0;
   for (int r = 0; r < R; ++r) {
-    const int64_t h0 = hoff[r], h1 = hoff[r + 1], t0 = toff[r], t1 = toff[r + 1];
-    if (t1 == t0 || t1 - t0 < m_lo || t1 - t0 > m_hi) continue;
+    const int64_t h0 = hoff[r], h1 = hoff[r + 1], m = toff[r + 1] - static_cast<int64_t>(toff[r]);
+    if (m == 0 || m < m_lo || m > m_hi) continue;
     const int64_t nb = ceil_div(h1, kBlockTokens) - h0 / kBlockTokens;
     int64_t nch = ceil_div(nb, chunk_blocks);
-    nch = nch < 1 ? 1 : (nch > kMaxChunks ? kMaxChunks : nch);
-    const int64_t cb = ceil_div(nb, nch);
-    n += ceil_div(nb, cb) * ceil_div(t1 - t0, group);
+    nch = nch < 1 ? 1 : (nch > max_chunks ? max_chunks : nch);
+    nch = ceil_div(nb, ceil_div(nb, nch));
+    const int64_t ng = ceil_div(m, group);
+    n += nch * ng;
+    // every group but the last is full
+    if (group > 32) nw += nch * (ng - 1 + (m - (ng - 1) * group > 32 ? 1 : 0));
   }
+  if (wide) *wide = nw;
   return n;
 }
 

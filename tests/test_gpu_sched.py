@@ -33,3 +33,24 @@ def test_schedule(requests, m_hi, host):
         y = db.forward().float().cpu().numpy()
         assert db.device_status() == 0
         assert rowerr(y, ref) <= 2e-2  # the bar of the bf16 forward
+
+
+@pytest.mark.parametrize("d,h", [(256, 8), (128, 4)])
+@pytest.mark.parametrize("L,m,host", [([9001], [40], True), ([9001], [40], False), ([4100], [3], True),
+                                      ([5000, 70, 1, 900, 2048], [3, 64, 2, 33, 12], True),
+                                      ([700, 2000, 64, 33], [1, 2, 40, 64], True)])
+def test_few_requests(L, m, host, d, h):
+    """Few requests: more than 16 history chunks each, and batches that mix both
+    widths and the reordered form in one attention launch."""
+    import torch
+    from paper_2511_06077_amd.device import DeviceBatch
+    b = W.make_custom_batch("few", L, m, d_model=d, n_heads=h, n_layers=2, dtype="bf16", seed=43)
+    db = DeviceBatch(b, host_offsets=host, keep_saved=True)
+    y = db.forward().float().cpu().numpy()
+    again = db.forward()
+    torch.cuda.synchronize()
+    assert np.array_equal(again.float().cpu().numpy(), y) and db.device_status() == 0
+    ref = O.forward(b.f64())
+    assert rowerr(y, ref["out"]) <= 2e-2
+    for i in range(2):
+        assert rowerr(db.saved_tensor("a")[i].cpu().numpy(), ref["a"][i]) <= 2e-2
