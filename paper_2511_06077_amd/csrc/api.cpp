@@ -233,6 +233,7 @@ struct Layout {
   size_t qn, wkp, wvp, wop, w1p, w2p, wqp, kv;
   // target update: its cut, the splits' parts of the state and their arrival counters
   UpdatePlan upd;
+  int bsplits;  // the same of the backward's target side (update_bwd_splits)
   int max_ch;  // the most chunk records of a target (forward, bf16 path)
   size_t spart, ucnt;
   // reordered: U, the y partials with their (max, sum) and chunk counts, its
@@ -429,6 +430,13 @@ stca_status_t make_layout_for(const stca_dims_t* dims, const stca_batch_t* b, in
     const bool bf = dims->dtype == STCA_BF16;
     // every layer's K | V rows, fp32 (with b32 one layer's at a time)
     L->kvs = L->bfused && !L->b32 ? 0 : m.take(4 * (L->b32 ? 1 : n) * nh * 2 * d);
+    L->bsplits = L->bfused ? update_bwd_splits(L->nt, L->d, L->F, device_cus()) : 1;
+    if (L->bsplits > 1) {
+      // (counters of a recomputation and a reverse launch per layer)
+      const size_t groups = static_cast<size_t>(ceil_div(L->nt, 32));
+      L->spart = m.take(4 * L->bsplits * groups * 32 * d);
+      L->ucnt = m.take(4 * 2 * n * groups);
+    }
     if (L->bfused) {
       L->fwkp = m.take(2 * n * d * d);
       L->fwvp = m.take(2 * n * d * d);
@@ -811,6 +819,10 @@ stca_status_t backward_generic(const Layout& L, int bf, const stca_batch_t* b, c
   if (!L.bfused) HIPCHK(launch_sched(sp[0], st));
   HIPCHK(rec.mark("sched"));
   void* dkv = L.brd ? nullptr : at<char>(ws, L.dkv);
+  // arrival counters of the target side's launches, and their exchange buffer
+  const int64_t ugroups = ceil_div(nt, 32);
+  auto counters = [&](int i) { return L.bsplits > 1 ? at<int32_t>(ws, L.ucnt) + i * ugroups : nullptr; };
+  float* spart = L.bsplits > 1 ? at<float>(ws, L.spart) : nullptr;
   // the recomputed per-layer tensors: in the workspace, or the training record
   const RecordLayout R = L.bfused ? record_layout(L) : RecordLayout{};
   char* rb = !L.bfused ? nullptr
@@ -880,7 +892,7 @@ stca_status_t backward_generic(const Layout& L, int bf, const stca_batch_t* b, c
       pj.job[7] = {w->w1, at<char>(ws, L.fw1t), F, d, 0, 1};
       pj.job[8] = {w->wo, at<char>(ws, L.fwot), d, d, 0, 1};
       pj.job[9] = {w->wq, at<char>(ws, L.fwqt), d, d, 0, 1};
-      HIPCHK(launch_setup(sp, ns, pj, 10, n, st));
+      HIPCHK(launch_setup(sp, ns, pj, 10, n, st, counters(0), 2 * n * ugroups));
     }
   }
   // persistent grid of the fused kernels: one workgroup per CU
@@ -927,6 +939,9 @@ stca_status_t backward_generic(const Layout& L, int bf, const stca_batch_t* b, c
     HIPCHK(rec.mark("attn_fwd"));
     up.mode = 1;
     up.layer = i;
+    up.splits = L.bsplits;
+    up.spart = spart;
+    up.cnt = counters(i);
     up.s_in = RS(i);
     up.a_out = RA(i);
     up.lse_out = RL(i);
@@ -1021,6 +1036,9 @@ stca_status_t backward_generic(const Layout& L, int bf, const stca_batch_t* b, c
       ug.W2TP = at<char>(ws, L.fw2t);
       ug.W1TP = at<char>(ws, L.fw1t);
       ug.WoTP = at<char>(ws, L.fwot);
+      ug.splits = L.bsplits;
+      ug.spart = spart;
+      ug.cnt = counters(n + i);
       if (i + 1 < n) {
         // ds = du + dq W_Q^T of layer i + 1, formed inside the update
         ug.du_in = du;

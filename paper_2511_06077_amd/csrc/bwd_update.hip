@@ -14,8 +14,18 @@
 // (lane = output column), B operand = activations staged in LDS (lane =
 // target), result lane = target, element v = output column 8 (v/4) + 4 hi +
 // v%4.
+//
+// Each launch is a chain of weight tiles (128 KB each at d = 256, streamed
+// from L2) and scattered row accesses per group, so at F = 4 d and at most
+// 32 targets for every two CUs two workgroups take a group, half of the
+// hidden columns each, and the last to arrive sums their parts (split.h).  A
+// workgroup that takes all four chunks sums them as the same two halves, so
+// a target's state (and its ReLU gates) has the same bits in a batch of any
+// size (four splits would sum in another order).  4096 targets at d = 256:
+// recomputation 50 -> 40 us, reverse 38 -> 32 us a layer.
 #include "common.h"
 #include "fast.h"
+#include "split.h"
 
 namespace stca {
 
@@ -41,9 +51,12 @@ __global__ __launch_bounds__(64 * (D / 32)) void update_precise_kernel(UpdatePre
   // columns at a time
   __shared__ __attribute__((aligned(16))) bf16_bits act[3][32 * AROW];
   __shared__ __attribute__((aligned(16))) bf16_bits hid[3][32 * AROW];
+  __shared__ int arrived;
   const int w = threadIdx.x / 64, lane = threadIdx.x % 64;
   const int tcol = lane % 32, hi = lane / 32;
-  const int64_t tb = (int64_t)blockIdx.x * 32;
+  const int splits = A.mode == 0 ? 1 : A.splits;  // (the initial queries are one product)
+  const int group = blockIdx.x / splits, split = blockIdx.x % splits;
+  const int64_t tb = (int64_t)group * 32;
   const int64_t t = tb + tcol;
   const bool tok = t < A.n_tgt;
   const int F = A.F;
@@ -150,8 +163,9 @@ __global__ __launch_bounds__(64 * (D / 32)) void update_precise_kernel(UpdatePre
   } else {
     const int ql = A.layer + 1;
     const bool next_q = ql < A.n_layers;
-    auto w1_tile = [&](int c) { return W1P + ((int64_t)A.layer * (F / 32) + c * NW + w) * KS * 64; };
-    auto w2_tile = [&](int c) { return W2P + ((int64_t)(A.layer * NW + w) * (F / 16) + c * KS) * 64; };
+    const int cs = PF ? split * NC : 0;  // this split's first hidden chunk
+    auto w1_tile = [&](int c) { return W1P + ((int64_t)A.layer * (F / 32) + (cs + c) * NW + w) * KS * 64; };
+    auto w2_tile = [&](int c) { return W2P + ((int64_t)(A.layer * NW + w) * (F / 16) + (cs + c) * KS) * 64; };
     const bf16x8* wo_tile = WoP + ((int64_t)(A.layer * NW + w) * KS) * 64;
     const bf16x8* wq_tile = WqP + ((int64_t)(ql * NW + w) * KS) * 64;
     bf16x8 wa[KS], wb[KS];
@@ -207,15 +221,16 @@ __global__ __launch_bounds__(64 * (D / 32)) void update_precise_kernel(UpdatePre
 #pragma unroll
           for (int i = 0; i < 16; ++i) av[i] *= inv;
           float4* sa = reinterpret_cast<float4*>(A.a_out + tt * D + j * DH + half * 16);
+          if (split == 0)
 #pragma unroll
-          for (int q = 0; q < 4; ++q) sa[q] = make_float4(av[4 * q], av[4 * q + 1], av[4 * q + 2], av[4 * q + 3]);
-          if (A.a16_out) {
+            for (int q = 0; q < 4; ++q) sa[q] = make_float4(av[4 * q], av[4 * q + 1], av[4 * q + 2], av[4 * q + 3]);
+          if (A.a16_out && split == 0) {
             uint2* s16 = reinterpret_cast<uint2*>(A.a16_out + tt * D + j * DH + half * 16);
 #pragma unroll
             for (int q = 0; q < 4; ++q)
               s16[q] = make_uint2(pack2(av[4 * q], av[4 * q + 1]), pack2(av[4 * q + 2], av[4 * q + 3]));
           }
-          if (half == 0) A.lse_out[tt * H + j] = (M + log2f(L)) * kLn2;
+          if (half == 0 && split == 0) A.lse_out[tt * H + j] = (M + log2f(L)) * kLn2;
         }
 #pragma unroll
         for (int q = 0; q < 4; ++q)
@@ -226,22 +241,26 @@ __global__ __launch_bounds__(64 * (D / 32)) void update_precise_kernel(UpdatePre
     if (PF) fetch(wb, w1_tile(0));
     // u = s + a W_O
     f32x16 u = PF ? gemm_r(wa, act, load_tile(A.s_in, D, 32 * w)) : gemm(wo_tile, act, load_tile(A.s_in, D, 32 * w));
-    store_tile(A.u_out, D, 32 * w, u);
-    store_tile16(A.u16_out, D, 32 * w, u);
+    if (split == 0) {
+      store_tile(A.u_out, D, 32 * w, u);
+      store_tile16(A.u16_out, D, 32 * w, u);
+    }
     __builtin_amdgcn_sched_barrier(0);
     if (PF) fetch(wa, w2_tile(0));
     __syncthreads();  // every wave is done reading a
     put_tile(act, 32 * w, u);
     __syncthreads();
-    // s' = u + ReLU(u W_1) W_2, D hidden columns at a time
-    s_next = u;
+    // s' = u + ReLU(u W_1) W_2, D hidden columns at a time (u counts in the
+    // first split's part)
+    s_next = split == 0 ? u : f32x16{};
+    f32x16 s_lo = {};
 #pragma unroll
     for (int c = 0; c < (PF ? NC : F / D); ++c) {
       f32x16 h = PF ? gemm_r(wb, act, f32x16{}) : gemm(w1_tile(c), act, f32x16{});
 #pragma unroll
       for (int v = 0; v < 16; ++v) h[v] = fmaxf(h[v], 0.f);
-      store_tile(A.h_out, F, c * D + 32 * w, h);
-      store_tile16(A.h16_out, F, c * D + 32 * w, h);
+      store_tile(A.h_out, F, (cs + c) * D + 32 * w, h);
+      store_tile16(A.h16_out, F, (cs + c) * D + 32 * w, h);
       __builtin_amdgcn_sched_barrier(0);
       if (PF) {
         if (c + 1 < NC)
@@ -251,11 +270,18 @@ __global__ __launch_bounds__(64 * (D / 32)) void update_precise_kernel(UpdatePre
       }
       put_tile(hid, 32 * w, h);
       __syncthreads();
+      if (NC == 4 && c == 2) s_lo = s_next, s_next = f32x16{};
       s_next = PF ? gemm_r(wa, hid, s_next) : gemm(w2_tile(c), hid, s_next);
       __builtin_amdgcn_sched_barrier(0);
       if (PF && c + 1 < NC) fetch(wa, w2_tile(c + 1));
       __syncthreads();  // hid is rewritten by the next chunk
     }
+    if (NC == 4)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) s_next[v] = s_lo[v] + s_next[v];
+    if (splits > 1 &&
+        !split_sum<64 * NW>(s_next, A.spart, A.cnt + group, splits, A.groups, group, split, &arrived))
+      return;
     store_tile(A.s_out, D, 32 * w, s_next);
     store_tile16(A.s16_out, D, 32 * w, s_next);
     if (!next_q) return;
@@ -282,9 +308,12 @@ __global__ __launch_bounds__(64 * (D / 32)) void update_grad_kernel(UpdateGrad A
   constexpr int AROW = D + 8;
   __shared__ __attribute__((aligned(16))) bf16_bits act[32 * AROW];
   __shared__ __attribute__((aligned(16))) bf16_bits hid[32 * AROW];
+  __shared__ int arrived;
   const int w = threadIdx.x / 64, lane = threadIdx.x % 64;
   const int tcol = lane % 32, hi = lane / 32;
-  const int64_t tb = (int64_t)blockIdx.x * 32;
+  const int splits = A.ds_out ? 1 : A.splits;  // (ds alone is one product)
+  const int group = blockIdx.x / splits, split = blockIdx.x % splits;
+  const int64_t tb = (int64_t)group * 32;
   const int64_t t = tb + tcol;
   const bool tok = t < A.n_tgt;
   const int F = A.F;
@@ -346,8 +375,9 @@ __global__ __launch_bounds__(64 * (D / 32)) void update_grad_kernel(UpdateGrad A
   const bf16x8* W2TP = static_cast<const bf16x8*>(A.W2TP);
   const bf16x8* W1TP = static_cast<const bf16x8*>(A.W1TP);
   const bf16x8* WoTP = static_cast<const bf16x8*>(A.WoTP);
-  auto w2t_tile = [&](int c) { return W2TP + ((int64_t)A.layer * (F / 32) + c * NW + w) * KS * 64; };
-  auto w1t_tile = [&](int c) { return W1TP + ((int64_t)(A.layer * NW + w) * KSF + c * KS) * 64; };
+  const int cs = PF ? split * NC : 0;  // this split's first hidden chunk
+  auto w2t_tile = [&](int c) { return W2TP + ((int64_t)A.layer * (F / 32) + (cs + c) * NW + w) * KS * 64; };
+  auto w1t_tile = [&](int c) { return W1TP + ((int64_t)(A.layer * NW + w) * KSF + (cs + c) * KS) * 64; };
   const bf16x8* wot_tile = WoTP + ((int64_t)(A.layer * NW + w) * KS) * 64;
   bf16x8 wa[KS], wb[KS];  // wb: W_2^T of chunk c (then W_O^T), wa: W_Q^T, then W_1^T of chunk c
   if (PF && !A.ds_out) fetch(wb, w2t_tile(0));
@@ -379,7 +409,7 @@ __global__ __launch_bounds__(64 * (D / 32)) void update_grad_kernel(UpdateGrad A
     }
     __syncthreads();  // every wave is done with dq
     put_tile(act, 32 * w, du);
-    store16(A.ds16_out, D, 32 * w, du);
+    if (split == 0) store16(A.ds16_out, D, 32 * w, du);
   } else {
     // ds (bf16) into LDS, and its bf16 copy
     for (int c = threadIdx.x; c < 32 * D / 4; c += 64 * NW) {
@@ -388,16 +418,18 @@ __global__ __launch_bounds__(64 * (D / 32)) void update_grad_kernel(UpdateGrad A
       if (tb + row < A.n_tgt) x = *reinterpret_cast<const float4*>(A.ds + (tb + row) * D + col);
       const uint2 v = make_uint2(pack2(x.x, x.y), pack2(x.z, x.w));
       *reinterpret_cast<uint2*>(act + row * AROW + col) = v;
-      if (tb + row < A.n_tgt) *reinterpret_cast<uint2*>(A.ds16_out + (tb + row) * D + col) = v;
+      if (tb + row < A.n_tgt && split == 0) *reinterpret_cast<uint2*>(A.ds16_out + (tb + row) * D + col) = v;
     }
     du = load32(A.ds, D, 32 * w);
   }
   __builtin_amdgcn_sched_barrier(0);
   if (PF) fetch(wa, w1t_tile(0));
   __syncthreads();
+  if (split > 0) du = f32x16{};  // (ds counts in the first split's part of du)
+  f32x16 du_lo = {};
 #pragma unroll
   for (int c = 0; c < (PF ? NC : F / D); ++c) {
-    const int col = c * D + 32 * w;
+    const int col = (cs + c) * D + 32 * w;
     f32x16 dh = PF ? gemm_r(wb, act, f32x16{}) : gemm(w2t_tile(c), act, f32x16{});
     const f32x16 h = load32(A.h, F, col);
 #pragma unroll
@@ -407,11 +439,17 @@ __global__ __launch_bounds__(64 * (D / 32)) void update_grad_kernel(UpdateGrad A
     if (PF) fetch(wb, c + 1 < NC ? w2t_tile(c + 1) : wot_tile);
     put_tile(hid, 32 * w, dh);
     __syncthreads();
+    if (NC == 4 && c == 2) du_lo = du, du = f32x16{};
     du = PF ? gemm_r(wa, hid, du) : gemm(w1t_tile(c), hid, du);
     __builtin_amdgcn_sched_barrier(0);
     if (PF && c + 1 < NC) fetch(wa, w1t_tile(c + 1));
     __syncthreads();  // hid is rewritten by the next chunk
   }
+  if (NC == 4)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) du[v] = du_lo[v] + du[v];
+  // (du_out may be du_in: every split has read it when all have arrived)
+  if (splits > 1 && !split_sum<64 * NW>(du, A.spart, A.cnt + group, splits, A.groups, group, split, &arrived)) return;
   store32(A.du_out, D, 32 * w, du);
   store16(A.du16_out, D, 32 * w, du);
   put_tile(act, 32 * w, du);  // act (ds) was last read before the previous barrier
@@ -422,42 +460,58 @@ __global__ __launch_bounds__(64 * (D / 32)) void update_grad_kernel(UpdateGrad A
 
 }  // namespace
 
+// At F = 4 d, two splits while the CUs take their workgroups in one round.
+int update_bwd_splits(int64_t n_tgt, int D, int F, int n_cu) {
+  const int64_t groups = ceil_div(n_tgt, 32);
+  if (F != 4 * D) return 1;
+  return groups * 2 <= n_cu ? 2 : 1;
+}
+
+static bool splits_ok(int D, int F, int splits, const float* spart, const int32_t* cnt) {
+  if (F % D != 0 || (splits != 1 && splits != 2)) return false;
+  return splits == 1 || (F == 4 * D && spart && cnt);
+}
+
+// by the hidden chunks a workgroup takes
+#define STCA_BY_CHUNKS(KERNEL, DD)                                          \
+  if (f.F != 4 * (DD))                                                      \
+    hipLaunchKernelGGL((KERNEL<DD, 0>), g, dim3(2 * (DD)), 0, st, A);       \
+  else if (A.splits == 2)                                                   \
+    hipLaunchKernelGGL((KERNEL<DD, 2>), g, dim3(2 * (DD)), 0, st, A);       \
+  else                                                                      \
+    hipLaunchKernelGGL((KERNEL<DD, 4>), g, dim3(2 * (DD)), 0, st, A)
+
 hipError_t fast_update_precise(int D, const UpdatePrecise& f, hipStream_t st) {
   if (f.n_tgt == 0) return hipSuccess;
-  if (f.F % D != 0) return hipErrorInvalidValue;
-  dim3 g(static_cast<unsigned>(ceil_div(f.n_tgt, 32)));
-#define STCA_UPDP(DD)                                                                              \
-  if (f.F == 4 * (DD))                                                                             \
-    hipLaunchKernelGGL((update_precise_kernel<DD, 4>), g, dim3(64 * (DD / 32)), 0, st, f);         \
-  else                                                                                             \
-    hipLaunchKernelGGL((update_precise_kernel<DD, 0>), g, dim3(64 * (DD / 32)), 0, st, f)
+  UpdatePrecise A = f;
+  A.groups = static_cast<int>(ceil_div(f.n_tgt, 32));
+  if (f.mode == 0) A.splits = 1;
+  if (!splits_ok(D, f.F, A.splits, f.spart, f.cnt)) return hipErrorInvalidValue;
+  const dim3 g(static_cast<unsigned>((int64_t)A.groups * A.splits));
   switch (D) {
-    case 64: STCA_UPDP(64); break;
-    case 128: STCA_UPDP(128); break;
-    case 256: STCA_UPDP(256); break;
+    case 64: STCA_BY_CHUNKS(update_precise_kernel, 64); break;
+    case 128: STCA_BY_CHUNKS(update_precise_kernel, 128); break;
+    case 256: STCA_BY_CHUNKS(update_precise_kernel, 256); break;
     default: return hipErrorInvalidValue;
   }
-#undef STCA_UPDP
   return hipGetLastError();
 }
 
 hipError_t fast_update_grad(int D, const UpdateGrad& f, hipStream_t st) {
   if (f.n_tgt == 0) return hipSuccess;
-  if (f.F % D != 0) return hipErrorInvalidValue;
-  dim3 g(static_cast<unsigned>(ceil_div(f.n_tgt, 32)));
-#define STCA_UPDG(DD)                                                                              \
-  if (f.F == 4 * (DD))                                                                             \
-    hipLaunchKernelGGL((update_grad_kernel<DD, 4>), g, dim3(64 * (DD / 32)), 0, st, f);            \
-  else                                                                                             \
-    hipLaunchKernelGGL((update_grad_kernel<DD, 0>), g, dim3(64 * (DD / 32)), 0, st, f)
+  UpdateGrad A = f;
+  A.groups = static_cast<int>(ceil_div(f.n_tgt, 32));
+  if (f.ds_out) A.splits = 1;
+  if (!splits_ok(D, f.F, A.splits, f.spart, f.cnt)) return hipErrorInvalidValue;
+  const dim3 g(static_cast<unsigned>((int64_t)A.groups * A.splits));
   switch (D) {
-    case 64: STCA_UPDG(64); break;
-    case 128: STCA_UPDG(128); break;
-    case 256: STCA_UPDG(256); break;
+    case 64: STCA_BY_CHUNKS(update_grad_kernel, 64); break;
+    case 128: STCA_BY_CHUNKS(update_grad_kernel, 128); break;
+    case 256: STCA_BY_CHUNKS(update_grad_kernel, 256); break;
     default: return hipErrorInvalidValue;
   }
-#undef STCA_UPDG
   return hipGetLastError();
 }
+#undef STCA_BY_CHUNKS
 
 }  // namespace stca

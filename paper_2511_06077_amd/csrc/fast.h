@@ -197,7 +197,15 @@ struct UpdatePrecise {
   float *a_out, *lse_out, *u_out, *h_out, *s_out, *q_out;
   bf16_bits *a16_out, *u16_out, *h16_out, *s16_out;
   const void *WoP, *W1P, *W2P, *WqP;
+  // mode 1: workgroups a group of 32 targets divides its hidden layer over
+  // (1 or 2, as update_bwd_splits); more than one at F = 4 D only, with
+  // spart [splits][groups][32 D] and cnt [groups], zero before the launch.
+  // The launcher sets groups.
+  int splits, groups;
+  float* spart;
+  int32_t* cnt;
 };
+int update_bwd_splits(int64_t n_tgt, int D, int F, int n_cu);
 hipError_t fast_update_precise(int D, const UpdatePrecise& f, hipStream_t st);
 // Reverse of one layer's target-side update (bwd_update.hip), per 32 targets:
 // dH = (ds W_2^T) masked where h > 0, du = ds + dH W_1^T, da = du W_O^T, on
@@ -206,7 +214,8 @@ hipError_t fast_update_precise(int D, const UpdatePrecise& f, hipStream_t st);
 // packed as bf16 operand tiles (PackJob.trans).
 // With dq16 set, the gradient of s' is formed first, ds = du_in + dq16 W_Q^T
 // (W_Q of layer q_layer, packed transposed in WqTP; du_in may be du_out:
-// each element is read before the same thread writes it), and ds is unused.
+// all of a group's workgroups have read it before the last one writes), and
+// ds is unused.
 // With ds_out set as well, only that ds is formed and written (fp32), and
 // nothing else is read or written.
 struct UpdateGrad {
@@ -222,6 +231,9 @@ struct UpdateGrad {
   const void* WqTP;
   int q_layer;
   float* ds_out;
+  int splits, groups;  // as in UpdatePrecise
+  float* spart;
+  int32_t* cnt;
 };
 hipError_t fast_update_grad(int D, const UpdateGrad& f, hipStream_t st);
 

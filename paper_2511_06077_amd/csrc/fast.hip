@@ -45,6 +45,7 @@
 #include "fast.h"
 #include "reord_attn.h"
 #include "ring.h"
+#include "split.h"
 
 namespace stca {
 
@@ -696,11 +697,8 @@ __global__ __launch_bounds__(64 * (D / 32)) void attn_mixed_kernel(FusedArgs A, 
 // hidden columns through W_1 and W_2, and leaves its part of s' (split 0's
 // starts at u) in `spart`; the last of a group to arrive (a counter per group
 // and layer, zeroed by the mode 0 launch) sums the parts in split order, so
-// the result does not depend on who is last, and forms Q'.  The parts go
-// through agent-scope relaxed atomics (stores that write through to memory,
-// waited for before the counter; loads that bypass the L2): agent-scope
-// fences instead write back each XCD's whole L2, once a wave, and cost more
-// than the kernel (one request of 40 targets: 370 us a call against 246).
+// the result does not depend on who is last, and forms Q' (split.h; with
+// agent-scope fences one request of 40 targets took 370 us a call, not 246).
 // Kernel time at d = 256: 128 targets of one chunk 21 -> 11 us, 40 targets of
 // 16 chunks 20 -> 13 us, 4096 targets (no splits, the merge alone changed)
 // 22.5 -> 19 us.
@@ -1063,36 +1061,10 @@ __global__ __launch_bounds__(64 * (D / 32)) void update_kernel(UpdateArgs A) {
       if (PF && c + 1 < nc) fetch(wa, w2_tile(c + 1));
       __syncthreads();
     }
-    if (A.splits > 1) {
-      // in register order (the reader's thread holds the same elements): every
-      // access of a wave is one contiguous 512-byte piece
-      auto part_at = [&](int k, int i) {
-        return reinterpret_cast<uint64_t*>(A.spart) + (((int64_t)k * A.groups + group) * 8 + i) * NT + threadIdx.x;
-      };
-#pragma unroll
-      for (int i = 0; i < 8; ++i)
-        __hip_atomic_store(part_at(split, i),
-                           (uint64_t)__float_as_uint(s_next[2 * i]) |
-                               ((uint64_t)__float_as_uint(s_next[2 * i + 1]) << 32),
-                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the part is in memory before its arrival is counted
-      __syncthreads();
-      if (threadIdx.x == 0)
-        arrived = __hip_atomic_fetch_add(A.cnt + (int64_t)A.layer * A.groups + group, 1, __ATOMIC_RELAXED,
-                                         __HIP_MEMORY_SCOPE_AGENT);
-      __syncthreads();
-      if (arrived != A.splits - 1) {
-        report();
-        return;
-      }
-      s_next = f32x16{};
-      for (int k = 0; k < A.splits; ++k)
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          const uint64_t v = __hip_atomic_load(part_at(k, i), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          s_next[2 * i] += __uint_as_float(static_cast<uint32_t>(v));
-          s_next[2 * i + 1] += __uint_as_float(static_cast<uint32_t>(v >> 32));
-        }
+    if (A.splits > 1 && !split_sum<NT>(s_next, A.spart, A.cnt + (int64_t)A.layer * A.groups + group, A.splits,
+                                       A.groups, group, split, &arrived)) {
+      report();
+      return;
     }
     if (live(tcol)) {
       if (ql >= 0) {

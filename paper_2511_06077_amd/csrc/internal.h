@@ -32,7 +32,7 @@ struct PackJobs;
 // Up to kMaxSetupScheds schedules and a repacking (fast_pack_many's jobs) in one launch.
 constexpr int kMaxSetupScheds = 3;
 hipError_t launch_setup(const SchedSpec* sched, int n_sched, const PackJobs& jobs, int n_jobs, int n_layers,
-                        hipStream_t st);
+                        hipStream_t st, int32_t* zero = nullptr, int64_t n_zero = 0);
 // *wide (nullable): how many of them hold more than 32 targets.
 int64_t host_count_units(const int32_t* hoff, const int32_t* toff, int R, int chunk_blocks, int group, int m_lo = 1,
                          int m_hi = 1 << 30, int max_chunks = kMaxChunks, int64_t* wide = nullptr);

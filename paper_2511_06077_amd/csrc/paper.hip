@@ -23,6 +23,7 @@
 // so the eight waves share one copy.
 #include "common.h"
 #include "paper.h"
+#include "split.h"
 
 namespace stca {
 
@@ -237,9 +238,10 @@ __global__ __launch_bounds__(256) void ln_rows_kernel(const float* __restrict__ 
 // packing, 11 launches a layer took 930 us of the 3730 us step at 2080 targets;
 // here a stage streams its weights once per target group (2.3 MB at the last
 // fusion of four layers, d = 256) and is bound by that stream and by the 3 x
-// MFMA of the terms: 59 us a stage, 3115 us the step (two splits).  With `splits` > 1 workgroups (group, split) divide the
-// hidden columns and the last to arrive sums their parts of y in split order
-// (agent-scope relaxed atomics, no fences), so few targets use more CUs.
+// MFMA of the terms: 59 us a stage, 3115 us the step (two splits).  With
+// `splits` > 1 workgroups (group, split) divide the hidden columns and the
+// last to arrive sums their parts of y in split order (split.h), so few
+// targets use more CUs.
 template <int D, int NC>
 __global__ __launch_bounds__(64 * (D / 32)) void paper_target_kernel(PaperTarget A) {
   constexpr int NW = D / 32;
@@ -465,31 +467,7 @@ __global__ __launch_bounds__(64 * (D / 32)) void paper_target_kernel(PaperTarget
     __syncthreads();
     gemm(WdP + ((int64_t)w * (A.F / 16) + (int64_t)(c0 + c) * KS) * 64, hid, y);
   }
-  if (A.splits > 1) {
-    // in register order (the reader's thread holds the same elements)
-    auto part_at = [&](int k, int i) {
-      return reinterpret_cast<uint64_t*>(A.spart) + (((int64_t)k * A.groups + group) * 8 + i) * NT + threadIdx.x;
-    };
-#pragma unroll
-    for (int i = 0; i < 8; ++i)
-      __hip_atomic_store(part_at(split, i),
-                         (uint64_t)__float_as_uint(y[2 * i]) | ((uint64_t)__float_as_uint(y[2 * i + 1]) << 32),
-                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the part is in memory before its arrival is counted
-    __syncthreads();
-    if (threadIdx.x == 0)
-      arrived = __hip_atomic_fetch_add(A.cnt + group, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __syncthreads();
-    if (arrived != A.splits - 1) return;
-    y = f32x16{};
-    for (int k = 0; k < A.splits; ++k)
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const uint64_t x = __hip_atomic_load(part_at(k, i), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        y[2 * i] += __uint_as_float(static_cast<uint32_t>(x));
-        y[2 * i + 1] += __uint_as_float(static_cast<uint32_t>(x >> 32));
-      }
-  }
+  if (A.splits > 1 && !split_sum<NT>(y, A.spart, A.cnt + group, A.splits, A.groups, group, split, &arrived)) return;
   if (A.z_out) {
     if (tok) {
       bf16_bits* p = A.z_out + t * D + 32 * w + 4 * hi;

@@ -369,10 +369,14 @@ struct SetupArgs {
   SchedJob sched[kMaxSetupScheds];
   int n_sched, n_jobs, n_layers;
   PackJobs pack;
+  int32_t* zero;  // n_zero words to clear (arrival counters of the call's later launches)
+  int64_t n_zero;
 };
 __global__ __launch_bounds__(kSchedThreads) void setup_kernel(SetupArgs A) {
   __shared__ SchedLds L;
   const int bid = blockIdx.x;
+  for (int64_t i = (int64_t)bid * kSchedThreads + threadIdx.x; i < A.n_zero; i += (int64_t)gridDim.x * kSchedThreads)
+    A.zero[i] = 0;
   if (bid < A.n_sched) {
     sched_body(A.sched[bid], L);
     return;
@@ -408,7 +412,7 @@ hipError_t launch_sched(const SchedSpec& s, hipStream_t st) {
 }
 
 hipError_t launch_setup(const SchedSpec* sched, int n_sched, const PackJobs& jobs, int n_jobs, int n_layers,
-                        hipStream_t st) {
+                        hipStream_t st, int32_t* zero, int64_t n_zero) {
   if (n_sched < 0 || n_sched > kMaxSetupScheds || n_jobs < 0 || n_jobs > kMaxPackJobs) return hipErrorInvalidValue;
   SetupArgs A{};
   for (int i = 0; i < n_sched; ++i)
@@ -417,6 +421,8 @@ hipError_t launch_setup(const SchedSpec* sched, int n_sched, const PackJobs& job
   A.n_jobs = n_jobs;
   A.n_layers = n_layers;
   A.pack = jobs;
+  A.zero = zero;
+  A.n_zero = zero ? n_zero : 0;
   int64_t blocks = n_sched;
   for (int j = 0; j < n_jobs; ++j)
     blocks += n_layers * ceil_div((int64_t)(jobs.job[j].N / 32) * (jobs.job[j].K / 16) * 64, kSchedThreads);
