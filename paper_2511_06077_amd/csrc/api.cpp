@@ -762,12 +762,24 @@ stca_status_t forward_generic(const Layout& L, int bf, const stca_batch_t* b, co
     float* a = saved ? at<float>(saved, SL.a) + (size_t)i * L.nt * d : at<float>(ws, L.abuf);
     float* u = saved ? at<float>(saved, SL.u) + (size_t)i * L.nt * d : at<float>(ws, L.ubuf);
     float* lse = saved ? at<float>(saved, SL.lse) + (size_t)i * L.nt * h : nullptr;
-    HIPCHK(gemm_generic(bf, bf, L.nh, d, d, hist, d, 0, W(w->wk, i, (size_t)d * d), d, 0, kv, 2 * d, 1.f,
-                        kEpiStore, nullptr, 0, nullptr, 0, st)); HIPCHK(rec.mark("gemm_k"));
-    HIPCHK(gemm_generic(bf, bf, L.nh, d, d, hist, d, 0, W(w->wv, i, (size_t)d * d), d, 0, kv + d, 2 * d, 1.f,
-                        kEpiStore, nullptr, 0, nullptr, 0, st)); HIPCHK(rec.mark("gemm_v"));
-    HIPCHK(gemm_generic(0, bf, L.nt, d, d, s, d, 0, W(w->wq, i, (size_t)d * d), d, 0, q, d, qscale, kEpiStore,
-                        nullptr, 0, nullptr, 0, st)); HIPCHK(rec.mark("gemm_q"));
+    if (!bf) {
+      // K, V and the queries, one launch
+      auto wf = [&](const void* base) { return static_cast<const float*>(base) + (size_t)i * d * d; };
+      const float* X = static_cast<const float*>(hist);
+      const int nh = static_cast<int>(L.nh), nt = static_cast<int>(L.nt);
+      const F32Gemm g[3] = {{nh, d, d, X, d, 0, wf(w->wk), d, 0, kv, 2 * d, 1.f},
+                            {nh, d, d, X, d, 0, wf(w->wv), d, 0, kv + d, 2 * d, 1.f},
+                            {nt, d, d, s, d, 0, wf(w->wq), d, 0, q, d, qscale}};
+      HIPCHK(gemm_f32_group(g, 3, st));
+      for (const char* m : {"gemm_k", "gemm_v", "gemm_q"}) HIPCHK(rec.mark(m));
+    } else {
+      HIPCHK(gemm_generic(bf, bf, L.nh, d, d, hist, d, 0, W(w->wk, i, (size_t)d * d), d, 0, kv, 2 * d, 1.f,
+                          kEpiStore, nullptr, 0, nullptr, 0, st)); HIPCHK(rec.mark("gemm_k"));
+      HIPCHK(gemm_generic(bf, bf, L.nh, d, d, hist, d, 0, W(w->wv, i, (size_t)d * d), d, 0, kv + d, 2 * d, 1.f,
+                          kEpiStore, nullptr, 0, nullptr, 0, st)); HIPCHK(rec.mark("gemm_v"));
+      HIPCHK(gemm_generic(0, bf, L.nt, d, d, s, d, 0, W(w->wq, i, (size_t)d * d), d, 0, q, d, qscale, kEpiStore,
+                          nullptr, 0, nullptr, 0, st)); HIPCHK(rec.mark("gemm_q"));
+    }
     HIPCHK(attn_generic(L.dh, h, units, L.max_units, hdr, q, kv, d, pacc, pml, L.nt, st)); HIPCHK(rec.mark("attn"));
     HIPCHK(merge_generic(L.dh, h, L.nt, tch, pacc, pml, a, lse, st)); HIPCHK(rec.mark("merge"));
     HIPCHK(gemm_generic(0, bf, L.nt, d, d, a, d, 0, W(w->wo, i, (size_t)d * d), d, 0, u, d, 1.f, kEpiAddRes, s, d,
@@ -862,6 +874,8 @@ stca_status_t backward_generic(const Layout& L, int bf, const stca_batch_t* b, c
     return gemm_generic(a_bf, b_bf, M, N, K, A, lda, tA, B, ldb, tB, C, ldc, alpha, epi, R, ldr, C2, 0, st);
   };
   const float qscale = kLog2e / std::sqrt(static_cast<float>(L.dh));
+  // layer i of a d x d weight in fp32 storage
+  auto WF = [&](const void* base, int i) { return static_cast<const float*>(base) + (size_t)i * d * d; };
   // History-side products (rows = history items) on bf16 inputs run on the
   // MFMA GEMM with [W_K | W_V] packed side by side, so K and V of a layer come
   // from one product, and every operand arranged with k contiguous (copies
@@ -962,14 +976,17 @@ stca_status_t backward_generic(const Layout& L, int bf, const stca_batch_t* b, c
       HIPCHK(gemm_mfma(static_cast<int>(nh), 2 * d, d, static_cast<const bf16_bits*>(hist), d, 0, WKVT(i), d, 1,
                        kv, 2 * d, 1.f, 0, nullptr, 0, st));
     } else {
-      HIPCHK(gemm(0, 0, nh, d, d, hist, d, 0, W(w->wk, i, (size_t)d * d), d, 0, kv, 2 * d, 1.f, kEpiStore,
-                  nullptr, 0, nullptr));
-      HIPCHK(gemm(0, 0, nh, d, d, hist, d, 0, W(w->wv, i, (size_t)d * d), d, 0, kv + d, 2 * d, 1.f, kEpiStore,
-                  nullptr, 0, nullptr));
+      // K, V and the scaled queries, one launch
+      const float* X = static_cast<const float*>(hist);
+      const F32Gemm g[3] = {{static_cast<int>(nh), d, d, X, d, 0, WF(w->wk, i), d, 0, kv, 2 * d, 1.f},
+                            {static_cast<int>(nh), d, d, X, d, 0, WF(w->wv, i), d, 0, kv + d, 2 * d, 1.f},
+                            {static_cast<int>(nt), d, d, RS(i), d, 0, WF(w->wq, i), d, 0, RQ(i), d, qscale}};
+      HIPCHK(gemm_f32_group(g, 3, st));
     }
     HIPCHK(rec.mark("kv_gemm"));
-    HIPCHK(gemm(0, bf, nt, d, d, RS(i), d, 0, W(w->wq, i, (size_t)d * d), d, 0, RQ(i), d, qscale, kEpiStore,
-                nullptr, 0, nullptr));
+    if (bf)
+      HIPCHK(gemm(0, bf, nt, d, d, RS(i), d, 0, W(w->wq, i, (size_t)d * d), d, 0, RQ(i), d, qscale, kEpiStore,
+                  nullptr, 0, nullptr));
     HIPCHK(rec.mark("target_gemm"));
     HIPCHK(attn_generic(L.dh, h, units, L.max_units, hdr, RQ(i), kv, d, at<float>(ws, L.part_acc),
                         at<float>(ws, L.part_ml), nt, st));
@@ -1085,17 +1102,19 @@ stca_status_t backward_generic(const Layout& L, int bf, const stca_batch_t* b, c
                        st));
       HIPCHK(gemm_mfma(nti, d, d, B(L.b_du), d, 0, WB(Wo), d, 1, da, d, 1.f, 0, nullptr, 0, st));
     } else {
-      HIPCHK(gemm(0, 0, F, d, nt, hid, F, 1, ds, d, 0, dw->dw2 + (size_t)i * F * d, d, 1.f, kEpiStore, nullptr, 0,
-                  nullptr));
-      HIPCHK(gemm(0, 0, nt, F, d, ds, d, 0, W2, d, 1, dhid, F, 1.f, kEpiStore, nullptr, 0, nullptr));
-      HIPCHK(relu_mask_mul(dhid, hid, nt * F, st));
-      HIPCHK(gemm(0, 0, d, F, nt, u, d, 1, dhid, F, 0, dw->dw1 + (size_t)i * d * F, F, 1.f, kEpiStore, nullptr, 0,
-                  nullptr));
-      HIPCHK(gemm(0, 0, nt, d, F, dhid, F, 0, W1, F, 1, du, d, 1.f, kEpiAddRes, ds, d, nullptr));
+      // each weight's gradient beside the product that carries on
+      const int nti = static_cast<int>(nt);
+      const float *w1 = static_cast<const float*>(W1), *w2 = static_cast<const float*>(W2);
+      const F32Gemm g2[2] = {{nti, F, d, ds, d, 0, w2, d, 1, dhid, F, 1.f, kEpiMask, hid, F},
+                             {F, d, nti, hid, F, 1, ds, d, 0, dw->dw2 + (size_t)i * F * d, d, 1.f}};
+      HIPCHK(gemm_f32_group(g2, 2, st));
+      const F32Gemm g1[2] = {{nti, d, F, dhid, F, 0, w1, F, 1, du, d, 1.f, kEpiAddRes, ds, d},
+                             {d, F, nti, u, d, 1, dhid, F, 0, dw->dw1 + (size_t)i * d * F, F, 1.f}};
+      HIPCHK(gemm_f32_group(g1, 2, st));
       // u = s + a Wo
-      HIPCHK(gemm(0, 0, d, d, nt, a, d, 1, du, d, 0, dw->dwo + (size_t)i * d * d, d, 1.f, kEpiStore, nullptr, 0,
-                  nullptr));
-      HIPCHK(gemm(0, 0, nt, d, d, du, d, 0, Wo, d, 1, da, d, 1.f, kEpiStore, nullptr, 0, nullptr));
+      const F32Gemm go[2] = {{nti, d, d, du, d, 0, WF(w->wo, i), d, 1, da, d, 1.f},
+                             {d, d, nti, a, d, 1, du, d, 0, dw->dwo + (size_t)i * d * d, d, 1.f}};
+      HIPCHK(gemm_f32_group(go, 2, st));
     }
     HIPCHK(rec.mark("target_gemm"));
     // attention (softmax weights rebuilt from the same q, K, V and lse that
@@ -1233,26 +1252,23 @@ stca_status_t backward_generic(const Layout& L, int bf, const stca_batch_t* b, c
                          d, 1.f, 1, nullptr, 0, st));
       }
     } else {
-      HIPCHK(gemm(0, 0, d, d, nt, s, d, 1, dq, d, 0, dw->dwq + (size_t)i * d * d, d, 1.f, kEpiStore, nullptr, 0,
-                  nullptr));
-      HIPCHK(gemm(0, 0, nt, d, d, dq, d, 0, Wq, d, 1, ds2, d, 1.f, kEpiAddRes, du, d, nullptr));
+      // q = s Wq and [K | V] = X [W_K | W_V]: their gradients, one launch
+      const float *X = static_cast<const float*>(hist), *dKV = static_cast<const float*>(dkv);
+      const int nti = static_cast<int>(nt), nhi = static_cast<int>(nh);
+      const size_t o = (size_t)i * d * d;
+      const F32Gemm g[5] = {
+          {nhi, d, d, dKV, 2 * d, 0, WF(w->wk, i), d, 1, dhist, d, 1.f, kEpiStore, nullptr, 0, 1, dKV + d, WF(w->wv, i)},
+          {d, d, nhi, X, d, 1, dKV, 2 * d, 0, dw->dwk + o, d, 1.f},
+          {d, d, nhi, X, d, 1, dKV + d, 2 * d, 0, dw->dwv + o, d, 1.f},
+          {nti, d, d, dq, d, 0, WF(w->wq, i), d, 1, ds2, d, 1.f, kEpiAddRes, du, d},
+          {d, d, nti, s, d, 1, dq, d, 0, dw->dwq + o, d, 1.f}};
+      HIPCHK(gemm_f32_group(g, 5, st));
     }
+    // (on the bf16 path every layer's dK | dV is kept and the history-side
+    // gradients are formed once after the loop)
     HIPCHK(rec.mark("target_gemm"));
-    // [K | V] = X [W_K | W_V]: on the bf16 path every layer's dK | dV is kept
-    // and the history-side gradients are formed once after the loop
     if (!bf) {
-      const float* dKV = static_cast<const float*>(dkv);
-      const void* Wk = W(w->wk, i, (size_t)d * d);
-      const void* Wv = W(w->wv, i, (size_t)d * d);
-      HIPCHK(gemm(0, 0, d, d, nh, hist, d, 1, dKV, 2 * d, 0, dw->dwk + (size_t)i * d * d, d, 1.f, kEpiStore,
-                  nullptr, 0, nullptr));
-      HIPCHK(gemm(0, 0, d, d, nh, hist, d, 1, dKV + d, 2 * d, 0, dw->dwv + (size_t)i * d * d, d, 1.f, kEpiStore,
-                  nullptr, 0, nullptr));
       HIPCHK(rec.mark("dw_kv"));
-      HIPCHK(gemm_generic(0, 0, nh, d, d, dKV, 2 * d, 0, Wk, d, 1, dhist, d, 1.f, kEpiStore, nullptr, 0, nullptr, 1,
-                          st));
-      HIPCHK(gemm_generic(0, 0, nh, d, d, dKV + d, 2 * d, 0, Wv, d, 1, dhist, d, 1.f, kEpiStore, nullptr, 0,
-                          nullptr, 1, st));
       HIPCHK(rec.mark("dx"));
     }
     std::swap(ds, ds2);

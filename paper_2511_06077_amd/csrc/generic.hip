@@ -27,29 +27,31 @@ __device__ __forceinline__ float ld(const T* p, int64_t i) {
 constexpr int GT = 64;  // output tile edge
 constexpr int GK = 32;  // k step
 
+// Tile (bx, by) and k range bz of `splits`.  A2, B2 (nullable): a second pair
+// of operands of the same forms, whose product is added.
 template <typename TA, typename TB>
-__global__ __launch_bounds__(256) void gemm_kernel(int M, int N, int K, const TA* __restrict__ A,
-                                                   int64_t lda, int transA, const TB* __restrict__ B,
-                                                   int64_t ldb, int transB, float* __restrict__ C,
-                                                   int64_t ldc, float alpha, int epi,
-                                                   const float* __restrict__ R, int64_t ldr,
-                                                   float* __restrict__ C2, int accumulate, int k_chunk) {
+__device__ __forceinline__ void gemm_body(int bx, int by, int bz, int splits, int M, int N, int K,
+                                          const TA* __restrict__ A, int64_t lda, int transA,
+                                          const TB* __restrict__ B, int64_t ldb, int transB, float* __restrict__ C,
+                                          int64_t ldc, float alpha, int epi, const float* __restrict__ R, int64_t ldr,
+                                          float* __restrict__ C2, int accumulate, int k_chunk, const TA* A2 = nullptr,
+                                          const TB* B2 = nullptr) {
   __shared__ float As[GK][GT + 1];
   __shared__ float Bs[GK][GT + 1];
   const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
   const int wm = (wave / 2) * 32, wn = (wave % 2) * 32;
   const int r32 = lane % 32, hi = lane / 32;
-  const int m0 = blockIdx.y * GT, n0 = blockIdx.x * GT;
+  const int m0 = by * GT, n0 = bx * GT;
   f32x16 acc = {};
   // split-K: workgroup z sums k in [z * k_chunk, (z + 1) * k_chunk) and adds
   // its partial into C atomically (C was cleared or holds what to add to)
-  const int kb = blockIdx.z * k_chunk;
+  const int kb = bz * k_chunk;
   const int ke = min(K, kb + k_chunk);
   constexpr int PER = GT * GK / 256;
   float ra[PER], rb[PER];
   // Consecutive threads walk each source's contiguous index, so global reads
   // coalesce.
-  auto load = [&](int k0) {
+  auto load = [&](const TA* A, const TB* B, int k0) {
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
       const int e = threadIdx.x + 256 * i;
@@ -72,12 +74,17 @@ __global__ __launch_bounds__(256) void gemm_kernel(int M, int N, int K, const TA
       Bs[kb2][nn] = rb[i];
     }
   };
-  load(kb);
+  load(A, B, kb);
   store();
   __syncthreads();
-  for (int k0 = kb; k0 < ke; k0 += GK) {
-    const bool more = k0 + GK < ke;
-    if (more) load(k0 + GK);
+  // (k tiles of the first pair, then of the second)
+  const int tiles = (ke - kb + GK - 1) / GK, all = A2 ? 2 * tiles : tiles;
+  for (int t = 0; t < all; ++t) {
+    const bool more = t + 1 < all;
+    if (more) {
+      const bool second = t + 1 >= tiles;
+      load(second ? A2 : A, second ? B2 : B, kb + (second ? t + 1 - tiles : t + 1) * GK);
+    }
     // operand lane l holds A[m = l % 32][k = l / 32] and B[k = l / 32][n = l % 32]
 #pragma unroll
     for (int kk = 0; kk < GK; kk += 2)
@@ -97,17 +104,60 @@ __global__ __launch_bounds__(256) void gemm_kernel(int M, int N, int K, const TA
     if (gm >= M) continue;
     float x = alpha * acc[v];
     float* c = C + (int64_t)gm * ldc + gn;
-    if (gridDim.z > 1) {
+    if (splits > 1) {
       atomicAdd(c, x);
       continue;
     }
     if (epi == kEpiAddRes) x += R[(int64_t)gm * ldr + gn];
+    if (epi == kEpiMask && !(R[(int64_t)gm * ldr + gn] > 0.f)) x = 0.f;
     if (epi == kEpiRelu) {
       if (C2) C2[(int64_t)gm * ldc + gn] = x;
       x = fmaxf(x, 0.f);
     }
     *c = accumulate ? *c + x : x;
   }
+}
+
+template <typename TA, typename TB>
+__global__ __launch_bounds__(256) void gemm_kernel(int M, int N, int K, const TA* __restrict__ A,
+                                                   int64_t lda, int transA, const TB* __restrict__ B,
+                                                   int64_t ldb, int transB, float* __restrict__ C,
+                                                   int64_t ldc, float alpha, int epi,
+                                                   const float* __restrict__ R, int64_t ldr,
+                                                   float* __restrict__ C2, int accumulate, int k_chunk) {
+  gemm_body<TA, TB>(blockIdx.x, blockIdx.y, blockIdx.z, gridDim.z, M, N, K, A, lda, transA, B, ldb, transB, C, ldc,
+                    alpha, epi, R, ldr, C2, accumulate, k_chunk);
+}
+
+// Independent fp32 products in one launch.  What bounds the fp32 path on small
+// batches is the chain of launches: a 64 x 64 tile of a product takes 5-10 us
+// (a load's latency per 32-deep k tile) on a chip that holds dozens of such
+// products, so the products of a layer that don't wait for each other go
+// together.  A training step of 4 requests of 256 rows and 4 targets (d = 64, two
+layers): 77 launches 549 us, 51 launches 319 us.
+struct F32Group {
+  F32Gemm g[kMaxF32Group];
+  int nx[kMaxF32Group], ny[kMaxF32Group], splits[kMaxF32Group], k_chunk[kMaxF32Group];
+  int end[kMaxF32Group];  // first workgroup after the product's
+  int n;
+};
+__global__ __launch_bounds__(256) void gemm_f32_group_kernel(F32Group G) {
+  int i = blockIdx.x, j = 0;
+  while (j + 1 < G.n && i >= G.end[j]) ++j;
+  if (j > 0) i -= G.end[j - 1];
+  const F32Gemm& g = G.g[j];
+  const int per = G.nx[j] * G.ny[j], t = i % per;
+  gemm_body<float, float>(t % G.nx[j], t / G.nx[j], i / per, G.splits[j], g.M, g.N, g.K, g.A, g.lda, g.transA, g.B,
+                          g.ldb, g.transB, g.C, g.ldc, g.alpha, g.epi, g.R, g.ldr, nullptr, g.accumulate, G.k_chunk[j],
+                          g.A2, g.B2);
+}
+
+// Clears the outputs that splits add into, one grid row each.
+__global__ void clear_group_kernel(F32Group G) {
+  const int j = blockIdx.y;
+  if (G.splits[j] == 1 || G.g[j].accumulate) return;
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < (int64_t)G.g[j].M * G.g[j].N) G.g[j].C[(i / G.g[j].N) * G.g[j].ldc + i % G.g[j].N] = 0.f;
 }
 
 // fp32-accurate products with bf16 weights on the bf16 matrix cores:
@@ -704,6 +754,37 @@ hipError_t gemm_generic(int a_bf16, int b_bf16, int M, int N, int K, const void*
   else if (b_bf16) STCA_GEMM(float, bf16_bits);
   else STCA_GEMM(float, float);
 #undef STCA_GEMM
+  return hipGetLastError();
+}
+
+// Long reductions with few output tiles split K as in gemm_generic, into
+// chunks down to 128 deep (four k tiles).
+hipError_t gemm_f32_group(const F32Gemm* g, int n, hipStream_t st) {
+  if (n < 0 || n > kMaxF32Group) return hipErrorInvalidValue;
+  F32Group G{};
+  int64_t blocks = 0, clear = 0;
+  for (int j = 0; j < n; ++j) {
+    if (g[j].M == 0 || g[j].N == 0) continue;
+    const int k = G.n++;
+    G.g[k] = g[j];
+    const int64_t nx = ceil_div(g[j].N, GT), ny = ceil_div(g[j].M, GT), tiles = nx * ny;
+    int64_t splits = 1;
+    if (g[j].epi == kEpiStore && !g[j].A2 && tiles < 256 && g[j].K >= 1024)
+      splits = std::max<int64_t>(1, std::min<int64_t>(ceil_div(512, tiles), g[j].K / 128));
+    G.k_chunk[k] = static_cast<int>(round_up(ceil_div(g[j].K, splits), GK));
+    if (G.k_chunk[k] > 0) splits = ceil_div(g[j].K, G.k_chunk[k]);
+    G.nx[k] = static_cast<int>(nx);
+    G.ny[k] = static_cast<int>(ny);
+    G.splits[k] = static_cast<int>(std::max<int64_t>(1, splits));
+    blocks += tiles * G.splits[k];
+    if (blocks >= (int64_t)1 << 24) return hipErrorInvalidValue;  // (2^32 threads)
+    G.end[k] = static_cast<int>(blocks);
+    if (G.splits[k] > 1 && !g[j].accumulate) clear = std::max<int64_t>(clear, (int64_t)g[j].M * g[j].N);
+  }
+  if (G.n == 0) return hipSuccess;
+  if (clear > 0)
+    hipLaunchKernelGGL(clear_group_kernel, dim3(static_cast<unsigned>(ceil_div(clear, 256)), G.n), dim3(256), 0, st, G);
+  hipLaunchKernelGGL(gemm_f32_group_kernel, dim3(static_cast<unsigned>(blocks)), dim3(256), 0, st, G);
   return hipGetLastError();
 }
 

@@ -38,7 +38,7 @@ int64_t host_count_units(const int32_t* hoff, const int32_t* toff, int R, int ch
                          int m_hi = 1 << 30, int max_chunks = kMaxChunks, int64_t* wide = nullptr);
 
 // ---- generic fp32-arithmetic path (generic.hip)
-enum GemmEpi { kEpiStore = 0, kEpiAddRes = 1, kEpiRelu = 2 };
+enum GemmEpi { kEpiStore = 0, kEpiAddRes = 1, kEpiRelu = 2, kEpiMask = 3 };
 // C[M,N] = epi(alpha * A[M,K] B[K,N]); A, B row-major with leading dims; C fp32.
 // kEpiAddRes: C = R + alpha*AB.  kEpiRelu: C = max(AB, 0) and, if C2, C2 = AB.
 // transA / transB read A as [K,M] / B as [N,K] (i.e. multiply by the transpose).
@@ -46,6 +46,28 @@ hipError_t gemm_generic(int a_bf16, int b_bf16, int M, int N, int K, const void*
                         int transA, const void* B, int64_t ldb, int transB, float* C, int64_t ldc,
                         float alpha, GemmEpi epi, const float* R, int64_t ldr, float* C2,
                         int accumulate, hipStream_t st);
+// Products of fp32 operands that don't depend on each other, in one launch;
+// conventions as in gemm_generic.  kEpiMask: C = R > 0 ? alpha*AB : 0.  With
+// A2, B2 (same forms and leading dims): AB + A2 B2.
+struct F32Gemm {
+  int M, N, K;
+  const float* A;
+  int64_t lda;
+  int transA;
+  const float* B;
+  int64_t ldb;
+  int transB;
+  float* C;
+  int64_t ldc;
+  float alpha;
+  GemmEpi epi;
+  const float* R;
+  int64_t ldr;
+  int accumulate;
+  const float *A2, *B2;
+};
+constexpr int kMaxF32Group = 6;
+hipError_t gemm_f32_group(const F32Gemm* g, int n, hipStream_t st);
 // MFMA GEMM, bf16 operands, fp32 accumulation and output:
 // C = alpha op(A) op(B) (+ C when accumulating), operand conventions as in
 // gemm_generic.  The contiguous extent of each operand (K for A untransposed

@@ -1,0 +1,37 @@
+"""GPU parity of the fp32-storage path's grouped products where a product's
+tiling changes: output tiles of 64 with remainders, 32-deep k tiles with
+remainders, long reductions split over K from 1024 rows on (several splits with
+a short last one), requests without targets."""
+import numpy as np
+import pytest
+
+from oracle import stca_oracle as O
+from paper_2511_06077_amd import workload as W
+from test_gpu_backward import TOL, check, gpu_grads
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def torch():
+    import torch as t
+    assert t.cuda.is_available(), "GPU tests need a GPU"
+    return t
+
+
+# d x d weight gradients over 2, 63, 65 and 1023 rows in one piece, over 1024,
+# 1100 and 2113 split (2113 = 14 chunks of 160, the last of 33); up to
+# 130 targets.  (Not over one row: its softmax weight is 1 and dW_Q, dW_K are zero
+# in the oracle, so a relative bound is none; the GPU leaves dP - D, which its
+# roundings bound by about 2^-23 |dP|.)
+@pytest.mark.parametrize("d,h,L,m", [(64, 2, [2], [1]), (64, 2, [60, 3], [1, 0]), (128, 2, [33, 32], [64, 1]),
+                                     (64, 8, [1000, 23], [3, 5]), (64, 2, [1024], [4]), (128, 4, [1100], [65]),
+                                     (64, 1, [2048, 65], [129, 1])])
+def test_f32_products(torch, d, h, L, m):
+    from paper_2511_06077_amd.device import DeviceBatch
+    b = W.make_custom_batch("gf32", L, m, d_model=d, n_heads=h, n_layers=2, dtype="f32", seed=97, with_grad=True)
+    y = DeviceBatch(b).forward().cpu().numpy().astype(np.float64)
+    ref = O.forward(b.f64())["out"]
+    # (sums of at most 4 d = 512 fp32 terms through two layers: 2^-24 sqrt(512) = 1.3e-6 a product)
+    assert np.abs(y - ref).max() <= 2e-5 * np.abs(ref).max()
+    check(b, gpu_grads(torch, b), TOL["f32"])
