@@ -98,20 +98,21 @@ typedef enum { STCA_F32 = 0, STCA_BF16 = 1 } stca_dtype_t;
  *          STCA_ATTN_REORDERED: every request in the reordered form, for
  *          requests of up to 256 / n_heads targets (d_h = 32, host offsets
  *          given); STCA_ERR_UNSUPPORTED for other batches.
- * bwd_form STCA_BWD_AUTO: with d_h = 32, ffn_hidden a multiple of d_model and
- *          host offsets showing at most 32 targets per request (128 with
- *          d_model 128 or 256), the backward on bf16 storage runs in the
- *          reordered form (the attention gradients through u = q W_K^T and
- *          h = da W_V^T per target and head, no K, V, dK or dV, in groups of
- *          128 / n_heads targets; Sec. 3.1's reordering applied to the
- *          backward; d_model 128 or 256) or in the fused form (K/V formed
- *          inside the attention kernels, dK | dV written for the
- *          history-side products; at most 32 targets per request).  It is
- *          reordered for more than 32 targets, for histories balanced over
- *          the compute units with at most 128 / n_heads targets, and else
- *          where an estimate of the two forms' kernels favours it.
- *          Otherwise K | V are formed by a GEMM and the attention runs in
- *          exact fp32 (generic).
+ * bwd_form STCA_BWD_AUTO: with d_h = 32, d_model in {64, 128, 256},
+ *          ffn_hidden a multiple of d_model and host offsets, the backward on
+ *          bf16 storage recomputes the forward with the history projected
+ *          inside the attention kernel.  For at most 32 targets per request it
+ *          then runs in the reordered form (the attention gradients through
+ *          u = q W_K^T and h = da W_V^T per target and head, no K, V, dK or
+ *          dV, in groups of 128 / n_heads targets; Sec. 3.1's reordering
+ *          applied to the backward; d_model 128 or 256) or in the fused form
+ *          (K/V formed inside the attention kernels, dK | dV written for the
+ *          history-side products): reordered for histories balanced over the
+ *          compute units with at most 128 / n_heads targets, else where an
+ *          estimate of the two forms' kernels favours it.  For more targets
+ *          the attention gradients are formed in fp32 over one layer's K | V
+ *          at a time.  Otherwise every layer's K | V are formed by a GEMM and
+ *          the attention runs in exact fp32 both ways (generic).
  *          STCA_BWD_GENERIC: always the generic form.  STCA_BWD_FUSED: the
  *          fused form.  STCA_BWD_REORDERED: the reordered form with one
  *          target group per request (at most 128 / n_heads targets).  Each is
@@ -119,7 +120,8 @@ typedef enum { STCA_F32 = 0, STCA_BF16 = 1 } stca_dtype_t;
  * chunk_blocks: history chunk length, in 32-row blocks, of the attention's
  *          split over a request's history (at most 16 chunks per request, so
  *          long histories get longer chunks); 0 = chosen from the batch size
- *          and the number of compute units.
+ *          and the number of compute units (then up to 64 chunks per request
+ *          in a forward of few requests).
  * Out-of-range values are STCA_ERR_INVALID_ARG. */
 typedef enum { STCA_KV_AUTO = 0, STCA_KV_FUSED = 1, STCA_KV_MATERIALIZE = 2 } stca_kv_form_t;
 typedef enum { STCA_ATTN_AUTO = 0, STCA_ATTN_STANDARD = 1, STCA_ATTN_REORDERED = 2 } stca_attn_form_t;
