@@ -1011,7 +1011,7 @@ stca_status_t backward_generic(const Layout& L, int bf, const stca_batch_t* b, c
   // rows of requests without targets keep a zero gradient (and dK|dV^T's
   // padding columns stay zero)
   if (L.brd) {
-    HIPCHK(rb_zero_untargeted(b->hist_off, b->tgt_off, b->n_requests, dhist, d, st));
+    HIPCHK(rb_zero_untargeted(b->hist_off, b->tgt_off, b->n_requests, nh, dhist, d, st));
   } else if (bf) {
     HIPCHK(zero_untargeted(b->hist_off, b->tgt_off, b->n_requests, nh, static_cast<bf16_bits*>(dkv), n * 2 * d,
                            n * 2 * d, dkvt, nh8, st));
@@ -1131,6 +1131,7 @@ stca_status_t backward_generic(const Layout& L, int bf, const stca_batch_t* b, c
       bf16_bits* Y = at<bf16_bits>(ws, L.rb_y);
       RbPrep pp{};
       pp.tgt_off = b->tgt_off;
+      pp.n_tgt = nt;
       pp.n_requests = b->n_requests;
       pp.groups = L.rb_groups;
       pp.layer = i;
@@ -1153,6 +1154,7 @@ stca_status_t backward_generic(const Layout& L, int bf, const stca_batch_t* b, c
       ra.X = hist;
       ra.n_hist = nh;
       ra.n_tgt = nt;
+      ra.max_units = L.rb_maxu;
       ra.layer = i;
       ra.n_layers = n;
       ra.U16 = pp.U16;
@@ -1169,9 +1171,10 @@ stca_status_t backward_generic(const Layout& L, int bf, const stca_batch_t* b, c
       ra.Zp = at<float>(ws, L.rb_zp);
       ra.Yp = at<float>(ws, L.rb_yp);
       ra.first = at<int32_t>(ws, L.rb_first);
-      HIPCHK(rb_attn(d, ra, static_cast<int>(L.rb_maxu), st));
+      HIPCHK(rb_attn(d, ra, st));
       if (L.rb_partials)
-        HIPCHK(rb_reduce(d, b->tgt_off, b->n_requests, L.rb_groups, ra.tchunks, ra.first, ra.Zp, ra.Yp, Z, Y, nt, st));
+        HIPCHK(rb_reduce(d, b->tgt_off, b->n_requests, L.rb_groups, ra.tchunks, ra.first, L.rb_maxu, ra.Zp, ra.Yp, Z, Y,
+                         nt, st));
       HIPCHK(rec.mark("attn_bwd"));
       const int nti = static_cast<int>(nt);
       GemmSpec g[2 * 8], gq[8];

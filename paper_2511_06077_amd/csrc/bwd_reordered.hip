@@ -101,6 +101,7 @@ __global__ __launch_bounds__(64 * (D / 32)) void rb_prep_kernel(RbPrep A) {
   const int r = blockIdx.x, g = blockIdx.y;
   if (r >= A.n_requests) return;
   const int h = threadIdx.x / 64, lane = threadIdx.x % 64, l32 = lane % 32, hi = lane / 32;
+  if (A.tgt_off[r] < 0 || A.tgt_off[r + 1] > A.n_tgt) return;  // (a request the scheduler refused)
   const int64_t t0 = A.tgt_off[r] + (int64_t)g * M;
   const int m = static_cast<int>(A.tgt_off[r + 1] - t0);  // targets from the group's first on
   if (m <= 0) return;
@@ -241,9 +242,13 @@ __global__ __launch_bounds__(512) void rb_attn_kernel(RbAttn A) {
   const bf16_bits* __restrict__ X = static_cast<const bf16_bits*>(A.X);
   constexpr int M = HM / (D / DH);  // targets of a group
 
+  // The slots and partials are sized from the host's offsets.  Where the device
+  // copy holds other ones, a unit may have a group or a rank past them: it does
+  // no work (a schedule of more units than the host counted has the status set).
   const int g = static_cast<int>((t0 - A.tgt_off[r]) / M);
-  const int64_t slot = (int64_t)r * A.groups + g;
   const int64_t rank = A.order[blockIdx.x];
+  if (g >= A.groups || rank >= A.max_units) return;
+  const int64_t slot = (int64_t)r * A.groups + g;
   float lse2 = A.stats[(slot * HM + jp) * 2];
   float dsum = A.stats[(slot * HM + jp) * 2 + 1];
   f32x16 acc[DT];  // role 0: Y, role 1: Z
@@ -478,18 +483,21 @@ __global__ __launch_bounds__(512) void rb_attn_kernel(RbAttn A) {
 template <int D>
 __global__ __launch_bounds__(256) void rb_reduce_kernel(const int32_t* __restrict__ toff, int n_requests, int groups,
                                                         const int32_t* __restrict__ tchunks,
-                                                        const int32_t* __restrict__ first, const float* __restrict__ Zp,
+                                                        const int32_t* __restrict__ first, int64_t max_units,
+                                                        const float* __restrict__ Zp,
                                                         const float* __restrict__ Yp, bf16_bits* __restrict__ Z,
                                                         bf16_bits* __restrict__ Y, int64_t n_tgt) {
   constexpr int H = D / DH, M = HM / H, kRedRows = 256 / (D / 4);
   const int r = blockIdx.x, g = blockIdx.y;
   if (r >= n_requests) return;
+  if (toff[r] < 0 || toff[r + 1] > n_tgt) return;  // (a request the scheduler refused)
   const int64_t t0 = toff[r] + (int64_t)g * M;
   const int m = min(M, static_cast<int>(toff[r + 1] - t0));
   if (m <= 0) return;
   const int nch = tchunks[t0];
   if (nch <= 1) return;
-  const int u0 = first[(int64_t)r * groups + g];
+  const int64_t u0 = first[(int64_t)r * groups + g];
+  if (u0 < 0 || u0 + nch > max_units) return;  // (no such partials: see rb_attn_kernel)
   // kRedRows targets of one head a block, four columns a thread
   const int hh = blockIdx.z % H;
   const int tt = blockIdx.z / H * kRedRows + threadIdx.x / (D / 4), dd = 4 * (threadIdx.x % (D / 4));
@@ -497,7 +505,7 @@ __global__ __launch_bounds__(256) void rb_reduce_kernel(const int32_t* __restric
     float4 z = make_float4(0.f, 0.f, 0.f, 0.f), y = z;
 #pragma unroll 4
     for (int c = 0; c < nch; ++c) {
-      const int64_t o = ((int64_t)(u0 + c) * HM + hh * M + tt) * D + dd;
+      const int64_t o = ((u0 + c) * HM + hh * M + tt) * D + dd;
       const float4 zc = *reinterpret_cast<const float4*>(Zp + o), yc = *reinterpret_cast<const float4*>(Yp + o);
       z.x += zc.x, z.y += zc.y, z.z += zc.z, z.w += zc.w;
       y.x += yc.x, y.y += yc.y, y.z += yc.z, y.w += yc.w;
@@ -514,11 +522,12 @@ __global__ __launch_bounds__(256) void rb_reduce_kernel(const int32_t* __restric
 }
 
 __global__ void rb_zero_rows_kernel(const int32_t* __restrict__ hoff, const int32_t* __restrict__ toff,
-                                    int n_requests, float* __restrict__ dst, int cols) {
+                                    int n_requests, int64_t n_hist, float* __restrict__ dst, int cols) {
   const int r = blockIdx.x;
   if (r >= n_requests || toff[r + 1] != toff[r]) return;
-  const int64_t cnt = (int64_t)(hoff[r + 1] - hoff[r]) * cols;
-  float* p = dst + (int64_t)hoff[r] * cols;
+  const int64_t h0 = max(0, hoff[r]), h1 = min<int64_t>(n_hist, hoff[r + 1]);
+  const int64_t cnt = (h1 - h0) * cols;
+  float* p = dst + h0 * cols;
   for (int64_t e = threadIdx.x; e < cnt; e += blockDim.x) p[e] = 0.f;
 }
 
@@ -534,9 +543,10 @@ hipError_t rb_prep(int D, const RbPrep& a, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t rb_attn(int D, const RbAttn& a, int grid, hipStream_t st) {
-  if (grid == 0) return hipSuccess;
-#define STCA_RBA(DD) hipLaunchKernelGGL(rb_attn_kernel<DD>, dim3(grid), dim3(512), 0, st, a)
+hipError_t rb_attn(int D, const RbAttn& a, hipStream_t st) {
+  if (a.max_units == 0) return hipSuccess;
+#define STCA_RBA(DD) \
+  hipLaunchKernelGGL(rb_attn_kernel<DD>, dim3(static_cast<unsigned>(a.max_units)), dim3(512), 0, st, a)
   if (D == 256) STCA_RBA(256);
   else if (D == 128) STCA_RBA(128);
   else return hipErrorInvalidValue;
@@ -545,11 +555,11 @@ hipError_t rb_attn(int D, const RbAttn& a, int grid, hipStream_t st) {
 }
 
 hipError_t rb_reduce(int D, const int32_t* tgt_off, int n_requests, int groups, const int32_t* tchunks, const int32_t* first,
-                     const float* Zp, const float* Yp, bf16_bits* Z, bf16_bits* Y, int64_t n_tgt, hipStream_t st) {
+                     int64_t max_units, const float* Zp, const float* Yp, bf16_bits* Z, bf16_bits* Y, int64_t n_tgt, hipStream_t st) {
   if (n_requests == 0) return hipSuccess;
 #define STCA_RBR(DD)                                                                                              \
   hipLaunchKernelGGL(rb_reduce_kernel<DD>, dim3(n_requests, groups, HM / (256 / (DD / 4))), dim3(256), 0, st, tgt_off,   \
-                     n_requests, groups, tchunks, first, Zp, Yp, Z, Y, n_tgt)
+                     n_requests, groups, tchunks, first, max_units, Zp, Yp, Z, Y, n_tgt)
   if (D == 256) STCA_RBR(256);
   else if (D == 128) STCA_RBR(128);
   else return hipErrorInvalidValue;
@@ -557,10 +567,11 @@ hipError_t rb_reduce(int D, const int32_t* tgt_off, int n_requests, int groups, 
   return hipGetLastError();
 }
 
-hipError_t rb_zero_untargeted(const int32_t* hoff, const int32_t* toff, int n_requests, float* dst, int cols,
-                              hipStream_t st) {
+hipError_t rb_zero_untargeted(const int32_t* hoff, const int32_t* toff, int n_requests, int64_t n_hist, float* dst,
+                              int cols, hipStream_t st) {
   if (n_requests == 0) return hipSuccess;
-  hipLaunchKernelGGL(rb_zero_rows_kernel, dim3(n_requests), dim3(256), 0, st, hoff, toff, n_requests, dst, cols);
+  hipLaunchKernelGGL(rb_zero_rows_kernel, dim3(n_requests), dim3(256), 0, st, hoff, toff, n_requests, n_hist, dst,
+                     cols);
   return hipGetLastError();
 }
 

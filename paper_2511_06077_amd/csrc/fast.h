@@ -136,6 +136,7 @@ constexpr int kRbPairs = 128;
 // layer's U rows then H rows.
 struct RbPrep {
   const int32_t* tgt_off;
+  int64_t n_tgt;
   int n_requests, groups, layer, n_layers;
   const float *Q, *da, *a, *lse;  // Q scaled by log2(e)/sqrt(d_h); lse natural, [n_tgt][H]
   const bf16_bits *Wk, *Wv;       // this layer's [D][D]
@@ -158,6 +159,7 @@ struct RbAttn {
   const void* X;
   int64_t n_hist, n_tgt;
   int groups, layer, n_layers;
+  int64_t max_units;  // entries of units, order, Zp and Yp
   const int32_t* tgt_off;
   const int32_t* order;  // rank of each unit in request, group, chunk order
   const _Float16* U16;
@@ -170,13 +172,13 @@ struct RbAttn {
   float *Zp, *Yp;
   int32_t* first;
 };
-hipError_t rb_attn(int D, const RbAttn& a, int grid, hipStream_t st);
+hipError_t rb_attn(int D, const RbAttn& a, hipStream_t st);
 // Z, Y of the requests of several chunks: the sum of their units' partials.
 hipError_t rb_reduce(int D, const int32_t* tgt_off, int n_requests, int groups, const int32_t* tchunks, const int32_t* first,
-                     const float* Zp, const float* Yp, bf16_bits* Z, bf16_bits* Y, int64_t n_tgt, hipStream_t st);
+                     int64_t max_units, const float* Zp, const float* Yp, bf16_bits* Z, bf16_bits* Y, int64_t n_tgt, hipStream_t st);
 // Zero the rows [hoff[r], hoff[r + 1]) x cols (fp32) of every request without targets.
-hipError_t rb_zero_untargeted(const int32_t* hoff, const int32_t* toff, int n_requests, float* dst, int cols,
-                              hipStream_t st);
+hipError_t rb_zero_untargeted(const int32_t* hoff, const int32_t* toff, int n_requests, int64_t n_hist, float* dst,
+                              int cols, hipStream_t st);
 // Target-side recomputation for the backward (bwd_update.hip), fp32-accurate
 // on the bf16 matrix cores.  mode 0: s^(0) = x_t (s_out), q^(0) (q_out).
 // mode 1 (layer): merge the partials into a (a_out) and lse (lse_out), u =
