@@ -234,7 +234,8 @@ struct Layout {
   // target update: its cut, the splits' parts of the state and their arrival counters
   UpdatePlan upd;
   int bsplits;  // the same of the backward's target side (update_bwd_splits)
-  int max_ch;  // the most chunk records of a target (forward, bf16 path)
+  int max_ch;   // the most chunk records of a target (forward, bf16 path)
+  int records;  // chunk records with room per target (the device schedule's limit: its offsets may be other ones)
   size_t spart, ucnt;
   // reordered: U, the y partials with their (max, sum) and chunk counts, its
   // schedule (its own header and units when both forms run), fp16 W_V
@@ -392,9 +393,9 @@ stca_status_t make_layout_for(const stca_dims_t* dims, const stca_batch_t* b, in
       const int64_t nb = ceil_div(b->hist_off_host[r + 1], kBlockTokens) - b->hist_off_host[r] / kBlockTokens;
       L->max_ch = std::max(L->max_ch, static_cast<int>(std::min<int64_t>(L->max_chunks, ceil_div(nb, L->chunk_blocks))));
     }
-    const size_t records = std::max(kMaxChunks, L->max_ch);
-    L->part_acc = m.take(4 * records * nt * d);
-    L->part_ml = m.take(8 * records * nt * L->h);
+    L->records = std::max(kMaxChunks, L->max_ch);
+    L->part_acc = m.take(4 * static_cast<size_t>(L->records) * nt * d);
+    L->part_ml = m.take(8 * static_cast<size_t>(L->records) * nt * L->h);
     if (p == 1) {
       L->qn = m.take(2 * nt * d);
       L->wkp = m.take(2 * n * d * d);
@@ -619,7 +620,7 @@ stca_status_t forward_fast(const Layout& L, const stca_batch_t* b, const void* h
     int ns = 0;
     if (std_part)
       sp[ns++] = {b->hist_off, b->tgt_off, b->n_requests, L.nh, L.nt, L.chunk_blocks, L.group, units, L.max_units,
-                  tch, hdr, L.std_lo, 1 << 30, device_cus(), nullptr, L.max_chunks};
+                  tch, hdr, L.std_lo, 1 << 30, device_cus(), nullptr, L.records};
     if (reo_part)
       sp[ns++] = {b->hist_off, b->tgt_off, b->n_requests, L.nh, L.nt, L.chunk_blocks2, L.group2, units2,
                   L.max_units2, tch_r, hdr2, L.reord_lo, L.reord_hi, device_cus()};

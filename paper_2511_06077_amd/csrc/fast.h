@@ -27,7 +27,7 @@ struct FastUpdate {
   void* out;
   void* QN;
   const void *WoP, *W1P, *W2P, *WqP;
-  int max_ch;  // no target has more chunk records (1..kMaxChunks)
+  int max_ch;  // no target has more chunk records (1..kMaxChunksFew for plan.tg < 32, else 1..kMaxChunks)
   UpdatePlan plan;
   float* spart;  // [splits][ceil(n_tgt / tg)][32 D]: the splits' parts of the state, and
   int32_t* cnt;  // [n_layers][ceil(n_tgt / tg)]: their arrival counters (null without splits)

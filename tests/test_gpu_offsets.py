@@ -54,3 +54,28 @@ def test_reordered_backward_stays_inside_its_buffers(torch, d, h, L, m, dev_L, d
     assert got == (stca.STCA_OK if status == "ok" else stca.STCA_ERR_INVALID_ARG)
     bad = [k for k, v in {"ws": ws, **g}.items() if not v.intact()]
     assert not bad, bad
+
+
+# a forward of few targets makes room for as many chunk records as the host's
+# lengths have chunks (47 of 3 blocks each here); the device copy shows one
+# request twice as long, whose history then goes out in longer chunks
+def test_few_target_forward_stays_inside_its_buffers(torch):
+    from oracle import stca_oracle as O
+    from paper_2511_06077_amd import stca
+    from paper_2511_06077_amd.device import DeviceBatch
+    kw = dict(d_model=256, n_heads=8, n_layers=2, dtype="bf16", seed=43)
+    b = W.make_custom_batch("foff", [4512, 4480], [40, 40], **kw)
+    dev = W.make_custom_batch("foff", [8960, 32], [40, 40], **kw)  # the device's offsets
+    db = DeviceBatch(b)
+    full = DeviceBatch(dev)
+    db.hist.copy_(full.hist)
+    db.tgt.copy_(full.tgt)
+    db.hoff.copy_(full.hoff)
+    ws, out = Guarded(torch, db.ws_bytes), Guarded(torch, 2 * b.n_tgt_total * 256)
+    stca.stca_forward(db.dims, db.batch, db.hist, db.tgt, full.weights, out.ptr, None, ws.ptr, db.ws_bytes,
+                      db.stream())
+    assert stca.stca_device_status(ws.ptr, db.stream()) == stca.STCA_OK
+    assert ws.intact() and out.intact()
+    y = out.view(torch, torch.bfloat16, (b.n_tgt_total, 256)).float().cpu().numpy()
+    ref = O.forward(dev.f64())["out"]
+    assert float((np.abs(y - ref).max(1) / np.abs(ref).max(1)).max()) <= 2e-2
