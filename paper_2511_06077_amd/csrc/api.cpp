@@ -518,7 +518,7 @@ stca_status_t make_layout_for(const stca_dims_t* dims, const stca_batch_t* b, in
       L->rb_e = m.take(2 * nh * L->rb_groups * n * 2 * hm);
       L->rb_w = m.take(2 * slots * n * 2 * hm * d);
       L->rb_u16 = m.take(2 * slots * hm * d);
-      L->rb_st = m.take(8 * slots * hm);
+      L->rb_st = m.take(16 * slots * hm);
       L->rb_z = m.take(2 * L->h * nt * d);
       L->rb_y = m.take(2 * L->h * nt * d);
       L->rb_q16 = m.take(2 * nt * d);
@@ -1159,6 +1159,8 @@ stca_status_t backward_generic(const Layout& L, int bf, const stca_batch_t* b, c
       ra.layer = i;
       ra.n_layers = n;
       ra.U16 = pp.U16;
+      ra.Q = pp.Q;
+      ra.WkP = at<char>(ws, L.fwkp);
       ra.Wr = pp.Wr;
       ra.stats = pp.stats;
       ra.E = at<bf16_bits>(ws, L.rb_e);

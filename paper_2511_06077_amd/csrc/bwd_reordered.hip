@@ -23,13 +23,20 @@
 //   rb_attn_kernel:  per unit (a history chunk of a request), history
 //                    blocks of 32 rows streamed into an LDS ring by direct
 //                    loads; eight waves, two per tile of 32 pairs: one forms
-//                    S = X U^T (fp16) and P, and Y += P^T X; the other
+//                    S = X U^T (fp16; in fp16's range, see below) and P,
+//                    and Y += P^T X; the other
 //                    dP = X H^T (bf16) and, one block later, dE, the
 //                    [ln(2) dE | P] words of this layer's columns of E and
 //                    Z += dE^T X.  Z and Y (bf16, [head][target][D]) are
 //                    written at the end of the request.
 // The products that follow (dq, dW_K, dW_V from Z and Y; dX = E W_r after
 // the last layer) are GEMMs.
+//
+// The inputs may use the whole bf16 range, K, V and q are what has to fit
+// fp16.  A block with an |x| past 65504 (its S is not finite) and every block of
+// a head with a |u| past kUMax (x could be below fp16's subnormals there, or
+// u not finite) are scored as S = (X W_K^j) q^T instead, in two bf16 terms of K
+// and q with no copy of x in fp16.  Checking costs 16 additions a block.
 #include <type_traits>
 
 #include "common.h"
@@ -43,6 +50,9 @@ namespace {
 constexpr int DH = 32;
 constexpr int HM = kRbPairs;  // (target, head) pairs per request, padded
 constexpr int kRbStages = 5;  // X blocks in the LDS ring
+// |u| up to this (log2 units): half of fp16's smallest step in each x, 2^-25,
+// moves a score by at most 2^-25 kUMax sqrt(D) = 2^-8
+constexpr float kUMax = 8192.f;
 
 __device__ __forceinline__ f32x16 mma(const bf16x8& a, const bf16x8& b, const f32x16& c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
@@ -154,11 +164,7 @@ __global__ __launch_bounds__(64 * (D / 32)) void rb_prep_kernel(RbPrep A) {
       }
     }
     dsum += __shfl_xor(dsum, 32);  // the two lane halves hold 16 dims each
-    if (t < M && hi == 0) {
-      float* st = A.stats + (slot * HM + h * M + t) * 2;
-      st[0] = tok ? A.lse[(t0 + t) * H + h] * kLog2e : INFINITY;
-      st[1] = tok ? dsum : 0.f;
-    }
+    float umax = 0.f;
 #pragma unroll
     for (int dt = 0; dt < D / 32; ++dt) {
       const int dim = 32 * dt + l32;
@@ -178,12 +184,17 @@ __global__ __launch_bounds__(64 * (D / 32)) void rb_prep_kernel(RbPrep A) {
         const int tt = 32 * rt + 8 * (v / 4) + 4 * hi + v % 4;
         if (tt < M) {
           const int64_t o = (int64_t)(h * M + tt) * D + dim;
+          umax = fmaxf(umax, fabsf(u[v]));
           U16[o] = static_cast<_Float16>(u[v]);
           Wu[o] = from_f32<bf16_bits>(u[v]);
           Wh[o] = from_f32<bf16_bits>(hv[v]);
         }
       }
     }
+    const bool big = __builtin_amdgcn_ballot_w64(umax > kUMax) != 0;
+    if (t < M && hi == 0)
+      *reinterpret_cast<float4*>(A.stats + (slot * HM + h * M + t) * 4) =
+          make_float4(tok ? A.lse[(t0 + t) * H + h] * kLog2e : INFINITY, tok ? dsum : 0.f, big ? 1.f : 0.f, 0.f);
   }
 }
 
@@ -249,8 +260,9 @@ __global__ __launch_bounds__(512) void rb_attn_kernel(RbAttn A) {
   const int64_t rank = A.order[blockIdx.x];
   if (g >= A.groups || rank >= A.max_units) return;
   const int64_t slot = (int64_t)r * A.groups + g;
-  float lse2 = A.stats[(slot * HM + jp) * 2];
-  float dsum = A.stats[(slot * HM + jp) * 2 + 1];
+  const float4 stat = *reinterpret_cast<const float4*>(A.stats + (slot * HM + jp) * 4);
+  float lse2 = stat.x, dsum = stat.y;
+  const bool big_u = __builtin_amdgcn_ballot_w64(stat.z != 0.f) != 0;
   f32x16 acc[DT];  // role 0: Y, role 1: Z
 #pragma unroll
   for (int i = 0; i < DT; ++i) acc[i] = f32x16{};
@@ -346,20 +358,21 @@ __global__ __launch_bounds__(512) void rb_attn_kernel(RbAttn A) {
     // B operands of this role's score product: U (fp16) or H (bf16) rows
     typedef typename std::conditional<ROLE == 0, f16x8, bf16x8>::type OpT;
     OpT bop[KS];
-    {
+    auto load_op = [&]() {
       const OpT* src = ROLE == 0
                            ? reinterpret_cast<const OpT*>(A.U16 + (slot * HM + jp) * D)
                            : reinterpret_cast<const OpT*>(
                                  A.Wr + (((slot * A.n_layers + A.layer) * 2 + 1) * HM + jp) * D);
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) bop[ks] = src[2 * ks + hi];
-    }
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+v"(bop[ks]));
+    };
     // These loads land before the ring's first load is issued: the compiler
     // does not see the ring's loads, and would otherwise wait for these inside
     // the loop with counts that, in issue order, also drain the ring's
     // prefetches and the E stores at every block.
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+v"(bop[ks]));
+    load_op();
     asm volatile("" : "+v"(lse2), "+v"(dsum));
     // this role's score product of a block: sc = X(block) op^T
     auto score = [&](const unsigned char* tile, f32x16& sc) {
@@ -374,6 +387,44 @@ __global__ __launch_bounds__(512) void rb_attn_kernel(RbAttn A) {
         if (ks + NA < KS) xa[ks % NA] = *reinterpret_cast<const OpT*>(tile + (sb ^ (32 * (ks + NA))));
         sc = mma(x, bop[ks], sc);
         __builtin_amdgcn_sched_barrier(0);
+      }
+    };
+    // role 0: the scores of a block without X or U in fp16, S = (X W_K^j) q^T
+    // for each head j of the tile's pairs, from the block in the ring
+    auto score_wide = [&](const unsigned char* tile, f32x16& sc) {
+      const int sb = score_base();
+      const bf16x8* __restrict__ WkP = static_cast<const bf16x8*>(A.WkP);
+      sc = f32x16{};
+#pragma unroll 1
+      for (int j = 32 * tile_id / M; j <= (32 * tile_id + 31) / M; ++j) {
+        // K^T: A operand the packed W_K^j (row = head dim), result lane = row
+        // of X, element v = head dim 8 (v / 4) + 4 hi + v % 4
+        f32x16 kt = {};
+#pragma unroll 2
+        for (int ks = 0; ks < KS; ++ks)
+          kt = mma(WkP[((int64_t)(A.layer * (D / DH) + j) * KS + ks) * 64 + lane],
+                   *reinterpret_cast<const bf16x8*>(tile + (sb ^ (32 * ks))), kt);
+        const int tt = jp - j * M;  // this lane's target of head j
+        const bool mine = tt >= 0 && tt < M && tt < m;
+        const float* q = A.Q + (t0 + (mine ? tt : 0)) * D + j * DH + 4 * hi;
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+          const float4 qa = *reinterpret_cast<const float4*>(q + 16 * s);
+          const float4 qb = *reinterpret_cast<const float4*>(q + 16 * s + 8);
+          const float qv[8] = {qa.x, qa.y, qa.z, qa.w, qb.x, qb.y, qb.z, qb.w};
+          bf16x8 kh, kl, qh, ql;
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            __bf16 a, b;
+            split_bf(kt[8 * s + e], a, b);
+            kh[e] = a, kl[e] = b;
+            split_bf(mine ? qv[e] : 0.f, a, b);
+            qh[e] = a, ql[e] = b;
+          }
+          sc = mma(kh, qh, sc);
+          sc = mma(kl, qh, sc);
+          sc = mma(kh, ql, sc);
+        }
       }
     };
     // role 1: dE, E's dE columns and Z for block k (its dP in this wave's
@@ -415,6 +466,13 @@ __global__ __launch_bounds__(512) void rb_attn_kernel(RbAttn A) {
       if (ROLE == 0) {
         const unsigned char* tile16 = t16 + (k % 2) * TB;
         score(tile16, sc);
+        float sum = 0.f;  // finite where all are
+#pragma unroll
+        for (int v = 0; v < 16; ++v) sum += sc[v];
+        if (big_u || __builtin_amdgcn_ballot_w64(!(fabsf(sum) < INFINITY)) != 0) {
+          score_wide(tile, sc);
+          load_op();  // (its registers are free above)
+        }
         const int64_t brow = (int64_t)(b0 + k) * 32;
         if (brow >= un.l0 && brow + 32 <= un.l1) {
 #pragma unroll

@@ -131,7 +131,8 @@ hipError_t fast_attn_fwd_precise(int D, const FastAttnFwdPrecise& f, int grid, h
 constexpr int kRbPairs = 128;
 // Per layer and slot: U = q W_K^j^T per pair (U16: fp16 [slots][kRbPairs][D];
 // also bf16 in the request's dX operand), H = da W_V^j^T (bf16), the
-// statistics (log2-unit lse, D = da . a per pair; [slots][kRbPairs][2]) and bf16
+// statistics per pair ([slots][kRbPairs][4]: log2-unit lse, D = da . a, 1 where a
+// |u| of the head leaves fp16's useful range, unused) and bf16
 // copies of q and da ([n_tgt][D]).  Wr: [slots][n_layers][2][kRbPairs][D], this
 // layer's U rows then H rows.
 struct RbPrep {
@@ -163,6 +164,8 @@ struct RbAttn {
   const int32_t* tgt_off;
   const int32_t* order;  // rank of each unit in request, group, chunk order
   const _Float16* U16;
+  const float* Q;    // as in RbPrep
+  const void* WkP;   // W_K packed in bf16, all layers (fast_pack_many)
   const bf16_bits* Wr;
   const float* stats;
   bf16_bits* E;
