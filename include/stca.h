@@ -99,9 +99,9 @@ typedef enum { STCA_F32 = 0, STCA_BF16 = 1 } stca_dtype_t;
  *          requests of up to 256 / n_heads targets (d_h = 32, host offsets
  *          given); STCA_ERR_UNSUPPORTED for other batches.
  * bwd_form STCA_BWD_AUTO: with d_h = 32, d_model in {64, 128, 256},
- *          ffn_hidden a multiple of d_model and host offsets, the backward on
- *          bf16 storage recomputes the forward with the history projected
- *          inside the attention kernel.  For at most 32 targets per request it
+ *          ffn_hidden a multiple of d_model and host offsets showing at most
+ *          32 targets per request, the backward on bf16 storage recomputes the
+ *          forward with the history projected inside the attention kernel and
  *          then runs in the reordered form (the attention gradients through
  *          u = q W_K^T and h = da W_V^T per target and head, no K, V, dK or
  *          dV, in groups of 128 / n_heads targets; Sec. 3.1's reordering
@@ -109,10 +109,9 @@ typedef enum { STCA_F32 = 0, STCA_BF16 = 1 } stca_dtype_t;
  *          (K/V formed inside the attention kernels, dK | dV written for the
  *          history-side products): reordered for histories balanced over the
  *          compute units with at most 128 / n_heads targets, else where an
- *          estimate of the two forms' kernels favours it.  For more targets
- *          the attention gradients are formed in fp32 over one layer's K | V
- *          at a time.  Otherwise every layer's K | V are formed by a GEMM and
- *          the attention runs in exact fp32 both ways (generic).
+ *          estimate of the two forms' kernels favours it.  Otherwise every
+ *          layer's K | V are formed by a GEMM and the attention runs in exact
+ *          fp32 both ways (generic).
  *          STCA_BWD_GENERIC: always the generic form.  STCA_BWD_FUSED: the
  *          fused form.  STCA_BWD_REORDERED: the reordered form with one
  *          target group per request (at most 128 / n_heads targets).  Each is

@@ -140,15 +140,15 @@ int rb_chunk_for(const stca_dims_t* dims, const stca_batch_t* b, int n_cu, int64
   return static_cast<int>(best);
 }
 
-// The bf16 backward recomputes the forward with the history projected inside
-// the attention kernel and the target side in one kernel per layer when
-// d_h = 32, the FFN width is a multiple of d and the host offsets are given;
-// its history side is then, for at most 32 targets per request, the fused
-// form (no K/V copy in HBM) or with d_model of 128 or 256 the reordered one (no
-// K, V, dK, dV; groups of rb_group targets), and for more targets the exact
-// fp32 attention over one layer's K | V at a time.  Otherwise every layer's K
-// | V are formed by a GEMM, the attention runs exactly in fp32 both ways and
-// the target side as separate GEMMs.  STCA_BWD_GENERIC forces that generic
+// The bf16 backward runs the target side in one kernel per layer, both ways,
+// when d_h = 32, the FFN width is a multiple of d and the host offsets are
+// given.  For at most 32 targets per request it recomputes the forward with the
+// history projected inside the attention kernel, and its history side is the
+// fused form (no K/V copy in HBM) or with d_model of 128 or 256 the reordered
+// one (no K, V, dK, dV; groups of rb_group targets).  For more targets every
+// layer's K | V are formed by a GEMM and the attention runs exactly in fp32
+// both ways, as in the generic form, which otherwise also takes the target side
+// as separate GEMMs.  STCA_BWD_GENERIC forces that generic
 // form; STCA_BWD_FUSED asks for the fused one, STCA_BWD_REORDERED for the
 // reordered one with one target group per request, and both are unsupported
 // for other batches.  3 (fp32 attention) / 2 (reordered) / 1 (fused) / 0
@@ -223,9 +223,10 @@ struct Layout {
   int64_t max_units2;
   bool mat;                   // K/V written to the workspace by one GEMM (bf16 path)
   bool wide;                  // materialised K/V, units of up to kWideGroup targets (bf16 path)
-  bool bfused;                // backward with the history projection inside the attention kernels
+  bool bfused;                // backward with the target side in one kernel per layer and, unless b32,
+                              // the history projection inside the attention kernels
   bool brd;                   // ... in the reordered form (no K, V, dK, dV)
-  bool b32;                   // ... in the recomputation only, the attention backward exact in fp32
+  bool b32;                   // ... over K | V in memory, the attention exact in fp32 both ways
   int group;                  // targets per attention unit
   // common
   size_t hdr, units, tchunks, part_acc, part_ml, state_a, state_b;
@@ -429,8 +430,8 @@ stca_status_t make_layout_for(const stca_dims_t* dims, const stca_batch_t* b, in
     }
   } else {
     const bool bf = dims->dtype == STCA_BF16;
-    // every layer's K | V rows, fp32 (with b32 one layer's at a time)
-    L->kvs = L->bfused && !L->b32 ? 0 : m.take(4 * (L->b32 ? 1 : n) * nh * 2 * d);
+    // every layer's K | V rows, fp32
+    L->kvs = L->bfused && !L->b32 ? 0 : m.take(4 * n * nh * 2 * d);
     L->bsplits = L->bfused ? update_bwd_splits(L->nt, L->d, L->F, device_cus()) : 1;
     if (L->bsplits > 1) {
       // (counters of a recomputation and a reverse launch per layer)
@@ -897,17 +898,17 @@ stca_status_t backward_generic(const Layout& L, int bf, const stca_batch_t* b, c
     if (!rec_out && !L.bfused) HIPCHK(transpose_bf16(X, d, static_cast<int>(nh), d, xt, nh8, nh8, st));
     if (L.bfused) {
       PackJobs pj{};
-      pj.job[0] = {w->wk, at<char>(ws, L.fwkp), d, d, 0};
-      pj.job[1] = {w->wv, at<char>(ws, L.fwvp), d, d, 0};
-      pj.job[2] = {w->wo, at<char>(ws, L.fwop), d, d, 0};
-      pj.job[3] = {w->wq, at<char>(ws, L.fwqp), d, d, 0};
-      pj.job[4] = {w->w1, at<char>(ws, L.fw1p), d, F, 0};
-      pj.job[5] = {w->w2, at<char>(ws, L.fw2p), F, d, 0};
-      pj.job[6] = {w->w2, at<char>(ws, L.fw2t), d, F, 0, 1};
-      pj.job[7] = {w->w1, at<char>(ws, L.fw1t), F, d, 0, 1};
-      pj.job[8] = {w->wo, at<char>(ws, L.fwot), d, d, 0, 1};
-      pj.job[9] = {w->wq, at<char>(ws, L.fwqt), d, d, 0, 1};
-      HIPCHK(launch_setup(sp, ns, pj, 10, n, st, counters(0), 2 * n * ugroups));
+      pj.job[0] = {w->wo, at<char>(ws, L.fwop), d, d, 0};
+      pj.job[1] = {w->wq, at<char>(ws, L.fwqp), d, d, 0};
+      pj.job[2] = {w->w1, at<char>(ws, L.fw1p), d, F, 0};
+      pj.job[3] = {w->w2, at<char>(ws, L.fw2p), F, d, 0};
+      pj.job[4] = {w->w2, at<char>(ws, L.fw2t), d, F, 0, 1};
+      pj.job[5] = {w->w1, at<char>(ws, L.fw1t), F, d, 0, 1};
+      pj.job[6] = {w->wo, at<char>(ws, L.fwot), d, d, 0, 1};
+      pj.job[7] = {w->wq, at<char>(ws, L.fwqt), d, d, 0, 1};
+      pj.job[8] = {w->wk, at<char>(ws, L.fwkp), d, d, 0};  // (not read with b32)
+      pj.job[9] = {w->wv, at<char>(ws, L.fwvp), d, d, 0};
+      HIPCHK(launch_setup(sp, ns, pj, L.b32 ? 8 : 10, n, st, counters(0), 2 * n * ugroups));
     }
   }
   // persistent grid of the fused kernels: one workgroup per CU
@@ -938,19 +939,27 @@ stca_status_t backward_generic(const Layout& L, int bf, const stca_batch_t* b, c
     HIPCHK(convert(bf, 0, tgt, RS(0), nt * d, st));
   }
   for (int i = 0; i < n && L.bfused && !rec_in; ++i) {
-    FastAttnFwdPrecise f{};
-    f.units = units;
-    f.hdr = hdr;
-    f.X = hist;
-    f.n_hist = nh;
-    f.WkP = at<char>(ws, L.fwkp);
-    f.WvP = at<char>(ws, L.fwvp);
-    f.layer = i;
-    f.Q = RQ(i);
-    f.part_acc = at<float>(ws, L.part_acc);
-    f.part_ml = at<char>(ws, L.part_ml);
-    f.n_tgt = nt;
-    HIPCHK(fast_attn_fwd_precise(d, f, fgrid, st));
+    if (L.b32) {
+      HIPCHK(gemm_mfma(static_cast<int>(nh), 2 * d, d, static_cast<const bf16_bits*>(hist), d, 0,
+                       wkv_all + (size_t)i * 2 * d, n * 2 * d, 0, KVS(i), 2 * d, 1.f, 0, nullptr, 0, st));
+      HIPCHK(rec.mark("kv_gemm"));
+      HIPCHK(attn_generic(L.dh, h, units, L.max_units, hdr, RQ(i), KVS(i), d, at<float>(ws, L.part_acc),
+                          at<float>(ws, L.part_ml), nt, st));
+    } else {
+      FastAttnFwdPrecise f{};
+      f.units = units;
+      f.hdr = hdr;
+      f.X = hist;
+      f.n_hist = nh;
+      f.WkP = at<char>(ws, L.fwkp);
+      f.WvP = at<char>(ws, L.fwvp);
+      f.layer = i;
+      f.Q = RQ(i);
+      f.part_acc = at<float>(ws, L.part_acc);
+      f.part_ml = at<char>(ws, L.part_ml);
+      f.n_tgt = nt;
+      HIPCHK(fast_attn_fwd_precise(d, f, fgrid, st));
+    }
     HIPCHK(rec.mark("attn_fwd"));
     up.mode = 1;
     up.layer = i;
@@ -1025,7 +1034,7 @@ stca_status_t backward_generic(const Layout& L, int bf, const stca_batch_t* b, c
     const float* s = RS(i);
     const float* u = RU(i);
     const float* a = RA(i);
-    const float* kv = L.b32 ? KVS(0) : L.bfused ? nullptr : KVS(i);
+    const float* kv = L.bfused && !L.b32 ? nullptr : KVS(i);
     const void* W1 = W(w->w1, i, (size_t)d * F);
     const void* W2 = W(w->w2, i, (size_t)d * F);
     const void* Wo = W(w->wo, i, (size_t)d * d);
@@ -1192,9 +1201,6 @@ stca_status_t backward_generic(const Layout& L, int bf, const stca_batch_t* b, c
       HIPCHK(convert(0, 1, dq, at<bf16_bits>(ws, L.b_dq), nt * d, st));
       HIPCHK(rec.mark("kv_grads"));
     } else if (L.b32) {
-      HIPCHK(gemm_mfma(static_cast<int>(nh), 2 * d, d, static_cast<const bf16_bits*>(hist), d, 0,
-                       wkv_all + (size_t)i * 2 * d, n * 2 * d, 0, KVS(0), 2 * d, 1.f, 0, nullptr, 0, st));
-      HIPCHK(rec.mark("kv_gemm"));
       HIPCHK(attn_bwd_generic(L.dh, h, units, L.max_units, hdr, b->tgt_off, RQ(i), kv, d, a, da, RL(i), dqp, dkv_i,
                               n * 2 * d, 1, nullptr, 0, nt, st));
     } else if (L.bfused) {
@@ -1428,7 +1434,7 @@ int stca_backward_launch_count(const stca_dims_t* dims, const stca_batch_t* batc
   // target side), dX, out
   if (L.brd) return 6 + 6 * L.n;
   if (L.bfused && !L.b32) return 7 + 5 * L.n;
-  // (fp32 attention: 2 per layer of the recomputation and 5 of the reverse)
+  // (fp32 attention: 3 per layer of the recomputation and 4 of the reverse)
   return dims->dtype == STCA_BF16 ? 6 + 7 * L.n : 4 + 9 * L.n;
 }
 

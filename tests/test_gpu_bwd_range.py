@@ -73,3 +73,22 @@ def test_history_range_target_groups(torch):
     db = DeviceBatch(s, backward=True)
     assert stca.stca_backward_launch_count(db.dims, db.batch) == 6 + 6 * b.wl.n_layers
     check(b, {k: v * back.get(k, 1.0) for k, v in gpu_grads(torch, s).items()}, TOL["bf16"])
+
+
+# With W_K, W_V times a power of two and W_Q, W_O divided by it, K is about 1e6
+# (past fp16) and V about 6e-8 (fp16's smallest step): with more than 32 targets a
+# request the attention is fp32 both ways and every gradient is as without
+@pytest.mark.parametrize("d,h", [(256, 8), (128, 4), (64, 2)])
+def test_projection_range_many_targets(torch, d, h):
+    from oracle import stca_oracle as O
+    for seed in range(107, 147):
+        b = W.make_custom_batch("gproj", [1, 33, 130, 64, 7, 500, 45], [33, 64, 0, 65, 129, 17, 16], d_model=d,
+                                n_heads=h, n_layers=2, dtype="bf16", seed=seed, with_grad=True)
+        if np.abs(O.forward(b.f64())["pre"]).min() > 2e-6:  # (as above)
+            break
+    else:
+        pytest.fail("every seed has a gate near zero")
+    f = {"wk": 2.0 ** 20, "wq": 2.0 ** -20, "wv": 2.0 ** -24, "wo": 2.0 ** 24}
+    w = {k: W.to_bf16_bits(W.bf16_bits_to_f32(v) * np.float32(f.get(k, 1.0))) for k, v in b.weights.items()}
+    g = gpu_grads(torch, dataclasses.replace(b, weights=w))
+    check(b, {k: v * f.get(k[1:], 1.0) for k, v in g.items()}, TOL["bf16"])
