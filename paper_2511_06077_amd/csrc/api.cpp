@@ -427,6 +427,16 @@ stca_status_t make_layout_for(const stca_dims_t* dims, const stca_batch_t* b, in
       L->abuf = m.take(4 * nt * d);
       L->ubuf = m.take(4 * nt * d);
       L->hid = m.take(4 * nt * F);
+      // parts of the split products (K, V and the queries of fp32 storage, from
+      // d = 1024 on), unless only they would take the batch past the library's
+      // own scratch array
+      const int di = static_cast<int>(d);
+      L->gpart_floats = dims->dtype == STCA_BF16 ? 0
+                                                 : 2 * gemm_f32_part_floats(static_cast<int>(nh), di, di) +
+                                                       gemm_f32_part_floats(static_cast<int>(nt), di, di);
+      if (m.off <= STCA_NOALLOC_SCRATCH_BYTES && m.off + 4 * L->gpart_floats > STCA_NOALLOC_SCRATCH_BYTES)
+        L->gpart_floats = 0;
+      L->gpart = m.take(4 * L->gpart_floats);
     }
   } else {
     const bool bf = dims->dtype == STCA_BF16;
@@ -468,9 +478,8 @@ stca_status_t make_layout_for(const stca_dims_t* dims, const stca_batch_t* b, in
     L->dwkv = bf && !L->brd ? m.take(4 * d * n * 2 * d) : 0;   // [d][n 2d] fp32
     // split-K partials: the largest of [dW_K | dW_V] (K = history rows) and
     // the target-side weight gradients (K = targets)
-    L->gpart_floats = 0;
+    const int di = static_cast<int>(d), Fi = static_cast<int>(F), nti = static_cast<int>(nt), nhi = static_cast<int>(nh);
     if (bf) {
-      const int di = static_cast<int>(d), Fi = static_cast<int>(F), nti = static_cast<int>(nt);
       // (the fused form runs the target-side weight gradients of a layer,
       // with dW_Q of the layer above, as one group whose splits share it)
       L->gpart_floats = std::max({L->brd ? 2 * L->h * gemm_mfma_part_floats(di, 32, nti)
@@ -478,8 +487,16 @@ stca_status_t make_layout_for(const stca_dims_t* dims, const stca_batch_t* b, in
                                                                  static_cast<int>(nh8), device_cus()),
                                   gemm_mfma_part_floats(Fi, di, nti) + gemm_mfma_part_floats(di, Fi, nti) +
                                       2 * gemm_mfma_part_floats(di, di, nti)});
+    } else {
+      // (of the groups of fp32 products: K, V and the queries; each weight
+      // gradient beside the product that carries on; the last of a layer)
+      L->gpart_floats =
+          std::max({2 * gemm_f32_part_floats(nhi, di, di) + gemm_f32_part_floats(nti, di, di),
+                    gemm_f32_part_floats(Fi, di, nti), gemm_f32_part_floats(di, Fi, nti),
+                    gemm_f32_part_floats(nti, di, di) + gemm_f32_part_floats(di, di, nti),
+                    2 * gemm_f32_part_floats(di, di, nhi) + gemm_f32_part_floats(di, di, nti)});
     }
-    L->gpart = bf ? m.take(4 * L->gpart_floats) : 0;
+    L->gpart = m.take(4 * L->gpart_floats);
     if (L->bfused) {
       L->rec = m.take(record_layout(*L).total);
     } else {
@@ -772,7 +789,7 @@ stca_status_t forward_generic(const Layout& L, int bf, const stca_batch_t* b, co
       const F32Gemm g[3] = {{nh, d, d, X, d, 0, wf(w->wk), d, 0, kv, 2 * d, 1.f},
                             {nh, d, d, X, d, 0, wf(w->wv), d, 0, kv + d, 2 * d, 1.f},
                             {nt, d, d, s, d, 0, wf(w->wq), d, 0, q, d, qscale}};
-      HIPCHK(gemm_f32_group(g, 3, st));
+      HIPCHK(gemm_f32_group(g, 3, at<float>(ws, L.gpart), L.gpart_floats, st));
       for (const char* m : {"gemm_k", "gemm_v", "gemm_q"}) HIPCHK(rec.mark(m));
     } else {
       HIPCHK(gemm_generic(bf, bf, L.nh, d, d, hist, d, 0, W(w->wk, i, (size_t)d * d), d, 0, kv, 2 * d, 1.f,
@@ -991,7 +1008,7 @@ stca_status_t backward_generic(const Layout& L, int bf, const stca_batch_t* b, c
       const F32Gemm g[3] = {{static_cast<int>(nh), d, d, X, d, 0, WF(w->wk, i), d, 0, kv, 2 * d, 1.f},
                             {static_cast<int>(nh), d, d, X, d, 0, WF(w->wv, i), d, 0, kv + d, 2 * d, 1.f},
                             {static_cast<int>(nt), d, d, RS(i), d, 0, WF(w->wq, i), d, 0, RQ(i), d, qscale}};
-      HIPCHK(gemm_f32_group(g, 3, st));
+      HIPCHK(gemm_f32_group(g, 3, at<float>(ws, L.gpart), L.gpart_floats, st));
     }
     HIPCHK(rec.mark("kv_gemm"));
     if (bf)
@@ -1117,14 +1134,14 @@ stca_status_t backward_generic(const Layout& L, int bf, const stca_batch_t* b, c
       const float *w1 = static_cast<const float*>(W1), *w2 = static_cast<const float*>(W2);
       const F32Gemm g2[2] = {{nti, F, d, ds, d, 0, w2, d, 1, dhid, F, 1.f, kEpiMask, hid, F},
                              {F, d, nti, hid, F, 1, ds, d, 0, dw->dw2 + (size_t)i * F * d, d, 1.f}};
-      HIPCHK(gemm_f32_group(g2, 2, st));
+      HIPCHK(gemm_f32_group(g2, 2, at<float>(ws, L.gpart), L.gpart_floats, st));
       const F32Gemm g1[2] = {{nti, d, F, dhid, F, 0, w1, F, 1, du, d, 1.f, kEpiAddRes, ds, d},
                              {d, F, nti, u, d, 1, dhid, F, 0, dw->dw1 + (size_t)i * d * F, F, 1.f}};
-      HIPCHK(gemm_f32_group(g1, 2, st));
+      HIPCHK(gemm_f32_group(g1, 2, at<float>(ws, L.gpart), L.gpart_floats, st));
       // u = s + a Wo
       const F32Gemm go[2] = {{nti, d, d, du, d, 0, WF(w->wo, i), d, 1, da, d, 1.f},
                              {d, d, nti, a, d, 1, du, d, 0, dw->dwo + (size_t)i * d * d, d, 1.f}};
-      HIPCHK(gemm_f32_group(go, 2, st));
+      HIPCHK(gemm_f32_group(go, 2, at<float>(ws, L.gpart), L.gpart_floats, st));
     }
     HIPCHK(rec.mark("target_gemm"));
     // attention (softmax weights rebuilt from the same q, K, V and lse that
@@ -1274,7 +1291,7 @@ stca_status_t backward_generic(const Layout& L, int bf, const stca_batch_t* b, c
           {d, d, nhi, X, d, 1, dKV + d, 2 * d, 0, dw->dwv + o, d, 1.f},
           {nti, d, d, dq, d, 0, WF(w->wq, i), d, 1, ds2, d, 1.f, kEpiAddRes, du, d},
           {d, d, nti, s, d, 1, dq, d, 0, dw->dwq + o, d, 1.f}};
-      HIPCHK(gemm_f32_group(g, 5, st));
+      HIPCHK(gemm_f32_group(g, 5, at<float>(ws, L.gpart), L.gpart_floats, st));
     }
     // (on the bf16 path every layer's dK | dV is kept and the history-side
     // gradients are formed once after the loop)

@@ -28,14 +28,15 @@ constexpr int GT = 64;  // output tile edge
 constexpr int GK = 32;  // k step
 
 // Tile (bx, by) and k range bz of `splits`.  A2, B2 (nullable): a second pair
-// of operands of the same forms, whose product is added.
+// of operands of the same forms, whose product is added.  part (nullable): the
+// k ranges' products are left there ([splits][M][N]) instead of added to C.
 template <typename TA, typename TB>
 __device__ __forceinline__ void gemm_body(int bx, int by, int bz, int splits, int M, int N, int K,
                                           const TA* __restrict__ A, int64_t lda, int transA,
                                           const TB* __restrict__ B, int64_t ldb, int transB, float* __restrict__ C,
                                           int64_t ldc, float alpha, int epi, const float* __restrict__ R, int64_t ldr,
                                           float* __restrict__ C2, int accumulate, int k_chunk, const TA* A2 = nullptr,
-                                          const TB* B2 = nullptr) {
+                                          const TB* B2 = nullptr, float* part = nullptr) {
   __shared__ float As[GK][GT + 1];
   __shared__ float Bs[GK][GT + 1];
   const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
@@ -44,7 +45,8 @@ __device__ __forceinline__ void gemm_body(int bx, int by, int bz, int splits, in
   const int m0 = by * GT, n0 = bx * GT;
   f32x16 acc = {};
   // split-K: workgroup z sums k in [z * k_chunk, (z + 1) * k_chunk) and adds
-  // its partial into C atomically (C was cleared or holds what to add to)
+  // its partial into C atomically (C was cleared or holds what to add to), or
+  // leaves it in `part`
   const int kb = bz * k_chunk;
   const int ke = min(K, kb + k_chunk);
   constexpr int PER = GT * GK / 256;
@@ -105,7 +107,8 @@ __device__ __forceinline__ void gemm_body(int bx, int by, int bz, int splits, in
     float x = alpha * acc[v];
     float* c = C + (int64_t)gm * ldc + gn;
     if (splits > 1) {
-      atomicAdd(c, x);
+      if (part) part[((int64_t)bz * M + gm) * N + gn] = x;
+      else atomicAdd(c, x);
       continue;
     }
     if (epi == kEpiAddRes) x += R[(int64_t)gm * ldr + gn];
@@ -139,6 +142,7 @@ struct F32Group {
   F32Gemm g[kMaxF32Group];
   int nx[kMaxF32Group], ny[kMaxF32Group], splits[kMaxF32Group], k_chunk[kMaxF32Group];
   int end[kMaxF32Group];  // first workgroup after the product's
+  float* part[kMaxF32Group];  // [splits][M][N] where splits > 1
   int n;
 };
 __global__ __launch_bounds__(256) void gemm_f32_group_kernel(F32Group G) {
@@ -149,15 +153,31 @@ __global__ __launch_bounds__(256) void gemm_f32_group_kernel(F32Group G) {
   const int per = G.nx[j] * G.ny[j], t = i % per;
   gemm_body<float, float>(t % G.nx[j], t / G.nx[j], i / per, G.splits[j], g.M, g.N, g.K, g.A, g.lda, g.transA, g.B,
                           g.ldb, g.transB, g.C, g.ldc, g.alpha, g.epi, g.R, g.ldr, nullptr, g.accumulate, G.k_chunk[j],
-                          g.A2, g.B2);
+                          g.A2, g.B2, G.part[j]);
 }
 
-// Clears the outputs that splits add into, one grid row each.
-__global__ void clear_group_kernel(F32Group G) {
-  const int j = blockIdx.y;
-  if (G.splits[j] == 1 || G.g[j].accumulate) return;
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < (int64_t)G.g[j].M * G.g[j].N) G.g[j].C[(i / G.g[j].N) * G.g[j].ldc + i % G.g[j].N] = 0.f;
+// The sum of the split products' parts in a fixed order, so that a gradient
+// repeats bitwise (atomics added them in order of arrival): kSumLanes elements
+// a workgroup, each over 256 / kSumLanes runs of parts, one thread a run, and
+// the runs in turn.  One grid row per product.
+constexpr int kSumLanes = 32, kSumRuns = 256 / kSumLanes;
+__global__ __launch_bounds__(256) void sum_group_kernel(F32Group G) {
+  __shared__ float run[kSumRuns][kSumLanes];
+  const int j = blockIdx.y, lane = threadIdx.x % kSumLanes, w = threadIdx.x / kSumLanes;
+  const F32Gemm& g = G.g[j];
+  const int64_t size = (int64_t)g.M * g.N, i = (int64_t)blockIdx.x * kSumLanes + lane;
+  if (G.splits[j] == 1 || (int64_t)blockIdx.x * kSumLanes >= size) return;
+  const int per = (G.splits[j] + kSumRuns - 1) / kSumRuns;
+  float s = 0.f;
+  if (i < size)
+#pragma unroll 8
+    for (int k = w * per; k < min((w + 1) * per, G.splits[j]); ++k) s += G.part[j][k * size + i];
+  run[w][lane] = s;
+  __syncthreads();
+  if (w > 0 || i >= size) return;
+  for (int k = 1; k < kSumRuns; ++k) s += run[k][lane];
+  float* c = g.C + (i / g.N) * g.ldc + i % g.N;
+  *c = g.accumulate ? *c + s : s;
 }
 
 // fp32-accurate products with bf16 weights on the bf16 matrix cores:
@@ -759,32 +779,49 @@ hipError_t gemm_generic(int a_bf16, int b_bf16, int M, int N, int K, const void*
 
 // Long reductions with few output tiles split K as in gemm_generic, into
 // chunks down to 128 deep (four k tiles).
-hipError_t gemm_f32_group(const F32Gemm* g, int n, hipStream_t st) {
+static int f32_splits(int M, int N, int K) {
+  const int64_t tiles = ceil_div(N, GT) * ceil_div(M, GT);
+  if (tiles >= 256 || K < 1024) return 1;
+  const int64_t s = std::max<int64_t>(1, std::min<int64_t>(ceil_div(512, tiles), K / 128));
+  return static_cast<int>(ceil_div(K, round_up(ceil_div(K, s), GK)));
+}
+
+int64_t gemm_f32_part_floats(int M, int N, int K) {
+  const int64_t s = f32_splits(M, N, K);
+  return s > 1 ? s * M * N : 0;
+}
+
+hipError_t gemm_f32_group(const F32Gemm* g, int n, float* part, int64_t part_floats, hipStream_t st) {
   if (n < 0 || n > kMaxF32Group) return hipErrorInvalidValue;
   F32Group G{};
-  int64_t blocks = 0, clear = 0;
+  int64_t blocks = 0, sums = 0;
   for (int j = 0; j < n; ++j) {
     if (g[j].M == 0 || g[j].N == 0) continue;
     const int k = G.n++;
     G.g[k] = g[j];
     const int64_t nx = ceil_div(g[j].N, GT), ny = ceil_div(g[j].M, GT), tiles = nx * ny;
-    int64_t splits = 1;
-    if (g[j].epi == kEpiStore && !g[j].A2 && tiles < 256 && g[j].K >= 1024)
-      splits = std::max<int64_t>(1, std::min<int64_t>(ceil_div(512, tiles), g[j].K / 128));
+    const int64_t size = (int64_t)g[j].M * g[j].N;
+    int64_t splits = g[j].epi == kEpiStore && !g[j].A2 ? f32_splits(g[j].M, g[j].N, g[j].K) : 1;
+    if (splits * size > part_floats) splits = 1;
+    if (splits > 1) {
+      G.part[k] = part;
+      part += splits * size;
+      part_floats -= splits * size;
+      sums = std::max(sums, size);
+    }
     G.k_chunk[k] = static_cast<int>(round_up(ceil_div(g[j].K, splits), GK));
-    if (G.k_chunk[k] > 0) splits = ceil_div(g[j].K, G.k_chunk[k]);
     G.nx[k] = static_cast<int>(nx);
     G.ny[k] = static_cast<int>(ny);
-    G.splits[k] = static_cast<int>(std::max<int64_t>(1, splits));
-    blocks += tiles * G.splits[k];
+    G.splits[k] = static_cast<int>(splits);
+    blocks += tiles * splits;
     if (blocks >= (int64_t)1 << 24) return hipErrorInvalidValue;  // (2^32 threads)
     G.end[k] = static_cast<int>(blocks);
-    if (G.splits[k] > 1 && !g[j].accumulate) clear = std::max<int64_t>(clear, (int64_t)g[j].M * g[j].N);
   }
   if (G.n == 0) return hipSuccess;
-  if (clear > 0)
-    hipLaunchKernelGGL(clear_group_kernel, dim3(static_cast<unsigned>(ceil_div(clear, 256)), G.n), dim3(256), 0, st, G);
   hipLaunchKernelGGL(gemm_f32_group_kernel, dim3(static_cast<unsigned>(blocks)), dim3(256), 0, st, G);
+  if (sums > 0)
+    hipLaunchKernelGGL(sum_group_kernel, dim3(static_cast<unsigned>(ceil_div(sums, kSumLanes)), G.n), dim3(256), 0, st,
+                       G);
   return hipGetLastError();
 }
 

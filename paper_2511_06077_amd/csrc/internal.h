@@ -67,7 +67,10 @@ struct F32Gemm {
   const float *A2, *B2;
 };
 constexpr int kMaxF32Group = 6;
-hipError_t gemm_f32_group(const F32Gemm* g, int n, hipStream_t st);
+// Long reductions are split over K where `part` has room for the parts of one
+// after the other (gemm_f32_part_floats each); their sum has a fixed order.
+hipError_t gemm_f32_group(const F32Gemm* g, int n, float* part, int64_t part_floats, hipStream_t st);
+int64_t gemm_f32_part_floats(int M, int N, int K);
 // MFMA GEMM, bf16 operands, fp32 accumulation and output:
 // C = alpha op(A) op(B) (+ C when accumulating), operand conventions as in
 // gemm_generic.  The contiguous extent of each operand (K for A untransposed

@@ -35,3 +35,24 @@ def test_f32_products(torch, d, h, L, m):
     # (sums of at most 4 d = 512 fp32 terms through two layers: 2^-24 sqrt(512) = 1.3e-6 a product)
     assert np.abs(y - ref).max() <= 2e-5 * np.abs(ref).max()
     check(b, gpu_grads(torch, b), TOL["f32"])
+
+
+# the same call gives the same bits: the parts of a split product are summed in
+# one order (rows 1024, 1100 and 2113 split the weight gradients over K, as
+# 1100 targets do, and d = 1024 the forward's products)
+@pytest.mark.parametrize("d,h,L,m", [(64, 2, [1024], [4]), (128, 4, [1100], [65]), (64, 1, [2048, 65], [129, 1]),
+                                     (64, 2, [40, 50], [600, 500]), (1024, 16, [70, 30], [3, 2])])
+def test_f32_repeats(torch, d, h, L, m):
+    from paper_2511_06077_amd.device import DeviceBatch, to_device
+    b = W.make_custom_batch("gf32r", L, m, d_model=d, n_heads=h, n_layers=2, dtype="f32", seed=97, with_grad=True)
+    db = DeviceBatch(b, backward=True)
+    dout = to_device(b.grad_out, "cuda")
+    y, g = db.forward().clone(), db.backward(dout)
+    ref = O.forward(b.f64())["out"]
+    # (sums of at most 4 d fp32 terms through two layers: 2^-24 sqrt(4096) = 4e-6 a product)
+    assert np.abs(y.cpu().numpy() - ref).max() <= 4e-5 * np.abs(ref).max()
+    for _ in range(3):
+        y2, g2 = db.forward(), db.backward(dout)
+        assert torch.equal(y, y2)
+        for k in g:
+            assert torch.equal(g[k], g2[k]), k
