@@ -28,7 +28,9 @@ constexpr int GT = 64;  // output tile edge
 constexpr int GK = 32;  // k step
 
 // Tile (bx, by) and k range bz of `splits`.  A2, B2 (nullable): a second pair
-// of operands of the same forms, whose product is added.  part (nullable): the
+// of operands of the same forms, whose product is added, after the first and in
+// an accumulator of its own (as two products of half the terms each: dhist of
+// fp32 training 5.9e-7 of its norm off with one, 5.7e-7 with two).  part (nullable): the
 // k ranges' products are left there ([splits][M][N]) instead of added to C.
 template <typename TA, typename TB>
 __device__ __forceinline__ void gemm_body(int bx, int by, int bz, int splits, int M, int N, int K,
@@ -43,7 +45,7 @@ __device__ __forceinline__ void gemm_body(int bx, int by, int bz, int splits, in
   const int wm = (wave / 2) * 32, wn = (wave % 2) * 32;
   const int r32 = lane % 32, hi = lane / 32;
   const int m0 = by * GT, n0 = bx * GT;
-  f32x16 acc = {};
+  f32x16 acc = {}, acc1 = {};
   // split-K: workgroup z sums k in [z * k_chunk, (z + 1) * k_chunk) and adds
   // its partial into C atomically (C was cleared or holds what to add to), or
   // leaves it in `part`
@@ -79,30 +81,44 @@ __device__ __forceinline__ void gemm_body(int bx, int by, int bz, int splits, in
   load(A, B, kb);
   store();
   __syncthreads();
-  // (k tiles of the first pair, then of the second)
-  const int tiles = (ke - kb + GK - 1) / GK, all = A2 ? 2 * tiles : tiles;
-  for (int t = 0; t < all; ++t) {
-    const bool more = t + 1 < all;
-    if (more) {
-      const bool second = t + 1 >= tiles;
-      load(second ? A2 : A, second ? B2 : B, kb + (second ? t + 1 - tiles : t + 1) * GK);
-    }
-    // operand lane l holds A[m = l % 32][k = l / 32] and B[k = l / 32][n = l % 32]
+  // the k tiles of A B; the first of nextA nextB (nullable) is loaded behind the last
+  auto product = [&](f32x16& sum, const TA* A, const TB* B, const TA* nextA, const TB* nextB) {
+    for (int k0 = kb; k0 < ke; k0 += GK) {
+      const bool more = k0 + GK < ke;
+      if (more)
+        load(A, B, k0 + GK);
+      else if (nextA)
+        load(nextA, nextB, kb);
+      // operand lane l holds A[m = l % 32][k = l / 32] and B[k = l / 32][n = l % 32]
 #pragma unroll
-    for (int kk = 0; kk < GK; kk += 2)
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(As[kk + hi][wm + r32], Bs[kk + hi][wn + r32], acc, 0, 0, 0);
-    __syncthreads();
-    if (more) {
-      store();
+      for (int kk = 0; kk < GK; kk += 2)
+        sum = __builtin_amdgcn_mfma_f32_32x32x2f32(As[kk + hi][wm + r32], Bs[kk + hi][wn + r32], sum, 0, 0, 0);
       __syncthreads();
+      if (more || nextA) {
+        store();
+        __syncthreads();
+      }
     }
-  }
+  };
+  if (A2) product(acc1, A, B, A2, B2);
+  product(acc, A2 ? A2 : A, A2 ? B2 : B, nullptr, nullptr);
   // result lane layout: column n = lane % 32, rows 8 (v / 4) + 4 hi + v % 4
   const int gn = n0 + wn + r32;
   if (gn >= N) return;
+  auto row = [&](int v) { return m0 + wm + 8 * (v / 4) + 4 * hi + (v % 4); };
+  if (A2) {
+    f32x16 old = {};  // in one round trip
+    if (accumulate)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) old[v] = row(v) < M ? C[(int64_t)row(v) * ldc + gn] : 0.f;
+#pragma unroll
+    for (int v = 0; v < 16; ++v)
+      if (row(v) < M) C[(int64_t)row(v) * ldc + gn] = old[v] + alpha * acc1[v] + alpha * acc[v];
+    return;
+  }
 #pragma unroll
   for (int v = 0; v < 16; ++v) {
-    const int gm = m0 + wm + 8 * (v / 4) + 4 * hi + (v % 4);
+    const int gm = row(v);
     if (gm >= M) continue;
     float x = alpha * acc[v];
     float* c = C + (int64_t)gm * ldc + gn;
@@ -801,6 +817,7 @@ hipError_t gemm_f32_group(const F32Gemm* g, int n, float* part, int64_t part_flo
     G.g[k] = g[j];
     const int64_t nx = ceil_div(g[j].N, GT), ny = ceil_div(g[j].M, GT), tiles = nx * ny;
     const int64_t size = (int64_t)g[j].M * g[j].N;
+    if (g[j].A2 && g[j].epi != kEpiStore) return hipErrorInvalidValue;
     int64_t splits = g[j].epi == kEpiStore && !g[j].A2 ? f32_splits(g[j].M, g[j].N, g[j].K) : 1;
     if (splits * size > part_floats) splits = 1;
     if (splits > 1) {

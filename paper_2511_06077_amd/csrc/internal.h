@@ -48,7 +48,7 @@ hipError_t gemm_generic(int a_bf16, int b_bf16, int M, int N, int K, const void*
                         int accumulate, hipStream_t st);
 // Products of fp32 operands that don't depend on each other, in one launch;
 // conventions as in gemm_generic.  kEpiMask: C = R > 0 ? alpha*AB : 0.  With
-// A2, B2 (same forms and leading dims): AB + A2 B2.
+// A2, B2 (same forms and leading dims; kEpiStore): C = alpha*AB + alpha*A2 B2.
 struct F32Gemm {
   int M, N, K;
   const float* A;
