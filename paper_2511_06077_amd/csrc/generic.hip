@@ -162,7 +162,8 @@ struct F32Group {
   int n;
 };
 __global__ __launch_bounds__(256) void gemm_f32_group_kernel(F32Group G) {
-  int i = blockIdx.x, j = 0;
+  int i = blockIdx.y * gridDim.x + blockIdx.x, j = 0;
+  if (i >= G.end[G.n - 1]) return;
   while (j + 1 < G.n && i >= G.end[j]) ++j;
   if (j > 0) i -= G.end[j - 1];
   const F32Gemm& g = G.g[j];
@@ -807,6 +808,9 @@ int64_t gemm_f32_part_floats(int M, int N, int K) {
   return s > 1 ? s * M * N : 0;
 }
 
+// (a grid holds fewer than 2^32 threads along x: more workgroups go along y)
+constexpr int64_t kGridX = 1 << 20;
+
 hipError_t gemm_f32_group(const F32Gemm* g, int n, float* part, int64_t part_floats, hipStream_t st) {
   if (n < 0 || n > kMaxF32Group) return hipErrorInvalidValue;
   F32Group G{};
@@ -831,11 +835,14 @@ hipError_t gemm_f32_group(const F32Gemm* g, int n, float* part, int64_t part_flo
     G.ny[k] = static_cast<int>(ny);
     G.splits[k] = static_cast<int>(splits);
     blocks += tiles * splits;
-    if (blocks >= (int64_t)1 << 24) return hipErrorInvalidValue;  // (2^32 threads)
+    if (blocks > 0x7fffffff - kGridX) return hipErrorInvalidValue;
     G.end[k] = static_cast<int>(blocks);
   }
   if (G.n == 0) return hipSuccess;
-  hipLaunchKernelGGL(gemm_f32_group_kernel, dim3(static_cast<unsigned>(blocks)), dim3(256), 0, st, G);
+  hipLaunchKernelGGL(gemm_f32_group_kernel,
+                     dim3(static_cast<unsigned>(std::min(blocks, kGridX)),
+                          static_cast<unsigned>(ceil_div(blocks, kGridX))),
+                     dim3(256), 0, st, G);
   if (sums > 0)
     hipLaunchKernelGGL(sum_group_kernel, dim3(static_cast<unsigned>(ceil_div(sums, kSumLanes)), G.n), dim3(256), 0, st,
                        G);

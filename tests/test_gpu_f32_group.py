@@ -71,3 +71,28 @@ def test_f32_dhist_error(torch, d, h, L, m, bar):
         errs.append(np.linalg.norm(gpu_grads(torch, b)["dhist"] - ref) / np.linalg.norm(ref))
     print(f"[grad] dhist error {np.mean(errs):.2e}", flush=True)
     assert np.mean(errs) <= bar
+
+
+# 2^24 workgroups and more in one group of products (K and V of 2^29 rows, d = 8):
+# rows from the ends and the middle of the batch against the oracle
+def test_f32_many_tiles(torch):
+    from paper_2511_06077_amd.device import DeviceBatch
+    R, per = 4096, 1 << 17
+    m = np.zeros(R, dtype=np.int64)
+    used = [0, R // 2 + 1, R - 1]
+    m[used] = 2
+    small = W.make_custom_batch("gtiles", [per] * len(used), [2] * len(used), d_model=8, n_heads=1, n_layers=1,
+                                dtype="f32", seed=5)
+    hist = torch.zeros((R * per, 8), device="cuda")
+    src = torch.from_numpy(small.hist).cuda()
+    for i, r in enumerate(used):
+        hist[r * per:(r + 1) * per] = src[i * per:(i + 1) * per]
+    wl = W.Workload("gtiles", R, 8, 1, 1, "f32", seed=5, ffn_mult=4)
+    b = W.Batch(wl, np.arange(R), np.full(R, per), m, (np.arange(R + 1) * per).astype(np.int32),
+                np.concatenate([[0], np.cumsum(m)]).astype(np.int32), None, None, small.weights)
+    db = DeviceBatch.from_tensors(b, hist, torch.from_numpy(small.tgt).cuda(),
+                                  {k: torch.from_numpy(v).cuda() for k, v in small.weights.items()})
+    y = db.forward().cpu().numpy()
+    ref = O.forward(small.f64())["out"]
+    # (softmax sums of 131072 fp32 terms in runs of at most 8192)
+    assert np.abs(y - ref).max() <= 2e-5 * np.abs(ref).max()
