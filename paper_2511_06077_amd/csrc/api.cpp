@@ -75,13 +75,16 @@ inline int rb_group(const stca_dims_t* dims) { return kRbPairs / dims->n_heads; 
 // descending size in alternating rounds, in blocks of work (about 2.7 us at
 // d = 256): a unit costs its blocks, 3 for loading its operands and, when its
 // request has several chunks, 6 for writing its Z and Y partials.  *span
-// receives the makespan.
+// receives the makespan.  (Runs in every call: requests of one length count
+// once, and a run of units of one size adds to a range of the loads; 256 requests
+// of stochastic lengths 113 -> 63 us of sizing, 33 without an estimate.)
 int rb_chunk_for(const stca_dims_t* dims, const stca_batch_t* b, int n_cu, int64_t* span = nullptr) {
   const int M = rb_group(dims);
-  struct Req {
+  struct Req {  // requests of nb blocks with ng target groups between them
     int32_t nb, ng;
   };
   std::vector<Req> req;
+  req.reserve(b->n_requests);
   int64_t total = 0, longest = 1, units = 0;
   for (int r = 0; r < b->n_requests; ++r) {
     const int32_t m = b->tgt_off_host[r + 1] - b->tgt_off_host[r];
@@ -89,7 +92,8 @@ int rb_chunk_for(const stca_dims_t* dims, const stca_batch_t* b, int n_cu, int64
     const int32_t nb = static_cast<int32_t>(ceil_div(b->hist_off_host[r + 1], kBlockTokens) -
                                             b->hist_off_host[r] / kBlockTokens);
     const int32_t ng = (m + M - 1) / M;
-    req.push_back({nb, ng});
+    if (!req.empty() && req.back().nb == nb) req.back().ng += ng;
+    else req.push_back({nb, ng});
     total += static_cast<int64_t>(nb) * ng;
     units += ng;
     longest = std::max<int64_t>(longest, nb);
@@ -105,31 +109,54 @@ int rb_chunk_for(const stca_dims_t* dims, const stca_batch_t* b, int n_cu, int64
     cand.erase(std::unique(cand.begin(), cand.end()), cand.end());
   }
   int64_t best = cand[0], best_span = -1;
+  // a / c by the reciprocal: a and c are whole and below 2^22, so a quotient that
+  // is not whole is further than the added 1e-9 from the next
+  const auto quotient = [](int32_t a, double inv) { return static_cast<int32_t>(a * inv + 1e-9); };
+  double inv[kMaxChunks + 1];
+  for (int k = 1; k <= kMaxChunks; ++k) inv[k] = 1. / k;
   std::vector<int32_t> cnt;
-  std::vector<int64_t> load;
+  std::vector<int64_t> step(n_cu + 1);  // loads as differences of neighbours
   for (int64_t c : cand) {
     c = std::min<int64_t>(c, 1 << 16);
     const int32_t ci = static_cast<int32_t>(c), top = static_cast<int32_t>(std::min<int64_t>(longest, 1 << 16));
     // (bounds the host work: beyond, or with a history of 2^21 rows, no estimate)
     if (longest > (1 << 16) || units * std::min<int64_t>(kMaxChunks, ceil_div(longest, c)) > 32 * (int64_t)n_cu) continue;
     cnt.assign(top + 10, 0);
+    const double inv_c = 1. / ci;
     for (const Req& q : req) {
-      int32_t nch = std::min((q.nb + ci - 1) / ci, static_cast<int32_t>(kMaxChunks));
-      const int32_t cb = (q.nb + nch - 1) / nch;
-      nch = (q.nb + cb - 1) / cb;
+      int32_t nch = std::min(quotient(q.nb + ci - 1, inv_c), static_cast<int32_t>(kMaxChunks));
+      const int32_t cb = quotient(q.nb + nch - 1, inv[nch]);
+      while ((nch - 1) * cb >= q.nb) --nch;  // no empty chunk
       const int32_t extra = nch > 1 ? 9 : 3;
       cnt[cb + extra < top + 10 ? cb + extra : top + 9] += q.ng * (nch - 1);
       cnt[std::min(q.nb - (nch - 1) * cb + extra, top + 9)] += q.ng;
     }
-    load.assign(n_cu, 0);
-    int pos = 0, step = 1;  // 0 .. n_cu - 1, n_cu - 1 .. 0, ...
+    std::fill(step.begin(), step.end(), 0);
+    int64_t whole = 0;  // of the rounds of one size
+    int dealt = 0;      // units of the current round
+    bool back = false;  // rounds go 0 .. n_cu - 1, n_cu - 1 .. 0, ...
     for (int32_t x = top + 9; x > 0; --x)
-      for (int32_t k = 0; k < cnt[x]; ++k) {
-        load[pos] += x;
-        if (pos + step < 0 || pos + step >= n_cu) step = -step;
-        else pos += step;
+      for (int32_t k = cnt[x]; k > 0;) {
+        if (dealt == 0 && k >= n_cu) {
+          const int32_t rounds = k / n_cu;
+          whole += static_cast<int64_t>(x) * rounds;
+          back ^= rounds % 2 != 0;
+          k -= rounds * n_cu;
+          continue;
+        }
+        const int32_t c = std::min(k, n_cu - dealt);
+        const int lo = back ? n_cu - dealt - c : dealt;
+        step[lo] += x;
+        step[lo + c] -= x;
+        dealt += c;
+        k -= c;
+        if (dealt == n_cu) dealt = 0, back = !back;
       }
-    const int64_t s = *std::max_element(load.begin(), load.end());
+    int64_t s = 0, load = whole;
+    for (int i = 0; i < n_cu; ++i) {
+      load += step[i];
+      s = std::max(s, load);
+    }
     if (best_span < 0 || s < best_span) {
       best_span = s;
       best = c;
