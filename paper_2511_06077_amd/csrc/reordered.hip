@@ -501,8 +501,9 @@ __global__ __launch_bounds__(kMergeThreads) void reord_merge_kernel(const float*
   }
 }
 
-template <typename K>
-hipError_t allow_lds(K kernel, size_t bytes) {
+// (a parameter of the template, so that each kernel has its own record)
+template <auto kernel>
+hipError_t allow_lds(size_t bytes) {
   static int set_for[64] = {0};  // per device: bytes granted so far
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
@@ -540,7 +541,7 @@ hipError_t fast_reord_attn(int D, const Unit* units, const WsHeader* hdr, int64_
   const size_t lds = reord::attn_lds(D);
 #define STCA_RA(DD)                                                                                               \
   do {                                                                                                            \
-    hipError_t e = allow_lds(reord_attn_kernel<DD>, lds);                                                         \
+    hipError_t e = allow_lds<reord_attn_kernel<DD>>(lds);                                                         \
     if (e != hipSuccess) return e;                                                                                \
     hipLaunchKernelGGL(reord_attn_kernel<DD>, dim3(static_cast<unsigned>(max_units)), dim3(128 * kWaves), lds, st, \
                        units, hdr, (const __bf16*)UN, (const bf16_bits*)X, n_hist, part_y, (float2*)part_ml,     \
