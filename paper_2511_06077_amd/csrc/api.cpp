@@ -75,7 +75,7 @@ inline int rb_group(const stca_dims_t* dims) { return kRbPairs / dims->n_heads; 
 // descending size in alternating rounds, in blocks of work (about 2.7 us at
 // d = 256): a unit costs its blocks, 3 for loading its operands and, when its
 // request has several chunks, 6 for writing its Z and Y partials.  *span
-// receives the makespan.  (Runs in every call: requests of one length count
+// receives the makespan, -1 for a batch past the estimate.  (Runs in every call: requests of one length count
 // once, and a run of units of one size adds to a range of the loads; 256 requests
 // of stochastic lengths 113 -> 63 us of sizing, 33 without an estimate.)
 int rb_chunk_for(const stca_dims_t* dims, const stca_batch_t* b, int n_cu, int64_t* span = nullptr) {
@@ -163,7 +163,7 @@ int rb_chunk_for(const stca_dims_t* dims, const stca_batch_t* b, int n_cu, int64
     }
   }
   if (best_span < 0) best = chunk_blocks_for(b, n_cu, 1, dims->chunk_blocks);
-  if (span) *span = best_span < 0 ? ceil_div(total, n_cu) : best_span;
+  if (span) *span = best_span;
   return static_cast<int>(best);
 }
 
@@ -210,26 +210,36 @@ int fused_bwd_for(const stca_dims_t* dims, const stca_batch_t* b, bool* record, 
   // histories balanced over the CUs: one unit per request, no partials
   if (rd && longest <= 2 * ceil_div(total, n_cu)) return 2;
   if (!ok) return shape ? 3 : 0;
-  // Otherwise the cheaper of the two by what their kernels took per layer
-  // (ns): fused, attention and ring GEMMs per block; reordered, the attention
-  // pass per block of its makespan, dX per (block, target group), and the
-  // preparation, partial sums and grouped products.  Measured a step, us,
-  // fused against reordered: stochastic lengths (256 requests) 3490, 2750;
-  // 256 ragged requests of 1..16 targets 2374, 2056, of 16..32 2616, 2715;
-  // 20 of them 716, 830; d = 128, 1..32 targets 1475, 1434.
+  // Otherwise the cheaper of the two, by a fit (ns a layer) to what they took on
+  // 800 batches of 4..4000 requests of 1..8000 rows and 1..32 targets (d = 256 and
+  // 128): the fused form pays for every block; the reordered one a fixed part,
+  // the makespan of its units, dX per (block, target group), the operands of
+  // every target group (slots) and the Z, Y partials of the units of requests cut
+  // into several chunks; 10 and 5 us on top keep near ties fused.  In those batches
+  // the choice is 0.3% off the better form on average (the fused form throughout
+  // 5.7% and 2.4%, an estimate without the last two terms 4.9% and 4.0%) and slower
+  // than the fused form by 1% or more in 4, by 3% at most.  Batches past
+  // rb_chunk_for's estimate keep the fused form, whose workspace does not grow with the
+  // number of requests.  A step, us, fused against reordered: stochastic lengths
+  // (256 requests of 2048 rows on average) 3490, 2750; 512 requests of 100..600 rows
+  // and 1..32 targets 2240, 2707.
   if (!wide_d || total < n_cu) return 1;
-  int64_t span = 0, pairs = 0;
+  int64_t span = 0, pairs = 0, slots = 0, parts = 0;
   *rb_chunk = rb_chunk_for(dims, b, n_cu, &span);
+  if (span < 0) return 1;
   for (int r = 0; r < b->n_requests; ++r) {
     const int64_t m = b->tgt_off_host[r + 1] - b->tgt_off_host[r];
-    if (m > 0)
-      pairs += (ceil_div(b->hist_off_host[r + 1], kBlockTokens) - b->hist_off_host[r] / kBlockTokens) *
-               ceil_div(m, rb_group(dims));
+    if (m < 1) continue;
+    const int64_t nb = ceil_div(b->hist_off_host[r + 1], kBlockTokens) - b->hist_off_host[r] / kBlockTokens;
+    const int64_t groups = ceil_div(m, rb_group(dims));
+    const int64_t nch = std::min<int64_t>(kMaxChunks, ceil_div(nb, *rb_chunk));
+    pairs += nb * groups;
+    slots += groups;
+    if (nch > 1) parts += nch * groups;
   }
-  const bool d256 = dims->d_model == 256;
-  const double fused = (d256 ? 41. : 23.) * total + 12e3;
-  const double reordered = d256 ? 2600. * span + 6.5 * pairs + 65e3 : 1500. * span + 3.6 * pairs + 40e3;
-  return reordered < fused ? 2 : 1;
+  const double diff = dims->d_model == 256 ? 22e3 + 100. * span + 18. * pairs + 196. * slots + 50. * parts - 41. * total
+                                           : 16.4e3 + 70. * span + 88. * slots + 35. * parts - 9. * total;
+  return diff < 0. ? 2 : 1;
 }
 
 struct Layout {

@@ -68,7 +68,7 @@ def test_history_range_target_groups(torch):
     from paper_2511_06077_amd.device import DeviceBatch
     rng = np.random.default_rng(6)
     b = W.make_custom_batch("grangegrp", rng.integers(700, 2400, 128), np.where(rng.random(128) < 0.2, 20, 9),
-                            d_model=256, n_heads=8, n_layers=1, dtype="bf16", seed=101, with_grad=True)
+                            d_model=256, n_heads=8, n_layers=2, dtype="bf16", seed=101, with_grad=True)
     s, back = scaled(b, exponents("mixed", 256))
     db = DeviceBatch(s, backward=True)
     assert stca.stca_backward_launch_count(db.dims, db.batch) == 6 + 6 * b.wl.n_layers

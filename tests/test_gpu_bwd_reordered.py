@@ -117,8 +117,8 @@ def test_reordered_unbalanced_histories(torch):
     from paper_2511_06077_amd.device import DeviceBatch
     rng = np.random.default_rng(5)
     L = np.where(rng.random(96) < 0.5, 8, rng.integers(2000, 8000, 96))
-    b = W.make_custom_batch("grunb", L, rng.integers(1, 17, 96), d_model=256, n_heads=8, n_layers=1, dtype="bf16",
-                            seed=103, with_grad=True)
+    b = W.make_custom_batch("grunb", L, rng.integers(1, 17, 96), d_model=256, n_heads=8, n_layers=2, dtype="bf16",
+                            seed=103, with_grad=True)  # (the forms' phase counts differ from two layers on)
     db = DeviceBatch(b, backward=True)
     assert stca.stca_backward_launch_count(db.dims, db.batch) == 6 + 6 * b.wl.n_layers
     check(b, gpu_grads(torch, b), TOL["bf16"])
@@ -141,3 +141,22 @@ def test_reordered_target_groups(torch):
     g = gpu_grads(torch, b)
     check(b, g, TOL["bf16"])
     assert not np.any(g["dhist"][b.hist_off[4]:b.hist_off[5]])
+
+
+# The choice's estimate: many short requests, whose operands per target group the
+# reordered form pays for, keep the fused form (d = 256: 2240 us a step, 2707
+# reordered), as do few unbalanced ones and a batch of more units than the
+# estimate deals (whose workspace would grow by 0.9 MB a target group); long ones
+# take the reordered form
+@pytest.mark.parametrize("d,h,R,L,m,reordered", [
+    (256, 8, 512, (100, 600), (1, 32), False), (128, 4, 40, (30, 2000), (1, 32), False),
+    (256, 8, 20000, (100, 3000), (1, 32), False), (256, 8, 256, (500, 4000), (1, 32), True),
+    (128, 4, 256, (500, 6000), (1, 32), True)])
+def test_choice_by_estimate(d, h, R, L, m, reordered):
+    from paper_2511_06077_amd import stca
+    rng = np.random.default_rng(1)
+    ho = np.concatenate([[0], np.cumsum(rng.integers(L[0], L[1], R))]).astype(np.int32)
+    to = np.concatenate([[0], np.cumsum(rng.integers(m[0], m[1] + 1, R))]).astype(np.int32)
+    dims = stca.dims(d, h, 4, 4 * d, stca.STCA_BF16)
+    batch = stca.batch(R, int(ho[-1]), int(to[-1]), 256, 512, ho, to)  # (sizes only: no offset is read on the device)
+    assert stca.stca_backward_launch_count(dims, batch) == (6 + 6 * 4 if reordered else 7 + 5 * 4)
