@@ -81,27 +81,29 @@ __device__ __forceinline__ void gemm_body(int bx, int by, int bz, int splits, in
   load(A, B, kb);
   store();
   __syncthreads();
-  // the k tiles of A B; the first of nextA nextB (nullable) is loaded behind the last
-  auto product = [&](f32x16& sum, const TA* A, const TB* B, const TA* nextA, const TB* nextB) {
-    for (int k0 = kb; k0 < ke; k0 += GK) {
-      const bool more = k0 + GK < ke;
-      if (more)
-        load(A, B, k0 + GK);
-      else if (nextA)
-        load(nextA, nextB, kb);
-      // operand lane l holds A[m = l % 32][k = l / 32] and B[k = l / 32][n = l % 32]
-#pragma unroll
-      for (int kk = 0; kk < GK; kk += 2)
-        sum = __builtin_amdgcn_mfma_f32_32x32x2f32(As[kk + hi][wm + r32], Bs[kk + hi][wn + r32], sum, 0, 0, 0);
-      __syncthreads();
-      if (more || nextA) {
-        store();
-        __syncthreads();
-      }
+  // (k tiles of the first pair, then of the second)
+  const int tiles = (ke - kb + GK - 1) / GK, all = A2 ? 2 * tiles : tiles;
+#pragma unroll 1
+  for (int t = 0; t < all; ++t) {
+    if (A2 && t == tiles) {
+      acc1 = acc;
+      acc = f32x16{};
     }
-  };
-  if (A2) product(acc1, A, B, A2, B2);
-  product(acc, A2 ? A2 : A, A2 ? B2 : B, nullptr, nullptr);
+    const bool more = t + 1 < all;
+    if (more) {
+      const bool second = t + 1 >= tiles;
+      load(second ? A2 : A, second ? B2 : B, kb + (second ? t + 1 - tiles : t + 1) * GK);
+    }
+    // operand lane l holds A[m = l % 32][k = l / 32] and B[k = l / 32][n = l % 32]
+#pragma unroll
+    for (int kk = 0; kk < GK; kk += 2)
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(As[kk + hi][wm + r32], Bs[kk + hi][wn + r32], acc, 0, 0, 0);
+    __syncthreads();
+    if (more) {
+      store();
+      __syncthreads();
+    }
+  }
   // result lane layout: column n = lane % 32, rows 8 (v / 4) + 4 hi + v % 4
   const int gn = n0 + wn + r32;
   if (gn >= N) return;
