@@ -95,8 +95,10 @@ inline int chunk_blocks_for(const stca_batch_t* b, int n_cu, int per_cu, int for
 // one, two, four or eight units per CU whose estimated makespan is least
 // (fewer units on ties).  The estimate cuts the requests the standard form serves
 // (targets in [m_lo, m_hi], `group` a unit) as the device scheduler does and deals their
-// units (those of up to 32 and of more targets run in separate launches, so
-// their makespans add) in descending size,
+// units in descending size (those of up to 32 and of more targets apart, and
+// adds the two makespans: what they take as launches of their own.  In the one
+// launch that a batch of both runs, workgroups of both share a CU and the sum
+// is an upper bound; the choice among the four lengths is as measured below),
 // round-robin over the CUs in alternating directions as the device
 // scheduler does, and charges each unit one block of fixed cost (its query
 // load, partial stores and merge).  Equal histories then run one unit per
@@ -175,6 +177,9 @@ inline int64_t max_units_for(const stca_batch_t* b, int chunk_blocks, int group,
 // that costs a layer least: 1.9 us a block of the chunk, and 1.2 us per 8 chunk
 // records that the update merges (a round trip).  0 when the batch fills the
 // CUs without.  Without host offsets the whole history counts as one request.
+// The two costs are those of d = 256 and serve d = 64 and 128 too, where a block
+// takes less (drawn batches of these are 1.06 to 1.26 times as fast as in at
+// most 16 chunks).
 // One request of 9001 rows and 40 targets: 18 blocks on 16 CUs 233 us a call, 8
 // blocks 176, 6 166, 5 167; 8 requests of 700 rows: 8 blocks 135, 5 120.
 inline int forward_chunks(const stca_batch_t* b, int n_cu, int m_lo) {

@@ -819,7 +819,7 @@ __global__ __launch_bounds__(64 * (D / 32)) void update_kernel(UpdateArgs A) {
   auto wq_tile = [&](int ql) { return A.WqP + ((int64_t)(ql * NW + w) * KS) * 64; };
 
   if (A.mode == 0) {
-    fetch(W3 ? wa : wb, wq_tile(0));
+    fetch(W3 ? wa : wb, wq_tile(0));  // (the set that the last product reads; no launch of this mode has W3)
     // the layers' arrival counters
     if (A.cnt)
       for (int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x; i < (int64_t)A.n_layers * A.groups;
@@ -1201,8 +1201,8 @@ hipError_t fast_attn_mixed(int D, const FastFused& f, const FastMixed& m, hipStr
 // 16 x 1 174, 8 x 4 (two rounds) 207; 1536 targets 16 x 2 170, 32 x 4 175,
 // 16 x 1 179; 3072 targets 16 x 1 202, 32 x 2 203; 18000 targets 32 x 1 739,
 // 16 x 1 854.  One request of 40 targets: 8 x 4 246, 16 x 4 256, 16 x 1 275.
-// Smaller models stream too little for the exchange to pay (d = 128, 1024
-// targets: 16 x 1 55, 16 x 2 59).
+// Smaller models stream too little for the exchange to pay (measured at d = 128
+// and 1024 targets alone: 16 x 1 55, 16 x 2 59).
 UpdatePlan update_plan(int64_t n_tgt, int D, int F, int n_cu) {
   UpdatePlan p;
   p.tg0 = ceil_div(n_tgt, 32) < n_cu ? 16 : 32;

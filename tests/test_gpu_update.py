@@ -13,13 +13,14 @@ def rowerr(y, ref):
     return float((np.abs(y - ref).max(-1) / np.maximum(np.abs(ref).max(-1), 1e-30)).max())
 
 
-# totals around the group and split limits at 256 CUs: 4 targets x 4 splits up
-# to 256, 8 x 4
-# up to 512, 16 x 4 up to 1024, 16 x 2 up to 2048, 16 x 1 up to 4096, then 32
+# totals around the group and split limits, given at 256 CUs and scaled to the
+# card's: 4 targets x 4 splits up to 256, 8 x 4 up to 512, 16 x 4 up to 1024,
+# 16 x 2 up to 2048, 16 x 1 up to 4096, then 32
 @pytest.mark.parametrize("nt", [1, 5, 256, 257, 512, 513, 1024, 1025, 2048, 2049, 4096, 4097])
 def test_update_cut(nt):
     import torch
     from paper_2511_06077_amd.device import DeviceBatch
+    nt = nt // 256 * torch.cuda.get_device_properties(0).multi_processor_count + nt % 256
     m = []
     while sum(m) < nt:
         m.append(min(61, nt - sum(m)))
