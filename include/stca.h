@@ -40,8 +40,10 @@
  *    and stca_device_status() then returns STCA_ERR_RANGE; outputs of such a
  *    call are undefined.  A K entry whose overflow drives its score to minus
  *    infinity only removes that history row from the softmax and is not
- *    detected.  The backward's fp16 operands (two-term, hi + lo) have the same
- *    range and are not checked.  Non-finite inputs propagate.
+ *    detected.  The backward of at most 32 targets per request recomputes the
+ *    attention on fp16 operands of two terms (hi + lo), which have the same
+ *    range and are not checked; with more targets, and in the generic form, K,
+ *    V and the queries are fp32.  Non-finite inputs propagate.
  *  - Request r owns hist rows [hist_off[r], hist_off[r+1]) and tgt rows
  *    [tgt_off[r], tgt_off[r+1]).  offsets[0] = 0, non-decreasing,
  *    offsets[R] = n_hist / n_tgt.  A request with targets must have at least
