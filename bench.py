@@ -81,6 +81,11 @@ def kernel_work(label: str, b: W.Batch, es: int, attn_form: int = stca.STCA_ATTN
         sel = (m > 0) & ~reord & ((m <= 32) if label == "fused" else (m > 32))
         return (4.0 * L[sel].sum() * d * d + 4.0 * (m[sel] * L[sel]).sum() * d,
                 es * L[sel].sum() * d)
+    if label == "attn_mixed":
+        # both widths in one launch, at d = 256 with the reordered requests
+        parts = ["fused", "fused_wide"] + (["reord_attn"] if d == 256 else [])
+        work = [kernel_work(p, b, es, attn_form) for p in parts]
+        return sum(w[0] for w in work), sum(w[1] for w in work)
     if label == "reord_attn":
         # one layer of the reordered form (Eq. attn-optimized): scores X U^T and
         # P^T X over the m h (target, head) rows of each request, X read once
@@ -204,7 +209,8 @@ def timed_forward(db, steps: int, warmup: int):
     for e in evs:
         for k in range(nl):
             lab = e.label(k)
-            per.setdefault(lab, []).append(e.elapsed_ms(k, k + 1))
+            if lab != "none":
+                per.setdefault(lab, []).append(e.elapsed_ms(k, k + 1))
     for e in evs:
         e.close()
     return total_ms, per
@@ -466,10 +472,10 @@ def paper_kernel_work(label: str, b: W.Batch):
     Lall = float(b.hist_len.sum())
     L = b.hist_len.astype(np.float64)
     m = b.n_tgt.astype(np.float64)
-    sel = (m > 0) & (m <= 32)
+    sel = (m > 0) & ((m <= 32) if label == "fused" else (m > 32) if label == "fused_wide" else True)
     if label == "swiglu_ln":
         return 6.0 * Lall * d * F, 2.0 * Lall * d * 2
-    if label == "fused":
+    if label in ("fused", "fused_wide", "attn_mixed"):  # (one width, the other, both in one launch)
         return 4.0 * L[sel].sum() * d * d + 4.0 * (m[sel] * L[sel]).sum() * d, 2.0 * L[sel].sum() * d
     return 0.0, 0.0
 
@@ -501,7 +507,8 @@ def paper_step(args) -> int:
     per = {}
     for e in evs:
         for k in range(nl):
-            per.setdefault(e.label(k), []).append(e.elapsed_ms(k, k + 1))
+            if e.label(k) != "none":
+                per.setdefault(e.label(k), []).append(e.elapsed_ms(k, k + 1))
         e.close()
     log(f"[bench] paper stack {args.steps} steps: {ms_step:.3f} ms/step")
     kernels = {}
@@ -522,7 +529,7 @@ def paper_step(args) -> int:
     roof["traffic"] = None
     n = wl.n_layers
     bound_ms = sum(max(paper_kernel_work(k, b)[0] / (PEAK_BF16_TFLOPS * 1e12),
-                       paper_kernel_work(k, b)[1] / (PEAK_HBM_GBS * 1e9)) for k in ("swiglu_ln", "fused")) * n * 1e3
+                       paper_kernel_work(k, b)[1] / (PEAK_HBM_GBS * 1e9)) for k in ("swiglu_ln", "attn_mixed")) * n * 1e3
     rec = {"metric": "targets scored/sec, STCA forward (paper-exact stack)",
            "value": b.n_tgt_total / (ms_step * 1e-3), "unit": "targets/s", "n_gpus": 1, "steps": args.steps,
            "warmup": args.warmup, "ms_per_step": ms_step, "higher_is_better": True, "scaling": "weak",

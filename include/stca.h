@@ -276,7 +276,11 @@ stca_status_t stca_backward_record(const stca_dims_t* dims, const stca_batch_t* 
  * stream it runs on.  events[0] is recorded before the first launch and
  * events[k+1] right after launch k; n_events must be at least
  * stca_forward_launch_count(dims, batch) + 1.  labels (nullable, n_events - 1
- * entries) receive static kernel names ("proj", "attn", "update", ...).
+ * entries) receive static kernel names ("proj", "attn", "update", ...).  The
+ * count has a place for every kernel that a batch may need; one whose work
+ * runs inside another launch ("setup": schedules and weight repacking;
+ * "attn_mixed": the attention of a batch of several widths or forms) has the
+ * label "none" and no duration.
  * The events must have been created by the caller (hipEventCreate). */
 int stca_forward_launch_count(const stca_dims_t* dims, const stca_batch_t* batch);
 stca_status_t stca_forward_profiled(const stca_dims_t* dims, const stca_batch_t* batch,

@@ -691,8 +691,8 @@ stca_status_t forward_fast(const Layout& L, const stca_batch_t* b, const void* h
     pj.job[nj++] = {w->w1, at<char>(ws, L.w1p), d, F, 1};
     pj.job[nj++] = {w->w2, at<char>(ws, L.w2p), F, d, 1};
     HIPCHK(launch_setup(sp, ns, pj, nj, n, st));
-    for (int i = 0; i < ns; ++i) HIPCHK(rec.mark("sched"));
-    HIPCHK(rec.mark("pack"));
+    HIPCHK(rec.mark("setup"));
+    for (int i = 0; i < ns; ++i) HIPCHK(rec.mark("none"));
   }
   char* kv = at<char>(ws, L.kv);
   if (L.mat) {
@@ -762,7 +762,7 @@ stca_status_t forward_fast(const Layout& L, const stca_batch_t* b, const void* h
       }
       for (int wide = 0; wide < 2; ++wide) {
         if (!mixed_launch && (wide ? L.any_wide : L.any_narrow)) HIPCHK(fast_fused(d, wide, fgrid, ff, st));
-        HIPCHK(rec.mark(wide ? "fused_wide" : "fused"));
+        HIPCHK(rec.mark(mixed_launch ? (wide ? "none" : "attn_mixed") : wide ? "fused_wide" : "fused"));
       }
     }
     if (reo_part) {
@@ -772,7 +772,7 @@ stca_status_t forward_fast(const Layout& L, const stca_batch_t* b, const void* h
       else if (!reord_inside)
         HIPCHK(fast_reord_attn(d, units2, hdr2, L.max_units2, at<char>(ws, L.un), hist, L.nh,
                                at<float>(ws, L.part_y), at<char>(ws, L.ml_r), L.nt, st));
-      HIPCHK(rec.mark("reord_attn"));
+      HIPCHK(rec.mark(reord_inside ? "none" : "reord_attn"));
       // a of the reordered requests as their single chunk of the update's partials
       HIPCHK(fast_reord_merge(d, at<float>(ws, L.part_y), at<char>(ws, L.ml_r), tch_r, at<char>(ws, L.wvp16), i,
                               at<float>(ws, L.part_acc), at<char>(ws, L.part_ml), tch, L.nt, st));

@@ -192,7 +192,7 @@ stca_status_t forward_paper_fast(const PaperLayout& L, const stca_batch_t* b, co
     pj.job[5] = {w->ffn_v, pk(L.wvup, 0), d, F, 0};
     pj.job[6] = {w->ffn_o, pk(L.wdp, 0), F, d, 0};
     HIPCHK(launch_setup(&sp, 1, pj, 7, n, st));
-    HIPCHK(rec.mark("sched"));
+    HIPCHK(rec.mark("setup"));
     // the weights without a layer axis, kMaxPackJobs at a time
     std::vector<PackJob> one = {{w->wz, pk(L.wzp, 0), (n + 1) * d, d, 0},
                                 {w->z_u, pk(L.zup, 0), d, F, 0},
@@ -255,7 +255,7 @@ stca_status_t forward_paper_fast(const PaperLayout& L, const stca_batch_t* b, co
     }
     for (int wide = 0; wide < 2; ++wide) {
       if (!mixed && (wide ? L.any_wide : L.any_narrow)) HIPCHK(fast_fused(d, wide, fgrid, ff, st));
-      HIPCHK(rec.mark(wide ? "fused_wide" : "fused"));
+      HIPCHK(rec.mark(mixed ? (wide ? "none" : "attn_mixed") : wide ? "fused_wide" : "fused"));
     }
     // o^(i) = [heads] W_O^(i) (Eq. layer-output); then q^(i+2) =
     // LN(SwiGLUFFN^(i+2)([o^(1) .. o^(i+1) || x_t] W_C^(i+2))) and its queries,

@@ -54,3 +54,26 @@ def test_few_requests(L, m, host, d, h):
     assert rowerr(y, ref["out"]) <= 2e-2
     for i in range(2):
         assert rowerr(db.saved_tensor("a")[i].cpu().numpy(), ref["a"][i]) <= 2e-2
+
+
+def test_profiled_labels_of_shared_launches():
+    """The places of kernels whose work runs inside another launch are labelled
+    "none": the schedules and the packing, and of a batch of three forms (one,
+    32 and 64 targets a request) the attention's."""
+    import torch
+    from paper_2511_06077_amd import stca
+    from paper_2511_06077_amd.device import DeviceBatch
+    b = W.make_custom_batch("labels", [300, 200, 400], [1, 32, 64], d_model=256, n_heads=8, n_layers=2, dtype="bf16",
+                            seed=47)
+    db = DeviceBatch(b)
+    n = stca.stca_forward_launch_count(db.dims, db.batch)
+    ev = stca.HipEvents(n + 1)
+    try:
+        stca.stca_forward_profiled(db.dims, db.batch, db.hist, db.tgt, db.weights, db.out, None, db.ws, db.ws_bytes,
+                                   db.stream(), ev.ev, ev.labels)
+        torch.cuda.synchronize()
+        labels = [ev.label(k) for k in range(n)]
+    finally:
+        ev.close()
+    assert labels == ["setup", "none", "none", "update"] + 2 * ["reord_u", "attn_mixed", "none", "none",
+                                                                "reord_merge", "update"]
