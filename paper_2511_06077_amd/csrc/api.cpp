@@ -4,6 +4,7 @@
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
+#include <new>
 
 #include "common.h"
 #include "fast.h"
@@ -608,8 +609,8 @@ stca_status_t make_layout_for(const stca_dims_t* dims, const stca_batch_t* b, in
 
 // A batch that fits the library's own scratch array only without the extra
 // workspace of few targets keeps fitting, without.
-stca_status_t make_layout(const stca_dims_t* dims, const stca_batch_t* b, int with_backward, bool with_saved,
-                          Layout* L) {
+stca_status_t make_layout_or_throw(const stca_dims_t* dims, const stca_batch_t* b, int with_backward, bool with_saved,
+                                   Layout* L) {
   const stca_status_t st = make_layout_for(dims, b, with_backward, with_saved, true, L);
   if (st != STCA_OK || with_backward || L->total <= STCA_NOALLOC_SCRATCH_BYTES ||
       (L->upd.splits == 1 && L->max_chunks == kMaxChunks))
@@ -619,6 +620,17 @@ stca_status_t make_layout(const stca_dims_t* dims, const stca_batch_t* b, int wi
       plain.total <= STCA_NOALLOC_SCRATCH_BYTES)
     *L = plain;
   return st;
+}
+
+// (the estimates keep lists of the requests: out of host memory, no exception
+// crosses the ABI)
+stca_status_t make_layout(const stca_dims_t* dims, const stca_batch_t* b, int with_backward, bool with_saved,
+                          Layout* L) {
+  try {
+    return make_layout_or_throw(dims, b, with_backward, with_saved, L);
+  } catch (const std::bad_alloc&) {
+    return STCA_ERR_HIP;
+  }
 }
 
 bool saved_layout(const stca_dims_t* dims, const stca_batch_t* b, stca_saved_layout_t* s) {

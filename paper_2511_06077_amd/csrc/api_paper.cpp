@@ -7,7 +7,7 @@
 // request for all its targets (Sec. 3.2).
 #include <algorithm>
 #include <cmath>
-#include <vector>
+#include <new>
 
 #include "api_common.h"
 #include "common.h"
@@ -52,7 +52,7 @@ bool paper_saved_layout(const stca_dims_t* dims, const stca_batch_t* b, stca_pap
   return true;
 }
 
-bool make_paper_layout(const stca_dims_t* dims, const stca_batch_t* b, PaperLayout* L) {
+bool make_paper_layout_or_throw(const stca_dims_t* dims, const stca_batch_t* b, PaperLayout* L) {
   const int p = path_of(dims);
   if (p < 0 || check_batch(b) != STCA_OK) return false;
   L->path = p;
@@ -135,6 +135,15 @@ bool make_paper_layout(const stca_dims_t* dims, const stca_batch_t* b, PaperLayo
   return true;
 }
 
+// (as the standard stack's: out of host memory, no exception crosses the ABI)
+bool make_paper_layout(const stca_dims_t* dims, const stca_batch_t* b, PaperLayout* L) {
+  try {
+    return make_paper_layout_or_throw(dims, b, L);
+  } catch (const std::bad_alloc&) {
+    return false;
+  }
+}
+
 int paper_launch_count(const PaperLayout& L) {
   // bf16: schedule, the SwiGLU pack and the other packs, the first query
   // stage; per layer the history transform, the attention (two widths) and the
@@ -194,20 +203,21 @@ stca_status_t forward_paper_fast(const PaperLayout& L, const stca_batch_t* b, co
     HIPCHK(launch_setup(&sp, 1, pj, 7, n, st));
     HIPCHK(rec.mark("setup"));
     // the weights without a layer axis, kMaxPackJobs at a time
-    std::vector<PackJob> one = {{w->wz, pk(L.wzp, 0), (n + 1) * d, d, 0},
-                                {w->z_u, pk(L.zup, 0), d, F, 0},
-                                {w->z_v, pk(L.zvp, 0), d, F, 0},
-                                {w->z_o, pk(L.zdp, 0), F, d, 0}};
+    pj.job[0] = {w->wz, pk(L.wzp, 0), (n + 1) * d, d, 0};
+    pj.job[1] = {w->z_u, pk(L.zup, 0), d, F, 0};
+    pj.job[2] = {w->z_v, pk(L.zvp, 0), d, F, 0};
+    pj.job[3] = {w->z_o, pk(L.zdp, 0), F, d, 0};
+    int c = 4;
     size_t rows = 0;
     for (int k = 2; k <= n; ++k) {
-      one.push_back({elems(w->wc, rows * d), pk(L.wcp, rows * d), k * d, d, 0});
+      if (c == kMaxPackJobs) {
+        HIPCHK(fast_pack_many(pj, c, 1, st));
+        c = 0;
+      }
+      pj.job[c++] = {elems(w->wc, rows * d), pk(L.wcp, rows * d), k * d, d, 0};
       rows += (size_t)k * d;
     }
-    for (size_t j = 0; j < one.size(); j += kMaxPackJobs) {
-      const int c = static_cast<int>(std::min<size_t>(kMaxPackJobs, one.size() - j));
-      std::copy(one.begin() + j, one.begin() + j + c, pj.job);
-      HIPCHK(fast_pack_many(pj, c, 1, st));
-    }
+    HIPCHK(fast_pack_many(pj, c, 1, st));
   }
   const int64_t groups = ceil_div(nt, 32);
   if (L.splits > 1) HIPCHK(fill_f32(at<float>(ws, L.cnt), 0.f, (n + 1) * groups, st));
@@ -400,7 +410,7 @@ stca_status_t run_paper(const stca_dims_t* dims, const stca_batch_t* b, const vo
   stca_status_t s = check_paper(dims, b, hist, tgt, w, z, saved, ws);
   if (s != STCA_OK) return s;
   PaperLayout L;
-  make_paper_layout(dims, b, &L);
+  if (!make_paper_layout(dims, b, &L)) return STCA_ERR_HIP;
   if (ws_bytes < L.total) return STCA_ERR_WORKSPACE;
   if (rec.ev && rec.n < paper_launch_count(L) + 1) return STCA_ERR_INVALID_ARG;
   stca_paper_saved_layout_t SL{};

@@ -285,3 +285,27 @@ def test_chunk_rule_ragged_histories_take_finer_cuts():
     sizes = {p: stca.stca_workspace_size(dims(chunk_blocks=_chunk_for(sum(L), p)), b) for p in (1, 2, 4, 8)}
     assert auto in (sizes[4], sizes[8])
     assert auto != sizes[1]
+
+
+def test_out_of_host_memory_is_an_error():
+    """The chunk estimates keep lists of a batch's requests; where these cannot
+    be allocated the call reports it (0 bytes) instead of ending the process."""
+    import subprocess
+    import sys
+    code = """
+import ctypes, resource
+import numpy as np
+from paper_2511_06077_amd import stca
+R = 40_000_000
+hist, tgt = np.arange(R + 1, dtype=np.int32), np.zeros(R + 1, dtype=np.int32)
+tgt[1:] = np.arange(1, R + 1)
+d = stca.dims(256, 8, 1, 1024, stca.STCA_BF16)
+b = stca.batch(R, R, R, 256, 512, hist, tgt)
+stca.lib()
+size = int(open('/proc/self/statm').read().split()[0]) * resource.getpagesize()
+resource.setrlimit(resource.RLIMIT_AS, (size + (64 << 20), resource.RLIM_INFINITY))
+print('bytes', stca.stca_workspace_size(d, b, True))
+"""
+    out = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=120)
+    assert out.returncode == 0, out.stderr[-500:]
+    assert out.stdout.split() == ["bytes", "0"]
