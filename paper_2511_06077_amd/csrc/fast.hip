@@ -699,9 +699,9 @@ __global__ __launch_bounds__(64 * (D / 32)) void attn_mixed_kernel(FusedArgs A, 
 // and layer, zeroed by the mode 0 launch) sums the parts in split order, so
 // the result does not depend on who is last, and forms Q' (split.h; with
 // agent-scope fences one request of 40 targets took 370 us a call, not 246).
-// Kernel time at d = 256: 128 targets of one chunk 21 -> 11 us, 40 targets of
-// 16 chunks 20 -> 13 us, 4096 targets of two chunks (no splits) 22.3
-// and 23.1 us in a trace of the headline batch, whose call takes as long as before.
+// Kernel time at d = 256, traced at a settled clock: 128 targets of one chunk 25
+// -> 15 us, one request of 40 targets 24 (16 chunks) -> 20 us (57 chunks), 4096
+// targets of two chunks (no splits) 22.3 and 22.9.
 struct UpdateArgs {
   int mode, layer, n_layers, F;
   int64_t n_tgt;
